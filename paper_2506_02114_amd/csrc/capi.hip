@@ -407,6 +407,7 @@ Tuned tune_map(mlm_lens *lens, const mlm_map_request &q, const Region &R, hipStr
             Timer tm(true, st);
             const int a = tm.mark();
             Tree T;
+            box_rays(T, R, 0, R.nr2 - 1);
             build_tree(lens, R, qc, T, st);
             T.mixed = qc.precision == MLM_PREC_MIXED;
             run_fmm(lens, T, order_for(qc, R, T), st);
@@ -831,6 +832,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
     const bool fmm = q.method == MLM_METHOD_FMM;
     int e_tree = -1, e_fmm = -1;
     if (fmm) {
+        box_rays(T, R, cb0, cb1);
         build_tree(lens, R, q, T, st);
         T.mixed = q.precision == MLM_PREC_MIXED;
         e_tree = tm.mark();
@@ -1438,6 +1440,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
                 }
                 m.tm = &pt;
                 m.e_tree0 = pt.mark();
+                box_rays(m.T, m.R, 0, m.R.nr2 - 1);
                 build_tree(m.lens, m.R, m.q, m.T, ps);
                 m.T.mixed = m.q.precision == MLM_PREC_MIXED;
                 m.e_tree1 = pt.mark();

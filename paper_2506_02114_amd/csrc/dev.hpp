@@ -59,6 +59,24 @@ __device__ inline int32_t lower_bound_u64(const uint64_t *a, int32_t n, uint64_t
     return lo;
 }
 
+// A colleague reference: >= 0 a node of the same level, -1 nothing (outside
+// the root), <= -2 the leaf -(ref + 2) of a coarser level containing the square.
+// Stars of square `sc` (level shift sh) inside the reference's range.
+__device__ inline void ref_stars(int32_t ref, uint64_t sc, int sh, const int32_t *__restrict__ slo,
+                                 const int32_t *__restrict__ shi, const uint64_t *__restrict__ keys, int32_t &s0,
+                                 int32_t &s1)
+{
+    s0 = s1 = 0;
+    if (ref >= 0) {
+        s0 = slo[ref];
+        s1 = shi[ref];
+    } else if (ref <= -2) {
+        const int32_t L = -ref - 2, a = slo[L], b = shi[L];
+        s0 = a + lower_bound_u64(keys + a, b - a, sc << sh);
+        s1 = s0 + lower_bound_u64(keys + s0, b - s0, (sc + 1) << sh);
+    }
+}
+
 template <class T>
 __device__ inline int64_t upper_bound_i64(const T *a, int64_t n, T v)
 {
@@ -144,6 +162,33 @@ __device__ inline int wave_find(int excl, int x)
         if (e <= x) lo += step;
     }
     return lo;
+}
+
+// the rectangle [x0, x1] x [y0, y1] that holds the rays of a request, widened
+// beyond the rounding of their positions
+struct RayBox {
+    double x0, x1, y0, y1;
+};
+
+RayBox ray_box(const Tree &T);
+
+// centre, half-length and its inverse of the square `code` of level lev
+__device__ inline void node_geom(uint64_t code, int lev, double L0, double &cx, double &cy, double &L,
+                                 double &invL)
+{
+    uint32_t i = compact_bits(code), j = compact_bits(code >> 1);
+    L = ldexp(L0, -lev);
+    invL = 1.0 / L;   // exact: L is a power of two
+    cx = -L0 + (double)(2 * (int64_t)i + 1) * L;
+    cy = -L0 + (double)(2 * (int64_t)j + 1) * L;
+}
+
+// whether the square meets the rays' rectangle
+__device__ inline bool in_box(uint64_t code, int lev, double L0, const RayBox &b)
+{
+    double cx, cy, L, invL;
+    node_geom(code, lev, L0, cx, cy, L, invL);
+    return cx + L >= b.x0 && cx - L <= b.x1 && cy + L >= b.y0 && cy - L <= b.y1;
 }
 
 template <class R> struct Cx;

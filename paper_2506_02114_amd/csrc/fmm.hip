@@ -7,6 +7,7 @@
 // the child's quadrant, M2L only on the offset between the two squares (one
 // of 40 in a 7x7 stencil).  The operators are tabulated once on the host in
 // extended precision.
+#include <algorithm>
 #include <cmath>
 #include <complex>
 #include <vector>
@@ -39,6 +40,10 @@ cld ipow(cld z, int n)
     return r;
 }
 
+// The tables of M2M and L2L are stored [quadrant][source coefficient k][target
+// coefficient l], so that the lanes of a wavefront (one target coefficient
+// each) read consecutive entries.
+
 // M2M, child quadrant (qi, qj): z0 = child centre - parent centre in child
 // half-lengths = (2qi-1) + i(2qj-1);  b_l = z0^l [-a_0/l + sum_{k=1}^{l} a_k z0^-k C(l-1,k-1)] / 2^l
 void table_m2m(int p, std::vector<double2> &out)
@@ -58,7 +63,7 @@ void table_m2m(int p, std::vector<double2> &out)
                     v = ipow(z0, l - k) * binom_ld(l - 1, k - 1);
                 }
                 v /= std::ldexp(1.0L, l);
-                out[(quad * P1 + l) * P1 + k] = make_double2((double)v.real(), (double)v.imag());
+                out[(quad * P1 + k) * P1 + l] = make_double2((double)v.real(), (double)v.imag());
             }
     }
 }
@@ -101,26 +106,20 @@ void table_l2l(int p, std::vector<double2> &out)
         for (int l = 0; l <= p; ++l)
             for (int k = l; k <= p; ++k) {
                 cld v = ipow(delta, k - l) * binom_ld(k, l) / std::ldexp(1.0L, l);
-                out[(quad * P1 + l) * P1 + k] = make_double2((double)v.real(), (double)v.imag());
+                out[(quad * P1 + k) * P1 + l] = make_double2((double)v.real(), (double)v.imag());
             }
     }
 }
 
-__device__ inline void node_geom(uint64_t code, int lev, double L0, double &cx, double &cy, double &L,
-                                 double &invL)
-{
-    uint32_t i = compact_bits(code), j = compact_bits(code >> 1);
-    L = ldexp(L0, -lev);
-    invL = 1.0 / L;   // exact: L is a power of two
-    cx = -L0 + (double)(2 * (int64_t)i + 1) * L;
-    cy = -L0 + (double)(2 * (int64_t)j + 1) * L;
-}
-
 // upward pass of one level: P2M at leaves, M2M from the four children
-// elsewhere.  R is the arithmetic type of the coefficients; star offsets from
-// the node centre are always formed in FP64.
+// elsewhere; half a wavefront per node, lane k its coefficient k.  The pass is
+// bound by the latency of its loads, so the products are unrolled and several
+// loads are in flight (the table has zeros above the diagonal: every lane runs
+// all p + 1 terms).  R is the arithmetic type of the coefficients; star
+// offsets from the node centre are always formed in FP64.
 template <class R>
-__global__ void k_upward(int64_t lo, int64_t hi, int lev, int p, double L0, const uint64_t *__restrict__ code,
+__global__ __launch_bounds__(BLK) void k_upward(int64_t lo, int64_t hi, int lev, int p, double L0,
+                         const uint64_t *__restrict__ code,
                          const int32_t *__restrict__ leaf, const int32_t *__restrict__ slo,
                          const int32_t *__restrict__ shi, const int32_t *__restrict__ child0,
                          const double *__restrict__ sx, const double *__restrict__ sy,
@@ -129,10 +128,9 @@ __global__ void k_upward(int64_t lo, int64_t hi, int lev, int p, double L0, cons
 {
     using C2 = typename Cx<R>::c2;
     const int P1 = p + 1;
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t q = lo + t / P1;
-    int k = (int)(t % P1);
-    if (q >= hi) return;
+    const int64_t q = lo + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 32;
+    const int k = threadIdx.x & 31;
+    if (q >= hi || k > p) return;
     C2 acc = Cx<R>::make(0, 0);
     if (leaf[q]) {
         double cx, cy, L, invL;
@@ -151,12 +149,12 @@ __global__ void k_upward(int64_t lo, int64_t hi, int lev, int p, double L0, cons
         }
         if (k > 0) acc = cscale(acc, (R)1 / (R)k);
     } else {
-        int32_t c0 = child0[q];
+        const C2 *a = mult + (int64_t)child0[q] * P1;
+        const C2 *op = m2m + k;
         for (int quad = 0; quad < 4; ++quad) {
-            const C2 *op = m2m + (quad * P1 + k) * P1;
-            const C2 *a = mult + (int64_t)(c0 + quad) * P1;
-            for (int kk = 0; kk <= k; ++kk) {
-                C2 o = op[kk], v = a[kk];
+#pragma unroll 8
+            for (int kk = 0; kk <= p; ++kk) {
+                const C2 o = op[(quad * P1 + kk) * P1], v = a[quad * P1 + kk];
                 acc.x += o.x * v.x - o.y * v.y;
                 acc.y += o.x * v.y + o.y * v.x;
             }
@@ -198,13 +196,16 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// downward pass of one level (>= 2), one wavefront per node: L2L from the
+// downward pass of the listed nodes of one level (>= 2), those whose square
+// meets the rays' rectangle (a star disc mostly reaches far beyond it: on the
+// 1e5-star map one node in seven does), one wavefront per node: L2L from the
 // parent (lane l: coefficient l), M2L from the same-level interaction nodes
 // through the factorised operator (the shared real matrix on the matrix
 // cores, the scalings on the vector units), P2L from the stars of
 // interaction squares inside coarser leaves
 template <class R>
-__global__ __launch_bounds__(64) void k_downward(int64_t lo, int64_t hi, int lev, int p, double L0,
+__global__ __launch_bounds__(64) void k_downward(int64_t lo, int lev, int p, double L0,
+                                                  const int32_t *__restrict__ act,
                                                   const uint64_t *__restrict__ code, const int32_t *__restrict__ parent,
                                                   const IEntry *__restrict__ ilist, const double *__restrict__ sx,
                                                   const double *__restrict__ sy, const double *__restrict__ sm,
@@ -218,9 +219,21 @@ __global__ __launch_bounds__(64) void k_downward(int64_t lo, int64_t hi, int lev
     using V4 = typename V4T<R>::t;
     __shared__ DownLds<R> L;   // one wavefront per workgroup and node
     const int lane = threadIdx.x;
-    const int64_t q = lo + (int64_t)blockIdx.x;
-    if (q >= hi) return;
     const int P1 = p + 1;
+    const int64_t q = act[lo + blockIdx.x];
+    const int lgr = p <= 16 ? 4 : 5;
+    const int mt_n = (p + 15) / 16, kt_n = (p + 3) / 4;
+    const int r = lane & 15, g4 = lane >> 4;
+    // this lane's operands of P for every product below, loaded once: P is the
+    // same for every node and group, and reading it inside the product loop
+    // made each matrix-core step wait for a global load
+    constexpr int KTMAX = (MAX_ORDER + 4) / 4;
+    R pa[KTMAX], pb[KTMAX];
+#pragma unroll
+    for (int ks = 0; ks < KTMAX; ++ks) {
+        pa[ks] = ks < kt_n ? Pm[r * 32 + ks * 4 + g4] : (R)0;
+        pb[ks] = ks < kt_n && mt_n > 1 ? Pm[(16 + r) * 32 + ks * 4 + g4] : (R)0;
+    }
     const uint64_t c = code[q];
     // the node's M2L sources into slots 0 .. ns-1 (lanes 0..26 hold the entries)
     const IEntry *list = ilist + q * NLIST;
@@ -241,19 +254,6 @@ __global__ __launch_bounds__(64) void k_downward(int64_t lo, int64_t hi, int lev
     const int l = lane;
     const R il = l > 0 ? (R)1 / (R)l : (R)0;
     C2 acc = Cx<R>::make(0, 0);
-    const int lgr = p <= 16 ? 4 : 5;
-    const int mt_n = (p + 15) / 16, kt_n = (p + 3) / 4;
-    const int r = lane & 15, g4 = lane >> 4;
-    // this lane's operands of P for every product below, loaded once: P is the
-    // same for every node and group, and reading it inside the product loop
-    // made each matrix-core step wait for a global load
-    constexpr int KTMAX = (MAX_ORDER + 4) / 4;
-    R pa[KTMAX], pb[KTMAX];
-#pragma unroll
-    for (int ks = 0; ks < KTMAX; ++ks) {
-        pa[ks] = ks < kt_n ? Pm[r * 32 + ks * 4 + g4] : (R)0;
-        pb[ks] = ks < kt_n && mt_n > 1 ? Pm[(16 + r) * 32 + ks * 4 + g4] : (R)0;
-    }
     for (int g0 = 0; g0 < ns; g0 += GS) {
         const int gn = min(GS, ns - g0);
         const int ncol = ((2 * gn + 15) / 16) * 16;
@@ -345,10 +345,11 @@ __global__ __launch_bounds__(64) void k_downward(int64_t lo, int64_t hi, int lev
     // L2L from the parent (levels 0 and 1 have no far field)
     if (lev >= 3) {
         const int quad = (int)((c & 1ull) | (((c >> 1) & 1ull) << 1));
-        const C2 *op = l2l + (quad * P1 + l) * P1;
+        const C2 *op = l2l + quad * P1 * P1 + l;
         const C2 *cp = local + (int64_t)parent[q] * P1;
-        for (int k = l; k <= p; ++k) {
-            const C2 o = op[k], v = cp[k];
+#pragma unroll 4
+        for (int k = 1; k <= p; ++k) {   // (the table is 0 for k < l)
+            const C2 o = op[k * P1], v = cp[k];
             acc.x += o.x * v.x - o.y * v.y;
             acc.y += o.x * v.y + o.y * v.x;
         }
@@ -365,64 +366,81 @@ __global__ void k_zero2(C2 *a, int64_t n)
     if (t < n) a[t] = C2{0, 0};
 }
 
-// per-leaf data for the ray kernels: geometry, the far field at the centre
-// (FP64), derivative of the Taylor series (rounded to R) and the stars of the
-// leaf's 3x3 block relative to its centre (FP64 in both modes: a ray's offset
-// from a star is formed from them)
+// per-leaf data for the ray kernels, of the leaves that meet the rays'
+// rectangle: geometry, the far field at the centre (FP64), derivative of the
+// Taylor series (rounded to R) and the stars of the leaf's 3x3 block relative
+// to its centre (FP64 in both modes: a ray's offset from a star is formed from
+// them).  One wavefront per leaf: lane l its coefficient l, lanes 0 .. 8 the
+// star ranges of the block's squares (from the colleague references), then
+// every lane copies stars.  (One thread per leaf, searching the whole key
+// array for each square, spent 83 us on the latency of its loads for the
+// 1e5-star map's 59k leaves, and 45 us for 1000 stars.)
 template <class R>
-__global__ void k_leaf_tables(int64_t nleaves, int p, double L0, const int32_t *__restrict__ leaf_node,
+__global__ __launch_bounds__(BLK) void k_leaf_tables(int64_t nleaves, int p, double L0, RayBox box,
+                              const int32_t *__restrict__ leaf_node,
                               const uint64_t *__restrict__ code, const int32_t *__restrict__ level,
-                              const int32_t *__restrict__ block, const int32_t *__restrict__ near_offs,
-                              const uint64_t *__restrict__ keys, int32_t n, const double *__restrict__ sx,
+                              const int32_t *__restrict__ near_offs, const int32_t *__restrict__ coll,
+                              const int32_t *__restrict__ slo, const int32_t *__restrict__ shi,
+                              const uint64_t *__restrict__ keys, const double *__restrict__ sx,
                               const double *__restrict__ sy, const double *__restrict__ sm,
                               const double2 *__restrict__ local, LeafInfo *__restrict__ info,
                               typename Cx<R>::c2 *__restrict__ deriv, double4 *__restrict__ near)
 {
-    int64_t lf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t lf = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
     if (lf >= nleaves) return;
-    int32_t q = leaf_node[lf];
-    int lev = level[q];
-    uint64_t c = code[q];
+    const int32_t q = leaf_node[lf];
+    const int lev = level[q];
+    const uint64_t c = code[q];
+    if (!in_box(c, lev, L0, box)) return;
     double cx, cy, L, invL;
     node_geom(c, lev, L0, cx, cy, L, invL);
-    LeafInfo li;
-    li.cx = cx;
-    li.cy = cy;
-    li.L = L;
-    li.invL = invL;
-    li.near_off = near_offs[lf];
-    li.near_cnt = block[q];
-    li.a_lo = li.na = li.b_lo = li.nb = li.ntx = li.pad = 0;
-    const int P1 = p + 1;
-    // d psi / dz = (1/L) sum_{l>=1} l c_l zeta^(l-1); its value at the centre
-    // (l = 1) is the whole field of the far stars, kept in FP64
-    const double2 d0 = cscale(local[(int64_t)q * P1 + 1], invL);
-    li.f0x = d0.x;
-    li.f0y = d0.y;
-    info[lf] = li;
-    for (int l = 0; l < p; ++l) {
-        const double2 d = cscale(local[(int64_t)q * P1 + l + 1], (double)(l + 1) * invL);
-        deriv[lf * p + l] = Cx<R>::make((R)d.x, (R)d.y);
+    // star ranges of the 3x3 block
+    int32_t s0 = 0, s1 = 0;
+    if (lane < 9) {
+        const int64_t a = (int64_t)compact_bits(c) + lane % 3 - 1, b = (int64_t)compact_bits(c >> 1) + lane / 3 - 1;
+        const int32_t ref = coll[(int64_t)q * 9 + lane];   // -1 outside the root
+        if (ref != -1) ref_stars(ref, morton2((uint32_t)a, (uint32_t)b), 2 * (KEY_BITS - lev), slo, shi, keys, s0, s1);
     }
-    uint32_t i = compact_bits(c), j = compact_bits(c >> 1);
-    int64_t side = 1ll << lev;
-    int sh = 2 * (KEY_BITS - lev);
-    int32_t o = li.near_off;
-    for (int dj = -1; dj <= 1; ++dj)
-        for (int di = -1; di <= 1; ++di) {
-            int64_t a = (int64_t)i + di, b = (int64_t)j + dj;
-            if (a < 0 || b < 0 || a >= side || b >= side) continue;
-            uint64_t cc = morton2((uint32_t)a, (uint32_t)b);
-            int32_t s0 = lower_bound_u64(keys, n, cc << sh), s1 = lower_bound_u64(keys, n, (cc + 1) << sh);
-            for (int32_t s = s0; s < s1; ++s) near[o++] = make_double4(sx[s] - cx, sy[s] - cy, sm[s], 0.0);
-        }
+    int total;
+    const int excl = wave_excl_scan(s1 - s0, lane, total);
+    const int32_t off = near_offs[lf];
+    if (lane == 0) {
+        LeafInfo li;
+        li.cx = cx;
+        li.cy = cy;
+        li.L = L;
+        li.invL = invL;
+        li.near_off = off;
+        li.near_cnt = total;
+        li.a_lo = li.na = li.b_lo = li.nb = li.ntx = li.pad = 0;
+        // d psi / dz = (1/L) sum_{l>=1} l c_l zeta^(l-1); its value at the centre
+        // (l = 1) is the whole field of the far stars, kept in FP64
+        const double2 d0 = cscale(local[(int64_t)q * (p + 1) + 1], invL);
+        li.f0x = d0.x;
+        li.f0y = d0.y;
+        info[lf] = li;
+    }
+    if (lane < p) {
+        const double2 d = cscale(local[(int64_t)q * (p + 1) + lane + 1], (double)(lane + 1) * invL);
+        deriv[lf * p + lane] = Cx<R>::make((R)d.x, (R)d.y);
+    }
+    for (int base = 0; base < total; base += 64) {
+        const int item = base + lane;
+        const int e = wave_find(excl, item);
+        const int32_t s = __shfl(s0, e, 64) + item - __shfl(excl, e, 64);
+        if (item < total) near[off + item] = make_double4(sx[s] - cx, sy[s] - cy, sm[s], 0.0);
+    }
 }
 
-__global__ void k_leaf_block(int64_t nleaves, const int32_t *__restrict__ leaf_node,
+__global__ void k_leaf_block(int64_t nleaves, double L0, RayBox box, const int32_t *__restrict__ leaf_node,
+                             const uint64_t *__restrict__ code, const int32_t *__restrict__ level,
                              const int32_t *__restrict__ block, int32_t *__restrict__ cnt)
 {
     int64_t lf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (lf < nleaves) cnt[lf] = block[leaf_node[lf]];
+    if (lf >= nleaves) return;
+    const int32_t q = leaf_node[lf];
+    cnt[lf] = in_box(code[q], level[q], L0, box) ? block[q] : 0;
 }
 
 }  // namespace
@@ -474,17 +492,17 @@ void run_fmm_t(mlm_lens *lens, Tree &T, int p, hipStream_t st, typename Cx<R>::c
     local = static_cast<C2 *>(ws.local.reserve((size_t)T.nnodes * P1 * sizeof(C2)));
     // upward
     for (int lev = T.nlevels - 1; lev >= 0; --lev) {
-        int64_t lo = T.level_lo[lev], hi = T.level_hi[lev], nt = (hi - lo) * P1;
-        hipLaunchKernelGGL(k_upward<R>, dim3(nblocks(nt)), dim3(BLK), 0, st, lo, hi, lev, p, T.L0, T.code, T.leaf,
+        int64_t lo = T.level_lo[lev], hi = T.level_hi[lev];
+        hipLaunchKernelGGL(k_upward<R>, dim3(nblocks((hi - lo) * 32)), dim3(BLK), 0, st, lo, hi, lev, p, T.L0, T.code, T.leaf,
                            T.slo, T.shi, T.child0, T.x, T.y, T.m, ws.ops_m2m.as<C2>(), mult);
     }
     // downward: levels 0, 1 have no far field
     int64_t top = T.nlevels > 2 ? T.level_lo[2] : T.nnodes;
     hipLaunchKernelGGL(k_zero2<C2>, dim3(nblocks(top * P1)), dim3(BLK), 0, st, local, top * P1);
     for (int lev = 2; lev < T.nlevels; ++lev) {
-        const int64_t lo = T.level_lo[lev], hi = T.level_hi[lev];
-        hipLaunchKernelGGL(k_downward<R>, dim3((unsigned)(hi - lo)), dim3(64), 0, st, lo, hi, lev, p, T.L0,
-                           T.code, T.parent, T.ilist, T.x, T.y, T.m, Sf, Tf, Pm, ws.ops_l2l.as<C2>(), mult, local);
+        if (T.nactive[lev] == 0) break;   // nor has any finer level
+        hipLaunchKernelGGL(k_downward<R>, dim3((unsigned)T.nactive[lev]), dim3(64), 0, st, T.level_lo[lev], lev, p,
+                           T.L0, T.active, T.code, T.parent, T.ilist, T.x, T.y, T.m, Sf, Tf, Pm, ws.ops_l2l.as<C2>(), mult, local);
     }
 }
 
@@ -506,20 +524,21 @@ void build_leaf_tables(mlm_lens *lens, Tree &T, hipStream_t st)
     int64_t nl = T.nleaves;
     int32_t *cnt = static_cast<int32_t *>(ws.flags.reserve(nl * 4));
     int32_t *offs = static_cast<int32_t *>(ws.near_offs.reserve(nl * 4));
-    hipLaunchKernelGGL(k_leaf_block, dim3(nblocks(nl)), dim3(BLK), 0, st, nl, T.leaf_node, T.block, cnt);
+    hipLaunchKernelGGL(k_leaf_block, dim3(nblocks(nl)), dim3(BLK), 0, st, nl, T.L0, ray_box(T), T.leaf_node,
+                       T.code, T.level, T.block, cnt);
     T.near_total = scan_total_public(lens, cnt, offs, nl, st);
     T.leaves = static_cast<LeafInfo *>(ws.leaves.reserve(nl * sizeof(LeafInfo)));
     const size_t nn = (size_t)(T.near_total > 0 ? T.near_total : 1);
     T.near = static_cast<double4 *>(ws.near.reserve(nn * sizeof(double4)));
     if (T.mixed) {
         T.deriv_f = static_cast<float2 *>(ws.deriv.reserve((size_t)nl * T.p * sizeof(float2)));
-        hipLaunchKernelGGL(k_leaf_tables<float>, dim3(nblocks(nl, 64)), dim3(64), 0, st, nl, T.p, T.L0, T.leaf_node,
-                           T.code, T.level, T.block, offs, T.keys, (int32_t)T.n, T.x, T.y, T.m, T.local,
+        hipLaunchKernelGGL(k_leaf_tables<float>, dim3(nblocks(nl * 64)), dim3(BLK), 0, st, nl, T.p, T.L0, ray_box(T),
+                           T.leaf_node, T.code, T.level, offs, T.coll, T.slo, T.shi, T.keys, T.x, T.y, T.m, T.local,
                            T.leaves, T.deriv_f, T.near);
     } else {
         T.deriv = static_cast<double2 *>(ws.deriv.reserve((size_t)nl * T.p * sizeof(double2)));
-        hipLaunchKernelGGL(k_leaf_tables<double>, dim3(nblocks(nl, 64)), dim3(64), 0, st, nl, T.p, T.L0,
-                           T.leaf_node, T.code, T.level, T.block, offs, T.keys, (int32_t)T.n, T.x, T.y, T.m, T.local,
+        hipLaunchKernelGGL(k_leaf_tables<double>, dim3(nblocks(nl * 64)), dim3(BLK), 0, st, nl, T.p, T.L0, ray_box(T),
+                           T.leaf_node, T.code, T.level, offs, T.coll, T.slo, T.shi, T.keys, T.x, T.y, T.m, T.local,
                            T.leaves, T.deriv, T.near);
     }
 }

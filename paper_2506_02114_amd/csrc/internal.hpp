@@ -75,6 +75,7 @@ Arena *&thread_arena();
 // ---------------------------------------------------------------------------
 constexpr int KEY_BITS = 24;     // square index bits per axis at the finest level
 constexpr int MAX_ORDER = 31;    // expansion order limit (32 coefficients)
+constexpr int MAX_LEVELS = 32;   // at least KEY_BITS + 1 tree levels
 constexpr int NLIST = 27;        // interaction squares per node
 constexpr int TILE = 8;          // ray tiles are TILE x TILE grid vertices
 
@@ -233,6 +234,13 @@ struct Tree {
     int32_t *parent = nullptr, *child0 = nullptr, *node_leaf = nullptr;
     int32_t *leaf_node = nullptr;
     IEntry *ilist = nullptr;
+    int32_t *coll = nullptr;             // 9 colleague references per node (dev.hpp)
+    // the rectangle that holds every ray of the request: only nodes whose
+    // square meets it need interaction lists, local expansions and leaf tables
+    bool boxed = false;
+    double box[4] = {0, 0, 0, 0};        // x from, to, y from, to
+    int32_t *active = nullptr;           // nodes to evaluate, level by level from level_lo[level]
+    int32_t nactive[MAX_LEVELS] = {};    // their number per level
     bool mixed = false;                  // FP32 Taylor evaluation (deriv_f) and near field
     double2 *mult = nullptr, *local = nullptr;   // FP64 in both modes
     // leaf tables
@@ -246,7 +254,7 @@ struct Tree {
 struct Workspace {
     DevBuf keys_in, keys, idx_in, idx, sx, sy, sm, scan_tmp;
     DevBuf code, level, leaf, slo, shi, block, parent, child0, coll, node_leaf, leaf_node, flags, offs;
-    DevBuf ilist, mult, local, ops_m2m, ops_m2l, ops_l2l;
+    DevBuf ilist, active, mult, local, ops_m2m, ops_m2l, ops_l2l;
     DevBuf leaves, near, deriv, near_offs;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigrows, bigrow0, rowoff, nbnd, nbndoff, diff, bandcnt, bandoff,
         bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, rsub0, rsub1, bitems, bqueue, tune_map;
@@ -254,7 +262,8 @@ struct Workspace {
     hipEvent_t fork = nullptr, join = nullptr;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
-    int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}
+    int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
+                                          // MAX_LEVELS counts of listed nodes
     int64_t spin_seq = 0;                 // sequence number of the last total asked for
     int ops_p = -1;                       // expansion order of the operator tables
     ~Workspace();
@@ -305,6 +314,10 @@ int64_t field_sample(const mlm_field_params &F, std::vector<double> &x, std::vec
 void shooting_region(const mlm_lens_params &P, double mean_m, double mean_m2, double ext1, double ext2,
                      const mlm_map_request &q, double &X1, double &X2, double &dX1, double &dX2);
 bool has_psi3(const mlm_lens_params &P);
+
+// the rays of vertex (or cell) rows [vb0, vb1] of the grid and of every
+// refinement of its cells: the rectangle the tree is evaluated in
+void box_rays(Tree &T, const Region &R, int64_t vb0, int64_t vb1);
 
 // tree.hip
 void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tree &T,

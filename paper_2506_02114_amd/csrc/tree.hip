@@ -10,8 +10,10 @@
 // 3x3 neighbourhood as such references ("colleagues"), found from its
 // parent's in O(1), and the block count and the interaction lists follow
 // from them without searching the whole key array.
+#include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 
 #include "dev.hpp"
 
@@ -20,6 +22,10 @@ namespace mlm {
 namespace {
 
 constexpr int BLK = 256;
+// first node of each level
+struct LevelStarts {
+    int32_t lo[MAX_LEVELS];
+};
 
 inline unsigned nblocks(int64_t n, int b = BLK) { return (unsigned)((n + b - 1) / b); }
 
@@ -69,24 +75,6 @@ __global__ void k_level(int64_t lo, int64_t hi, int lev, const uint64_t *__restr
     const int32_t s0 = a + lower_bound_u64(keys + a, b - a, c << sh);
     slo[q] = s0;
     shi[q] = s0 + lower_bound_u64(keys + s0, b - s0, (c + 1) << sh);
-}
-
-// A colleague reference: >= 0 a node of the same level, -1 nothing (outside
-// the root), <= -2 the leaf -(ref + 2) of a coarser level containing the square.
-// Stars of square `sc` (level shift sh) inside the reference's range.
-__device__ inline void ref_stars(int32_t ref, uint64_t sc, int sh, const int32_t *__restrict__ slo,
-                                 const int32_t *__restrict__ shi, const uint64_t *__restrict__ keys, int32_t &s0,
-                                 int32_t &s1)
-{
-    s0 = s1 = 0;
-    if (ref >= 0) {
-        s0 = slo[ref];
-        s1 = shi[ref];
-    } else if (ref <= -2) {
-        const int32_t L = -ref - 2, a = slo[L], b = shi[L];
-        s0 = a + lower_bound_u64(keys + a, b - a, sc << sh);
-        s1 = s0 + lower_bound_u64(keys + s0, b - s0, (sc + 1) << sh);
-    }
 }
 
 // square (a, b) of level lev, one of the children of the parent-level
@@ -176,52 +164,87 @@ __global__ void k_leaf_index(int64_t nnodes, const int32_t *__restrict__ leaf,
 
 __global__ void k_zero_first(int64_t *p) { p[0] = 0; }
 
-// interaction squares of every node of level >= 2: the children of the
-// parent's 3x3 block that are outside the node's own 3x3 block (27 of them),
-// read from the parent's colleagues: a node (M2L), a part of a leaf (P2L from
-// its stars in the square) or nothing
-__global__ void k_ilist(int64_t lo, int64_t hi, const uint64_t *__restrict__ code,
-                        const int32_t *__restrict__ level, const int32_t *__restrict__ parent,
-                        const int32_t *__restrict__ child0, const int32_t *__restrict__ slo,
-                        const int32_t *__restrict__ shi, const uint64_t *__restrict__ keys,
-                        const int32_t *__restrict__ coll, IEntry *__restrict__ list)
+__global__ void k_zero_counts(int32_t *p, int n)
+{
+    if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+}
+
+// (dst: pinned host memory)
+__global__ void k_copy_counts(const int32_t *__restrict__ src, int32_t *dst, int n)
+{
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = src[threadIdx.x];
+    __threadfence_system();
+}
+
+// The nodes of levels >= 2 whose square meets the rays' rectangle, listed level
+// by level (level lev's from act[level_lo[lev]] on, in no particular order:
+// nodes are evaluated independently) and counted in cnt[lev] (zeroed).  Lanes
+// of a wavefront whose nodes share a level take one range of its list.
+__global__ __launch_bounds__(BLK) void k_active(int64_t lo, int64_t hi, double L0, RayBox box,
+                                                const uint64_t *__restrict__ code,
+                                                const int32_t *__restrict__ level, LevelStarts starts,
+                                                int32_t *__restrict__ act, int32_t *__restrict__ cnt)
 {
     const int64_t q = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= hi) return;
-    const int lev = level[q];
+    const int lane = threadIdx.x & 63;
+    const int lev = q < hi ? level[q] : -1;
+    unsigned long long todo = __ballot(lev >= 0 && in_box(code[q], lev, L0, box));
+    while (todo) {
+        const int lead = __ffsll(todo) - 1;
+        const int l = __shfl(lev, lead, 64);
+        const unsigned long long same = __ballot((todo >> lane & 1) && lev == l);
+        int base = 0;
+        if (lane == lead) base = atomicAdd(cnt + l, __popcll(same));
+        base = __shfl(base, lead, 64);
+        if (same >> lane & 1) act[starts.lo[l] + base + __popcll(same & ((1ull << lane) - 1ull))] = (int32_t)q;
+        todo &= ~same;
+    }
+}
+
+// interaction squares of the listed nodes of levels >= 2: the children of the
+// parent's 3x3 block that are outside the node's own 3x3 block (27 of them),
+// read from the parent's colleagues: a node (M2L), a part of a leaf (P2L from
+// its stars in the square) or nothing.  One wavefront per node, a lane per
+// child square (36, the 27 kept in lane order): a thread walking its node's
+// squares one after the other spent the pass on the latency of their loads
+// (43 us for 78k nodes).
+__global__ __launch_bounds__(BLK) void k_ilist(int64_t lo, int n, int lev, const int32_t *__restrict__ act,
+                                               const uint64_t *__restrict__ code,
+                                               const int32_t *__restrict__ parent,
+                                               const int32_t *__restrict__ child0, const int32_t *__restrict__ slo,
+                                               const int32_t *__restrict__ shi, const uint64_t *__restrict__ keys,
+                                               const int32_t *__restrict__ coll, IEntry *__restrict__ list)
+{
+    const int lane = threadIdx.x & 63;
+    const int sh = 2 * (KEY_BITS - lev), k = blockIdx.x * (BLK / 64) + (threadIdx.x >> 6);
+    if (k >= n) return;
+    const int64_t q = act[lo + k];
     const uint64_t c = code[q];
     const int64_t i = compact_bits(c), j = compact_bits(c >> 1);
-    const int64_t pi = i >> 1, pj = j >> 1;
-    const int sh = 2 * (KEY_BITS - lev);
     const int32_t *pc = coll + (int64_t)parent[q] * 9;
-    int e = 0;
-    for (int qj = -1; qj <= 1; ++qj)
-        for (int qi = -1; qi <= 1; ++qi) {
-            const int32_t pref = pc[(qj + 1) * 3 + (qi + 1)];
-            for (int cj = 0; cj < 2; ++cj)
-                for (int ci = 0; ci < 2; ++ci) {
-                    const int64_t si = 2 * (pi + qi) + ci, sj = 2 * (pj + qj) + cj;
-                    const int64_t dx = si - i, dy = sj - j;
-                    if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1) continue;
-                    IEntry en;
-                    en.off = (int32_t)((dx + 3) + 7 * (dy + 3));
-                    en.src = -2;
-                    en.slo = en.shi = 0;
-                    const int32_t ref = child_ref(pref, (uint32_t)si, (uint32_t)sj, child0);
-                    if (ref >= 0) {
-                        en.src = ref;
-                    } else if (ref <= -2) {
-                        int32_t s0, s1;
-                        ref_stars(ref, morton2((uint32_t)si, (uint32_t)sj), sh, slo, shi, keys, s0, s1);
-                        if (s1 > s0) {
-                            en.src = -1;
-                            en.slo = s0;
-                            en.shi = s1;
-                        }
-                    }
-                    list[(q - lo) * NLIST + e++] = en;
-                }
+    const int b = lane >> 2;   // parent's colleague, its child (lane & 3)
+    const int64_t si = 2 * ((i >> 1) + b % 3 - 1) + (lane & 1), sj = 2 * ((j >> 1) + b / 3 - 1) + (lane >> 1 & 1);
+    const int64_t dx = si - i, dy = sj - j;
+    const bool keep = lane < 36 && !(dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1);
+    const int e = __popcll(__ballot(keep) & ((1ull << lane) - 1ull));
+    if (!keep) return;
+    IEntry en;
+    en.off = (int32_t)((dx + 3) + 7 * (dy + 3));
+    en.src = -2;
+    en.slo = en.shi = 0;
+    const int32_t ref = child_ref(pc[b], (uint32_t)si, (uint32_t)sj, child0);
+    if (ref >= 0) {
+        en.src = ref;
+    } else if (ref <= -2) {
+        int32_t s0, s1;
+        ref_stars(ref, morton2((uint32_t)si, (uint32_t)sj), sh, slo, shi, keys, s0, s1);
+        if (s1 > s0) {
+            en.src = -1;
+            en.slo = s0;
+            en.shi = s1;
         }
+    }
+    list[q * NLIST + e] = en;
 }
 
 template <class T>
@@ -252,7 +275,7 @@ TotalSlot total_slot(mlm_lens *lens)
         return t;
     }
     Workspace &ws = lens->ws;
-    if (!ws.spin) ws.spin = static_cast<int64_t *>(coherent_pinned(2 * sizeof(int64_t)));
+    if (!ws.spin) ws.spin = static_cast<int64_t *>(coherent_pinned(2 * sizeof(int64_t) + MAX_LEVELS * sizeof(int32_t)));
     t.host = ws.spin;
     t.seq = ++ws.spin_seq;
     return t;
@@ -322,6 +345,23 @@ int64_t scan_total_i64(mlm_lens *lens, const int64_t *in, int64_t *out, int64_t 
     return read_total(t, st);
 }
 
+void box_rays(Tree &T, const Region &R, int64_t vb0, int64_t vb1)
+{
+    // one cell and the rounding of the largest coordinate to spare
+    const double e1 = R.d1 + 1e-12 * R.L0, e2 = R.d2 + 1e-12 * R.L0;
+    T.boxed = true;
+    T.box[0] = R.x0 - e1;
+    T.box[1] = R.x0 + (double)(R.nr1 - 1) * R.d1 + e1;
+    T.box[2] = R.y0 + (double)vb0 * R.d2 - e2;
+    T.box[3] = R.y0 + (double)vb1 * R.d2 + e2;
+}
+
+RayBox ray_box(const Tree &T)
+{
+    if (!T.boxed) return RayBox{-HUGE_VAL, HUGE_VAL, -HUGE_VAL, HUGE_VAL};
+    return RayBox{T.box[0], T.box[1], T.box[2], T.box[3]};
+}
+
 void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tree &T, hipStream_t st)
 {
     Workspace &ws = lens->ws;
@@ -355,7 +395,7 @@ void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tre
     T.level_lo.assign(1, 0);
     T.level_hi.assign(1, 1);
     size_t used = 0;
-    int32_t *coll = nullptr;   // 9 colleague references per node
+    int32_t *&coll = T.coll;   // 9 colleague references per node
     auto ensure = [&](size_t need) {
         T.code = grow_keep<uint64_t>(ws.code, used, need, st);
         T.level = grow_keep<int32_t>(ws.level, used, need, st);
@@ -393,20 +433,47 @@ void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tre
     }
     T.nnodes = T.level_hi.back();
 
-    // 3. leaf numbering
+    // 3. the nodes of levels >= 2 that the rays need, listed level by level
+    // (in the sort's input buffer, free by now, where it is large enough: it
+    // is unless leaves hold a star or two), their counts stored to the host
+    // before the total it next waits for
+    const size_t act_bytes = (size_t)(T.nnodes + MAX_LEVELS) * sizeof(int32_t);
+    T.active = static_cast<int32_t *>(act_bytes <= ws.keys_in.cap ? ws.keys_in.p : ws.active.reserve(act_bytes));
+    int32_t *cnt = T.active + T.nnodes;
+    if (T.nlevels > 2) {
+        const int64_t lo = T.level_lo[2], hi = T.nnodes;
+        LevelStarts starts{};
+        for (int lev = 0; lev < T.nlevels; ++lev) starts.lo[lev] = (int32_t)T.level_lo[lev];
+        hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(64), 0, st, cnt, MAX_LEVELS);
+        hipLaunchKernelGGL(k_active, dim3(nblocks(hi - lo)), dim3(BLK), 0, st, lo, hi, T.L0, ray_box(T), T.code,
+                           T.level, starts, T.active, cnt);
+    }
+    const TotalSlot slot = total_slot(lens);
+    int32_t *host_cnt = slot.host ? reinterpret_cast<int32_t *>(slot.host + 2) : nullptr;
+    if (T.nlevels > 2 && host_cnt) hipLaunchKernelGGL(k_copy_counts, dim3(1), dim3(64), 0, st, cnt, host_cnt, MAX_LEVELS);
+
+    // 4. leaf numbering
     int32_t *offs = static_cast<int32_t *>(ws.offs.reserve(T.nnodes * 4));
     T.node_leaf = static_cast<int32_t *>(ws.node_leaf.reserve(T.nnodes * 4));
-    T.nleaves = scan_total(lens, T.leaf, offs, T.nnodes, st);
+    dev_scan_i32(T.leaf, offs, T.nnodes, false, scan_tmp(ws, scan_tmp_bytes(T.nnodes)), slot.dev, slot.host, slot.seq, st);
+    T.nleaves = read_total(slot, st);
     T.leaf_node = static_cast<int32_t *>(ws.leaf_node.reserve(T.nleaves * 4));
     hipLaunchKernelGGL(k_leaf_index, dim3(nblocks(T.nnodes)), dim3(BLK), 0, st, T.nnodes, T.leaf, offs,
                        T.node_leaf, T.leaf_node);
 
-    // 4. interaction lists of the nodes of levels >= 2
+    // 5. interaction lists of the listed nodes
     T.ilist = static_cast<IEntry *>(ws.ilist.reserve((size_t)T.nnodes * NLIST * sizeof(IEntry)));
     if (T.nlevels > 2) {
-        int64_t lo = T.level_lo[2], hi = T.nnodes;
-        hipLaunchKernelGGL(k_ilist, dim3(nblocks(hi - lo)), dim3(BLK), 0, st, lo, hi, T.code, T.level, T.parent,
-                           T.child0, T.slo, T.shi, T.keys, coll, T.ilist + lo * NLIST);
+        if (host_cnt) {
+            std::copy(host_cnt, host_cnt + MAX_LEVELS, T.nactive);
+        } else {
+            MLM_HIP(hipMemcpyAsync(T.nactive, cnt, sizeof T.nactive, hipMemcpyDeviceToHost, st));
+            MLM_HIP(hipStreamSynchronize(st));
+        }
+        for (int lev = 2; lev < T.nlevels && T.nactive[lev] > 0; ++lev)
+            hipLaunchKernelGGL(k_ilist, dim3(nblocks(T.nactive[lev], BLK / 64)), dim3(BLK), 0, st, T.level_lo[lev],
+                               T.nactive[lev], lev, T.active, T.code, T.parent, T.child0, T.slo, T.shi, T.keys, coll,
+                               T.ilist);
     }
 }
 
