@@ -175,6 +175,7 @@ namespace {
 
 constexpr int64_t STRIP_VERTS = 1ll << 26;   // vertices per strip buffer (1 GiB of double2)
 constexpr int64_t IRS_STRIP_RAYS = 1ll << 30;   // rays per inverse-ray-shooting launch (nothing stored per ray)
+constexpr int64_t IRS_STRIP_PATCH_RAYS = 1ll << 29;   // the same by patches (448 bytes of coefficients per 1024 rays)
 constexpr double FINE_CELLS_PER_PIXEL = 256.0;  // cells per map pixel from which the cell pass takes its 16 x 16 window
 
 __global__ void k_fill(double *p, int64_t n, double v)
@@ -868,17 +869,21 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         unsigned long long *irs_cnt =
             static_cast<unsigned long long *>(ws.irs_counts.reserve((size_t)npix * sizeof(unsigned long long)));
         hipLaunchKernelGGL(k_zero_u64n, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, irs_cnt, npix);
-        const int64_t rows = std::max<int64_t>(1, IRS_STRIP_RAYS / std::max<int64_t>(R.nr1 - 1, 1));
+        // (inside a scratch arena, without room for the patches' coefficients,
+        // rays are shot one by one)
+        const int side = fmm && !thread_arena() ? patch_side(R, T, cb1 - cb0) : 0;
+        const int64_t rows = std::max<int64_t>(1, (side ? IRS_STRIP_PATCH_RAYS : IRS_STRIP_RAYS) / std::max<int64_t>(R.nr1 - 1, 1));
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             const int64_t r1 = std::min(cb1, r0 + rows);
             int64_t nt = 0;
             if (fmm) {
-                nt = plan_tiles(lens, T, R, r0, r1, st, true);
+                nt = plan_tiles(lens, T, R, r0, r1, st, true, side ? side : TILE);
                 hipLaunchKernelGGL(k_strip_work, dim3((unsigned)((T.nleaves + 255) / 256)), dim3(256), 0, st,
                                    T.nleaves, T.leaves, cnt);
             }
             const int ea = tm.mark();
-            if (fmm) launch_shoot_irs(lens, T, R, lc, g, nt, r0, irs_cnt, st);
+            if (side) launch_irs_patches(lens, T, R, lc, g, nt, r0, irs_cnt, st);
+            else if (fmm) launch_shoot_irs(lens, T, R, lc, g, nt, r0, irs_cnt, st);
             else launch_shoot_irs_direct(lens, R, lc, g, r0, r1, irs_cnt, st);
             const int eb = tm.mark();
             MLM_HIP(hipStreamSynchronize(st));
@@ -914,6 +919,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         // cells (the shooting region covers the map, so cells per map pixel
         // is how finely the cells divide a pixel on average).
         const bool fine = (double)(R.nr1 - 1) * (double)(R.nr2 - 1) >= FINE_CELLS_PER_PIXEL * (double)g.n1 * (double)g.n2;
+        const int side = fmm && !q.w_out && !thread_arena() ? patch_side(R, T, cb1 - cb0 + 1) : 0;
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             int64_t r1 = std::min(cb1, r0 + rows_per_strip - 1);   // cells [r0, r1), vertex rows [r0, r1]
             int64_t vb0 = r0, vb1 = r1 + 1;
@@ -921,12 +927,13 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             if (wdev) w_here = q.device_out ? wdev + 2 * (vb0 - cb0) * R.nr1 : wdev;
             int64_t nt = 0;
             if (fmm) {
-                nt = plan_tiles(lens, T, R, vb0, vb1, st);
+                nt = plan_tiles(lens, T, R, vb0, vb1, st, false, side ? side : TILE);
                 hipLaunchKernelGGL(k_strip_work, dim3((unsigned)((T.nleaves + 255) / 256)), dim3(256), 0, st, T.nleaves,
                                    T.leaves, cnt);
             }
             int ea = tm.mark();
-            if (fmm) launch_shoot(lens, T, R, lc, g, nt, vb0, verts, w_here, st);
+            if (side) launch_shoot_patches(lens, T, R, lc, g, nt, vb0, verts, st);
+            else if (fmm) launch_shoot(lens, T, R, lc, g, nt, vb0, verts, w_here, st);
             else launch_shoot_direct(lens, R, lc, g, vb0, vb1, verts, w_here, st);
             int eb = tm.mark();
             // IPM: the cell pass apportions the ordinary triangles; the large ones

@@ -241,6 +241,7 @@ struct Tree {
     double box[4] = {0, 0, 0, 0};        // x from, to, y from, to
     int32_t *active = nullptr;           // nodes to evaluate, level by level from level_lo[level]
     int32_t nactive[MAX_LEVELS] = {};    // their number per level
+    int64_t nactive_leaves = 0;          // leaves that meet the rectangle
     bool mixed = false;                  // FP32 Taylor evaluation (deriv_f) and near field
     double2 *mult = nullptr, *local = nullptr;   // FP64 in both modes
     // leaf tables
@@ -256,6 +257,7 @@ struct Workspace {
     DevBuf code, level, leaf, slo, shi, block, parent, child0, coll, node_leaf, leaf_node, flags, offs;
     DevBuf ilist, active, mult, local, ops_m2m, ops_m2l, ops_l2l;
     DevBuf leaves, near, deriv, near_offs;
+    DevBuf binom, patch_info, patch_coef;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigrows, bigrow0, rowoff, nbnd, nbndoff, diff, bandcnt, bandoff,
         bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, rsub0, rsub1, bitems, bqueue, tune_map;
     hipStream_t side = nullptr;           // second stream of a map: the large-triangle passes beside the cell pass
@@ -332,7 +334,7 @@ LensConst lens_const(const mlm_lens *lens, const Region &R);
 // ray tiles of the grid vertices of rows [vb0, vb1), or (centres) of the
 // cell centres of cell rows [vb0, vb1)
 int64_t plan_tiles(mlm_lens *lens, Tree &T, const Region &R, int64_t vb0, int64_t vb1,
-                   hipStream_t st, bool centres = false);
+                   hipStream_t st, bool centres = false, int tile = TILE);
 // inverse ray shooting of the cell centres of cell rows [cb0, cb1): counts
 // per pixel (n2 x n1) are added to `counts`
 void launch_shoot_irs(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
@@ -347,6 +349,15 @@ bool shoot_staged(const Region &R, const Tree &T);
 void launch_shoot(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc,
                   const MapGeom &g, int64_t ntiles, int64_t vb0, double2 *verts, double *w_out,
                   hipStream_t st);
+// patch.hip: shooting by patches of rays that share one power series, for grids
+// far denser than the stars.  The patch's side (0: shoot ray by ray), for
+// `rows` rows of rays; patches are planned as tiles of that side.
+constexpr double PATCH_RAYS_PER_LEAF = 16384.0;
+int patch_side(const Region &R, const Tree &T, int64_t rows);
+void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
+                          int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st);
+void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
+                        int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st);
 void launch_shoot_direct(mlm_lens *lens, const Region &R, const LensConst &lc, const MapGeom &g,
                          int64_t vb0, int64_t vb1, double2 *verts, double *w_out,
                          hipStream_t st);

@@ -36,7 +36,8 @@ __device__ inline int64_t first_in_cell(double x0, double d, double h, int64_t l
 __global__ void k_tile_counts(int64_t nleaves, const int32_t *__restrict__ leaf_node,
                               const uint64_t *__restrict__ code, const int32_t *__restrict__ level, double L0,
                               int L0_exp, double x0, double d1, int64_t nr1, double y0, double d2, int64_t vb0,
-                              int64_t vb1, double h, LeafInfo *__restrict__ info, int32_t *__restrict__ cnt)
+                              int64_t vb1, double h, int tile, LeafInfo *__restrict__ info,
+                              int32_t *__restrict__ cnt)
 {
     int64_t lf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (lf >= nleaves) return;
@@ -54,8 +55,8 @@ __global__ void k_tile_counts(int64_t nleaves, const int32_t *__restrict__ leaf_
     li.na = (int32_t)(a1 - a0);
     li.b_lo = (int32_t)b0;
     li.nb = (int32_t)(b1 - b0);
-    li.ntx = (li.na + TILE - 1) / TILE;
-    int32_t nty = (li.nb + TILE - 1) / TILE;
+    li.ntx = (li.na + tile - 1) / tile;
+    int32_t nty = (li.nb + tile - 1) / tile;
     cnt[lf] = (li.na > 0 && li.nb > 0) ? li.ntx * nty : 0;
 }
 
@@ -325,7 +326,8 @@ LensConst lens_const(const mlm_lens *lens, const Region &R)
     return lc;
 }
 
-int64_t plan_tiles(mlm_lens *lens, Tree &T, const Region &R, int64_t vb0, int64_t vb1, hipStream_t st, bool centres)
+int64_t plan_tiles(mlm_lens *lens, Tree &T, const Region &R, int64_t vb0, int64_t vb1, hipStream_t st, bool centres,
+                   int tile)
 {
     Workspace &ws = lens->ws;
     int64_t nl = T.nleaves;
@@ -338,7 +340,7 @@ int64_t plan_tiles(mlm_lens *lens, Tree &T, const Region &R, int64_t vb0, int64_
     int32_t *cnt = static_cast<int32_t *>(ws.flags.reserve(nl * 4));
     int32_t *off = static_cast<int32_t *>(ws.tile_off.reserve(nl * 4));
     hipLaunchKernelGGL(k_tile_counts, dim3(nblocks(nl)), dim3(BLK), 0, st, nl, T.leaf_node, T.code, T.level, T.L0,
-                       T.L0_exp, R.x0, R.d1, ncols, R.y0, R.d2, vb0, vb1, h, T.leaves, cnt);
+                       T.L0_exp, R.x0, R.d1, ncols, R.y0, R.d2, vb0, vb1, h, tile, T.leaves, cnt);
     int64_t ntiles = scan_total_public(lens, cnt, off, nl, st);
     if (ntiles > 0) {
         int32_t *tl = static_cast<int32_t *>(ws.tile_leaf.reserve(ntiles * 4));

@@ -22,6 +22,8 @@ namespace mlm {
 namespace {
 
 constexpr int BLK = 256;
+constexpr int ACTIVE_LEAVES = MAX_LEVELS - 1;   // (no tree has that level)
+
 // first node of each level
 struct LevelStarts {
     int32_t lo[MAX_LEVELS];
@@ -178,17 +180,21 @@ __global__ void k_copy_counts(const int32_t *__restrict__ src, int32_t *dst, int
 
 // The nodes of levels >= 2 whose square meets the rays' rectangle, listed level
 // by level (level lev's from act[level_lo[lev]] on, in no particular order:
-// nodes are evaluated independently) and counted in cnt[lev] (zeroed).  Lanes
+// nodes are evaluated independently) and counted in cnt[lev] (zeroed), the
+// leaves among them in cnt[ACTIVE_LEAVES].  Lanes
 // of a wavefront whose nodes share a level take one range of its list.
 __global__ __launch_bounds__(BLK) void k_active(int64_t lo, int64_t hi, double L0, RayBox box,
                                                 const uint64_t *__restrict__ code,
-                                                const int32_t *__restrict__ level, LevelStarts starts,
+                                                const int32_t *__restrict__ level,
+                                                const int32_t *__restrict__ leaf, LevelStarts starts,
                                                 int32_t *__restrict__ act, int32_t *__restrict__ cnt)
 {
     const int64_t q = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const int lev = q < hi ? level[q] : -1;
     unsigned long long todo = __ballot(lev >= 0 && in_box(code[q], lev, L0, box));
+    const unsigned long long leaves = todo & __ballot(lev >= 0 && leaf[q] != 0);
+    if (lane == 0 && leaves) atomicAdd(cnt + ACTIVE_LEAVES, __popcll(leaves));
     while (todo) {
         const int lead = __ffsll(todo) - 1;
         const int l = __shfl(lev, lead, 64);
@@ -446,7 +452,7 @@ void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tre
         for (int lev = 0; lev < T.nlevels; ++lev) starts.lo[lev] = (int32_t)T.level_lo[lev];
         hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(64), 0, st, cnt, MAX_LEVELS);
         hipLaunchKernelGGL(k_active, dim3(nblocks(hi - lo)), dim3(BLK), 0, st, lo, hi, T.L0, ray_box(T), T.code,
-                           T.level, starts, T.active, cnt);
+                           T.level, T.leaf, starts, T.active, cnt);
     }
     const TotalSlot slot = total_slot(lens);
     int32_t *host_cnt = slot.host ? reinterpret_cast<int32_t *>(slot.host + 2) : nullptr;
@@ -462,6 +468,7 @@ void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tre
                        T.node_leaf, T.leaf_node);
 
     // 5. interaction lists of the listed nodes
+    T.nactive_leaves = T.nleaves;
     T.ilist = static_cast<IEntry *>(ws.ilist.reserve((size_t)T.nnodes * NLIST * sizeof(IEntry)));
     if (T.nlevels > 2) {
         if (host_cnt) {
@@ -470,6 +477,7 @@ void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tre
             MLM_HIP(hipMemcpyAsync(T.nactive, cnt, sizeof T.nactive, hipMemcpyDeviceToHost, st));
             MLM_HIP(hipStreamSynchronize(st));
         }
+        T.nactive_leaves = T.nactive[ACTIVE_LEAVES];
         for (int lev = 2; lev < T.nlevels && T.nactive[lev] > 0; ++lev)
             hipLaunchKernelGGL(k_ilist, dim3(nblocks(T.nactive[lev], BLK / 64)), dim3(BLK), 0, st, T.level_lo[lev],
                                T.nactive[lev], lev, T.active, T.code, T.parent, T.child0, T.slo, T.shi, T.keys, coll,
