@@ -253,9 +253,8 @@ typedef struct mlm_map_request {
     double refine_threshold;   /* logit above which the network flags a cell (default 0) */
     struct mlm_refiner *refiner;   /* network for MLM_REFINE_LEARNED */
     int32_t mapping;           /* MLM_MAP_IPM (default) or MLM_MAP_IRS */
-    int32_t one_stream;        /* 0 (default): the large-triangle passes of the IPM run on a
-                                  second stream of the lens beside the cell pass (fork and join
-                                  through events on req->stream); 1: every kernel on req->stream */
+    int32_t one_stream;        /* no effect: every kernel runs on req->stream (the large-triangle
+                                  passes of the IPM once ran on a second one unless this was 1) */
     double x1c, x2c;           /* image-plane centre of the shooting region, used when
                                   centre_set (with dx1, dx2 > 0 as its half-sizes) */
     int32_t centre_set;

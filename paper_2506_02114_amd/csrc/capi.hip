@@ -138,9 +138,6 @@ void DevBuf::release()
 
 Workspace::~Workspace()
 {
-    if (side) (void)hipStreamDestroy(side);
-    if (fork) (void)hipEventDestroy(fork);
-    if (join) (void)hipEventDestroy(join);
     std::lock_guard<std::mutex> g(g_alloc_mu);
     if (pinned) (void)hipHostFree(pinned);
     if (spin) (void)hipHostFree(spin);
@@ -176,7 +173,10 @@ namespace {
 constexpr int64_t STRIP_VERTS = 1ll << 26;   // vertices per strip buffer (1 GiB of double2)
 constexpr int64_t IRS_STRIP_RAYS = 1ll << 30;   // rays per inverse-ray-shooting launch (nothing stored per ray)
 constexpr int64_t IRS_STRIP_PATCH_RAYS = 1ll << 29;   // the same by patches (448 bytes of coefficients per 1024 rays)
-constexpr double FINE_CELLS_PER_PIXEL = 256.0;  // cells per map pixel from which the cell pass takes its 16 x 16 window
+constexpr int64_t BIG_HOLD = 4ll << 20;       // large triangles kept over strips before they are banded (0.5 GiB)
+constexpr int64_t BIG_CELLS_PER_SLOT = 4;     // cells per entry of the large-triangle lists
+constexpr double QUEUE_CELLS_PER_PIXEL = 64.0;   // cells per map pixel from which the cell pass queues (k_ipm_fine)
+constexpr double FINE_CELLS_PER_PIXEL = 400.0;  // cells per map pixel from which the cell pass is k_ipm_fine
 
 __global__ void k_fill(double *p, int64_t n, double v)
 {
@@ -223,13 +223,12 @@ struct Timer {
     hipStream_t st;
     std::vector<hipEvent_t> ev;
     Timer(bool on_, hipStream_t st_) : on(on_), st(st_) {}
-    int mark() { return mark_on(st); }
-    int mark_on(hipStream_t s)
+    int mark()
     {
         if (!on) return -1;
         hipEvent_t e;
         MLM_HIP(hipEventCreate(&e));
-        MLM_HIP(hipEventRecord(e, s));
+        MLM_HIP(hipEventRecord(e, st));
         ev.push_back(e);
         return (int)ev.size() - 1;
     }
@@ -320,7 +319,7 @@ constexpr int64_t BAND_ITEMS_TARGET = 4096;
 
 struct BatchWs {
     std::mutex mu;
-    DevBuf maps, verts, tbig, toff, prep, rows, row0, bcnt, boffs, bcur, blist, counters, bounds, slice_map, slice_lo,
+    DevBuf maps, verts, tbig, toff, prep, bands, bcnt, boffs, bcur, blist, counters, bounds, slice_map, slice_lo,
         items, queue;
     hipStream_t prep_st[PREP_THREADS] = {};   // created on first use, default priority
     std::vector<hipEvent_t> ready;            // per map: prepared (recorded on its preparing stream)
@@ -794,6 +793,57 @@ mlm_status mlm_map_region(const mlm_lens *lens, const mlm_map_request *req, mlm_
 namespace mlm {
 namespace {
 
+// the large triangles set up in the lens's workspace (nb of them) apportioned:
+// by bands of bh pixel rows, or (bh 0: the map is too wide) triangle by triangle
+// through the row differences; the band pass's timing events go to marks
+void apportion_bands(mlm_lens *lens, int64_t nb, int bh, const MapGeom &g, double *map, double *diff,
+                     unsigned long long *work, Timer &tm, std::vector<std::pair<int, int>> &marks, hipStream_t st)
+{
+    Workspace &ws = lens->ws;
+    const BigPrep *prep = ws.bigprep.as<BigPrep>();
+    const uint32_t *bands = ws.bigbands.as<uint32_t>();
+    if (bh <= 0) {
+        launch_big(nb, prep, g, map, diff, st);
+        return;
+    }
+    const int32_t nbands = (int32_t)((g.n2 + bh - 1) / bh);
+    int32_t *bcnt = static_cast<int32_t *>(ws.bandcnt.reserve((size_t)nbands * sizeof(int32_t)));
+    unsigned long long *boffs =
+        static_cast<unsigned long long *>(ws.bandoff.reserve((size_t)(nbands + 1) * sizeof(unsigned long long)));
+    unsigned long long *bcur =
+        static_cast<unsigned long long *>(ws.bandcur.reserve((size_t)(nbands + 1) * sizeof(unsigned long long)));
+    hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((nbands + 255) / 256)), dim3(256), 0, st, bcnt, nbands);
+    launch_band_count(nb, bands, nbands, bcnt, st);
+    const int64_t nlist = scan_i32_to_u64(lens, bcnt, boffs, nbands, st);
+    int32_t *blist = static_cast<int32_t *>(ws.bandlist.reserve((size_t)(nlist > 0 ? nlist : 1) * sizeof(int32_t)));
+    MLM_HIP(hipMemcpyAsync(bcur, boffs, (size_t)nbands * sizeof(unsigned long long), hipMemcpyDeviceToDevice, st));
+    launch_band_scatter(nb, bands, nbands, bcur, blist, st);
+    // the persistent band pass: every band with a list, cut into slices of at
+    // most `cut` entries
+    std::vector<unsigned long long> hoff((size_t)nbands + 1);
+    MLM_HIP(hipMemcpyAsync(hoff.data(), boffs, hoff.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+    MLM_HIP(hipStreamSynchronize(st));
+    const int64_t cut = std::max<int64_t>(BAND_SLICE_MIN, nlist / BAND_ITEMS_TARGET);
+    std::vector<BandItem> items;
+    for (int64_t b = 0; b < nbands; ++b) {
+        const int64_t lo = (int64_t)hoff[b], hi = (int64_t)hoff[b + 1];
+        if (hi <= lo) continue;
+        const int64_t k = (hi - lo + cut - 1) / cut;
+        for (int64_t a = lo; a < hi; a += cut) items.push_back(BandItem{b, a, std::min(hi, a + cut), k > 1 ? 1 : 0, 0});
+    }
+    const int64_t nitems = (int64_t)items.size();
+    BandItem *ditems = static_cast<BandItem *>(ws.bitems.reserve((size_t)std::max<int64_t>(nitems, 1) * sizeof(BandItem)));
+    unsigned long long *queue = static_cast<unsigned long long *>(ws.bqueue.reserve(QUEUE_BYTES));
+    if (nitems > 0) {
+        MLM_HIP(hipMemcpyAsync(ditems, items.data(), (size_t)nitems * sizeof(BandItem), hipMemcpyHostToDevice, st));
+        MLM_HIP(hipStreamSynchronize(st));   // the host item table is released on return
+    }
+    const int e0 = tm.mark();
+    launch_band_queue1(ditems, nitems, split_items(items.data(), nitems), queue, blist, prep, bh, g, map, work, st);
+    const int e1 = tm.mark();
+    marks.emplace_back(e0, e1);
+}
+
 // one map (the body of mlm_map and of mlm_map_noalloc); the lens is locked
 void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats)
 {
@@ -814,8 +864,8 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
     fill(map, npix, 0.0, st);
     // counters: [0] skipped triangles, [1] ray-star pairs, [2] rays, [3] unused,
     // [4] band row items, [5] band boundary pieces (if timing), [6] (triangle,
-    // pixel) pieces (timing 2), [7] unused, then (if
-    // timing) WORK_SLOTS partial sums each of small triangles, column items
+    // pixel) pieces (timing 2), [7] rows of the large triangles (timing 2),
+    // then (if timing) WORK_SLOTS partial sums each of small triangles, column items
     // and column pieces
     constexpr int NCNT = 8 + 3 * WORK_SLOTS;
     unsigned long long *cnt = static_cast<unsigned long long *>(ws.counters.reserve(NCNT * sizeof(unsigned long long)));
@@ -855,7 +905,9 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
     g.big_px = big_pixels_of(q);
     LensConst lc = lens_const(lens, R);
 
-    int64_t n_big = 0, n_big_rows = 0, n_cand = 0, n_refined = 0;
+    int64_t n_big = 0, n_cand = 0, n_refined = 0;
+    int64_t held = 0, hold = 0;                     // large triangles set up and not yet banded; how many may be
+    std::vector<std::pair<int, int>> band_marks;    // timing events of the band passes
     double t_refine = 0.0;
     bool refine_stats_zeroed = false;
 
@@ -912,14 +964,20 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         double *wdev = nullptr;
         if (q.w_out) wdev = q.device_out ? q.w_out : static_cast<double *>(ws.wbuf.reserve((size_t)nbuf * sizeof(double2)));
 
-        // The cell pass sums its deposits in a 48 x 48 pixel LDS window per tile
-        // of 16 x 16 cells, or in a 16 x 16 one where the map holds so many
-        // cells per pixel that a tile lands in a pixel or two: there clearing
-        // and flushing 2304 window entries would cost more than the tile's
-        // cells (the shooting region covers the map, so cells per map pixel
-        // is how finely the cells divide a pixel on average).
-        const bool fine = (double)(R.nr1 - 1) * (double)(R.nr2 - 1) >= FINE_CELLS_PER_PIXEL * (double)g.n1 * (double)g.n2;
-        const int side = fmm && !q.w_out && !thread_arena() ? patch_side(R, T, cb1 - cb0 + 1) : 0;
+        // Where the map holds many cells per pixel most cells meet one pixel line
+        // at most, and the cell pass is the one that sorts out the others (the
+        // shooting region covers the map, so cells per map pixel is how finely
+        // the cells divide a pixel on average).  Measured, k_ipm against
+        // k_ipm_fine with its 48-pixel window: at 14 cells a pixel 4.3 and 5.5 ms
+        // (1e5-star map), at 55 (elongated cells) 0.43 and 0.46, at 60 4.9 and
+        // 5.5, at 78 1.5 and 1.2, at 90 0.48 and 0.39; the 24-pixel window at 900
+        // and at 1300.
+        const double cells_px = (double)(R.nr1 - 1) * (double)(R.nr2 - 1) / ((double)g.n1 * (double)g.n2);
+        const int fine = cells_px >= FINE_CELLS_PER_PIXEL ? 2 : (cells_px >= QUEUE_CELLS_PER_PIXEL ? 1 : 0);
+        // (cell refinement shoots its rays one by one, and its decisions compare
+        // them with the grid's: those go the same way there)
+        const bool single = q.w_out || q.refine != MLM_REFINE_NONE || thread_arena();
+        const int side = fmm && !single ? patch_side(R, T, cb1 - cb0 + 1) : 0;
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             int64_t r1 = std::min(cb1, r0 + rows_per_strip - 1);   // cells [r0, r1), vertex rows [r0, r1]
             int64_t vb0 = r0, vb1 = r1 + 1;
@@ -936,96 +994,63 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             else if (fmm) launch_shoot(lens, T, R, lc, g, nt, vb0, verts, w_here, st);
             else launch_shoot_direct(lens, R, lc, g, vb0, vb1, verts, w_here, st);
             int eb = tm.mark();
-            // IPM: the cell pass apportions the ordinary triangles; the large ones
-            // are counted per cell tile, gathered, binned by pixel bands and
-            // apportioned band by band.  With row bands and a second stream (the
-            // default) that chain runs beside the cell pass: it counts the large
-            // triangles itself and adds its band rows to the map atomically.
+            // IPM: the cell pass apportions the ordinary triangles and lists the
+            // large ones, which are then set up, binned by pixel bands and
+            // apportioned band by band.  Where a list was too short (or, inside a
+            // scratch arena, not kept) they are counted and gathered by cell tiles.
+            // (Counting, gathering and banding them on a second stream beside the
+            // cell pass made the 1e5-star map 9.46 ms, this 9.35: both passes are
+            // bound by vector issue, so side by side they only share it.)
             const int64_t ncells = (R.nr1 - 1) * (r1 - r0);
             const int64_t ntl = ipm_tile_count(R.nr1, r1 - r0);
             const int bh = band_height(g.n1, g.n2);
-            const bool overlap = bh > 0 && !q.one_stream && !thread_arena();
-            hipStream_t bst = st;   // stream of the large-triangle chain
-            if (overlap) {
-                if (!ws.side) MLM_HIP(hipStreamCreateWithFlags(&ws.side, hipStreamNonBlocking));
-                if (!ws.fork) MLM_HIP(hipEventCreateWithFlags(&ws.fork, hipEventDisableTiming));
-                if (!ws.join) MLM_HIP(hipEventCreateWithFlags(&ws.join, hipEventDisableTiming));
-                bst = ws.side;
-                MLM_HIP(hipEventRecord(ws.fork, st));
-                MLM_HIP(hipStreamWaitEvent(bst, ws.fork, 0));
-            }
-            int32_t *tbig = static_cast<int32_t *>(ws.tbig.reserve((size_t)std::max<int64_t>(ntl, 1) * sizeof(int32_t)));
-            int64_t *toff = static_cast<int64_t *>(ws.tbigoff.reserve((size_t)(ntl + 1) * sizeof(int64_t)));
-            if (overlap) {
-                launch_big_count(verts, R.nr1, r0, r1, vb0, g, tbig, bst);
-            } else if (ntl > 0) {
-                hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((ntl + 255) / 256)), dim3(256), 0, st, tbig, ntl);
+            BigList bl;
+            bl.count = static_cast<unsigned long long *>(ws.bigcount.reserve(BIG_SHARDS * BIG_STRIDE * sizeof(unsigned long long)));
+            if (!thread_arena()) {
+                bl.cap = std::max<int64_t>(1024, (ncells / BIG_CELLS_PER_SLOT + BIG_SHARDS - 1) / BIG_SHARDS);
+                bl.list = static_cast<int64_t *>(ws.biglist.reserve((size_t)(BIG_SHARDS * bl.cap) * sizeof(int64_t)));
             }
             const int e_cells0 = tm.mark();
-            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, overlap ? nullptr : tbig, q.precision == MLM_PREC_MIXED,
-                       fine, q.timing >= 2 ? cnt + 8 : nullptr, st);
+            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, q.precision == MLM_PREC_MIXED, fine,
+                       q.timing >= 2 ? cnt + 8 : nullptr, st);
             const int e_cells = tm.mark();
-            int e_band0 = -1, e_band1 = -1;
-            const int64_t nb = scan_i32_to_i64(lens, tbig, toff, ntl, bst);
+            BigStarts at{};
+            const bool listed = bl.cap > 0 && read_big_counts(lens, bl, at, st);
+            int64_t nb = at.lo[BIG_SHARDS];
+            int64_t *toff = nullptr;
+            if (!listed) {
+                int32_t *tbig = static_cast<int32_t *>(ws.tbig.reserve((size_t)std::max<int64_t>(ntl, 1) * sizeof(int32_t)));
+                toff = static_cast<int64_t *>(ws.tbigoff.reserve((size_t)(ntl + 1) * sizeof(int64_t)));
+                launch_big_count(verts, R.nr1, r0, r1, vb0, g, tbig, st);
+                nb = scan_i32_to_i64(lens, tbig, toff, ntl, st);
+            }
+            // set-ups are kept over the strips and banded together, as far as
+            // they fit: a band costs its rows of the map however few triangles it
+            // lists, and binning fills the chip only with many (the 2.1e10-ray
+            // map's 312 strips one by one: 126 ms of bands and 66 of binning;
+            // together 25 and 8)
+            if (held > 0 && held + nb > hold) {
+                apportion_bands(lens, held, bh, g, map, diff, q.timing >= 2 ? cnt + 4 : nullptr, tm, band_marks, st);
+                held = 0;
+            }
             if (nb > 0) {
-                BigPrep *prep = static_cast<BigPrep *>(ws.bigprep.reserve((size_t)nb * sizeof(BigPrep)));
-                int64_t *rows = static_cast<int64_t *>(ws.bigrows.reserve((size_t)nb * sizeof(int64_t)));
-                int32_t *row0 = static_cast<int32_t *>(ws.bigrow0.reserve((size_t)nb * sizeof(int32_t)));
-                launch_big_gather(verts, R.nr1, r0, r1, vb0, g, nb, toff, prep, rows, row0, bst);
-                if (bh > 0) {
-                    // large triangles by pixel bands: owned rows, LDS accumulation
-                    const int32_t nbands = (int32_t)((g.n2 + bh - 1) / bh);
-                    int32_t *bcnt = static_cast<int32_t *>(ws.bandcnt.reserve((size_t)nbands * sizeof(int32_t)));
-                    unsigned long long *boffs =
-                        static_cast<unsigned long long *>(ws.bandoff.reserve((size_t)(nbands + 1) * sizeof(unsigned long long)));
-                    unsigned long long *bcur =
-                        static_cast<unsigned long long *>(ws.bandcur.reserve((size_t)(nbands + 1) * sizeof(unsigned long long)));
-                    hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((nbands + 255) / 256)), dim3(256), 0, bst, bcnt, nbands);
-                    launch_band_count(nb, row0, rows, bh, nbands, bcnt, bst);
-                    const int64_t nlist = scan_i32_to_u64(lens, bcnt, boffs, nbands, bst);
-                    int32_t *blist = static_cast<int32_t *>(ws.bandlist.reserve((size_t)(nlist > 0 ? nlist : 1) * sizeof(int32_t)));
-                    MLM_HIP(hipMemcpyAsync(bcur, boffs, (size_t)nbands * sizeof(unsigned long long), hipMemcpyDeviceToDevice, bst));
-                    launch_band_scatter(nb, row0, rows, bh, nbands, bcur, blist, bst);
-                    // the persistent band pass: every band with a list, cut into
-                    // slices of at most `cut` entries
-                    std::vector<unsigned long long> hoff((size_t)nbands + 1);
-                    MLM_HIP(hipMemcpyAsync(hoff.data(), boffs, hoff.size() * sizeof(unsigned long long),
-                                           hipMemcpyDeviceToHost, bst));
-                    MLM_HIP(hipStreamSynchronize(bst));
-                    const int64_t cut = std::max<int64_t>(BAND_SLICE_MIN, nlist / BAND_ITEMS_TARGET);
-                    std::vector<BandItem> items;
-                    for (int64_t b = 0; b < nbands; ++b) {
-                        const int64_t lo = (int64_t)hoff[b], hi = (int64_t)hoff[b + 1];
-                        if (hi <= lo) continue;
-                        const int64_t k = (hi - lo + cut - 1) / cut;
-                        for (int64_t a = lo; a < hi; a += cut)
-                            items.push_back(BandItem{b, a, std::min(hi, a + cut), k > 1 ? 1 : 0, 0});
-                    }
-                    const int64_t nitems = (int64_t)items.size();
-                    BandItem *ditems =
-                        static_cast<BandItem *>(ws.bitems.reserve((size_t)std::max<int64_t>(nitems, 1) * sizeof(BandItem)));
-                    unsigned long long *queue = static_cast<unsigned long long *>(ws.bqueue.reserve(QUEUE_BYTES));
-                    if (nitems > 0) {
-                        MLM_HIP(hipMemcpyAsync(ditems, items.data(), (size_t)nitems * sizeof(BandItem),
-                                               hipMemcpyHostToDevice, bst));
-                        MLM_HIP(hipStreamSynchronize(bst));   // the host item table is released at the end of this block
-                    }
-                    e_band0 = tm.mark_on(bst);
-                    launch_band_queue1(ditems, nitems, split_items(items.data(), nitems), queue, blist, prep, rows,
-                                       bh, g, map, q.timing >= 2 ? cnt + 4 : nullptr, overlap, bst);
-                    e_band1 = tm.mark_on(bst);
-                } else {
-                    launch_big(nb, prep, rows, g, map, diff, st);
+                if (held == 0) {
+                    const int64_t left = (cb1 - r1 + rows_per_strip - 2) / std::max<int64_t>(rows_per_strip - 1, 1);
+                    hold = thread_arena() || bh <= 0 ? nb : std::max(nb, std::min(BIG_HOLD, nb + nb / 4 * 5 * left));
+                    ws.bigprep.reserve((size_t)hold * sizeof(BigPrep));
+                    ws.bigbands.reserve((size_t)hold * sizeof(uint32_t));
                 }
-                if (q.timing >= 2) {   // statistics only
-                    int64_t *rowoff = static_cast<int64_t *>(ws.rowoff.reserve((size_t)nb * sizeof(int64_t)));
-                    n_big_rows += scan_total_i64(lens, rows, rowoff, nb, bst);
-                }
+                BigPrep *prep = ws.bigprep.as<BigPrep>() + held;
+                uint32_t *bands = ws.bigbands.as<uint32_t>() + held;
+                if (listed) launch_big_setup(verts, R.nr1, r0, vb0, g, bl, at, bh, prep, bands, st);
+                else launch_big_gather(verts, R.nr1, r0, r1, vb0, g, nb, toff, bh, prep, bands, st);
+                if (q.timing >= 2) launch_count_rows(nb, prep, cnt + 7, st);   // statistics only
+                held += nb;
                 n_big += nb;
             }
-            if (overlap) {   // the map waits for both streams
-                MLM_HIP(hipEventRecord(ws.join, bst));
-                MLM_HIP(hipStreamWaitEvent(st, ws.join, 0));
+            if (held > 0 && (r1 == cb1 || held == hold)) {
+                apportion_bands(lens, held, bh, g, map, diff, q.timing >= 2 ? cnt + 4 : nullptr, tm, band_marks, st);
+                held = 0;
             }
             if (q.timing >= 2) launch_count_pieces(verts, R.nr1, r0, r1, vb0, g, cnt + 6, st);   // statistics only
             int ec = tm.mark();
@@ -1083,7 +1108,6 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             t_ipm += tm.ms(eb, ec);
             t_refine += tm.ms(ec, ed);
             t_cells += tm.ms(e_cells0, e_cells);
-            t_band += tm.ms(e_band0, e_band1);
             tiles += nt;
             r0 = r1;
         }
@@ -1096,6 +1120,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
     MLM_HIP(hipMemcpyAsync(hc, cnt, NCNT * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     int e_end = tm.mark();
     MLM_HIP(hipStreamSynchronize(st));
+    for (const auto &m : band_marks) t_band += tm.ms(m.first, m.second);
     if (stats) {
         mlm_map_stats S{};
         S.n_rays = irs ? (cb1 - cb0) * (R.nr1 - 1) : (cb1 - cb0 + 1) * R.nr1;
@@ -1116,7 +1141,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         S.n_shoot_launches = nstrips;
         S.n_ipm_launches = nstrips;
         S.n_big = n_big;
-        S.n_big_rows = n_big_rows;
+        S.n_big_rows = q.timing >= 2 ? (int64_t)hc[7] : 0;
         S.t_cells_ms = t_cells;
         S.t_band_ms = t_band;
         S.n_band_rows = q.timing >= 2 ? (int64_t)hc[4] : 0;
@@ -1575,9 +1600,8 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
         const int64_t nb = scan_i32_to_i64(scan_lens, tbig, toff, ctl, st);
         if (nb > 0) {
             BigPrep *prep = static_cast<BigPrep *>(B.prep.reserve((size_t)nb * sizeof(BigPrep)));
-            int64_t *rows = static_cast<int64_t *>(B.rows.reserve((size_t)nb * sizeof(int64_t)));
-            int32_t *row0 = static_cast<int32_t *>(B.row0.reserve((size_t)nb * sizeof(int32_t)));
-            launch_big_gather_batch(dmaps, nm, ctl, toff, prep, rows, row0, st);
+            uint32_t *bands = static_cast<uint32_t *>(B.bands.reserve((size_t)nb * sizeof(uint32_t)));
+            launch_big_gather_batch(dmaps, nm, ctl, toff, prep, bands, st);
             // each map's slice of the gathered list, cut into workgroup-sized
             // slices for the binning passes
             int64_t *bnd = static_cast<int64_t *>(B.bounds.reserve((size_t)(nm + 1) * sizeof(int64_t)));
@@ -1606,7 +1630,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
             MLM_HIP(hipMemcpyAsync(dmaps, hm.data(), (size_t)nm * sizeof(BatchMap), hipMemcpyHostToDevice, st));
             int32_t *bcnt = static_cast<int32_t *>(B.bcnt.reserve((size_t)bl * sizeof(int32_t)));
             hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((bl + 255) / 256)), dim3(256), 0, st, bcnt, bl);
-            launch_band_count_batch(dmaps, ns, dsm, dsl, max_bands, row0, rows, bcnt, st);
+            launch_band_count_batch(dmaps, ns, dsm, dsl, max_bands, bands, bcnt, st);
             unsigned long long *boffs =
                 static_cast<unsigned long long *>(B.boffs.reserve((size_t)(bl + 1) * sizeof(unsigned long long)));
             const int64_t nlist = scan_i32_to_u64(scan_lens, bcnt, boffs, bl, st);
@@ -1614,7 +1638,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
             unsigned long long *bcur =
                 static_cast<unsigned long long *>(B.bcur.reserve((size_t)bl * sizeof(unsigned long long)));
             MLM_HIP(hipMemcpyAsync(bcur, boffs, (size_t)bl * sizeof(unsigned long long), hipMemcpyDeviceToDevice, st));
-            launch_band_scatter_batch(dmaps, ns, dsm, dsl, max_bands, row0, rows, bcur, blist, st);
+            launch_band_scatter_batch(dmaps, ns, dsm, dsl, max_bands, bands, bcur, blist, st);
             // work items of the persistent band pass: every band with a list,
             // cut into slices of at most `cut` entries so that the items number
             // a few per workgroup the device holds
@@ -1636,7 +1660,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
             unsigned long long *queue = static_cast<unsigned long long *>(B.queue.reserve(QUEUE_BYTES));
             if (nitems > 0)
                 MLM_HIP(hipMemcpyAsync(ditems, items.data(), (size_t)nitems * sizeof(BandItem), hipMemcpyHostToDevice, st));
-            launch_band_queue(dmaps, nm, ditems, nitems, split_items(items.data(), nitems), queue, blist, prep, rows,
+            launch_band_queue(dmaps, nm, ditems, nitems, split_items(items.data(), nitems), queue, blist, prep,
                               max_band_lds, st);
             MLM_HIP(hipStreamSynchronize(st));   // the host item table is released at the end of this block
         }

@@ -123,16 +123,23 @@ struct LensConst {
 };
 
 // per-triangle data of the row-parallel IPM: counter-clockwise vertices
-// relative to the integer origin (ou, ov), edge slopes su = du/dv, the
-// deposit per unit of twice the piece area, and per edge the factor of the
-// squared distance past the edge's first column in its row term,
-// -scale sign(dv) |dv/du| (0 for edges with du = 0) (120 bytes)
-struct BigPrep {
+// relative to the integer origin (ou, ov), edge slopes su = du/dv, per edge the
+// factor of the squared distance past the edge's first column in its row term,
+// -scale sign(dv) |dv/du| (0 for edges with du = 0), the deposit per unit of
+// twice the piece area, and the pixel rows from ov on that it covers in the
+// map.  One 128-byte cache line each: the band pass reads a triangle once for
+// every band it crosses, mostly from beyond L2, and is bound by those reads.
+struct alignas(128) BigPrep {
     double u[3], v[3];
     double su[3];
-    double ou, ov, scale;
     double kc[3];
+    double scale;
+    int32_t ou, ov, rows, pad;
 };
+
+// the bands a large triangle crosses, first | last << 16 (the bands of a map
+// number fewer than 2^16: their histograms fit LDS); none: first > last
+constexpr uint32_t NO_BANDS = 1;
 
 // ray-grid geometry of a shooting launch: points (x0 + (a + h) d1,
 // y0 + (b + h) d2), a < nr1, rows b from vb0 (h = 0: the grid's vertices;
@@ -257,15 +264,14 @@ struct Workspace {
     DevBuf code, level, leaf, slo, shi, block, parent, child0, coll, node_leaf, leaf_node, flags, offs;
     DevBuf ilist, active, mult, local, ops_m2m, ops_m2l, ops_l2l;
     DevBuf leaves, near, deriv, near_offs;
+    DevBuf bigcount, biglist;
     DevBuf binom, patch_info, patch_coef;
-    DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigrows, bigrow0, rowoff, nbnd, nbndoff, diff, bandcnt, bandoff,
+    DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
         bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, rsub0, rsub1, bitems, bqueue, tune_map;
-    hipStream_t side = nullptr;           // second stream of a map: the large-triangle passes beside the cell pass
-    hipEvent_t fork = nullptr, join = nullptr;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
     int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
-                                          // MAX_LEVELS counts of listed nodes
+                                          // MAX_LEVELS counts of listed nodes or BIG_SHARDS of large triangles
     int64_t spin_seq = 0;                 // sequence number of the last total asked for
     int ops_p = -1;                       // expansion order of the operator tables
     ~Workspace();
@@ -375,45 +381,61 @@ constexpr int64_t BIN_TRIS = 2048;
 // cell tiles of the cell pass over cell rows [cb0, cb0 + nrows): one workgroup and one
 // large-triangle count each
 int64_t ipm_tile_count(int64_t nr1, int64_t nrows);
-// (fine: the 16 x 16 pixel LDS window, for maps of many cells per pixel)
+// (fine: the pass for maps of many cells per pixel)
+// lists of the large triangles that the cell pass meets: BIG_SHARDS of cap
+// entries each, their counts BIG_STRIDE apart (a count above cap: the list is
+// incomplete)
+constexpr int BIG_SHARDS = 64;
+constexpr int BIG_STRIDE = 16;
+struct BigList {
+    unsigned long long *count = nullptr;
+    int64_t *list = nullptr;
+    int64_t cap = 0;
+};
+struct BigStarts {
+    int64_t lo[BIG_SHARDS + 1];   // the lists laid end to end: list i's first slot
+};
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                double *map, unsigned long long *counters, int32_t *tile_big, bool mixed, bool fine,
+                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int fine,
                 unsigned long long *work, hipStream_t st);
-// the large triangles of the tiles into prep/rows/row0 at the tiles' offsets
+void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,
+                      const BigStarts &at, int bh, BigPrep *prep, uint32_t *bands, hipStream_t st);
+// the counts of the lists (waits for them), laid end to end; false if one is incomplete
+bool read_big_counts(mlm_lens *lens, const BigList &bl, BigStarts &at, hipStream_t st);
+// the large triangles of the tiles into prep and their bands of bh rows (bh 0: not
+// asked for) into bands, at the tiles' offsets
 // tile_off (nbig in all; with fewer than one a tile, a resident grid skips
 // the empty tiles)
 void launch_big_gather(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                       int64_t nbig, const int64_t *tile_off, BigPrep *prep, int64_t *rows, int32_t *row0,
+                       int64_t nbig, const int64_t *tile_off, int bh, BigPrep *prep, uint32_t *bands,
                        hipStream_t st);
-void launch_big(int64_t nbig, const BigPrep *prep, const int64_t *rows, const MapGeom &g, double *map, double *diff,
-                hipStream_t st);
+void launch_big(int64_t nbig, const BigPrep *prep, const MapGeom &g, double *map, double *diff, hipStream_t st);
+// statistics: the pixel rows of nbig large triangles, added to *out
+void launch_count_rows(int64_t nbig, const BigPrep *prep, unsigned long long *out, hipStream_t st);
 void launch_diff_rows(const MapGeom &g, const double *diff, double *map, hipStream_t st);
 // statistics: (triangle, pixel) pieces of cell rows [cb0, cb1) inside the map, added to *out
 void launch_count_pieces(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
                          unsigned long long *out, hipStream_t st);
 int band_height(int32_t n1, int32_t n2);
-void launch_band_count(int64_t nbig, const int32_t *row0, const int64_t *rows, int bh, int32_t nbands, int32_t *count,
-                       hipStream_t st);
-void launch_band_scatter(int64_t nbig, const int32_t *row0, const int64_t *rows, int bh, int32_t nbands,
-                         unsigned long long *cursor, int32_t *list, hipStream_t st);
+void launch_band_count(int64_t nbig, const uint32_t *bands, int32_t nbands, int32_t *count, hipStream_t st);
+void launch_band_scatter(int64_t nbig, const uint32_t *bands, int32_t nbands, unsigned long long *cursor, int32_t *list,
+                         hipStream_t st);
 void launch_big_count(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
                       int32_t *tile_big, hipStream_t st);
 void launch_ipm_batch(const BatchMap *maps, int32_t nmaps, int64_t nctiles, int32_t *tile_big, hipStream_t st);
 void launch_big_gather_batch(const BatchMap *maps, int32_t nmaps, int64_t nctiles, const int64_t *tile_off,
-                             BigPrep *prep, int64_t *rows, int32_t *row0, hipStream_t st);
+                             BigPrep *prep, uint32_t *bands, hipStream_t st);
 void launch_band_count_batch(const BatchMap *maps, int64_t nslices, const int32_t *slice_map, const int64_t *slice_lo,
-                             int32_t max_bands, const int32_t *row0, const int64_t *rows, int32_t *count,
-                             hipStream_t st);
+                             int32_t max_bands, const uint32_t *bands, int32_t *count, hipStream_t st);
 void launch_band_scatter_batch(const BatchMap *maps, int64_t nslices, const int32_t *slice_map,
-                               const int64_t *slice_lo, int32_t max_bands, const int32_t *row0, const int64_t *rows,
+                               const int64_t *slice_lo, int32_t max_bands, const uint32_t *bands,
                                unsigned long long *cursor, int32_t *list, hipStream_t st);
 void launch_band_queue(const BatchMap *maps, int32_t nmaps, const BandItem *items, int64_t nitems,
                        const ItemParts &parts, unsigned long long *queue, const int32_t *list, const BigPrep *prep,
-                       const int64_t *rows, int64_t lds_doubles, hipStream_t st);
+                       int64_t lds_doubles, hipStream_t st);
 void launch_band_queue1(const BandItem *items, int64_t nitems, const ItemParts &parts, unsigned long long *queue,
-                        const int32_t *list,
-                        const BigPrep *prep, const int64_t *rows, int bh, const MapGeom &g, double *map,
-                        unsigned long long *work, bool atomic_all, hipStream_t st);
+                        const int32_t *list, const BigPrep *prep, int bh, const MapGeom &g, double *map,
+                        unsigned long long *work, hipStream_t st);
 int64_t scan_i32_to_u64(mlm_lens *lens, const int32_t *in, unsigned long long *out, int64_t n, hipStream_t st);
 
 // scan.hip: device-wide prefix sums (tmp: scan_tmp_bytes(n)); the total is

@@ -125,12 +125,11 @@ __device__ inline void deposit(double *map, const MapGeom &g, int i, int j, doub
 // pixel window of a workgroup in LDS: deposits inside it are summed there and
 // added to the map once per pixel at the end; the rest go straight to the map.
 // Its side N is 48 pixels (wide enough for most tiles' images at a few cells
-// per pixel; 18 KiB, so more cell-pass workgroups share a CU with the band
-// pass beside it than at 64), or 16 where a tile's cells cover far less than
-// a pixel each (a highly magnified map), so that clearing and flushing the
-// window does not cost more than the tile's deposits.
+// per pixel; 18 KiB), or 24 where a tile's cells cover far less than a pixel
+// each (a highly magnified map), so that clearing and flushing the window does
+// not cost more than the tile's deposits.
 constexpr int WIN = 48;        // window side in pixels (WIN x WIN doubles)
-constexpr int WIN_FINE = 16;   // the side for maps of many cells per pixel
+constexpr int WIN_FINE = 24;   // the side for maps of many cells per pixel
 
 template <int N> struct Window {
     double *acc;          // N x N, row-major
@@ -400,50 +399,65 @@ __device__ inline int setup_column(const ColSetup &c, int r, const MapGeom &g, d
     return column_pieces<double>(c.T, c.sv, c.su, cl, c.fv0, i, c.j0, c.j1, c.scale, g, map, w);
 }
 
-// IPM of the ordinary triangles.  A workgroup takes a tile of 16 x 16 cells
-// (each wavefront 16 x 4): one thread per cell deposits single-pixel
-// triangles and classifies the rest (cell (a, b) splits along v00-v11 into
-// T1 = (v00, v10, v11) and T2 = (v00, v11, v01)); then each wavefront spreads
-// its triangles' pixel columns evenly over its lanes.  A tile of cells maps to
-// a compact patch of the source plane, so deposits are summed in an LDS
-// window around the tile's image first.  Large triangles are only counted:
-// one total per tile, for the gather pass.
-constexpr int CT = 16;   // cells per tile side
+struct CellWork {   // work counts (statistics)
+    unsigned small = 0, items = 0, pieces = 0;
+};
 
-// cell tile `tile` of a strip (a whole workgroup of 256 threads; acc is its
-// N x N LDS window)
-template <bool MIXED, int N>
-__device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t nrows,
-                                int64_t vb0, const MapGeom &g, double *__restrict__ map,
-                                unsigned long long *__restrict__ counters, int32_t *__restrict__ tile_big, int64_t tile,
-                                double *acc, unsigned long long *__restrict__ work)
+// The large triangles a cell pass meets, listed for the row-band passes:
+// BIG_SHARDS lists of `cap` entries each (2 x (cell within the strip) +
+// triangle), a workgroup appending to one of them, so that the wavefronts'
+// updates of the counts rarely meet at one address.  A count may pass cap:
+// entries beyond it are not written, and the caller then gathers the strip's
+// large triangles by tiles instead.  A wavefront asks for its range as soon as
+// it has classified its cells and writes it after their columns, so that it
+// does not wait for the atomic (one range per workgroup, asked for at the end,
+// made the 1e5-star map's cell pass 4.4 instead of 4.2 ms).
+struct BigRange {
+    unsigned long long base = 0;   // first entry of the wavefront's range (valid in lane 0)
+    int at = 0;                    // this lane's first entry within it
+};
+__device__ inline BigRange reserve_big(const BigList &bl, int big)
 {
-    const int64_t ncol = nr1 - 1;
-    const int64_t tiles_a = (ncol + CT - 1) / CT;
-    const int64_t ta = tile % tiles_a, tb = tile / tiles_a;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t a = ta * CT + (lane & (CT - 1));
-    const int64_t brow = tb * CT + wave * 4 + (lane >> 4);   // cell row within the strip
-    for (int k = threadIdx.x; k < N * N; k += blockDim.x) acc[k] = 0.0;
-    // window anchored on the image of the tile's centre vertex
-    Window<N> w;
-    w.acc = acc;
-    {
-        const int64_t ca = min(ta * CT + CT / 2, ncol), cb = min(tb * CT + CT / 2, nrows);
-        const double2 c = verts[(cb0 + cb - vb0) * nr1 + ca];
-        const double fu = isfinite(c.x) ? fmin(fmax(floor(c.x), -1e9), 1e9) : 0.0;
-        const double fv = isfinite(c.y) ? fmin(fmax(floor(c.y), -1e9), 1e9) : 0.0;
-        w.i0 = (int)fu - N / 2;
-        w.j0 = (int)fv - N / 2;
-    }
-    __syncthreads();
-    unsigned n_small = 0, n_items = 0, n_pieces = 0;   // work counts (statistics)
+    BigRange r;
+    const int lane = threadIdx.x & 63;
+    const uint64_t m0 = __ballot(big & 1), m1 = __ballot(big & 2), lt = (1ull << lane) - 1ull;
+    if ((m0 | m1) == 0) return r;
+    r.at = __popcll(m0 & lt) + __popcll(m1 & lt);
+    const int sh = (int)(blockIdx.x * 2654435761u >> 26);   // spread whatever the tiles' row length
+    if (lane == 0)
+        r.base = atomicAdd(bl.count + (size_t)sh * BIG_STRIDE, (unsigned long long)(__popcll(m0) + __popcll(m1)));
+    return r;
+}
+__device__ inline void write_big(const BigList &bl, const BigRange &r, int big, int64_t cell)
+{
+    if (!__any(big != 0)) return;
+    const int sh = (int)(blockIdx.x * 2654435761u >> 26);
+    int64_t k = (int64_t)__shfl(r.base, 0, 64) + r.at;
+    for (int m = 0; m < 2; ++m)
+        if (big >> m & 1) {
+            if (k < bl.cap) bl.list[sh * bl.cap + k] = 2 * cell + m;
+            ++k;
+        }
+}
+
+// What the cell pass does with one cell a thread (the cell (a, b) splits along
+// v00-v11 into T1 = (v00, v10, v11) and T2 = (v00, v11, v01)): single-pixel
+// triangles are deposited, those within 2 x 2 pixels apportioned in place, and
+// the pixel columns of the others (the medium ones) are spread evenly over the
+// wavefront's lanes.  Which of the two triangles are large (bit k) is returned,
+// and they are listed in `bl` (LIST; `cell`: the cell's number in the strip).
+// Called by whole wavefronts.
+template <bool MIXED, int N, bool LIST>
+__device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11, P2 v01, const MapGeom &g,
+                                              double *__restrict__ map, const Window<N> &w,
+                                              unsigned long long *__restrict__ counters, const BigList &bl,
+                                              int64_t cell, CellWork &cw)
+{
+    const int lane = threadIdx.x & 63;
     int mcols[2] = {0, 0};      // pixel columns of each medium triangle of the cell (0: none)
     int mi0[2] = {0, 0};
-    P2 v00{0.0, 0.0}, v10{0.0, 0.0}, v11{0.0, 0.0}, v01{0.0, 0.0};
-    int nb = 0;   // large triangles of the cell
-    if (a < ncol && brow < nrows) {
-        load_cell_at(verts, nr1, cb0 + brow - vb0, a, v00, v10, v11, v01);
+    int big = 0;
+    if (have) {
         int pi, pj;
         if (cell_in_one_pixel(v00, v10, v11, v01, g, pi, pj)) {
             if (pi >= 0) deposit_w(w, map, g, pi, pj, 2.0 * g.tri_weight);
@@ -463,23 +477,19 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
                     if (c.small) {
                         const double fu0 = floor(fmin(A.u, fmin(B.u, C.u))), fv0 = floor(fmin(A.v, fmin(B.v, C.v)));
                         small_triangle(A, B, C, fu0, fv0, g, map, w);
-                        ++n_small;
+                        ++cw.small;
                     } else {
                         mcols[k] = c.cols;
                         mi0[k] = c.i0;
                     }
                 } else {
-                    ++nb;
+                    big |= 1 << k;
                 }
             }
         }
     }
-    if (tile_big) {   // the tile's count of large triangles (tile_big is zeroed beforehand)
-        int s = nb;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (lane == 0 && s) atomicAdd(tile_big + tile, s);
-    }
+    BigRange range;
+    if constexpr (LIST) range = reserve_big(bl, big);
     // the medium triangles' pixel columns, spread evenly over the wavefront's
     // lanes: first triangle of every cell, then the second
 #pragma unroll
@@ -495,29 +505,92 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
             const int r = item - __shfl(excl, L, 64);
             const ColSetup c = shfl_setup(own, L);
             if (item < total) {
-                n_pieces += (unsigned)setup_column<MIXED>(c, r, g, map, w);
-                ++n_items;
+                cw.pieces += (unsigned)setup_column<MIXED>(c, r, g, map, w);
+                ++cw.items;
             }
         }
     }
-    if (work) {   // one sum per wavefront and count, spread over WORK_SLOTS slots per count
-        unsigned v[3] = {n_small, n_items, n_pieces};
+    if constexpr (LIST) write_big(bl, range, big, cell);
+    return big;
+}
+
+// work counts of a workgroup: one sum per wavefront and count, spread over
+// WORK_SLOTS slots per count
+__device__ inline void add_work(unsigned long long *__restrict__ work, int64_t tile, const CellWork &cw)
+{
+    unsigned v[3] = {cw.small, cw.items, cw.pieces};
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 3; ++k) {
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-            if (lane == 0 && v[k]) atomicAdd(work + k * WORK_SLOTS + (tile & (WORK_SLOTS - 1)), (unsigned long long)v[k]);
-        }
+        for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+        if ((threadIdx.x & 63) == 0 && v[k])
+            atomicAdd(work + k * WORK_SLOTS + (tile & (WORK_SLOTS - 1)), (unsigned long long)v[k]);
     }
-    __syncthreads();
+}
+
+// the window of a tile, anchored on the image of its centre vertex c
+template <int N> __device__ inline Window<N> tile_window(double *acc, double2 c)
+{
+    Window<N> w;
+    w.acc = acc;
+    const double fu = isfinite(c.x) ? fmin(fmax(floor(c.x), -1e9), 1e9) : 0.0;
+    const double fv = isfinite(c.y) ? fmin(fmax(floor(c.y), -1e9), 1e9) : 0.0;
+    w.i0 = (int)fu - N / 2;
+    w.j0 = (int)fv - N / 2;
+    return w;
+}
+
+// the window's sums to the map (inside it: only in-map pixels were deposited)
+template <int N> __device__ inline void flush_window(const Window<N> &w, double *__restrict__ map, const MapGeom &g)
+{
     for (int k = threadIdx.x; k < N * N; k += blockDim.x) {
-        const double v = acc[k];
-        if (v != 0.0) {
-            const int i = w.i0 + (k % N), j = w.j0 + (k / N);
-            deposit(map, g, i, j, v);   // inside the map: only in-map pixels were deposited
-        }
+        const double v = w.acc[k];
+        if (v != 0.0) deposit(map, g, w.i0 + (k % N), w.j0 + (k / N), v);
     }
-    __syncthreads();   // the window may be reused by the workgroup's next tile
+}
+
+// IPM of the ordinary triangles.  A workgroup takes a tile of 16 x 16 cells
+// (each wavefront 16 x 4), one cell a thread.  A tile of cells maps to a
+// compact patch of the source plane, so deposits are summed in an LDS window
+// around the tile's image first.
+constexpr int CT = 16;   // cells per tile side
+
+// cell tile `tile` of a strip (a whole workgroup of 256 threads; acc is its
+// N x N LDS window); the large triangles go to `bl`, or (batch) are counted
+// in tile_big for the gather pass
+template <bool MIXED, int N, bool LIST>
+__device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t nrows,
+                                int64_t vb0, const MapGeom &g, double *__restrict__ map,
+                                unsigned long long *__restrict__ counters, const BigList &bl,
+                                int32_t *__restrict__ tile_big, int64_t tile,
+                                double *acc, unsigned long long *__restrict__ work)
+{
+    const int64_t ncol = nr1 - 1;
+    const int64_t tiles_a = (ncol + CT - 1) / CT;
+    const int64_t ta = tile % tiles_a, tb = tile / tiles_a;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t a = ta * CT + (lane & (CT - 1));
+    const int64_t brow = tb * CT + wave * 4 + (lane >> 4);   // cell row within the strip
+    // (the cell's corners are asked for before the barrier, beside the window's
+    // anchor: one wait for memory instead of two)
+    const bool have = a < ncol && brow < nrows;
+    P2 v00, v10, v11, v01;
+    load_cell_at(verts, nr1, cb0 + min(brow, nrows - 1) - vb0, min(a, ncol - 1), v00, v10, v11, v01);
+    const int64_t ca = min(ta * CT + CT / 2, ncol), cb = min(tb * CT + CT / 2, nrows);
+    const Window<N> w = tile_window<N>(acc, verts[(cb0 + cb - vb0) * nr1 + ca]);
+    for (int k = threadIdx.x; k < N * N; k += blockDim.x) acc[k] = 0.0;
+    __syncthreads();
+    CellWork cw;
+    const int big = apportion_cell<MIXED, N, LIST>(have, v00, v10, v11, v01, g, map, w, counters, bl, brow * ncol + a, cw);
+    if constexpr (!LIST) {   // the tile's count of large triangles (tile_big is zeroed beforehand)
+        int s = (big & 1) + (big >> 1);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0 && s) atomicAdd(tile_big + tile, s);
+    }
+    if (work) add_work(work, tile, cw);
+    __syncthreads();
+    flush_window<N>(w, map, g);
 }
 
 // Registers capped at 128 per lane (four waves per SIMD, no spills): the
@@ -526,27 +599,148 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
 template <bool MIXED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
                                              int64_t nrows, int64_t vb0, MapGeom g, double *__restrict__ map,
-                                             unsigned long long *__restrict__ counters, int32_t *__restrict__ tile_big,
+                                             unsigned long long *__restrict__ counters, BigList bl,
                                              unsigned long long *__restrict__ work)
 {
     __shared__ double acc[WIN * WIN];
-    ipm_tile<MIXED, WIN>(verts, nr1, cb0, nrows, vb0, g, map, counters, tile_big, blockIdx.x, acc, work);
+    ipm_tile<MIXED, WIN, true>(verts, nr1, cb0, nrows, vb0, g, map, counters, bl, nullptr, blockIdx.x, acc, work);
 }
 
-// the same with the 16 x 16 window
-template <bool MIXED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_fine(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
-                                             int64_t nrows, int64_t vb0, MapGeom g, double *__restrict__ map,
-                                             unsigned long long *__restrict__ counters, int32_t *__restrict__ tile_big,
-                                             unsigned long long *__restrict__ work)
+// The cell pass where cells are far smaller than pixels (a highly magnified
+// map holds hundreds a pixel): nearly every cell lies in one pixel or crosses
+// one pixel line, but in a wavefront of 64 some cell always does more, and
+// every lane then paid for the whole of apportion_cell (944 instruction slots
+// a wavefront on the 2.1e10-ray map, 502 ms in all; here 245).  A thread walks
+// FR cells of a grid column, deposits those two kinds, and queues the others in
+// LDS; the queue, a few per cent of the tile's cells, is then worked off with
+// full lanes.  N: the window's side.
+//
+// A cell inside a 2 x 1 (or 1 x 2) pixel box: the line x = 1 cuts the corner at
+// a triangle's lone vertex x0, the fraction (1 - x0)^2 / ((x1 - x0) (x2 - x0))
+// of its area (coordinates relative to the box, exact: a double minus a nearby
+// integer).  The cells of a column move slowly over the pixels, so a thread
+// sums its deposits in registers while they fall into the same pixels.
+constexpr int FC = 32;         // tile columns (cells)
+constexpr int FR = 4;          // cells of a thread, one below the other
+constexpr int FROWS = 256 / FC * FR;   // tile rows
+
+// share of a triangle's area where x < 1 (x: its vertices' coordinates)
+__device__ inline double left_share(double a, double b, double c, bool &crossed)
 {
-    __shared__ double acc[WIN_FINE * WIN_FINE];
-    ipm_tile<MIXED, WIN_FINE>(verts, nr1, cb0, nrows, vb0, g, map, counters, tile_big, blockIdx.x, acc, work);
+    const double lo = fmin(a, b), hi = fmax(a, b);
+    const double mn = fmin(lo, c), mx = fmax(hi, c), md = fmax(lo, fmin(hi, c));
+    const bool low = md < 1.0;               // the lone vertex lies right of the line
+    const double e = low ? mx - 1.0 : 1.0 - mn, h = low ? mx - md : md - mn;
+    const double q = fdiv(e * e, (mx - mn) * h);
+    crossed = mn < 1.0 && mx >= 1.0;
+    return !crossed ? (mx < 1.0 ? 1.0 : 0.0) : (low ? 1.0 - q : q);
+}
+
+template <bool MIXED, int N>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_fine(
+    const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t nrows, int64_t vb0, MapGeom g,
+    double *__restrict__ map, unsigned long long *__restrict__ counters, BigList bl,
+    unsigned long long *__restrict__ work)
+{
+    __shared__ double acc[N * N];
+    __shared__ unsigned short queue[FC * FROWS];   // cells of the tile
+    __shared__ int nq;
+    const int64_t ncol = nr1 - 1;
+    const int64_t tiles_a = (ncol + FC - 1) / FC;
+    const int64_t ta = (int64_t)blockIdx.x % tiles_a, tb = (int64_t)blockIdx.x / tiles_a;
+    const int tc = threadIdx.x % FC, tr = threadIdx.x / FC * FR;
+    const int64_t a = ta * FC + tc, row0 = tb * FROWS + tr;
+    // all of the thread's vertices at once, asked for before the barrier, beside
+    // the window's anchor (rows and columns beyond the strip: its last): loaded
+    // row by row behind it, the pass spent 61 % of its time waiting for them
+    const int rows = (int)max((int64_t)0, min((int64_t)FR, nrows - row0));
+    P2 va[FR + 1], vb[FR + 1];
+    {
+        using GD = const __attribute__((address_space(1))) double;
+        GD *r = (GD *)verts + 2 * ((cb0 + min(row0, nrows) - vb0) * nr1 + min(a, ncol - 1));
+#pragma unroll
+        for (int s = 0; s <= FR; ++s) {
+            GD *q = r + 2 * min(s, rows) * nr1;
+            va[s] = P2{q[0], q[1]};
+            vb[s] = P2{q[2], q[3]};
+        }
+    }
+    const int64_t ca = min(ta * FC + FC / 2, ncol), cb = min(tb * FROWS + FROWS / 2, nrows);
+    const Window<N> w = tile_window<N>(acc, verts[(cb0 + cb - vb0) * nr1 + ca]);
+    for (int k = threadIdx.x; k < N * N; k += blockDim.x) acc[k] = 0.0;
+    if (threadIdx.x == 0) nq = 0;
+    __syncthreads();
+    CellWork cw;
+    if (a < ncol && rows > 0) {
+        // the pixels being summed: a cell's first, and the one across the line
+        int pi = -1, pj = -1, qi = -1, qj = -1;
+        double ps = 0.0, qs = 0.0;
+        auto put = [&](int i, int j, double val) {
+            if (val != 0.0 && (unsigned)i < (unsigned)g.n1 && (unsigned)j < (unsigned)g.n2)
+                deposit_w(w, map, g, i, j, val * g.tri_weight);
+        };
+#pragma unroll
+        for (int s = 0; s < FR; ++s) {
+            if (s >= rows) break;
+            const P2 v00 = va[s], v10 = vb[s], v01 = va[s + 1], v11 = vb[s + 1];
+            const double fu = floor(fmin(fmin(v00.u, v10.u), fmin(v11.u, v01.u)));
+            const double fv = floor(fmin(fmin(v00.v, v10.v), fmin(v11.v, v01.v)));
+            const double du = fmax(fmax(v00.u, v10.u), fmax(v11.u, v01.u)) - fu;
+            const double dv = fmax(fmax(v00.v, v10.v), fmax(v11.v, v01.v)) - fv;
+            const bool along_u = du < 2.0 && dv < 1.0;
+            bool queued = !(along_u || (du < 1.0 && dv < 2.0));   // (a NaN is caught below: no area)
+            const double s1 = twice_area(v00, v10, v11, fu, fv), s2 = twice_area(v00, v11, v01, fu, fv);
+            queued = queued || !(fabs(s1) > 0.0 && fabs(s2) > 0.0);
+            if (queued) {
+                queue[atomicAdd(&nq, 1)] = (unsigned short)((tr + s) * FC + tc);
+            } else {
+                const double o = along_u ? fu : fv;
+                const double x0 = (along_u ? v00.u : v00.v) - o, x1 = (along_u ? v10.u : v10.v) - o;
+                const double x2 = (along_u ? v11.u : v11.v) - o, x3 = (along_u ? v01.u : v01.v) - o;
+                bool c1, c2;
+                const double left = left_share(x0, x1, x2, c1) + left_share(x0, x2, x3, c2);
+                cw.small += (unsigned)c1 + (unsigned)c2;
+                const int i = (int)fu, j = (int)fv, i2 = i + (along_u ? 1 : 0), j2 = j + (along_u ? 0 : 1);
+                if (i != pi || j != pj) {
+                    put(pi, pj, ps);
+                    pi = i;
+                    pj = j;
+                    ps = 0.0;
+                }
+                ps += left;
+                if (c1 || c2 || left < 2.0) {
+                    if (i2 != qi || j2 != qj) {
+                        put(qi, qj, qs);
+                        qi = i2;
+                        qj = j2;
+                        qs = 0.0;
+                    }
+                    qs += 2.0 - left;
+                }
+            }
+        }
+        put(pi, pj, ps);
+        put(qi, qj, qs);
+    }
+    __syncthreads();
+    const int n = nq;
+    for (int k0 = threadIdx.x & ~63; k0 < n; k0 += 256) {   // the same for a whole wavefront
+        const int k = k0 + (threadIdx.x & 63);
+        const bool have = k < n;
+        const int c = have ? queue[k] : 0;
+        P2 v00{0.0, 0.0}, v10{0.0, 0.0}, v11{0.0, 0.0}, v01{0.0, 0.0};
+        if (have) load_cell_at(verts, nr1, cb0 + tb * FROWS + c / FC - vb0, ta * FC + c % FC, v00, v10, v11, v01);
+        apportion_cell<MIXED, N, true>(have, v00, v10, v11, v01, g, map, w, counters, bl,
+                                              (tb * FROWS + c / FC) * ncol + ta * FC + c % FC, cw);
+    }
+    if (work) add_work(work, blockIdx.x, cw);
+    __syncthreads();
+    flush_window<N>(w, map, g);
 }
 
 // every cell tile of every map of a fused batch in one launch (one
 // workgroup per tile of the concatenated tile list)
-__global__ __launch_bounds__(256) void k_ipm_batch(const BatchMap *__restrict__ maps, int32_t nmaps,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_batch(const BatchMap *__restrict__ maps, int32_t nmaps,
                                                    int64_t ntiles, int32_t *__restrict__ tile_big)
 {
     __shared__ double acc[WIN * WIN];
@@ -555,11 +749,11 @@ __global__ __launch_bounds__(256) void k_ipm_batch(const BatchMap *__restrict__ 
         const int32_t m = batch_find(maps, nmaps, t, &BatchMap::ctile_lo);
         const BatchMap &d = maps[m];
         if (d.mixed)
-            ipm_tile<true, WIN>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, tile_big + d.ctile_lo, t - d.ctile_lo,
-                           acc, nullptr);
+            ipm_tile<true, WIN, false>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, BigList{}, tile_big + d.ctile_lo,
+                                       t - d.ctile_lo, acc, nullptr);
         else
-            ipm_tile<false, WIN>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, tile_big + d.ctile_lo, t - d.ctile_lo,
-                            acc, nullptr);
+            ipm_tile<false, WIN, false>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, BigList{}, tile_big + d.ctile_lo,
+                                        t - d.ctile_lo, acc, nullptr);
     }
 }
 
@@ -575,12 +769,11 @@ __device__ inline int cell_big_mask(P2 v00, P2 v10, P2 v11, P2 v01, const MapGeo
 // set-up of the cell's large triangles (`mask`), written to slots [slot,
 // end): integer local origin (inside or at the edge of the map, so nearby
 // pixel boundaries are exact), counter-clockwise local vertices, edge slopes,
-// the deposit scale, and the pixel rows it covers (their count in rows[], the
-// first in row0[]: compact copies for the binning passes, which need nothing
-// else)
+// the deposit scale and the pixel rows it covers; the bands of bh rows among
+// them go to bands[], all that the binning passes read
 __device__ inline void gather_cell(P2 v00, P2 v10, P2 v11, P2 v01, int mask, int64_t slot, int64_t end,
-                                   const MapGeom &g, BigPrep *__restrict__ prep, int64_t *__restrict__ rows,
-                                   int32_t *__restrict__ row0)
+                                   const MapGeom &g, int bh, BigPrep *__restrict__ prep,
+                                   uint32_t *__restrict__ bands)
 {
     const P2 tri[2][3] = {{v00, v10, v11}, {v00, v11, v01}};
     for (int k = 0; k < 2 && slot < end; ++k) {
@@ -606,20 +799,40 @@ __device__ inline void gather_cell(P2 v00, P2 v10, P2 v11, P2 v01, int mask, int
             bp.v[m] = T[m].v;
             bp.su[m] = su[m];
         }
-        bp.ou = ou;
-        bp.ov = ov;
+        bp.ou = (int32_t)ou;
+        bp.ov = (int32_t)ov;
+        bp.pad = 0;
         bp.scale = g.tri_weight / S2;
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
             const double dv = T[m == 2 ? 0 : m + 1].v - T[m].v;
             bp.kc[m] = dv > 0.0 ? -bp.scale * fabs(sv[m]) : (dv < 0.0 ? bp.scale * fabs(sv[m]) : 0.0);
         }
-        prep[slot] = bp;
         const double j1 = fmin(floor(vmax), (double)(g.n2 - 1));
-        rows[slot] = j1 >= ov ? (int64_t)(j1 - ov) + 1 : 0;
-        row0[slot] = (int32_t)ov;
+        bp.rows = j1 >= ov ? (int32_t)(j1 - ov) + 1 : 0;
+        prep[slot] = bp;
+        if (bh > 0)
+            bands[slot] = bp.rows > 0 ? (uint32_t)(bp.ov / bh) | (uint32_t)((bp.ov + bp.rows - 1) / bh) << 16 : NO_BANDS;
         ++slot;
     }
+}
+
+// the same for the listed large triangles, slot k the k-th of the lists laid
+// end to end (list sh's entries are slots [at.lo[sh], at.lo[sh + 1]))
+__global__ __launch_bounds__(256) void k_big_setup(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
+                                                   int64_t vb0, MapGeom g, BigList bl, BigStarts at, int bh,
+                                                   BigPrep *__restrict__ prep, uint32_t *__restrict__ bands)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= at.lo[BIG_SHARDS]) return;
+    int sh = 0;
+#pragma unroll
+    for (int step = BIG_SHARDS / 2; step >= 1; step >>= 1)
+        if (at.lo[sh + step] <= k) sh += step;
+    const int64_t e = bl.list[sh * bl.cap + (k - at.lo[sh])], cell = e >> 1, ncol = nr1 - 1;
+    P2 v00, v10, v11, v01;
+    load_cell_at(verts, nr1, cb0 + cell / ncol - vb0, cell % ncol, v00, v10, v11, v01);
+    gather_cell(v00, v10, v11, v01, 1 << (e & 1), k, k + 1, g, bh, prep, bands);
 }
 
 // The large triangles of one cell tile (one workgroup of 256 threads, the
@@ -628,9 +841,8 @@ __device__ inline void gather_cell(P2 v00, P2 v10, P2 v11, P2 v01, int mask, int
 // Slots of that range this pass does not fill (none, as both passes classify
 // alike) are left as triangles without rows.
 __device__ inline void gather_tile(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t nrows,
-                                   int64_t vb0, const MapGeom &g, int64_t tile, int64_t lo, int64_t hi,
-                                   BigPrep *__restrict__ prep, int64_t *__restrict__ rows,
-                                   int32_t *__restrict__ row0, int32_t *wsum)
+                                   int64_t vb0, const MapGeom &g, int64_t tile, int64_t lo, int64_t hi, int bh,
+                                   BigPrep *__restrict__ prep, uint32_t *__restrict__ bands, int32_t *wsum)
 {
     const int64_t ncol = nr1 - 1;
     const int64_t tiles_a = (ncol + CT - 1) / CT;
@@ -654,17 +866,17 @@ __device__ inline void gather_tile(const double2 *__restrict__ verts, int64_t nr
         if (w < wave) slot += wsum[w];
         found += wsum[w];
     }
-    if (mask) gather_cell(v00, v10, v11, v01, mask, slot, min(slot + nb, hi), g, prep, rows, row0);
+    if (mask) gather_cell(v00, v10, v11, v01, mask, slot, min(slot + nb, hi), g, bh, prep, bands);
     for (int64_t s = lo + found + threadIdx.x; s < hi; s += blockDim.x) {
-        rows[s] = 0;
-        row0[s] = 0;
+        prep[s].rows = 0;
+        if (bh > 0) bands[s] = NO_BANDS;
     }
 }
 
 // The number of large triangles of every cell tile (the cell pass's
 // classification, cells over the threads as there), stored per tile: what the
-// gather needs, without the cell pass, so the large-triangle passes can run
-// beside it.
+// gather by tiles needs where the cell pass's lists were too short (or, inside
+// a scratch arena, were not kept).
 __global__ __launch_bounds__(256) void k_big_count(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
                                                    int64_t nrows, int64_t vb0, MapGeom g, int32_t *__restrict__ tile_big)
 {
@@ -692,13 +904,13 @@ __global__ __launch_bounds__(256) void k_big_count(const double2 *__restrict__ v
 
 __global__ __launch_bounds__(256) void k_big_gather(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
                                                     int64_t nrows, int64_t vb0, MapGeom g,
-                                                    const int64_t *__restrict__ tile_off, BigPrep *__restrict__ prep,
-                                                    int64_t *__restrict__ rows, int32_t *__restrict__ row0)
+                                                    const int64_t *__restrict__ tile_off, int bh,
+                                                    BigPrep *__restrict__ prep, uint32_t *__restrict__ bands)
 {
     __shared__ int32_t wsum[4];
     const int64_t t = blockIdx.x, lo = tile_off[t], hi = tile_off[t + 1];
     if (lo == hi) return;   // the whole workgroup
-    gather_tile(verts, nr1, cb0, nrows, vb0, g, t, lo, hi, prep, rows, row0, wsum);
+    gather_tile(verts, nr1, cb0, nrows, vb0, g, t, lo, hi, bh, prep, bands, wsum);
 }
 
 // Calls f(t) for the tiles t < tiles that hold large triangles (tile_off[t] <
@@ -739,26 +951,26 @@ __device__ inline void for_big_tiles(int64_t tiles, const int64_t *__restrict__ 
 __global__ __launch_bounds__(256) void k_big_gather_sparse(const double2 *__restrict__ verts, int64_t nr1,
                                                            int64_t cb0, int64_t nrows, int64_t vb0, MapGeom g,
                                                            int64_t tiles, const int64_t *__restrict__ tile_off,
-                                                           BigPrep *__restrict__ prep, int64_t *__restrict__ rows,
-                                                           int32_t *__restrict__ row0)
+                                                           int bh, BigPrep *__restrict__ prep,
+                                                           uint32_t *__restrict__ bands)
 {
     __shared__ int32_t wsum[4];
     for_big_tiles(tiles, tile_off, [&](int64_t t) {
-        gather_tile(verts, nr1, cb0, nrows, vb0, g, t, tile_off[t], tile_off[t + 1], prep, rows, row0, wsum);
+        gather_tile(verts, nr1, cb0, nrows, vb0, g, t, tile_off[t], tile_off[t + 1], bh, prep, bands, wsum);
     });
 }
 
 // the batch's cell tiles: tile_off is the scan over all maps' tiles
 __global__ __launch_bounds__(256) void k_big_gather_batch(const BatchMap *__restrict__ maps, int32_t nmaps,
                                                           const int64_t *__restrict__ tile_off,
-                                                          BigPrep *__restrict__ prep, int64_t *__restrict__ rows,
-                                                          int32_t *__restrict__ row0)
+                                                          BigPrep *__restrict__ prep,
+                                                          uint32_t *__restrict__ bands)
 {
     __shared__ int32_t wsum[4];
     const int64_t t = blockIdx.x, lo = tile_off[t], hi = tile_off[t + 1];
     if (lo == hi) return;   // the whole workgroup
     const BatchMap &d = maps[batch_find(maps, nmaps, t, &BatchMap::ctile_lo)];
-    gather_tile(d.verts, d.nr1, 0, d.nrows, 0, d.g, t - d.ctile_lo, lo, hi, prep, rows, row0, wsum);
+    gather_tile(d.verts, d.nr1, 0, d.nrows, 0, d.g, t - d.ctile_lo, lo, hi, d.bh, prep, bands, wsum);
 }
 
 // The edges of a large triangle clipped to pixel row j (local coordinates),
@@ -775,7 +987,7 @@ __device__ inline bool row_info(const BigPrep &bp, int64_t j, const MapGeom &g, 
 {
     const P2 T[3] = {P2{bp.u[0], bp.v[0]}, P2{bp.u[1], bp.v[1]}, P2{bp.u[2], bp.v[2]}};
     const double su[3] = {bp.su[0], bp.su[1], bp.su[2]};
-    ri.rl = (double)j - bp.ov;
+    ri.rl = (double)j - (double)bp.ov;
     const double rl = ri.rl;
     strip_segments<1>(T, su, rl, rl + 1.0, ri.S);
     double rumin = 1e300, rumax = -1e300;
@@ -786,7 +998,7 @@ __device__ inline bool row_info(const BigPrep &bp, int64_t j, const MapGeom &g, 
             rumax = fmax(rumax, fmax(ri.S.a[k], ri.S.b[k]));
         }
     if (rumin > rumax) return false;
-    const double ga = fmax(floor(rumin), -bp.ou), gb = fmin(floor(rumax), (double)(g.n1 - 1) - bp.ou);
+    const double ga = fmax(floor(rumin), -(double)bp.ou), gb = fmin(floor(rumax), (double)(g.n1 - 1) - (double)bp.ou);
     if (ga > gb) return false;
     // a pixel is fully inside when every corner is on the inner side of each edge
     double fa = -1e300, fb = 1e300;
@@ -824,8 +1036,8 @@ struct RowSlot {
     int64_t j, ga, pa, pb, gb;
 };
 
-__global__ __launch_bounds__(256) void k_big(int64_t nbig, const BigPrep *__restrict__ prep,
-                                             const int64_t *__restrict__ rows, MapGeom g, double *__restrict__ map,
+__global__ __launch_bounds__(256) void k_big(int64_t nbig, const BigPrep *__restrict__ prep, MapGeom g,
+                                             double *__restrict__ map,
                                              double *__restrict__ diff)
 {
     __shared__ RowSlot slots[256];
@@ -833,7 +1045,7 @@ __global__ __launch_bounds__(256) void k_big(int64_t nbig, const BigPrep *__rest
     const int64_t wave0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
     const int64_t k = wave0 + lane;
     RowSlot *ws = slots + (threadIdx.x & ~63);
-    const int nrow = k < nbig ? (int)rows[k] : 0;
+    const int nrow = k < nbig ? prep[k].rows : 0;
     int rtotal;
     const int rexcl = wave_excl_scan(nrow, lane, rtotal);
     for (int rbase = 0; rbase < rtotal; rbase += 64) {
@@ -855,7 +1067,7 @@ __global__ __launch_bounds__(256) void k_big(int64_t nbig, const BigPrep *__rest
                 }
                 RowSlot &sl = ws[lane];
                 sl.S = ri.S;
-                sl.ou = bp.ou;
+                sl.ou = (double)bp.ou;
                 sl.scale = bp.scale;
                 sl.j = j;
                 sl.ga = ri.ga;
@@ -907,12 +1119,6 @@ __global__ __launch_bounds__(256) void k_big(int64_t nbig, const BigPrep *__rest
 constexpr int BAND_THREADS = 768;
 constexpr int64_t BAND_LDS_DOUBLES = 8192;    // band difference rows (64 KiB)
 
-__device__ inline void band_range(int64_t j0, int64_t rows, int bh, int64_t &b0, int64_t &b1)
-{
-    b0 = j0 / bh;
-    b1 = (j0 + rows - 1) / bh;
-}
-
 // Per-band counts of a workgroup's triangles from their band ranges [b0, b1]:
 // each adds +1 at b0 and -1 past b1 in `hist` (nb + 1 entries, zeroed), and
 // a prefix sum over the bands turns that in place into the counts (O(1)
@@ -950,17 +1156,15 @@ __host__ __device__ inline size_t band_hist_words(int64_t nb) { return (size_t)(
 // those updates, all on the few hundred band entries, were the cost).
 // bin_count adds the workgroup's per-band counts to count[] (hist: LDS of
 // band_hist_words(nb) words).
-__device__ inline void bin_count(int64_t lo, int64_t hi, const int32_t *__restrict__ row0,
-                                 const int64_t *__restrict__ rows, int bh, int32_t nb, int32_t *hist,
-                                 int32_t *__restrict__ count)
+__device__ inline void bin_count(int64_t lo, int64_t hi, const uint32_t *__restrict__ bands, int32_t nb,
+                                 int32_t *hist, int32_t *__restrict__ count)
 {
     for (int32_t b = threadIdx.x; b <= nb; b += blockDim.x) hist[b] = 0;
     __syncthreads();
     for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) {
-        const int64_t n = rows[k];
-        if (n <= 0) continue;
-        int64_t b0, b1;
-        band_range(row0[k], n, bh, b0, b1);
+        const uint32_t br = bands[k];
+        const int b0 = (int)(br & 0xffffu), b1 = (int)(br >> 16);
+        if (b0 > b1) continue;
         atomicAdd(&hist[b0], 1);
         atomicAdd(&hist[b1 + 1], -1);
     }
@@ -972,8 +1176,7 @@ __device__ inline void bin_count(int64_t lo, int64_t hi, const int32_t *__restri
 // triangle indices into their bands' lists: the workgroup reserves one range
 // per band from cursor[] and hands out slots inside it from LDS (sh:
 // band_hist_words(nb) words, then nb 8-byte range starts)
-__device__ inline void bin_scatter(int64_t lo, int64_t hi, const int32_t *__restrict__ row0,
-                                   const int64_t *__restrict__ rows, int bh, int32_t nb, int32_t *sh,
+__device__ inline void bin_scatter(int64_t lo, int64_t hi, const uint32_t *__restrict__ bands, int32_t nb, int32_t *sh,
                                    unsigned long long *__restrict__ cursor, int32_t *__restrict__ list)
 {
     int32_t *hist = sh;
@@ -981,10 +1184,9 @@ __device__ inline void bin_scatter(int64_t lo, int64_t hi, const int32_t *__rest
     for (int32_t b = threadIdx.x; b <= nb; b += blockDim.x) hist[b] = 0;
     __syncthreads();
     for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) {
-        const int64_t n = rows[k];
-        if (n <= 0) continue;
-        int64_t b0, b1;
-        band_range(row0[k], n, bh, b0, b1);
+        const uint32_t br = bands[k];
+        const int b0 = (int)(br & 0xffffu), b1 = (int)(br >> 16);
+        if (b0 > b1) continue;
         atomicAdd(&hist[b0], 1);
         atomicAdd(&hist[b1 + 1], -1);
     }
@@ -995,34 +1197,31 @@ __device__ inline void bin_scatter(int64_t lo, int64_t hi, const int32_t *__rest
     }
     __syncthreads();
     for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) {
-        const int64_t n = rows[k];
-        if (n <= 0) continue;
-        int64_t b0, b1;
-        band_range(row0[k], n, bh, b0, b1);
-        for (int64_t b = b0; b <= b1; ++b) {
+        const uint32_t br = bands[k];
+        const int b0 = (int)(br & 0xffffu), b1 = (int)(br >> 16);
+        if (b0 > b1) continue;
+        for (int b = b0; b <= b1; ++b) {
             const int32_t o = atomicAdd(&hist[b], 1);
             list[base[b] + o] = (int32_t)k;
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_band_count(int64_t nbig, const int32_t *__restrict__ row0,
-                                                    const int64_t *__restrict__ rows, int bh, int32_t nbands,
+__global__ __launch_bounds__(256) void k_band_count(int64_t nbig, const uint32_t *__restrict__ bands, int32_t nbands,
                                                     int32_t *__restrict__ count)
 {
     extern __shared__ int32_t hist[];
     const int64_t lo = (int64_t)blockIdx.x * BIN_TRIS;
-    bin_count(lo, min(lo + BIN_TRIS, nbig), row0, rows, bh, nbands, hist, count);
+    bin_count(lo, min(lo + BIN_TRIS, nbig), bands, nbands, hist, count);
 }
 
-__global__ __launch_bounds__(256) void k_band_scatter(int64_t nbig, const int32_t *__restrict__ row0,
-                                                      const int64_t *__restrict__ rows, int bh, int32_t nbands,
+__global__ __launch_bounds__(256) void k_band_scatter(int64_t nbig, const uint32_t *__restrict__ bands, int32_t nbands,
                                                       unsigned long long *__restrict__ cursor,
                                                       int32_t *__restrict__ list)
 {
     extern __shared__ int32_t sh[];
     const int64_t lo = (int64_t)blockIdx.x * BIN_TRIS;
-    bin_scatter(lo, min(lo + BIN_TRIS, nbig), row0, rows, bh, nbands, sh, cursor, list);
+    bin_scatter(lo, min(lo + BIN_TRIS, nbig), bands, nbands, sh, cursor, list);
 }
 
 // A workgroup takes a band of bh pixel rows (or a slice of its list); a
@@ -1037,8 +1236,7 @@ __global__ __launch_bounds__(256) void k_band_scatter(int64_t nbig, const int32_
 // (the covered interior costs nothing).  Columns left of the map fold into
 // column 0, those right of it are dropped.  The differences live in LDS, so
 // no device-wide atomic is needed per deposit; the rows are added to the map
-// once per band (atomically when the band is shared or the cell pass runs
-// beside it).
+// once per band (atomically when the band is shared).
 
 // edge P->Q clipped to the pixel row rl <= v <= rl + 1 (su = du/dv, finite):
 // the u of its ends and its extent dv; false if it has none in the row (an
@@ -1056,8 +1254,7 @@ __device__ inline bool row_clip(P2 P, P2 Q, double rl, double su, double &ua, do
 // band `band` of one map: its listed triangles are list[r0, r1); bdiff is
 // the workgroup's LDS (bh x n1 doubles), wsum two LDS counters
 __device__ inline void band_rows(int64_t band, int64_t r0, int64_t r1, const int32_t *__restrict__ list,
-                                 const BigPrep *__restrict__ prep, const int64_t *__restrict__ rows, int bh,
-                                 const MapGeom &g, double *__restrict__ map, unsigned long long *__restrict__ work,
+                                 const BigPrep *__restrict__ prep, int bh, const MapGeom &g, double *__restrict__ map, unsigned long long *__restrict__ work,
                                  double *bdiff, unsigned long long *wsum, bool atomic_flush)
 {
     if (threadIdx.x < 2) wsum[threadIdx.x] = 0;
@@ -1076,11 +1273,11 @@ __device__ inline void band_rows(int64_t band, int64_t r0, int64_t r1, const int
         if (rr >= nrow) break;
         const int64_t k = list[r0 + li];
         const BigPrep bp = prep[k];
-        const int j = (int)jb0 + rr, ov = (int)bp.ov;   // ov in [0, n2)
-        if (j < ov || j - ov >= rows[k]) continue;
+        const int j = (int)jb0 + rr, ov = bp.ov;   // ov in [0, n2)
+        if (j < ov || j - ov >= bp.rows) continue;
         ++my_rows;
         const double rl = (double)(j - ov);
-        const int ou = (int)bp.ou;             // in [0, n1]
+        const int ou = bp.ou;                  // in [0, n1]
         double *drow = bdiff + rr * n1 + ou;   // indexed by local column
         const int cmin = -ou, cmax = (int)n1 - 1 - ou;
 #pragma unroll
@@ -1158,7 +1355,7 @@ __device__ inline void band_rows(int64_t band, int64_t r0, int64_t r1, const int
             v += carry;
             carry = __shfl(v, 63, 64);
             if (i < n1 && v != 0.0) {
-                if (atomic_flush) unsafeAtomicAdd(mr + i, v);   // the cell pass may be adding to these rows
+                if (atomic_flush) unsafeAtomicAdd(mr + i, v);   // other slices of the band may be adding to these rows
                 else mr[i] += v;
             }
         }
@@ -1197,8 +1394,7 @@ __global__ __launch_bounds__(BAND_THREADS) __attribute__((amdgpu_waves_per_eu(6)
                                                              const BandItem *__restrict__ items, ItemParts parts,
                                                              unsigned long long *__restrict__ queue,
                                                              const int32_t *__restrict__ list,
-                                                             const BigPrep *__restrict__ prep,
-                                                             const int64_t *__restrict__ rows)
+                                                             const BigPrep *__restrict__ prep)
 {
     extern __shared__ double bdiff[];
     __shared__ unsigned long long wsum[2];
@@ -1213,21 +1409,18 @@ __global__ __launch_bounds__(BAND_THREADS) __attribute__((amdgpu_waves_per_eu(6)
         const BandItem it = items[i];
         const int32_t m = batch_find(maps, nmaps, it.gband, &BatchMap::band_lo);
         const BatchMap &d = maps[m];
-        band_rows(it.gband - d.band_lo, it.lo, it.hi, list, prep, rows, d.bh, d.g, d.map, nullptr, bdiff, wsum,
+        band_rows(it.gband - d.band_lo, it.lo, it.hi, list, prep, d.bh, d.g, d.map, nullptr, bdiff, wsum,
                   it.shared != 0);
     }
 }
 
-// The same for one map: items over its bands (BandItem.gband is the band);
-// with `atomic_all` every band's rows are added atomically (the cell pass
-// runs beside it).
+// The same for one map: items over its bands (BandItem.gband is the band).
 __global__ __launch_bounds__(BAND_THREADS) __attribute__((amdgpu_waves_per_eu(6))) void k_band_queue1(const BandItem *__restrict__ items, ItemParts parts,
                                                               unsigned long long *__restrict__ queue,
                                                               const int32_t *__restrict__ list,
-                                                              const BigPrep *__restrict__ prep,
-                                                              const int64_t *__restrict__ rows, int bh, MapGeom g,
+                                                              const BigPrep *__restrict__ prep, int bh, MapGeom g,
                                                               double *__restrict__ map,
-                                                              unsigned long long *__restrict__ work, int atomic_all)
+                                                              unsigned long long *__restrict__ work)
 {
     extern __shared__ double bdiff[];
     __shared__ unsigned long long wsum[2];
@@ -1240,8 +1433,7 @@ __global__ __launch_bounds__(BAND_THREADS) __attribute__((amdgpu_waves_per_eu(6)
         __syncthreads();
         if (i < 0) break;
         const BandItem it = items[i];
-        band_rows(it.gband, it.lo, it.hi, list, prep, rows, bh, g, map, work, bdiff, wsum,
-                  atomic_all != 0 || it.shared != 0);
+        band_rows(it.gband, it.lo, it.hi, list, prep, bh, g, map, work, bdiff, wsum, it.shared != 0);
     }
 }
 
@@ -1253,28 +1445,26 @@ __global__ __launch_bounds__(BAND_THREADS) __attribute__((amdgpu_waves_per_eu(6)
 __global__ __launch_bounds__(256) void k_band_count_batch(const BatchMap *__restrict__ maps,
                                                           const int32_t *__restrict__ slice_map,
                                                           const int64_t *__restrict__ slice_lo,
-                                                          const int32_t *__restrict__ row0,
-                                                          const int64_t *__restrict__ rows,
+                                                          const uint32_t *__restrict__ bands,
                                                           int32_t *__restrict__ count)
 {
     extern __shared__ int32_t hist[];
     const BatchMap &d = maps[slice_map[blockIdx.x]];
     const int64_t lo = slice_lo[blockIdx.x];
-    bin_count(lo, min(lo + BIN_TRIS, d.big_hi), row0, rows, d.bh, (int32_t)d.nbands, hist, count + d.band_lo);
+    bin_count(lo, min(lo + BIN_TRIS, d.big_hi), bands, (int32_t)d.nbands, hist, count + d.band_lo);
 }
 
 __global__ __launch_bounds__(256) void k_band_scatter_batch(const BatchMap *__restrict__ maps,
                                                             const int32_t *__restrict__ slice_map,
                                                             const int64_t *__restrict__ slice_lo,
-                                                            const int32_t *__restrict__ row0,
-                                                            const int64_t *__restrict__ rows,
+                                                            const uint32_t *__restrict__ bands,
                                                             unsigned long long *__restrict__ cursor,
                                                             int32_t *__restrict__ list)
 {
     extern __shared__ int32_t sh[];
     const BatchMap &d = maps[slice_map[blockIdx.x]];
     const int64_t lo = slice_lo[blockIdx.x];
-    bin_scatter(lo, min(lo + BIN_TRIS, d.big_hi), row0, rows, d.bh, (int32_t)d.nbands, sh, cursor + d.band_lo, list);
+    bin_scatter(lo, min(lo + BIN_TRIS, d.big_hi), bands, (int32_t)d.nbands, sh, cursor + d.band_lo, list);
 }
 
 // map[j][i] += sum_{k <= i} diff[j][k]; one wavefront per pixel row
@@ -1360,17 +1550,42 @@ __global__ __launch_bounds__(256) void k_count_pieces(const double2 *__restrict_
     if ((threadIdx.x & 63) == 0 && n) atomicAdd(out, n);
 }
 
+// statistics: the pixel rows of the large triangles
+__global__ __launch_bounds__(256) void k_count_rows(int64_t nbig, const BigPrep *__restrict__ prep,
+                                                    unsigned long long *__restrict__ out)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    unsigned long long n = k < nbig ? (unsigned long long)prep[k].rows : 0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+    if ((threadIdx.x & 63) == 0 && n) atomicAdd(out, n);
+}
+
 }  // namespace
 
+static __global__ void k_zero_shards(unsigned long long *count) { count[(size_t)threadIdx.x * BIG_STRIDE] = 0ull; }
+
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                double *map, unsigned long long *counters, int32_t *tile_big, bool mixed, bool fine,
+                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int fine,
                 unsigned long long *work, hipStream_t st)
 {
-    const int64_t nrows = cb1 - cb0, tiles = ipm_tile_count(nr1, nrows);
-    if (tiles <= 0) return;
-    auto *k = fine ? (mixed ? k_ipm_fine<true> : k_ipm_fine<false>) : (mixed ? k_ipm<true> : k_ipm<false>);
+    const int64_t nrows = cb1 - cb0, ncol = nr1 - 1;
+    const int64_t tiles = fine ? ((ncol + FC - 1) / FC) * ((nrows + FROWS - 1) / FROWS) : ipm_tile_count(nr1, nrows);
+    if (ncol <= 0 || nrows <= 0) return;
+    hipLaunchKernelGGL(k_zero_shards, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count);
+    auto *k = fine == 2 ? (mixed ? k_ipm_fine<true, WIN_FINE> : k_ipm_fine<false, WIN_FINE>)
+              : fine ? (mixed ? k_ipm_fine<true, WIN> : k_ipm_fine<false, WIN>) : (mixed ? k_ipm<true> : k_ipm<false>);
     hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, nrows, vb0, g, map, counters,
-                       tile_big, work);
+                       bl, work);
+}
+
+void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,
+                      const BigStarts &at, int bh, BigPrep *prep, uint32_t *bands, hipStream_t st)
+{
+    const int64_t n = at.lo[BIG_SHARDS];
+    if (n > 0)
+        hipLaunchKernelGGL(k_big_setup, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, verts, nr1, cb0, vb0, g,
+                           bl, at, bh, prep, bands);
 }
 
 // grid of a persistent kernel: the workgroups of `threads` threads of `kernel`
@@ -1394,7 +1609,7 @@ int64_t ipm_tile_count(int64_t nr1, int64_t nrows)
 }
 
 void launch_big_gather(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                       int64_t nbig, const int64_t *tile_off, BigPrep *prep, int64_t *rows, int32_t *row0,
+                       int64_t nbig, const int64_t *tile_off, int bh, BigPrep *prep, uint32_t *bands,
                        hipStream_t st)
 {
     const int64_t tiles = ipm_tile_count(nr1, cb1 - cb0);
@@ -1402,10 +1617,10 @@ void launch_big_gather(const double2 *verts, int64_t nr1, int64_t cb0, int64_t c
     if (nbig < tiles) {   // fewer large triangles than tiles: most tiles are empty
         const int64_t grid = resident_grid(reinterpret_cast<const void *>(&k_big_gather_sparse), 256, 0, tiles);
         hipLaunchKernelGGL(k_big_gather_sparse, dim3((unsigned)grid), dim3(256), 0, st, verts, nr1, cb0, cb1 - cb0,
-                           vb0, g, tiles, tile_off, prep, rows, row0);
+                           vb0, g, tiles, tile_off, bh, prep, bands);
     } else {
         hipLaunchKernelGGL(k_big_gather, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, cb1 - cb0, vb0, g,
-                           tile_off, prep, rows, row0);
+                           tile_off, bh, prep, bands);
     }
 }
 
@@ -1418,11 +1633,10 @@ void launch_big_count(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb
                            tile_big);
 }
 
-void launch_big(int64_t nbig, const BigPrep *prep, const int64_t *rows, const MapGeom &g, double *map, double *diff,
-                hipStream_t st)
+void launch_big(int64_t nbig, const BigPrep *prep, const MapGeom &g, double *map, double *diff, hipStream_t st)
 {
     if (nbig > 0)
-        hipLaunchKernelGGL(k_big, dim3((unsigned)((nbig + 255) / 256)), dim3(256), 0, st, nbig, prep, rows, g, map, diff);
+        hipLaunchKernelGGL(k_big, dim3((unsigned)((nbig + 255) / 256)), dim3(256), 0, st, nbig, prep, g, map, diff);
 }
 
 // LDS bytes of the scatter pass's workgroup for nb bands (the largest of the
@@ -1454,24 +1668,23 @@ int band_height(int32_t n1, int32_t n2)
     return (int)bh;
 }
 
-void launch_band_count(int64_t nbig, const int32_t *row0, const int64_t *rows, int bh, int32_t nbands, int32_t *count,
-                       hipStream_t st)
+void launch_band_count(int64_t nbig, const uint32_t *bands, int32_t nbands, int32_t *count, hipStream_t st)
 {
     (void)hipGetLastError();   // clear what earlier calls left, so the check below sees this launch
     if (nbig > 0)
         hipLaunchKernelGGL(k_band_count, dim3((unsigned)((nbig + BIN_TRIS - 1) / BIN_TRIS)), dim3(256),
-                           band_hist_words(nbands) * sizeof(int32_t), st, nbig, row0, rows, bh, nbands, count);
+                           band_hist_words(nbands) * sizeof(int32_t), st, nbig, bands, nbands, count);
     MLM_HIP(hipGetLastError());   // a refused launch leaves the band lists unset: fail here
 }
 
-void launch_band_scatter(int64_t nbig, const int32_t *row0, const int64_t *rows, int bh, int32_t nbands,
-                         unsigned long long *cursor, int32_t *list, hipStream_t st)
+void launch_band_scatter(int64_t nbig, const uint32_t *bands, int32_t nbands, unsigned long long *cursor, int32_t *list,
+                         hipStream_t st)
 {
     const size_t shmem = bin_lds_bytes(nbands);
     (void)hipGetLastError();   // clear what earlier calls left, so the check below sees this launch
     if (nbig > 0)
-        hipLaunchKernelGGL(k_band_scatter, dim3((unsigned)((nbig + BIN_TRIS - 1) / BIN_TRIS)), dim3(256), shmem, st, nbig, row0, rows,
-                           bh, nbands, cursor, list);
+        hipLaunchKernelGGL(k_band_scatter, dim3((unsigned)((nbig + BIN_TRIS - 1) / BIN_TRIS)), dim3(256), shmem, st, nbig, bands,
+                           nbands, cursor, list);
     MLM_HIP(hipGetLastError());
 }
 
@@ -1484,11 +1697,11 @@ void launch_ipm_batch(const BatchMap *maps, int32_t nmaps, int64_t nctiles, int3
 }
 
 void launch_big_gather_batch(const BatchMap *maps, int32_t nmaps, int64_t nctiles, const int64_t *tile_off,
-                             BigPrep *prep, int64_t *rows, int32_t *row0, hipStream_t st)
+                             BigPrep *prep, uint32_t *bands, hipStream_t st)
 {
     if (nctiles > 0)
         hipLaunchKernelGGL(k_big_gather_batch, dim3((unsigned)nctiles), dim3(256), 0, st, maps, nmaps, tile_off, prep,
-                           rows, row0);
+                           bands);
 }
 
 static __global__ void k_zero_queue(unsigned long long *q)
@@ -1514,7 +1727,7 @@ ItemParts split_items(const BandItem *items, int64_t n)
 
 void launch_band_queue(const BatchMap *maps, int32_t nmaps, const BandItem *items, int64_t nitems,
                        const ItemParts &parts, unsigned long long *queue, const int32_t *list, const BigPrep *prep,
-                       const int64_t *rows, int64_t lds_doubles, hipStream_t st)
+                       int64_t lds_doubles, hipStream_t st)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_queue),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1528,12 +1741,12 @@ void launch_band_queue(const BatchMap *maps, int32_t nmaps, const BandItem *item
     const int64_t grid = resident_grid(reinterpret_cast<const void *>(&k_band_queue), BAND_THREADS, shmem, nitems);
     hipLaunchKernelGGL(k_zero_queue, dim3(1), dim3(64), 0, st, queue);
     hipLaunchKernelGGL(k_band_queue, dim3((unsigned)grid), dim3(BAND_THREADS), shmem, st, maps, nmaps, items, parts,
-                       queue, list, prep, rows);
+                       queue, list, prep);
 }
 
 void launch_band_queue1(const BandItem *items, int64_t nitems, const ItemParts &parts, unsigned long long *queue,
-                        const int32_t *list, const BigPrep *prep, const int64_t *rows, int bh, const MapGeom &g,
-                        double *map, unsigned long long *work, bool atomic_all, hipStream_t st)
+                        const int32_t *list, const BigPrep *prep, int bh, const MapGeom &g, double *map,
+                        unsigned long long *work, hipStream_t st)
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_queue1),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1545,30 +1758,29 @@ void launch_band_queue1(const BandItem *items, int64_t nitems, const ItemParts &
     const int64_t grid = resident_grid(reinterpret_cast<const void *>(&k_band_queue1), BAND_THREADS, shmem, nitems);
     hipLaunchKernelGGL(k_zero_queue, dim3(1), dim3(64), 0, st, queue);
     hipLaunchKernelGGL(k_band_queue1, dim3((unsigned)grid), dim3(BAND_THREADS), shmem, st, items, parts, queue, list,
-                       prep, rows, bh, g, map, work, atomic_all ? 1 : 0);
+                       prep, bh, g, map, work);
 }
 
 void launch_band_count_batch(const BatchMap *maps, int64_t nslices, const int32_t *slice_map, const int64_t *slice_lo,
-                             int32_t max_bands, const int32_t *row0, const int64_t *rows, int32_t *count,
-                             hipStream_t st)
+                             int32_t max_bands, const uint32_t *bands, int32_t *count, hipStream_t st)
 {
     (void)hipGetLastError();   // clear what earlier calls left, so the check below sees this launch
     if (nslices > 0)
         hipLaunchKernelGGL(k_band_count_batch, dim3((unsigned)nslices), dim3(256),
-                           band_hist_words(max_bands) * sizeof(int32_t), st, maps, slice_map, slice_lo, row0, rows,
+                           band_hist_words(max_bands) * sizeof(int32_t), st, maps, slice_map, slice_lo, bands,
                            count);
     MLM_HIP(hipGetLastError());
 }
 
 void launch_band_scatter_batch(const BatchMap *maps, int64_t nslices, const int32_t *slice_map,
-                               const int64_t *slice_lo, int32_t max_bands, const int32_t *row0, const int64_t *rows,
+                               const int64_t *slice_lo, int32_t max_bands, const uint32_t *bands,
                                unsigned long long *cursor, int32_t *list, hipStream_t st)
 {
     const size_t shmem = bin_lds_bytes(max_bands);
     (void)hipGetLastError();   // clear what earlier calls left, so the check below sees this launch
     if (nslices > 0)
         hipLaunchKernelGGL(k_band_scatter_batch, dim3((unsigned)nslices), dim3(256), shmem, st, maps, slice_map,
-                           slice_lo, row0, rows, cursor, list);
+                           slice_lo, bands, cursor, list);
     MLM_HIP(hipGetLastError());
 }
 
@@ -1580,6 +1792,12 @@ void launch_count_pieces(const double2 *verts, int64_t nr1, int64_t cb0, int64_t
     if (ncells > 0)
         hipLaunchKernelGGL(k_count_pieces, dim3((unsigned)((ncells + 255) / 256)), dim3(256), 0, st, verts, nr1, cb0,
                            ncells, vb0, g, out);
+}
+
+void launch_count_rows(int64_t nbig, const BigPrep *prep, unsigned long long *out, hipStream_t st)
+{
+    if (nbig > 0)
+        hipLaunchKernelGGL(k_count_rows, dim3((unsigned)((nbig + 255) / 256)), dim3(256), 0, st, nbig, prep, out);
 }
 
 void launch_diff_rows(const MapGeom &g, const double *diff, double *map, hipStream_t st)

@@ -45,12 +45,23 @@ __global__ void k_tile_counts(int64_t nleaves, const int32_t *__restrict__ leaf_
     int lev = level[q];
     uint64_t c = code[q];
     int64_t i = compact_bits(c), j = compact_bits(c >> 1);
+    LeafInfo &li = info[lf];
+    {   // a leaf clear of the rows' rectangle (most, in a strip) holds none of them
+        double cx, cy, L, invL;
+        node_geom(c, lev, L0, cx, cy, L, invL);
+        const double e1 = d1 + 1e-12 * L0, e2 = d2 + 1e-12 * L0;
+        if (cx + L < x0 - e1 || cx - L > x0 + (double)nr1 * d1 + e1 || cy + L < y0 + (double)vb0 * d2 - e2 ||
+            cy - L > y0 + (double)vb1 * d2 + e2) {
+            li.na = li.nb = 0;
+            cnt[lf] = 0;
+            return;
+        }
+    }
     double scale = ldexp(1.0, lev - L0_exp);   // 2^lev / (2 L0)
     int64_t a0 = first_in_cell(x0, d1, h, 0, nr1, L0, scale, lev, i);
     int64_t a1 = first_in_cell(x0, d1, h, a0, nr1, L0, scale, lev, i + 1);
     int64_t b0 = first_in_cell(y0, d2, h, vb0, vb1, L0, scale, lev, j);
     int64_t b1 = first_in_cell(y0, d2, h, b0, vb1, L0, scale, lev, j + 1);
-    LeafInfo &li = info[lf];
     li.a_lo = (int32_t)a0;
     li.na = (int32_t)(a1 - a0);
     li.b_lo = (int32_t)b0;

@@ -171,6 +171,16 @@ __global__ void k_zero_counts(int32_t *p, int n)
     if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
 }
 
+// the counts of the large-triangle lists, then the sequence number, to the host
+__global__ __launch_bounds__(BIG_SHARDS) void k_publish_counts(const unsigned long long *__restrict__ count,
+                                                               int64_t *host, int64_t seq)
+{
+    host[2 + threadIdx.x] = (int64_t)count[(size_t)threadIdx.x * BIG_STRIDE];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(host + 1, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // (dst: pinned host memory)
 __global__ void k_copy_counts(const int32_t *__restrict__ src, int32_t *dst, int n)
 {
@@ -281,7 +291,7 @@ TotalSlot total_slot(mlm_lens *lens)
         return t;
     }
     Workspace &ws = lens->ws;
-    if (!ws.spin) ws.spin = static_cast<int64_t *>(coherent_pinned(2 * sizeof(int64_t) + MAX_LEVELS * sizeof(int32_t)));
+    if (!ws.spin) ws.spin = static_cast<int64_t *>(coherent_pinned((2 + BIG_SHARDS) * sizeof(int64_t)));
     t.host = ws.spin;
     t.seq = ++ws.spin_seq;
     return t;
@@ -349,6 +359,20 @@ int64_t scan_total_i64(mlm_lens *lens, const int64_t *in, int64_t *out, int64_t 
     const TotalSlot t = total_slot(lens);
     dev_scan_i64(in, out, n, false, scan_tmp(lens->ws, scan_tmp_bytes(n)), t.dev, t.host, t.seq, st);
     return read_total(t, st);
+}
+
+bool read_big_counts(mlm_lens *lens, const BigList &bl, BigStarts &at, hipStream_t st)
+{
+    const TotalSlot t = total_slot(lens);   // (pinned: lists are not kept inside a scratch arena)
+    hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count, t.host, t.seq);
+    (void)read_total(t, st);
+    bool whole = true;
+    at.lo[0] = 0;
+    for (int k = 0; k < BIG_SHARDS; ++k) {
+        at.lo[k + 1] = at.lo[k] + t.host[2 + k];
+        whole = whole && t.host[2 + k] <= bl.cap;
+    }
+    return whole;
 }
 
 void box_rays(Tree &T, const Region &R, int64_t vb0, int64_t vb1)
