@@ -36,6 +36,7 @@ struct Error {
 struct DevBuf {
     void *p = nullptr;
     size_t cap = 0;
+    int dev = 0;                  // device of p
     void *reserve(size_t bytes);  // contents are not preserved when it grows
     // grows keeping the first `keep` bytes (copied on `st`)
     void *grow_keep(size_t keep, size_t bytes, hipStream_t st);
@@ -272,6 +273,8 @@ struct Workspace {
     size_t pinned_cap = 0;
     int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
                                           // MAX_LEVELS counts of listed nodes or BIG_SHARDS of large triangles
+    size_t spin_cap = 0;
+    int spin_dev = 0, pinned_dev = 0;
     int64_t spin_seq = 0;                 // sequence number of the last total asked for
     int ops_p = -1;                       // expansion order of the operator tables
     ~Workspace();
@@ -283,6 +286,7 @@ struct mlm_lens {
     mlm_lens_params params{};
     int64_t n = 0;
     int device = 0;
+    mlm::DevBuf bx, by, bm;
     double *d_x = nullptr, *d_y = nullptr, *d_m = nullptr;
     double mass_sum = 0, mass2_sum = 0, max_abs = 0, r_star = 0;
     double ext1 = 0, ext2 = 0;            // star region: (R_*, R_*) or the rectangle's (c1, c2)
@@ -300,6 +304,7 @@ struct mlm_refiner {
     std::mutex mu;
     ~mlm_refiner()
     {
+        (void)hipDeviceSynchronize();   // the buffers go back to the pool idle
         if (gst) (void)hipStreamDestroy(gst);
     }
 };
@@ -504,6 +509,6 @@ void mlp_step_reset(int64_t *tstep, double *lacc, bool steps, hipStream_t st);
 // helpers
 void *pinned(mlm_lens *lens, size_t bytes);
 // host memory the device writes coherently while it runs (zeroed)
-void *coherent_pinned(size_t bytes);
+void *coherent_pinned(size_t bytes, size_t &cap, int &dev);
 
 }  // namespace mlm

@@ -291,7 +291,7 @@ TotalSlot total_slot(mlm_lens *lens)
         return t;
     }
     Workspace &ws = lens->ws;
-    if (!ws.spin) ws.spin = static_cast<int64_t *>(coherent_pinned((2 + BIG_SHARDS) * sizeof(int64_t)));
+    if (!ws.spin) ws.spin = static_cast<int64_t *>(coherent_pinned((2 + BIG_SHARDS) * sizeof(int64_t), ws.spin_cap, ws.spin_dev));
     t.host = ws.spin;
     t.seq = ++ws.spin_seq;
     return t;
