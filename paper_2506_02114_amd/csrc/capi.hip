@@ -284,11 +284,6 @@ __global__ void k_fill(double *p, int64_t n, double v)
     if (t < n) p[t] = v;
 }
 
-__global__ void k_zero_u64(unsigned long long *p, int n)
-{
-    if (threadIdx.x < n) p[threadIdx.x] = 0;
-}
-
 __global__ void k_zero_i32(int32_t *p, int64_t n)
 {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1175,10 +1170,10 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 } else {
                     launch_compact(ncells, nullptr, nullptr, base, cand, st);
                 }
-                uint8_t *lab = static_cast<uint8_t *>(ws.rlabel.reserve((size_t)std::max<int64_t>(ncand, 1)));
-                unsigned long long *rst3 = static_cast<unsigned long long *>(ws.rstats.reserve(4 * sizeof(unsigned long long)));
+                unsigned long long *rst3 = static_cast<unsigned long long *>(ws.rstats.reserve(REFINE_SLOTS * REFINE_STRIDE * sizeof(unsigned long long)));
                 if (!refine_stats_zeroed) {
-                    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, rst3, 4);
+                    hipLaunchKernelGGL(k_zero_u64n, dim3((REFINE_SLOTS * REFINE_STRIDE + 255) / 256), dim3(256), 0, st, rst3,
+                                       (int64_t)REFINE_SLOTS * REFINE_STRIDE);
                     refine_stats_zeroed = true;
                 }
                 // level by level: test every item of a level, number the refined
@@ -1191,13 +1186,14 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                     int32_t *flag = static_cast<int32_t *>(ws.rtflag.reserve((size_t)nlev * sizeof(int32_t)));
                     int64_t *pos = static_cast<int64_t *>(ws.rtpos.reserve((size_t)(nlev + 1) * sizeof(int64_t)));
                     launch_refine_test(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, cand, list,
-                                       R.nr1, vb0, verts, flag, d == 0 ? lab : nullptr, rst3, st);
+                                       R.nr1, vb0, verts, flag, rst3, st);
                     const int64_t nref = scan_i32_to_i64(lens, flag, pos, nlev, st);
                     if (d == 0) n_refined += nref;
                     if (nref == 0) break;
                     void *out = next->reserve((size_t)(4 * nref) * sub);
-                    launch_refine_expand(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, cand, list,
-                                         R.nr1, vb0, verts, flag, pos, map, out, st);
+                    int64_t *item = static_cast<int64_t *>(ws.ritem.reserve((size_t)nref * sizeof(int64_t)));
+                    launch_refine_expand(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, nref, cand,
+                                         list, R.nr1, vb0, verts, flag, pos, item, map, out, st);
                     list = out;
                     nlev = 4 * nref;
                     next = next == &ws.rsub0 ? &ws.rsub1 : &ws.rsub0;
@@ -1262,10 +1258,12 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         S.n_refine_candidates = n_cand;
         S.n_refined = n_refined;
         if (refine_stats_zeroed) {
-            unsigned long long h3[4];
-            MLM_HIP(hipMemcpy(h3, ws.rstats.p, sizeof h3, hipMemcpyDeviceToHost));
-            S.n_refine_tests = (int64_t)h3[0];
-            S.n_refine_large = (int64_t)h3[2];
+            std::vector<unsigned long long> h3((size_t)REFINE_SLOTS * REFINE_STRIDE);
+            MLM_HIP(hipMemcpy(h3.data(), ws.rstats.p, h3.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+            for (int k = 0; k < REFINE_SLOTS; ++k) {
+                S.n_refine_tests += (int64_t)h3[(size_t)k * REFINE_STRIDE];
+                S.n_refine_large += (int64_t)h3[(size_t)k * REFINE_STRIDE + 2];
+            }
         }
         S.t_refine_ms = t_refine;
         *stats = S;

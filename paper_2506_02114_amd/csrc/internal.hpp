@@ -268,7 +268,7 @@ struct Workspace {
     DevBuf bigcount, biglist;
     DevBuf binom, patch_info, patch_coef;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
-        bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, rsub0, rsub1, bitems, bqueue, tune_map;
+        bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
     int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
@@ -469,14 +469,18 @@ void launch_histogram(const double *mu, int64_t npix, double lo, double hi, int 
                       hipStream_t st);
 
 // refine.hip
+// the refinement's counts (statistics): REFINE_SLOTS partial sums of three counts
+// each, REFINE_STRIDE apart
+constexpr int REFINE_SLOTS = 256;
+constexpr int REFINE_STRIDE = 16;
 size_t refine_subcell_bytes();
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, int32_t *flag, uint8_t *label, unsigned long long *stats, hipStream_t st);
+                        const double2 *verts, int32_t *flag, unsigned long long *stats, hipStream_t st);
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
-                          int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                          const double2 *verts, const int32_t *flag, const int64_t *pos, double *map, void *out,
-                          hipStream_t st);
+                          int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
+                          int64_t vb0, const double2 *verts, const int32_t *flag, const int64_t *pos, int64_t *item,
+                          double *map, void *out, hipStream_t st);
 void launch_sample_features(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t n,
                             const int64_t *ab, float *feats, hipStream_t st);
 void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau,

@@ -14,6 +14,7 @@
 // (12 -> 64 -> 64 -> 1, BF16 weights, FP32 accumulation on the matrix cores)
 // flags from each cell's mapped corners and ear signs, plus every folded cell.
 #include <algorithm>
+#include <cstddef>
 #include <vector>
 
 #include "cellfeat.hpp"
@@ -75,8 +76,6 @@ __device__ inline void column_deposits(const RTri &t, int64_t i, int64_t jc, int
     }
 }
 
-
-
 struct RefineArgs {
     double x0, y0, d1, d2;
     LensConst lc;
@@ -91,15 +90,19 @@ struct RefineArgs {
     int max_depth, window;
 };
 
-// source position (pixel units) of image point (x0 + A d1, y0 + B d2)
+// image point (x0 + A d1, y0 + B d2), evaluated as written
+__device__ inline void image_point(const RefineArgs &ra, double A, double B, double &x, double &y)
+{
+#pragma clang fp contract(off)
+    x = ra.x0 + A * ra.d1;
+    y = ra.y0 + B * ra.d2;
+}
+
+// source position (pixel units) of an image point
 __device__ inline void shoot_uv(const RefineArgs &ra, double A, double B, double &u, double &v)
 {
     double x, y;
-    {
-#pragma clang fp contract(off)
-        x = ra.x0 + A * ra.d1;
-        y = ra.y0 + B * ra.d2;
-    }
+    image_point(ra, A, B, x, y);
     const int64_t lf = find_leaf(x, y, ra.nlevels, ra.L0, ra.L0_exp, ra.child0, ra.leaf, ra.node_leaf);
     if (lf < 0) {
         u = v = nan("");
@@ -115,62 +118,132 @@ __device__ inline void shoot_uv(const RefineArgs &ra, double A, double B, double
     v = uv.y;
 }
 
-// deposits of a (sub)cell's two triangles, times `sign`, into the map
-__device__ inline void add_cell(const RefineArgs &ra, double *map, double w, const double *u4, const double *v4,
-                                double sign)
-{
-#pragma unroll 1
-    for (int k = 0; k < 2; ++k) {
-        // triangle k of the cell: corners (0, 1, 2) or (0, 2, 3)
-        const double tu[3] = {u4[0], k ? u4[2] : u4[1], k ? u4[3] : u4[2]};
-        const double tv[3] = {v4[0], k ? v4[2] : v4[1], k ? v4[3] : v4[2]};
-        bool ok = true;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) ok = ok && isfinite(tu[m]) && isfinite(tv[m]);
-        if (!ok) continue;
-        const double fu = floor(fmin(tu[0], fmin(tu[1], tu[2]))), fv = floor(fmin(tv[0], fmin(tv[1], tv[2])));
-        const int64_t i0 = max((int64_t)fu, (int64_t)0);
-        const int64_t i1 = min((int64_t)floor(fmax(tu[0], fmax(tu[1], tu[2]))), (int64_t)ra.g.n1 - 1);
-        const int64_t j0 = max((int64_t)fv, (int64_t)0);
-        const int64_t j1 = min((int64_t)floor(fmax(tv[0], fmax(tv[1], tv[2]))), (int64_t)ra.g.n2 - 1);
-        if (i0 > i1 || j0 > j1) continue;
-        const RTri tri = rtri(tu[0], tv[0], tu[1], tv[1], tu[2], tv[2], fu, fv, sign * w);
-        for (int64_t jc = j0; jc <= j1; jc += RCH) {
-            const int nr = (int)min((int64_t)RCH, j1 - jc + 1);
-            for (int64_t i = i0; i <= i1; ++i) {
-                double d[RCH];
-#pragma unroll
-                for (int r = 0; r < RCH; ++r) d[r] = 0.0;
-                column_deposits(tri, i, jc, nr, fu, fv, d);
-#pragma unroll
-                for (int r = 0; r < RCH; ++r)
-                    if (r < nr && d[r] != 0.0) unsafeAtomicAdd(map + (jc + r) * (int64_t)ra.g.n1 + i, d[r]);
-            }
-        }
-    }
-}
-
 struct SubCell {
     double A0, B0, h;
     int d;
     double u[4], v[4];
 };
 
-// The test of one subcell; fills its 3 x 3 grid of source points (corners
-// from the subcell, five new rays) and returns whether it is refined.
+// ray k of the five new ones of a subcell's 3 x 3 grid, in halves of its side:
+// (1, 0), (0, 1), (1, 1), (2, 1), (1, 2)
+__device__ inline double ray_a(const SubCell &c, int k) { return c.A0 + (k == 1 ? 0.0 : (k == 3 ? c.h : 0.5 * c.h)); }
+__device__ inline double ray_b(const SubCell &c, int k) { return c.B0 + (k == 0 ? 0.0 : (k == 4 ? c.h : 0.5 * c.h)); }
+
+// The five rays of a subcell.  They nearly always lie in one leaf, and a
+// wavefront's subcells do too: then the leaf's stars and coefficients are read
+// once for all of them, as scalars (the lanes of each leaf in turn), and the
+// tree is descended once.  The arithmetic is shoot_uv's, in its order: the
+// refinement's decisions compare these rays with the grid's.  (Ray by ray, each
+// lane loading its own stars, a wavefront's tests took some 13000 instruction
+// slots, with this and test_line 3400.)
+__device__ inline void shoot_five(const RefineArgs &ra, const SubCell &c, double (&u)[5], double (&v)[5])
+{
+    double x[5], y[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) image_point(ra, ray_a(c, k), ray_b(c, k), x[k], y[k]);
+    int lf = (int)find_leaf(x[2], y[2], ra.nlevels, ra.L0, ra.L0_exp, ra.child0, ra.leaf, ra.node_leaf);
+    bool one = lf >= 0;
+    if (one) {   // the leaf's square holds the others: the same cell index at its level
+        const double cx = ra.leaves[lf].cx, cy = ra.leaves[lf].cy, sc = 0.5 * ra.leaves[lf].invL;
+        const double i = floor((cx + ra.L0) * sc), j = floor((cy + ra.L0) * sc);
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            one = one && floor((x[k] + ra.L0) * sc) == i && floor((y[k] + ra.L0) * sc) == j;
+    }
+    bool todo = one;
+    double ax[5], ay[5];
+    while (__any(todo)) {
+        const uint64_t m = __ballot(todo);
+        if (!(todo && lf == __builtin_amdgcn_readlane(lf, __ffsll((unsigned long long)m) - 1))) continue;
+        // wavefront-uniform to the compiler too (the lanes here share lf, and it
+        // would put that, a vector, in the place of the lane read above)
+        const int ul = __builtin_amdgcn_readfirstlane(lf);
+        // (read as constant memory, so that the wavefront's loads are scalar ones)
+        using CD = const __attribute__((address_space(4))) double;
+        using CI = const __attribute__((address_space(4))) int32_t;
+        CD *lp = (CD *)(ra.leaves + ul);
+        const struct {
+            double cx, cy, invL;
+            int32_t near_cnt;
+        } li{lp[offsetof(LeafInfo, cx) / 8], lp[offsetof(LeafInfo, cy) / 8], lp[offsetof(LeafInfo, invL) / 8],
+             ((CI *)lp)[offsetof(LeafInfo, near_cnt) / 4]};
+        CD *ns = (CD *)(ra.near + ((CI *)lp)[offsetof(LeafInfo, near_off) / 4]);
+        CD *dv = (CD *)(ra.deriv + (int64_t)ul * ra.p);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) ax[k] = ay[k] = 0.0;
+#pragma unroll 2
+        for (int32_t s = 0; s < li.near_cnt; ++s) {
+            const double4 st = make_double4(ns[4 * s], ns[4 * s + 1], ns[4 * s + 2], 0.0);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) near_star<double>(x[k] - li.cx, y[k] - li.cy, st, ax[k], ay[k]);
+        }
+        double sr[5], si[5];
+        double zr[5], zi[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            sr[k] = dv[2 * ra.p - 2];
+            si[k] = dv[2 * ra.p - 1];
+            zr[k] = (x[k] - li.cx) * li.invL;
+            zi[k] = (y[k] - li.cy) * li.invL;
+        }
+#pragma unroll 2
+        for (int l = ra.p - 2; l >= 0; --l) {
+            const double2 cf = make_double2(dv[2 * l], dv[2 * l + 1]);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                const double nr = sr[k] * zr[k] - si[k] * zi[k] + cf.x;
+                const double ni = sr[k] * zi[k] + si[k] * zr[k] + cf.y;
+                sr[k] = nr;
+                si[k] = ni;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            ax[k] += sr[k];
+            ay[k] -= si[k];
+        }
+        todo = false;
+    }
+    // (behind the loop: inside it the compiler lifts the rectangular sheet's
+    // logarithms, which need no leaf, out of their branch)
+    if (one) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            double w1, w2;
+            double2 uv;
+            finish_vertex(ra.lc, ra.g, x[k], y[k], ax[k], ay[k], w1, w2, uv);
+            u[k] = uv.x;
+            v[k] = uv.y;
+        }
+    } else {
+#pragma unroll 1
+        for (int k = 0; k < 5; ++k) {
+            double uk, vk;
+            shoot_uv(ra, ray_a(c, k), ray_b(c, k), uk, vk);
+#pragma unroll
+            for (int m = 0; m < 5; ++m)
+                if (m == k) {
+                    u[m] = uk;
+                    v[m] = vk;
+                }
+        }
+    }
+}
+
 // the subcell's 3 x 3 grid of source points: its corners and five new rays
 __device__ inline void fill_grid(const RefineArgs &ra, const SubCell &c, double (&gu)[3][3], double (&gv)[3][3])
 {
+    double u[5], v[5];
+    shoot_five(ra, c, u, v);
     gu[0][0] = c.u[0]; gv[0][0] = c.v[0];
     gu[0][2] = c.u[1]; gv[0][2] = c.v[1];
     gu[2][2] = c.u[2]; gv[2][2] = c.v[2];
     gu[2][0] = c.u[3]; gv[2][0] = c.v[3];
-    const double hh = 0.5 * c.h;
-    shoot_uv(ra, c.A0 + hh, c.B0, gu[0][1], gv[0][1]);
-    shoot_uv(ra, c.A0, c.B0 + hh, gu[1][0], gv[1][0]);
-    shoot_uv(ra, c.A0 + hh, c.B0 + hh, gu[1][1], gv[1][1]);
-    shoot_uv(ra, c.A0 + c.h, c.B0 + hh, gu[1][2], gv[1][2]);
-    shoot_uv(ra, c.A0 + hh, c.B0 + c.h, gu[2][1], gv[2][1]);
+    gu[0][1] = u[0]; gv[0][1] = v[0];
+    gu[1][0] = u[1]; gv[1][0] = v[1];
+    gu[1][1] = u[2]; gv[1][1] = v[2];
+    gu[1][2] = u[3]; gv[1][2] = v[3];
+    gu[2][1] = u[4]; gv[2][1] = v[4];
 }
 
 // triangle t of a refinement test: t = 0, 1 the (sub)cell's two, t = 2 ..
@@ -196,13 +269,20 @@ __device__ inline void test_triangle(int t, const SubCell &c, const double (&gu)
     }
 }
 
-__device__ inline bool refine_test(const RefineArgs &ra, const SubCell &c, double (&gu)[3][3], double (&gv)[3][3],
-                                   int &too_large)
+// What a test says: refined or not, or that another kind of test has to decide,
+// for a grid within 2 x 2 pixels or for a wider one
+enum Verdict { KEEP = 0, REFINE = 1, NEEDS_BOX = 2, NEEDS_COLUMNS = 3 };
+
+// the box of the 3 x 3 grid: whether it is finite and within the window
+__device__ inline bool grid_box(const RefineArgs &ra, const double (&gu)[3][3], const double (&gv)[3][3], double &umin,
+                                double &umax, double &vmin, double &vmax)
 {
-    fill_grid(ra, c, gu, gv);
-    double umin = 1e300, umax = -1e300, vmin = 1e300, vmax = -1e300;
+    umin = vmin = 1e300;
+    umax = vmax = -1e300;
     bool finite = true;
+#pragma unroll
     for (int r = 0; r < 3; ++r)
+#pragma unroll
         for (int s = 0; s < 3; ++s) {
             finite = finite && isfinite(gu[r][s]) && isfinite(gv[r][s]);
             umin = fmin(umin, gu[r][s]);
@@ -210,22 +290,29 @@ __device__ inline bool refine_test(const RefineArgs &ra, const SubCell &c, doubl
             vmin = fmin(vmin, gv[r][s]);
             vmax = fmax(vmax, gv[r][s]);
         }
-    if (!finite || !(umax - umin <= ra.window && vmax - vmin <= ra.window)) {
-        too_large = 1;
-        return false;
-    }
+    return finite && umax - umin <= ra.window && vmax - vmin <= ra.window;
+}
+
+__device__ inline bool cell_folded(const SubCell &c)
+{
     float f[12];
     cell_features(c.u, c.v, f);
-    if (folded(f)) return true;
+    return folded(f);
+}
+
+// Calls f(i, j, d) with what splitting the (sub)cell changes in every in-map
+// pixel of the grid's box (its children's deposits less its own), for a grid in
+// any box: pixel column by column, a pass of RCH rows at a time, one triangle
+// after the other (t uniform across the wavefront, so the vertex choice is a
+// scalar branch and only one triangle's column state is live)
+template <class F>
+__device__ inline void split_columns(const RefineArgs &ra, const SubCell &c, const double (&gu)[3][3],
+                                     const double (&gv)[3][3], double umin, double umax, double vmin, double vmax, F &&f)
+{
     const double w = ra.g.tri_weight * c.h * c.h;   // parent triangle weight
     const double ou = floor(umin), ov = floor(vmin);
     const int64_t i0 = max((int64_t)ou, (int64_t)0), i1 = min((int64_t)floor(umax), (int64_t)ra.g.n1 - 1);
     const int64_t j0 = max((int64_t)ov, (int64_t)0), j1 = min((int64_t)floor(vmax), (int64_t)ra.g.n2 - 1);
-    // L1 over the in-map pixels of (children's deposits - the cell's): pixel
-    // column by column, a pass of RCH rows at a time, one triangle after the
-    // other (t uniform across the wavefront, so the vertex choice is a scalar
-    // branch and only one triangle's column state is live)
-    double l1 = 0.0;
     for (int64_t jc = j0; jc <= j1; jc += RCH) {
         const int nr = (int)min((int64_t)RCH, j1 - jc + 1);
         for (int64_t i = i0; i <= i1; ++i) {
@@ -241,10 +328,121 @@ __device__ inline bool refine_test(const RefineArgs &ra, const SubCell &c, doubl
             }
 #pragma unroll
             for (int k = 0; k < RCH; ++k)
-                if (k < nr) l1 += fabs(diff[k]);
+                if (k < nr) f(i, jc + k, diff[k]);
         }
     }
-    return l1 > ra.tau * 2.0 * w;
+}
+
+// share of a triangle's area where x < 1 (x: its vertices' coordinates relative
+// to the box): the line cuts the corner at the lone vertex, (1 - x0)^2 / ((x1 -
+// x0) (x2 - x0)) of the area
+__device__ inline double line_share(double a, double b, double c)
+{
+    const double lo = fmin(a, b), hi = fmax(a, b);
+    const double mn = fmin(lo, c), mx = fmax(hi, c), md = fmax(lo, fmin(hi, c));
+    const bool low = md < 1.0;
+    const double e = low ? mx - 1.0 : 1.0 - mn, h = low ? mx - md : md - mn;
+    const double q = fdiv(e * e, (mx - mn) * h);
+    return mx < 1.0 ? 1.0 : (mn >= 1.0 ? 0.0 : (low ? 1.0 - q : q));
+}
+
+// The test of a grid within two pixels: one pixel line at most crosses it, so a
+// triangle's deposits are its shares on either side.  Five of six tests are of
+// this kind, and their ten triangles cost 30 instructions each instead of 220 a
+// pixel column.
+__device__ inline Verdict test_line(const RefineArgs &ra, const SubCell &c, const double (&gu)[3][3],
+                                    const double (&gv)[3][3], double umin, double umax, double vmin, double vmax)
+{
+    const double fu = floor(umin), fv = floor(vmin);
+    const bool two_u = umax - fu >= 1.0, two_v = vmax - fv >= 1.0;
+    if (!(umax - fu < 2.0 && vmax - fv < 2.0)) return NEEDS_COLUMNS;
+    if (two_u && two_v) return NEEDS_BOX;
+    // the first pixel and, where a line crosses the grid, the one beyond
+    const double i = fu, j = fv, i2 = fu + (two_u ? 1.0 : 0.0), j2 = fv + (two_v ? 1.0 : 0.0);
+    const double n1 = ra.g.n1, n2 = ra.g.n2;
+    const bool in1 = i >= 0.0 && j >= 0.0 && i < n1 && j < n2;
+    const bool in2 = (two_u || two_v) && i2 >= 0.0 && j2 >= 0.0 && i2 < n1 && j2 < n2;
+    const double o = two_v ? fv : fu;
+    double d1 = 0.0, d2 = 0.0;   // (children's deposits - the cell's) in units of its triangle weight
+#pragma unroll
+    for (int t = 0; t < 10; ++t) {
+        double a0, b0, a1, b1, a2, b2;
+        test_triangle(t, c, gu, gv, a0, b0, a1, b1, a2, b2);
+        const double S = area2(a0, b0, a1, b1, a2, b2);
+        const double x0 = (two_v ? b0 : a0) - o, x1 = (two_v ? b1 : a1) - o, x2 = (two_v ? b2 : a2) - o;
+        const double f = S != 0.0 ? (t < 2 ? -1.0 : 0.25) : 0.0, q = line_share(x0, x1, x2);
+        d1 += f * q;
+        d2 += f * (1.0 - q);
+    }
+    const double l1 = (in1 ? fabs(d1) : 0.0) + (in2 ? fabs(d2) : 0.0);
+    return l1 > ra.tau * 2.0 ? REFINE : KEEP;
+}
+
+// The same for a grid within the 2 x 2 pixels from (fu, fv): d[0 .. 4) what
+// splitting changes in the pixels (0, 0), (1, 0), (0, 1), (1, 1) of the box, in
+// units of the cell's triangle weight.  A triangle's share left of u = 1 and
+// below v = 1 is that of the corner u = 1 cuts off, clipped at v = 1 (or, the
+// corner lying right of it, the share below v = 1 less that).
+__device__ inline void split_box(const SubCell &c, const double (&gu)[3][3], const double (&gv)[3][3], double fu,
+                                 double fv, double (&d)[4])
+{
+    d[0] = d[1] = d[2] = d[3] = 0.0;
+#pragma unroll 1
+    for (int t = 0; t < 10; ++t) {
+        double a0, b0, a1, b1, a2, b2;
+        test_triangle(t, c, gu, gv, a0, b0, a1, b1, a2, b2);
+        const double f = area2(a0, b0, a1, b1, a2, b2) != 0.0 ? (t < 2 ? -1.0 : 0.25) : 0.0;
+        a0 -= fu; a1 -= fu; a2 -= fu;
+        b0 -= fv; b1 -= fv; b2 -= fv;
+        const double l = line_share(a0, a1, a2), h = line_share(b0, b1, b2);
+        double q = l * h;   // one of them 0 or 1
+        if (l > 0.0 && l < 1.0 && h > 0.0 && h < 1.0) {
+            const bool la = a0 < 1.0, lb = a1 < 1.0, lc = a2 < 1.0;
+            const double p0 = lb == lc ? a0 : (la == lc ? a1 : a2), r0 = lb == lc ? b0 : (la == lc ? b1 : b2);
+            const double p1 = lb == lc ? a1 : (la == lc ? a2 : a0), r1 = lb == lc ? b1 : (la == lc ? b2 : b0);
+            const double p2 = lb == lc ? a2 : (la == lc ? a0 : a1), r2 = lb == lc ? b2 : (la == lc ? b0 : b1);
+            const double t1 = fdiv(1.0 - p0, p1 - p0), t2 = fdiv(1.0 - p0, p2 - p0);
+            const double k = t1 * t2 * line_share(r0, r0 + t1 * (r1 - r0), r0 + t2 * (r2 - r0));
+            q = p0 < 1.0 ? k : h - k;
+        }
+        d[0] += f * q;
+        d[1] += f * (h - q);
+        d[2] += f * (l - q);
+        d[3] += f * ((1.0 - l) - (h - q));
+    }
+}
+
+// The test of one subcell, of the kind `kind` (KEEP: the first, by one line,
+// which sends the others on): its 3 x 3 grid of source points (corners from the
+// subcell, five new rays) and whether it is refined.
+template <int kind>
+__device__ inline Verdict refine_test(const RefineArgs &ra, const SubCell &c, int &too_large)
+{
+    double gu[3][3], gv[3][3], umin, umax, vmin, vmax;
+    fill_grid(ra, c, gu, gv);
+    const bool small = grid_box(ra, gu, gv, umin, umax, vmin, vmax);
+    if constexpr (kind == KEEP) {
+        if (!small) {
+            too_large = 1;
+            return KEEP;
+        }
+        if (cell_folded(c)) return REFINE;
+        return test_line(ra, c, gu, gv, umin, umax, vmin, vmax);
+    } else if constexpr (kind == NEEDS_BOX) {
+        const double fu = floor(umin), fv = floor(vmin), n1 = ra.g.n1, n2 = ra.g.n2;
+        double d[4], l1 = 0.0;
+        split_box(c, gu, gv, fu, fv, d);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double i = fu + (k & 1), j = fv + (k >> 1);
+            if (i >= 0.0 && j >= 0.0 && i < n1 && j < n2) l1 += fabs(d[k]);
+        }
+        return l1 > ra.tau * 2.0 ? REFINE : KEEP;
+    } else {
+        double l1 = 0.0;
+        split_columns(ra, c, gu, gv, umin, umax, vmin, vmax, [&](int64_t, int64_t, double d) { l1 += fabs(d); });
+        return l1 > ra.tau * 2.0 * (ra.g.tri_weight * c.h * c.h) ? REFINE : KEEP;
+    }
 }
 
 // Refinement level by level (breadth first): every (sub)cell of a level is
@@ -261,8 +459,9 @@ __device__ inline SubCell level_item(int64_t t, const int64_t *__restrict__ cand
 {
     if (list) return list[t];
     SubCell c;
-    const int64_t cell = cand[t];
-    const int64_t a = cell % (nr1 - 1), b = cell / (nr1 - 1);
+    // (a strip's cells number fewer than 2^32: its first row is vb0)
+    const uint32_t cell = (uint32_t)(cand[t] - (nr1 - 1) * vb0), ncol = (uint32_t)(nr1 - 1);
+    const int64_t a = cell % ncol, b = vb0 + cell / ncol;
     c.A0 = (double)a;
     c.B0 = (double)b;
     c.h = 1.0;
@@ -276,56 +475,99 @@ __device__ inline SubCell level_item(int64_t t, const int64_t *__restrict__ cand
     return c;
 }
 
-// flag[t] = the item is refined (and label[t] too, for candidate cells);
-// stats: [0] tested, [1] refined, [2] too large (one atomic per wavefront each)
-// (at most 168 registers, three waves per SIMD, a few bytes spilled: the
-// compiler's 173 held two, and the test is latency-bound on its rays' loads)
-__global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_test(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
-                                                      const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                      const double2 *__restrict__ verts, int32_t *__restrict__ flag,
-                                                      uint8_t *__restrict__ label,
-                                                      unsigned long long *__restrict__ stats)
+// counts of a wavefront's items added to its workgroup's slot of stats: [0]
+// tested, [1] refined, [2] too large (one atomic per wavefront each; at one
+// address for all, some 5 ns each, they took two thirds of the test's time)
+__device__ inline void add_stats(unsigned long long *__restrict__ stats, int tested, int refined, int large)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int refine = 0, large = 0, tested = 0;
-    if (t < n) {
-        const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
-        double gu[3][3], gv[3][3];
-        refine = refine_test(ra, c, gu, gv, large) ? 1 : 0;
-        tested = 1;
-        flag[t] = refine;
-        if (label) label[t] = (uint8_t)refine;
-    }
-    if (stats) {
-        int v[3] = {tested, refine, large};
+    int v[3] = {tested, refined, large};
+    stats += (size_t)(blockIdx.x % REFINE_SLOTS) * REFINE_STRIDE;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 3; ++k) {
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-            if ((threadIdx.x & 63) == 0 && v[k]) atomicAdd(stats + k, (unsigned long long)v[k]);
-        }
+        for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+        if ((threadIdx.x & 63) == 0 && v[k]) atomicAdd(stats + k, (unsigned long long)v[k]);
     }
 }
 
-// the refined items (flag[t]; pos: exclusive scan of the flags): the map
-// loses the item's deposits and gains its four children's, and the children
-// are written to out[4 pos[t] .. 4 pos[t] + 3]
-__global__ __launch_bounds__(RBLK) void k_refine_expand(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
-                                                        const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                        const double2 *__restrict__ verts,
-                                                        const int32_t *__restrict__ flag,
-                                                        const int64_t *__restrict__ pos, double *__restrict__ map,
-                                                        SubCell *__restrict__ out)
+// flag[t] = the verdict on item t, from the test that a grid within two pixels
+// needs; the others are left to k_refine_rest, so that the few lanes that need
+// more do not hold up the rest of their wavefronts.  Bound by instruction
+// issue: 26 ms over the levels of the learned refinement of a 400 x 400 map of
+// 20,000 stars, with k_refine_rest's 19 where one kernel for all took 90.
+__global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_test(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
+                                                      const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
+                                                      const double2 *__restrict__ verts, int32_t *__restrict__ flag,
+                                                      unsigned long long *__restrict__ stats)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n || !flag[t]) return;
-    const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
+    int large = 0;
+    Verdict v = KEEP;
+    if (t < n) {
+        const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
+        v = refine_test<KEEP>(ra, c, large);
+        flag[t] = v;
+    }
+    add_stats(stats, t < n ? 1 : 0, v == REFINE ? 1 : 0, large);
+}
+
+// The items of a level that need the test `kind`: a workgroup reads REST flags,
+// gathers those items in LDS and tests them with full lanes.
+constexpr int REST = 1024;
+template <int kind>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_rest(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
+                                                     const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
+                                                     const double2 *__restrict__ verts, int32_t *__restrict__ flag,
+                                                     unsigned long long *__restrict__ stats)
+{
+    __shared__ unsigned short queue[REST];
+    __shared__ int nq;
+    if (threadIdx.x == 0) nq = 0;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * REST;
+    for (int k = threadIdx.x; k < REST; k += blockDim.x)
+        if (lo + k < n && flag[lo + k] == kind) queue[atomicAdd(&nq, 1)] = (unsigned short)k;
+    __syncthreads();
+    const int m = nq;
+    for (int k0 = threadIdx.x & ~63; k0 < m; k0 += 256) {   // the same for a whole wavefront
+        const int k = k0 + (threadIdx.x & 63);
+        int refined = 0;
+        if (k < m) {
+            const int64_t t = lo + queue[k];
+            const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
+            int large = 0;
+            refined = refine_test<kind>(ra, c, large) == REFINE ? 1 : 0;   // (not too large: that was decided)
+            flag[t] = refined;
+        }
+        add_stats(stats, 0, refined, 0);
+    }
+}
+
+// item[pos[t]] = t for the refined items (pos: exclusive scan of the flags)
+__global__ __launch_bounds__(256) void k_refined_list(int64_t n, const int32_t *__restrict__ flag,
+                                                      const int64_t *__restrict__ pos, int64_t *__restrict__ item)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n && flag[t]) item[pos[t]] = t;
+}
+
+// the k-th refined item, k < n: the map loses its deposits and gains its four
+// children's, and the children are written to out[4 k .. 4 k + 3].  (Over all
+// the items of a level, a refined one in thirty, this took as long as 0.6 of
+// the tests.)
+__global__ __launch_bounds__(RBLK) void k_refine_expand(RefineArgs ra, int64_t n, const int64_t *__restrict__ item,
+                                                        const int64_t *__restrict__ cand,
+                                                        const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
+                                                        const double2 *__restrict__ verts, double *__restrict__ map,
+                                                        SubCell *__restrict__ out)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const SubCell c = level_item(item[k], cand, list, nr1, vb0, verts);
     double gu[3][3], gv[3][3];
     fill_grid(ra, c, gu, gv);
-    const double w = ra.g.tri_weight * c.h * c.h;
-    if (map) add_cell(ra, map, w, c.u, c.v, -1.0);
     const double hh = 0.5 * c.h;
-    SubCell *dst = out + 4 * pos[t];
+    SubCell *dst = out + 4 * k;
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -341,9 +583,29 @@ __global__ __launch_bounds__(RBLK) void k_refine_expand(RefineArgs ra, int64_t n
                 ch.u[m] = cu[m];
                 ch.v[m] = cv[m];
             }
-            if (map) add_cell(ra, map, 0.25 * w, ch.u, ch.v, +1.0);   // a refined child takes it back itself
             dst[2 * r + s] = ch;
         }
+    // the change per pixel (a refined child takes its own back), summed over the
+    // ten triangles before it goes to the map: neighbouring cells meet at a few
+    // pixels, and their atomics there were what the pass waited for
+    double umin, umax, vmin, vmax;
+    (void)grid_box(ra, gu, gv, umin, umax, vmin, vmax);
+    const double fu = floor(umin), fv = floor(vmin), n1 = ra.g.n1, n2 = ra.g.n2;
+    if (umax - fu < 2.0 && vmax - fv < 2.0) {
+        const double w = ra.g.tri_weight * c.h * c.h;
+        double d[4];
+        split_box(c, gu, gv, fu, fv, d);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const double i = fu + (m & 1), j = fv + (m >> 1);
+            if (d[m] != 0.0 && i >= 0.0 && j >= 0.0 && i < n1 && j < n2)
+                unsafeAtomicAdd(map + (int64_t)j * ra.g.n1 + (int64_t)i, d[m] * w);
+        }
+    } else {
+        split_columns(ra, c, gu, gv, umin, umax, vmin, vmax, [&](int64_t i, int64_t j, double d) {
+            if (d != 0.0) unsafeAtomicAdd(map + j * (int64_t)ra.g.n1 + i, d);
+        });
+    }
 }
 
 // features of arbitrary cells, corners shot on the spot
@@ -378,9 +640,11 @@ __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void 
     shoot_uv(ra, c.A0 + 1.0, c.B0, c.u[1], c.v[1]);
     shoot_uv(ra, c.A0 + 1.0, c.B0 + 1.0, c.u[2], c.v[2]);
     shoot_uv(ra, c.A0, c.B0 + 1.0, c.u[3], c.v[3]);
-    double gu[3][3], gv[3][3];
     int large = 0;
-    label[t] = refine_test(ra, c, gu, gv, large) ? 1 : 0;
+    Verdict r = refine_test<KEEP>(ra, c, large);
+    if (r == NEEDS_BOX) r = refine_test<NEEDS_BOX>(ra, c, large);
+    else if (r == NEEDS_COLUMNS) r = refine_test<NEEDS_COLUMNS>(ra, c, large);
+    label[t] = r == REFINE ? 1 : 0;
 }
 
 // cand[pos[t]] = base + t for flagged t (pos: exclusive scan of the flags,
@@ -427,24 +691,27 @@ size_t refine_subcell_bytes() { return sizeof(SubCell); }
 
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, int32_t *flag, uint8_t *label, unsigned long long *stats, hipStream_t st)
+                        const double2 *verts, int32_t *flag, unsigned long long *stats, hipStream_t st)
 {
     if (n <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);
     hipLaunchKernelGGL(k_refine_test, dim3((unsigned)((n + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, n, cand,
-                       static_cast<const SubCell *>(list), nr1, vb0, verts, flag, label, stats);
+                       static_cast<const SubCell *>(list), nr1, vb0, verts, flag, stats);
+    for (auto *rest : {k_refine_rest<NEEDS_BOX>, k_refine_rest<NEEDS_COLUMNS>})
+        hipLaunchKernelGGL(rest, dim3((unsigned)((n + REST - 1) / REST)), dim3(256), 0, st, ra, n, cand,
+                           static_cast<const SubCell *>(list), nr1, vb0, verts, flag, stats);
 }
 
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
-                          int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                          const double2 *verts, const int32_t *flag, const int64_t *pos, double *map, void *out,
-                          hipStream_t st)
+                          int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
+                          int64_t vb0, const double2 *verts, const int32_t *flag, const int64_t *pos, int64_t *item,
+                          double *map, void *out, hipStream_t st)
 {
-    if (n <= 0) return;
+    if (nref <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);
-    hipLaunchKernelGGL(k_refine_expand, dim3((unsigned)((n + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, n, cand,
-                       static_cast<const SubCell *>(list), nr1, vb0, verts, flag, pos, map,
-                       static_cast<SubCell *>(out));
+    hipLaunchKernelGGL(k_refined_list, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, flag, pos, item);
+    hipLaunchKernelGGL(k_refine_expand, dim3((unsigned)((nref + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, nref, item,
+                       cand, static_cast<const SubCell *>(list), nr1, vb0, verts, map, static_cast<SubCell *>(out));
 }
 
 void launch_sample_features(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t n,

@@ -38,3 +38,30 @@ def test_map_equals_clipping(orc, n1, n2, nr1, nr2, gamma, big):
     pos = ref.mu > 1e-6
     assert np.abs(mu[pos] / ref.mu[pos] - 1).max() < 1e-9
     assert np.abs(mu[~pos] - ref.mu[~pos]).max(initial=0.0) < 1e-10
+
+
+@pytest.mark.parametrize("nr1,nr2,gamma,window", [
+    (81, 75, 0.1, 8),       # cells of a fraction of a pixel: the test by one pixel line
+    (40, 41, -0.3, 8),      # about a pixel: the test of a 2 x 2 box
+    (17, 19, 0.2, 8),       # several pixels: the test by columns
+    (17, 19, 0.2, 2),       # most of them left alone
+])
+def test_plain_refinement_equals_the_oracle(orc, nr1, nr2, gamma, window):
+    import torch
+    import paper_2506_02114_amd as mlm
+    torch.cuda.init()
+    sf = W.star_field(12, 0.3, "salpeter", seed=5)
+    spec = dict(hw1=1.1, hw2=0.9, n1=20, n2=17, nray1=nr1, nray2=nr2, order=16)
+    rf = dict(refine_window=window, refine_depth=2)
+    gl = mlm.Lens(0.3, 0.05, gamma, sf.x, sf.y, sf.m)
+    mu, st = gl.map(refine="plain", **spec, **rf)
+    ol = orc.Lens(0.3, 0.05, gamma, sf.x, sf.y, sf.m)
+    ref = orc.magnification_map(ol, spec, method="fmm", p=16)
+    a, b = np.meshgrid(np.arange(nr1 - 1), np.arange(nr2 - 1))
+    labels, dmu, _ = orc.refine_cells(ref.region, ol, a.ravel(), b.ravel(), fmm=orc.FMM(ol, ref.region.L0, 16),
+                                      max_depth=2, window=window)
+    # the same cells refined (a draw with one at the threshold to 1e-9 would be a
+    # coincidence of 1e-5), so the maps differ by their deposits' rounding alone
+    assert st["n_refined"] == int(labels.sum())
+    want = ref.mu + dmu
+    assert np.abs(mu - want).max() < 1e-9 * np.abs(want).max()
