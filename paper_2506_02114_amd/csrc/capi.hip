@@ -460,7 +460,8 @@ int order_for(const mlm_map_request &q, const Region &R, const Tree &T)
     return auto_order(R.mean_m, R.mean_m2, std::ldexp(R.L0, -(T.nlevels - 1)), q.eps > 0 ? q.eps : 1e-7);
 }
 
-void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats);
+void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats,
+              const Region *region = nullptr);
 
 // Autotuner of a class of maps (precision, order, log2 of rays per star):
 // 1. the leaf size (the split threshold of app. C.1) that minimises the time
@@ -945,11 +946,14 @@ void apportion_bands(mlm_lens *lens, int64_t nb, int bh, const MapGeom &g, doubl
 }
 
 // one map (the body of mlm_map and of mlm_map_noalloc); the lens is locked
-void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats)
+// (region: its region, if the caller has it)
+void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats,
+              const Region *region)
 {
     const mlm_map_request &q = *req;
     Region R{};
-    setup_region(lens, req, &R);
+    if (region) R = *region;
+    else setup_region(lens, req, &R, &lens->ws, stream_of(req));
     int64_t cb0 = q.row_begin > 0 ? q.row_begin : 0;
     int64_t cb1 = q.row_end < 0 ? R.nr2 - 1 : q.row_end;
     if (cb0 > cb1 || cb1 > R.nr2 - 1) fail(MLM_EINVAL, "cell rows [%lld, %lld) outside [0, %lld)", (long long)cb0,
@@ -1364,7 +1368,7 @@ mlm_status mlm_map_noalloc(mlm_lens *lens, const mlm_map_request *req, double *m
     a.base = scratch_on(dev);
     a.cap = SCRATCH_BYTES;
     ArenaScope scope(a, lens->ws, stream_of(req));
-    map_impl(lens, req, mu, stats);
+    map_impl(lens, req, mu, stats, &R);
     API_END
 }
 
@@ -1503,7 +1507,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
         for (int32_t i = 0; i < nmaps; ++i) {
             mlm_map_request qi = reqs[i];
             Region Ri{};
-            setup_region(lenses[i], &qi, &Ri);
+            setup_region(lenses[i], &qi, &Ri, &lenses[i]->ws, st);
             (void)tune_map(lenses[i], qi, Ri, st);
         }
     // Regions, sizes and the chunks first (host arithmetic only): chunks of
@@ -1514,7 +1518,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
         MapPlan &m = P[i];
         m.lens = lenses[i];
         m.q = reqs[i];
-        setup_region(m.lens, &m.q, &m.R);
+        setup_region(m.lens, &m.q, &m.R, &m.lens->ws, st);
         if (m.R.nr1 > INT32_MAX || m.R.nr2 > INT32_MAX) fail(MLM_ERANGE, "map %d: ray grid too large", i);
         m.bh = band_height(m.q.n1, m.q.n2);
         if (m.bh <= 0) fail(MLM_ENOTSUP, "map %d: %d x %d pixels is too wide for batched row bands", i, m.q.n1, m.q.n2);
@@ -2077,8 +2081,8 @@ mlm_status mlm_cell_samples(mlm_lens *lens, const mlm_map_request *req, const in
         fail(MLM_ENOTSUP, "cell samples need FP64 and the FMM");
     std::lock_guard<std::mutex> guard(lens->mu);
     Region R{};
-    setup_region(lens, req, &R);
     hipStream_t st = stream_of(req);
+    setup_region(lens, req, &R, &lens->ws, st);
     Tree T;
     prepare_fmm(lens, R, *req, T, st);
     Workspace &ws = lens->ws;
@@ -2112,8 +2116,8 @@ mlm_status mlm_deflect(mlm_lens *lens, const mlm_map_request *req, const double 
     check_request(req);
     std::lock_guard<std::mutex> guard(lens->mu);
     Region R{};
-    setup_region(lens, req, &R);
     hipStream_t st = stream_of(req);
+    setup_region(lens, req, &R, &lens->ws, st);
     Workspace &ws = lens->ws;
     const double *zd = z_xy;
     double *wd = w_xy;
@@ -2125,11 +2129,8 @@ mlm_status mlm_deflect(mlm_lens *lens, const mlm_map_request *req, const double 
     }
     if (n > 0) {
         // every point must lie in the root square
-        std::vector<double> hz(2 * n);
-        MLM_HIP(hipMemcpyAsync(hz.data(), zd, n * 2 * sizeof(double), hipMemcpyDeviceToHost, st));
-        MLM_HIP(hipStreamSynchronize(st));
-        for (int64_t i = 0; i < 2 * n; ++i)
-            if (!(std::fabs(hz[i]) < R.L0)) fail(MLM_ERANGE, "point %lld lies outside the root square", (long long)(i / 2));
+        const int64_t bad = first_outside(lens, zd, 2 * n, R.L0, st);
+        if (bad < 2 * n) fail(MLM_ERANGE, "point %lld lies outside the root square", (long long)(bad / 2));
     }
     LensConst lc = lens_const(lens, R);
     Tree T;
@@ -2153,8 +2154,8 @@ mlm_status mlm_fmm_export(mlm_lens *lens, const mlm_map_request *req, mlm_tree_i
     check_request(req);
     std::lock_guard<std::mutex> guard(lens->mu);
     Region R{};
-    setup_region(lens, req, &R);
     hipStream_t st = stream_of(req);
+    setup_region(lens, req, &R, &lens->ws, st);
     Tree T;
     prepare_fmm(lens, R, *req, T, st);
     MLM_HIP(hipStreamSynchronize(st));

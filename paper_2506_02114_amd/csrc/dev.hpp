@@ -222,4 +222,13 @@ __device__ inline double near_div(double a, double b)
 __device__ inline float near_div(float a, float b) { return qdiv(a, b); }
 __device__ inline float qdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
+// a total to the host: the value, then its sequence number behind a
+// system-scope fence, so a host thread that sees the number sees the value
+__device__ inline void store_host_total(int64_t *total_host, int64_t v, int64_t seq)
+{
+    total_host[0] = v;
+    __threadfence_system();
+    __hip_atomic_store(total_host + 1, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace mlm

@@ -266,6 +266,7 @@ struct Workspace {
     DevBuf ilist, active, mult, local, ops_m2m, ops_m2l, ops_l2l;
     DevBuf leaves, near, deriv, near_offs;
     DevBuf bigcount, biglist;
+    DevBuf search;
     DevBuf binom, patch_info, patch_coef;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
         bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map;
@@ -312,7 +313,11 @@ struct mlm_refiner {
 namespace mlm {
 
 // region.cpp (host arithmetic, compiled without floating-point contraction)
-mlm_status setup_region(const mlm_lens *lens, const mlm_map_request *req, Region *R);
+// (ws, st: the lens's workspace and stream, where the caller runs on the device
+// and holds the lens: the macroimages of a lens with third-order terms are then
+// searched for there)
+mlm_status setup_region(const mlm_lens *lens, const mlm_map_request *req, Region *R, Workspace *ws = nullptr,
+                        hipStream_t st = nullptr);
 int auto_order(double mean_m, double mean_m2, double L, double eps);
 
 // field.cpp (host arithmetic, compiled without floating-point contraction)
@@ -325,7 +330,8 @@ int64_t field_sample(const mlm_field_params &F, std::vector<double> &x, std::vec
 // mass moments; (ext1, ext2): half-sizes of the star region's bounding box,
 // searched for the images of the map when the lens has third-order terms
 void shooting_region(const mlm_lens_params &P, double mean_m, double mean_m2, double ext1, double ext2,
-                     const mlm_map_request &q, double &X1, double &X2, double &dX1, double &dX2);
+                     const mlm_map_request &q, double &X1, double &X2, double &dX1, double &dX2,
+                     Workspace *ws = nullptr, hipStream_t st = nullptr);
 bool has_psi3(const mlm_lens_params &P);
 
 // the rays of vertex (or cell) rows [vb0, vb1] of the grid and of every
@@ -333,6 +339,8 @@ bool has_psi3(const mlm_lens_params &P);
 void box_rays(Tree &T, const Region &R, int64_t vb0, int64_t vb1);
 
 // tree.hip
+// the first of n coordinates not within (-L0, L0) (n: none)
+int64_t first_outside(mlm_lens *lens, const double *z, int64_t n, double L0, hipStream_t st);
 void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tree &T,
                 hipStream_t st);
 

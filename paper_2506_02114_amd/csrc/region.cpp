@@ -1,9 +1,10 @@
 // Shooting region, ray grid, tree root and expansion order of a map request.
-// Host arithmetic only; built with -ffp-contract=off so every formula is
+// Host arithmetic (but for the search of a lattice, the same on the device); built with -ffp-contract=off so every formula is
 // evaluated as written (plain IEEE double operations).
+#include <algorithm>
 #include <cmath>
 
-#include "internal.hpp"
+#include "cubic.hpp"
 
 namespace mlm {
 
@@ -30,36 +31,53 @@ bool has_psi3(const mlm_lens_params &P) { return P.psi3[0] != 0 || P.psi3[1] != 
  * perturbative); this one holds for any third-order model, at the cost of
  * shooting the box around all macroimages together.
  */
-constexpr int LAT = 2048;
+static LatticeBox search_lattice_host(const CubicSearch &S)
+{
+    LatticeBox B{LAT, -1, LAT, -1};
+    for (int j = 0; j < LAT; ++j) {
+        const double y = S.y(j);
+        for (int i = 0; i < LAT; ++i)
+            if (S.hit(S.x(i), y)) {
+                B.i0 = std::min(B.i0, i);
+                B.i1 = std::max(B.i1, i);
+                B.j0 = std::min(B.j0, j);
+                B.j1 = std::max(B.j1, j);
+            }
+    }
+    return B;
+}
 
-void cubic_region(const mlm_lens_params &P, double ext1, double ext2, double border, const mlm_map_request &q,
-                  double &X1, double &X2, double &dX1, double &dX2)
+// ws: the workspace of a call that runs on the device (the lattice is searched
+// there: a map that needs it took 14.6 ms with the 4.2 million points looked at
+// one after the other here, and takes 8.1), or null (a call that only asks for
+// the region, or one that must not allocate)
+static void cubic_region(const mlm_lens_params &P, double ext1, double ext2, double border, const mlm_map_request &q,
+                         double &X1, double &X2, double &dX1, double &dX2, Workspace *ws, hipStream_t st)
 {
     if (!(ext1 > 0) || !(ext2 > 0))
         fail(MLM_EINVAL, "a lens with third-order terms and no stars needs its shooting region stated "
                          "(centre_set, x1c, x2c, dx1, dx2)");
     const double kappa = P.kappa_star + P.kappa_smooth;
-    const double lam1 = 1.0 - kappa + P.gamma, lam2 = 1.0 - kappa - P.gamma;
-    const double a = P.psi3[0], b = P.psi3[1], c = P.psi3[2], d = P.psi3[3];
-    const double lo1 = q.y1c - q.hw1 - border, hi1 = q.y1c + q.hw1 + border;
-    const double lo2 = q.y2c - q.hw2 - border, hi2 = q.y2c + q.hw2 + border;
-    const double s1 = 2.0 * ext1 / (LAT - 1), s2 = 2.0 * ext2 / (LAT - 1);
-    double xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
-    for (int j = 0; j < LAT; ++j) {
-        const double y = -ext2 + j * s2;
-        for (int i = 0; i < LAT; ++i) {
-            const double x = -ext1 + i * s1;
-            const double w1 = lam1 * x - 0.5 * (a * x * x + 2.0 * b * x * y + c * y * y);
-            const double w2 = lam2 * y - 0.5 * (b * x * x + 2.0 * c * x * y + d * y * y);
-            if (w1 >= lo1 && w1 <= hi1 && w2 >= lo2 && w2 <= hi2) {
-                xmin = std::fmin(xmin, x);
-                xmax = std::fmax(xmax, x);
-                ymin = std::fmin(ymin, y);
-                ymax = std::fmax(ymax, y);
-            }
-        }
-    }
-    if (xmin > xmax) fail(MLM_ERANGE, "no image of the map inside the star region");
+    CubicSearch S{};
+    S.lam1 = 1.0 - kappa + P.gamma;
+    S.lam2 = 1.0 - kappa - P.gamma;
+    S.a = P.psi3[0];
+    S.b = P.psi3[1];
+    S.c = P.psi3[2];
+    S.d = P.psi3[3];
+    S.lo1 = q.y1c - q.hw1 - border;
+    S.hi1 = q.y1c + q.hw1 + border;
+    S.lo2 = q.y2c - q.hw2 - border;
+    S.hi2 = q.y2c + q.hw2 + border;
+    S.ext1 = ext1;
+    S.ext2 = ext2;
+    S.s1 = 2.0 * ext1 / (LAT - 1);
+    S.s2 = 2.0 * ext2 / (LAT - 1);
+    const double s1 = S.s1, s2 = S.s2;
+    const LatticeBox B = ws ? search_lattice(S, *ws, st) : search_lattice_host(S);
+    if (B.i0 > B.i1) fail(MLM_ERANGE, "no image of the map inside the star region");
+    // (x and y grow with the index)
+    double xmin = S.x(B.i0), xmax = S.x(B.i1), ymin = S.y(B.j0), ymax = S.y(B.j1);
     xmin = std::fmax(xmin - s1, -ext1);
     xmax = std::fmin(xmax + s1, ext1);
     ymin = std::fmax(ymin - s2, -ext2);
@@ -71,7 +89,8 @@ void cubic_region(const mlm_lens_params &P, double ext1, double ext2, double bor
 }
 
 void shooting_region(const mlm_lens_params &P, double mean_m, double mean_m2, double ext1, double ext2,
-                     const mlm_map_request &q, double &X1, double &X2, double &dX1, double &dX2)
+                     const mlm_map_request &q, double &X1, double &X2, double &dX1, double &dX2, Workspace *ws,
+                     hipStream_t st)
 {
     const double kappa = P.kappa_star + P.kappa_smooth;
     const double lam1 = 1.0 - kappa + P.gamma, lam2 = 1.0 - kappa - P.gamma;
@@ -88,7 +107,7 @@ void shooting_region(const mlm_lens_params &P, double mean_m, double mean_m2, do
         return;
     }
     if (cubic) {
-        cubic_region(P, ext1, ext2, border, q, X1, X2, dX1, dX2);
+        cubic_region(P, ext1, ext2, border, q, X1, X2, dX1, dX2, ws, st);
         if (q.dx1 > 0) dX1 = q.dx1;
         if (q.dx2 > 0) dX2 = q.dx2;
         return;
@@ -102,7 +121,7 @@ void shooting_region(const mlm_lens_params &P, double mean_m, double mean_m2, do
     dX2 = q.dx2 > 0 ? q.dx2 : (q.hw2 + border) / std::fabs(lam2);
 }
 
-mlm_status setup_region(const mlm_lens *lens, const mlm_map_request *q, Region *R)
+mlm_status setup_region(const mlm_lens *lens, const mlm_map_request *q, Region *R, Workspace *ws, hipStream_t st)
 {
     if (!(q->hw1 > 0) || !(q->hw2 > 0) || !std::isfinite(q->hw1) || !std::isfinite(q->hw2) ||
         q->n1 <= 0 || q->n2 <= 0 || !std::isfinite(q->y1c) || !std::isfinite(q->y2c))
@@ -125,7 +144,7 @@ mlm_status setup_region(const mlm_lens *lens, const mlm_map_request *q, Region *
     R->border = (n && P.kappa_star > 0) ? std::sqrt(P.kappa_star * R->mean_m2 / (f * R->mean_m)) : 0.0;
     double ext1 = lens->ext1, ext2 = lens->ext2;
     if (P.sheet == MLM_SHEET_NONE || !(ext1 > 0)) ext1 = ext2 = n ? lens->max_abs : 0.0;
-    shooting_region(P, R->mean_m, R->mean_m2, ext1, ext2, *q, R->X1, R->X2, R->dX1, R->dX2);
+    shooting_region(P, R->mean_m, R->mean_m2, ext1, ext2, *q, R->X1, R->X2, R->dX1, R->dX2, ws, st);
     R->pix1 = 2.0 * q->hw1 / (double)q->n1;
     R->pix2 = 2.0 * q->hw2 / (double)q->n2;
 

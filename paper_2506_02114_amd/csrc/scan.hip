@@ -70,15 +70,6 @@ __global__ __launch_bounds__(SC_THREADS) void k_tile_sums(const TI *__restrict__
 
 // exclusive scan of the nt tile sums in place (one workgroup); the total goes
 // to total_dev and/or total_host when given
-// the total to the host: the value, then its sequence number behind a
-// system-scope fence, so a host thread that sees the number sees the value
-__device__ inline void store_host_total(int64_t *total_host, int64_t v, int64_t seq)
-{
-    total_host[0] = v;
-    __threadfence_system();
-    __hip_atomic_store(total_host + 1, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 template <class TO>
 __global__ __launch_bounds__(SC_THREADS) void k_scan_sums(TO *__restrict__ sums, int64_t nt, int64_t *total_dev,
                                                          int64_t *total_host, int64_t seq)

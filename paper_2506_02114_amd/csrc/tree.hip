@@ -15,6 +15,7 @@
 #include <chrono>
 #include <cmath>
 
+#include "cubic.hpp"
 #include "dev.hpp"
 
 namespace mlm {
@@ -169,6 +170,72 @@ __global__ void k_zero_first(int64_t *p) { p[0] = 0; }
 __global__ void k_zero_counts(int32_t *p, int n)
 {
     if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+}
+
+// The check of the points of a deflection: the points read once (copied to the
+// host and looked at there, 400,000 points took 0.6 ms of the call's 2.0).
+constexpr int OUTSIDE_BLOCKS = 512;
+
+// part[block]: the first coordinate of the block's share that is not within
+// (-L0, L0), or n
+__global__ __launch_bounds__(BLK) void k_outside(const double *__restrict__ z, int64_t n, double L0,
+                                                 int64_t *__restrict__ part)
+{
+    __shared__ unsigned long long first;
+    if (threadIdx.x == 0) first = (unsigned long long)n;
+    __syncthreads();
+    int64_t bad = n;
+    for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK)
+        if (!(fabs(z[i]) < L0)) {
+            bad = i;
+            break;
+        }
+    if (bad < n) atomicMin(&first, (unsigned long long)bad);
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = (int64_t)first;
+}
+
+// the least of the parts to total_dev or the host
+__global__ __launch_bounds__(64) void k_outside_first(const int64_t *__restrict__ part, int np, int64_t n,
+                                                      int64_t *total_dev, int64_t *total_host, int64_t seq)
+{
+    int64_t m = n;
+    for (int i = threadIdx.x; i < np; i += 64) m = min(m, part[i]);
+    for (int d = 32; d; d >>= 1) m = min(m, (int64_t)__shfl_xor((long long)m, d, 64));
+    if (threadIdx.x == 0) {
+        if (total_dev) *total_dev = m;
+        if (total_host) store_host_total(total_host, m, seq);
+    }
+}
+
+// Which rows and columns of the lattice hit the widened map: a workgroup takes
+// LAT_ROWS rows, a thread every BLK-th column of them.
+constexpr int LAT_ROWS = 4;
+
+__global__ __launch_bounds__(BLK) void k_lattice(CubicSearch S, LatticeBox *__restrict__ part)
+{
+    __shared__ LatticeBox B;
+    if (threadIdx.x == 0) B = LatticeBox{LAT, -1, LAT, -1};
+    __syncthreads();
+    LatticeBox b{LAT, -1, LAT, -1};
+    for (int j = blockIdx.x * LAT_ROWS; j < (int)(blockIdx.x + 1) * LAT_ROWS; ++j) {
+        const double y = S.y(j);
+        for (int i = threadIdx.x; i < LAT; i += BLK)
+            if (S.hit(S.x(i), y)) {
+                b.i0 = min(b.i0, i);
+                b.i1 = max(b.i1, i);
+                b.j0 = min(b.j0, j);
+                b.j1 = max(b.j1, j);
+            }
+    }
+    if (b.i1 >= 0) {
+        atomicMin(&B.i0, b.i0);
+        atomicMax(&B.i1, b.i1);
+        atomicMin(&B.j0, b.j0);
+        atomicMax(&B.j1, b.j1);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = B;
 }
 
 // the counts of the large-triangle lists, then the sequence number, to the host
@@ -373,6 +440,31 @@ bool read_big_counts(mlm_lens *lens, const BigList &bl, BigStarts &at, hipStream
         whole = whole && t.host[2 + k] <= bl.cap;
     }
     return whole;
+}
+
+int64_t first_outside(mlm_lens *lens, const double *z, int64_t n, double L0, hipStream_t st)
+{
+    const int np = (int)std::min<int64_t>((n + BLK - 1) / BLK, OUTSIDE_BLOCKS);
+    int64_t *part = static_cast<int64_t *>(lens->ws.search.reserve(OUTSIDE_BLOCKS * sizeof(int64_t)));
+    const TotalSlot t = total_slot(lens);
+    hipLaunchKernelGGL(k_outside, dim3(np), dim3(BLK), 0, st, z, n, L0, part);
+    hipLaunchKernelGGL(k_outside_first, dim3(1), dim3(64), 0, st, part, np, n, t.dev, t.host, t.seq);
+    return read_total(t, st);
+}
+
+LatticeBox search_lattice(const CubicSearch &S, Workspace &ws, hipStream_t st)
+{
+    constexpr int np = LAT / LAT_ROWS;
+    static_assert(np * LAT_ROWS == LAT, "whole workgroups of rows");
+    LatticeBox *part = static_cast<LatticeBox *>(ws.search.reserve(np * sizeof(LatticeBox)));
+    hipLaunchKernelGGL(k_lattice, dim3(np), dim3(BLK), 0, st, S, part);
+    std::vector<LatticeBox> h(np);
+    MLM_HIP(hipMemcpyAsync(h.data(), part, np * sizeof(LatticeBox), hipMemcpyDeviceToHost, st));
+    MLM_HIP(hipStreamSynchronize(st));
+    LatticeBox B = h[0];
+    for (const LatticeBox &b : h)
+        B = LatticeBox{std::min(B.i0, b.i0), std::max(B.i1, b.i1), std::min(B.j0, b.j0), std::max(B.j1, b.j1)};
+    return B;
 }
 
 void box_rays(Tree &T, const Region &R, int64_t vb0, int64_t vb1)
