@@ -368,7 +368,7 @@ void check_request(const mlm_map_request *q)
 }
 
 // tree + FMM + leaf tables for a request
-void prepare_fmm(mlm_lens *lens, const Region &R, const mlm_map_request &q, Tree &T, hipStream_t st)
+void prepare_fmm(mlm_lens *lens, const Region &R, const mlm_map_request &q, Tree &T, hipStream_t st, bool all = false)
 {
     build_tree(lens, R, q, T, st);
     T.mixed = q.precision == MLM_PREC_MIXED;
@@ -377,7 +377,7 @@ void prepare_fmm(mlm_lens *lens, const Region &R, const mlm_map_request &q, Tree
         double Lmin = std::ldexp(R.L0, -(T.nlevels - 1));
         p = auto_order(R.mean_m, R.mean_m2, Lmin, q.eps > 0 ? q.eps : 1e-7);
     }
-    run_fmm(lens, T, p, st);
+    run_fmm(lens, T, p, st, all);
     build_leaf_tables(lens, T, st);
 }
 
@@ -2157,7 +2157,7 @@ mlm_status mlm_fmm_export(mlm_lens *lens, const mlm_map_request *req, mlm_tree_i
     hipStream_t st = stream_of(req);
     setup_region(lens, req, &R, &lens->ws, st);
     Tree T;
-    prepare_fmm(lens, R, *req, T, st);
+    prepare_fmm(lens, R, *req, T, st, true);
     MLM_HIP(hipStreamSynchronize(st));
     mlm_tree_info I{};
     I.n_nodes = T.nnodes;

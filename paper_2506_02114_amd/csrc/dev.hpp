@@ -59,6 +59,29 @@ __device__ inline int32_t lower_bound_u64(const uint64_t *a, int32_t n, uint64_t
     return lo;
 }
 
+// the indices in sorted a[lo, hi) of the first keys >= v and >= w (v <= w):
+// both searches in step, so that their loads are in flight together
+__device__ inline void two_bounds_u64(const uint64_t *a, int32_t lo, int32_t hi, uint64_t v, uint64_t w, int32_t &i,
+                                      int32_t &j)
+{
+    int32_t l0 = lo, l1 = lo;
+    for (int32_t n0 = hi - lo; n0 > 0;) {   // n0: length of either range
+        const int32_t half = n0 >> 1;
+        const bool up0 = a[l0 + half] < v, up1 = a[l1 + half] < w;
+        // (of an even length the upper part has half - 1 keys: its range is taken
+        // one longer, with a key that is known not to be less, so both keep step)
+        l0 += up0 ? half + 1 : 0;
+        l1 += up1 ? half + 1 : 0;
+        n0 = half;
+        if (n0 > 0) {
+            l0 = min(l0, hi - n0);
+            l1 = min(l1, hi - n0);
+        }
+    }
+    i = l0;
+    j = l1;
+}
+
 // A colleague reference: >= 0 a node of the same level, -1 nothing (outside
 // the root), <= -2 the leaf -(ref + 2) of a coarser level containing the square.
 // Stars of square `sc` (level shift sh) inside the reference's range.
@@ -72,8 +95,7 @@ __device__ inline void ref_stars(int32_t ref, uint64_t sc, int sh, const int32_t
         s1 = shi[ref];
     } else if (ref <= -2) {
         const int32_t L = -ref - 2, a = slo[L], b = shi[L];
-        s0 = a + lower_bound_u64(keys + a, b - a, sc << sh);
-        s1 = s0 + lower_bound_u64(keys + s0, b - s0, (sc + 1) << sh);
+        two_bounds_u64(keys, a, b, sc << sh, (sc + 1) << sh, s0, s1);
     }
 }
 

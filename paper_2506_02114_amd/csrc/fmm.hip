@@ -21,6 +21,12 @@ int64_t scan_total_public(mlm_lens *lens, const int32_t *in, int32_t *out, int64
 namespace {
 
 constexpr int BLK = 256;
+
+// first node of each level (and one past the last's)
+struct LevelRange {
+    int32_t first[MAX_LEVELS];
+};
+
 inline unsigned nblocks(int64_t n, int b = BLK) { return (unsigned)((n + b - 1) / b); }
 
 using cld = std::complex<long double>;
@@ -111,56 +117,131 @@ void table_l2l(int p, std::vector<double2> &out)
     }
 }
 
-// upward pass of one level: P2M at leaves, M2M from the four children
-// elsewhere; half a wavefront per node, lane k its coefficient k.  The pass is
-// bound by the latency of its loads, so the products are unrolled and several
-// loads are in flight (the table has zeros above the diagonal: every lane runs
-// all p + 1 terms).  R is the arithmetic type of the coefficients; star
-// offsets from the node centre are always formed in FP64.
+// a b with its roundings fixed (which of its products are contracted is
+// otherwise the compiler's choice, line by line; the mixed mode rounds the
+// coefficients to FP32, where one unit of difference here may show)
+template <class R> __device__ inline R mul_re(R ax, R ay, R bx, R by) { return fma(ax, bx, -(ay * by)); }
+template <class R> __device__ inline R mul_im(R ax, R ay, R bx, R by) { return fma(ay, bx, ax * by); }
+template <class C2> __device__ inline void add_product(C2 &acc, const C2 &a, const C2 &b)
+{
+    acc.x += mul_re(a.x, a.y, b.x, b.y);
+    acc.y += mul_im(a.x, a.y, b.x, b.y);
+}
+
+// Upward pass of one level: P2M at a leaf, M2M from the four children elsewhere;
+// half a wavefront per node, lane k its coefficient k.  A launch starts with cold
+// caches, and a load takes about 1 us then: the operator table (28 KB at order 20)
+// goes to LDS in one round of loads while the nodes' own data are fetched, all of
+// a node's data at once, and the lanes load a leaf's stars, or the children's
+// coefficients, side by side and hand them round (a level of
+// the 1000-star tree: 7.2 us, and 8.2 with each lane loading every star and entry
+// itself; of the 1e5-star tree: 10.7 on average, and 15.9).  Large levels
+// are walked by as many workgroups as fit the chip.  R is the arithmetic type of
+// the coefficients; star offsets from the node centre are always formed in FP64.
+constexpr int UP_BLOCKS = 1024;
+
+struct UpArgs {
+    int p;
+    double L0;
+    const uint64_t *code;
+    const int32_t *leaf, *slo, *shi, *child0;
+    const double *sx, *sy, *sm;
+};
+
+// z^k for k < 32 by binary powering, without branches (a lane per k); the
+// roundings are cpowi's
+__device__ inline double2 cpow32(double2 z, int k)
+{
+    double2 r = make_double2(1.0, 0.0);
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+        const double tx = mul_re(r.x, r.y, z.x, z.y), ty = mul_im(r.x, r.y, z.x, z.y);
+        r.x = (k >> b) & 1 ? tx : r.x;
+        r.y = (k >> b) & 1 ? ty : r.y;
+        const double zx = fma(z.x, z.x, -(z.y * z.y)), zy = z.x * z.y;
+        z = make_double2(zx, zy + zy);
+    }
+    return r;
+}
+
+// a leaf's coefficient k: a_0 = sum m_i, a_k = -(1/k) sum m_i zeta_i^k
 template <class R>
-__global__ __launch_bounds__(BLK) void k_upward(int64_t lo, int64_t hi, int lev, int p, double L0,
-                         const uint64_t *__restrict__ code,
-                         const int32_t *__restrict__ leaf, const int32_t *__restrict__ slo,
-                         const int32_t *__restrict__ shi, const int32_t *__restrict__ child0,
-                         const double *__restrict__ sx, const double *__restrict__ sy,
-                         const double *__restrict__ sm, const typename Cx<R>::c2 *__restrict__ m2m,
-                         typename Cx<R>::c2 *__restrict__ mult)
+__device__ inline void p2m(const UpArgs &u, uint64_t code, int32_t s0, int32_t s1, int k, int lev, R &ax, R &ay)
 {
     using C2 = typename Cx<R>::c2;
-    const int P1 = p + 1;
-    const int64_t q = lo + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 32;
-    const int k = threadIdx.x & 31;
-    if (q >= hi || k > p) return;
-    C2 acc = Cx<R>::make(0, 0);
-    if (leaf[q]) {
-        double cx, cy, L, invL;
-        node_geom(code[q], lev, L0, cx, cy, L, invL);
-        // a_0 = sum m_i;  a_k = -(1/k) sum m_i zeta_i^k
-        for (int32_t s = slo[q]; s < shi[q]; ++s) {
-            const R m = (R)sm[s];
-            if (k == 0) {
-                acc.x += m;
-            } else {
-                C2 z = Cx<R>::make((R)((sx[s] - cx) * invL), (R)((sy[s] - cy) * invL));
-                C2 zk = cpowi(z, k);
-                acc.x -= m * zk.x;
-                acc.y -= m * zk.y;
-            }
-        }
-        if (k > 0) acc = cscale(acc, (R)1 / (R)k);
-    } else {
-        const C2 *a = mult + (int64_t)child0[q] * P1;
-        const C2 *op = m2m + k;
-        for (int quad = 0; quad < 4; ++quad) {
-#pragma unroll 8
-            for (int kk = 0; kk <= p; ++kk) {
-                const C2 o = op[(quad * P1 + kk) * P1], v = a[quad * P1 + kk];
-                acc.x += o.x * v.x - o.y * v.y;
-                acc.y += o.x * v.y + o.y * v.x;
+    double cx, cy, L, invL;
+    node_geom(code, lev, u.L0, cx, cy, L, invL);
+    ax = ay = 0;
+    for (int32_t base = s0; base < s1; base += 32) {
+        const int32_t s = min(base + k, s1 - 1);
+        const R zx = (R)((u.sx[s] - cx) * invL), zy = (R)((u.sy[s] - cy) * invL), ms = (R)u.sm[s];
+        const int n = min(32, s1 - base);
+        for (int j = 0; j < n; j += 2) {   // two stars' powers side by side
+            const int j1 = min(j + 1, n - 1);
+            const R m0 = __shfl(ms, j, 32), m1 = __shfl(ms, j1, 32);
+            const C2 z0 = Cx<R>::make(__shfl(zx, j, 32), __shfl(zy, j, 32));
+            const C2 z1 = Cx<R>::make(__shfl(zx, j1, 32), __shfl(zy, j1, 32));
+            const C2 w0 = cpow32(z0, k), w1 = cpow32(z1, k);
+            ax = k ? fma(-m0, w0.x, ax) : ax + m0;
+            ay = k ? fma(-m0, w0.y, ay) : ay;
+            if (j + 1 < n) {
+                ax = k ? fma(-m1, w1.x, ax) : ax + m1;
+                ay = k ? fma(-m1, w1.y, ay) : ay;
             }
         }
     }
-    mult[q * P1 + k] = acc;
+    if (k > 0) {
+        const R ik = (R)1 / (R)k;
+        ax *= ik;
+        ay *= ik;
+    }
+}
+
+// (the first workgroup also clears the local expansions of the first `none` nodes)
+template <class R>
+__global__ __launch_bounds__(BLK) void k_upward(UpArgs u, int64_t lo, int64_t end, int lev,
+                                                const typename Cx<R>::c2 *__restrict__ m2m, typename Cx<R>::c2 *mult,
+                                                typename Cx<R>::c2 *__restrict__ local, int64_t none)
+{
+    extern __shared__ double2 up_lds[];
+    using C2 = typename Cx<R>::c2;
+    constexpr int PER = BLK / 32;
+    const int P1 = u.p + 1, n = 4 * P1, h = threadIdx.x >> 5, k = threadIdx.x & 31;
+    C2 *op = reinterpret_cast<C2 *>(up_lds), *a = op + n * P1 + h * n;
+    for (int e = threadIdx.x; e < n * P1; e += BLK) op[e] = m2m[e];
+    if (blockIdx.x == 0)
+        for (int64_t e = threadIdx.x; e < none * P1; e += BLK) local[e] = Cx<R>::make(0, 0);
+    bool first = true;
+    for (int64_t q0 = lo + (int64_t)blockIdx.x * PER; q0 < end; q0 += (int64_t)gridDim.x * PER) {
+        const bool valid = q0 + h < end;
+        const int64_t q = valid ? q0 + h : lo;   // (the first node stands in for one beyond the end)
+        const int32_t leaf = u.leaf[q], c0 = u.child0[q], s0 = u.slo[q], s1 = u.shi[q];
+        const uint64_t code = u.code[q];
+        const bool inner = leaf == 0;
+        R ax = 0, ay = 0;
+        if (inner) {
+            const C2 *c = mult + (int64_t)c0 * P1;
+#pragma unroll
+            for (int e = 0; e < (MAX_ORDER + 1) / 8; ++e)
+                if (e * 32 + k < n) a[e * 32 + k] = c[e * 32 + k];
+        } else {
+            p2m<R>(u, code, s0, s1, k, lev, ax, ay);
+        }
+        if (first) __syncthreads();   // (the table; the trips are the workgroup's)
+        first = false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (k <= u.p && inner) {
+            // (the table has zeros above the diagonal: every lane runs all the terms)
+#pragma unroll 4
+            for (int e = 0; e < n; ++e) {
+                const C2 o = op[e * P1 + k], v = a[e];
+                ax += mul_re(o.x, o.y, v.x, v.y);
+                ay += mul_im(o.x, o.y, v.x, v.y);
+            }
+        }
+        if (k <= u.p && valid) mult[q * P1 + k] = Cx<R>::make(ax, ay);
+    }
 }
 
 // Matrix-core product of the factorised M2L: Y (32 x 64) = P (32 x 32) B
@@ -196,31 +277,74 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// downward pass of the listed nodes of one level (>= 2), those whose square
-// meets the rays' rectangle (a star disc mostly reaches far beyond it: on the
-// 1e5-star map one node in seven does), one wavefront per node: L2L from the
-// parent (lane l: coefficient l), M2L from the same-level interaction nodes
-// through the factorised operator (the shared real matrix on the matrix
-// cores, the scalings on the vector units), P2L from the stars of
-// interaction squares inside coarser leaves
+// coefficient l of node q with its parent's part (levels 0 and 1 have no far field)
 template <class R>
-__global__ __launch_bounds__(64) void k_downward(int64_t lo, int lev, int p, double L0,
-                                                  const int32_t *__restrict__ act,
-                                                  const uint64_t *__restrict__ code, const int32_t *__restrict__ parent,
-                                                  const IEntry *__restrict__ ilist, const double *__restrict__ sx,
-                                                  const double *__restrict__ sy, const double *__restrict__ sm,
-                                                  const typename Cx<R>::c2 *__restrict__ Sf,
-                                                  const typename Cx<R>::c2 *__restrict__ Tf, const R *__restrict__ Pm,
-                                                  const typename Cx<R>::c2 *__restrict__ l2l,
-                                                  const typename Cx<R>::c2 *__restrict__ mult,
-                                                  typename Cx<R>::c2 *__restrict__ local)
+__device__ inline typename Cx<R>::c2 add_l2l(typename Cx<R>::c2 acc, int64_t q, int l, int lev, int p,
+                                             const uint64_t *__restrict__ code, const int32_t *__restrict__ parent,
+                                             const typename Cx<R>::c2 *__restrict__ l2l,
+                                             const typename Cx<R>::c2 *local)
+{
+    using C2 = typename Cx<R>::c2;
+    if (lev < 3) return acc;
+    const uint64_t c = code[q];
+    const int quad = (int)((c & 1ull) | (((c >> 1) & 1ull) << 1)), P1 = p + 1;
+    const C2 *op = l2l + quad * P1 * P1 + l;
+    const C2 *cp = local + (int64_t)parent[q] * P1;
+    // (the table is 0 for k < l)
+    // (loads in rounds of ten, beyond p on the last index, so that none is left
+    // over for a loop of single ones)
+    for (int k0 = 1; k0 <= p; k0 += 10) {
+        C2 o[10], v[10];
+#pragma unroll
+        for (int j = 0; j < 10; ++j) {
+            o[j] = op[min(k0 + j, p) * P1];
+            v[j] = cp[min(k0 + j, p)];
+        }
+#pragma unroll
+        for (int j = 0; j < 10; ++j)
+            if (k0 + j <= p) add_product(acc, o[j], v[j]);
+    }
+    return acc;
+}
+
+// What the far squares give the listed nodes of the levels >= 2, those whose
+// square meets the rays' rectangle (a star disc mostly reaches far beyond it: on
+// the 1e5-star map one node in seven does), one wavefront per node: M2L from the
+// same-level interaction nodes through the factorised operator (the shared real
+// matrix on the matrix cores, the scalings on the vector units), P2L from the
+// stars of interaction squares inside coarser leaves (lane l: coefficient l).
+// No level needs another's result here, so all levels go in one launch (with the
+// parents' part in it, level by level, the 1000-star tree took 52 us of kernels;
+// this and k_l2l take 28, and of the 1e5-star tree 415 where that took 500)
+// (listed.first[lev] listed nodes come before level lev's); k_l2l adds the
+// parents' part.  p2l: the P2L part per listed node, kept apart since a
+// coefficient's sum runs M2L, L2L, P2L.  Without p2l (inside a scratch arena) a
+// launch takes one level, and adds the parents' part itself.
+template <class R>
+__global__ __launch_bounds__(64) void k_m2l(LevelRange lo, LevelRange listed, int nlevels, int k0, int count, int p, double L0,
+                                            const int32_t *__restrict__ act, const uint64_t *__restrict__ code,
+                                            const IEntry *__restrict__ ilist, const double *__restrict__ sx,
+                                            const double *__restrict__ sy, const double *__restrict__ sm,
+                                            const typename Cx<R>::c2 *__restrict__ Sf,
+                                            const typename Cx<R>::c2 *__restrict__ Tf, const R *__restrict__ Pm,
+                                            const int32_t *__restrict__ parent,
+                                            const typename Cx<R>::c2 *__restrict__ l2l,
+                                            const typename Cx<R>::c2 *__restrict__ mult,
+                                            typename Cx<R>::c2 *local, typename Cx<R>::c2 *__restrict__ p2l_out)
 {
     using C2 = typename Cx<R>::c2;
     using V4 = typename V4T<R>::t;
     __shared__ DownLds<R> L;   // one wavefront per workgroup and node
     const int lane = threadIdx.x;
     const int P1 = p + 1;
-    const int64_t q = act[lo + blockIdx.x];
+    // consecutive nodes, whose sources are mostly the same, to one XCD (their
+    // workgroups are dealt out to the eight in turn): one L2 then holds them
+    const int per = (int)(gridDim.x / NXCD), at = (int)(blockIdx.x % NXCD) * per + (int)(blockIdx.x / NXCD);
+    if (at >= count) return;
+    const int k = k0 + at;
+    int lev = 2;
+    while (lev + 1 < nlevels && k >= listed.first[lev + 1]) ++lev;
+    const int64_t q = act[lo.first[lev] + k - listed.first[lev]];
     const int lgr = p <= 16 ? 4 : 5;
     const int mt_n = (p + 15) / 16, kt_n = (p + 3) / 4;
     const int r = lane & 15, g4 = lane >> 4;
@@ -257,16 +381,18 @@ __global__ __launch_bounds__(64) void k_downward(int64_t lo, int lev, int p, dou
     for (int g0 = 0; g0 < ns; g0 += GS) {
         const int gn = min(GS, ns - g0);
         const int ncol = ((2 * gn + 15) / 16) * 16;
-        for (int e = lane; e < (ncol / 2) << lgr; e += 64) {
-            const int k1 = e & ((1 << lgr) - 1), s2 = e >> lgr;   // row k1 = k - 1, source g0 + s2
-            R re = 0, im = 0;
-            if (s2 < gn && k1 < p) {
-                const C2 b = mult[(int64_t)L.src[g0 + s2] * P1 + k1 + 1], f = Sf[L.off[g0 + s2] * 32 + k1 + 1];
-                re = b.x * f.x - b.y * f.y;
-                im = b.x * f.y + b.y * f.x;
-            }
-            L.B[k1 * BRS + 2 * s2] = re;
-            L.B[k1 * BRS + 2 * s2 + 1] = im;
+        // a lane keeps its row k1 = k - 1 and walks the sources (loaded on any index
+        // where there is nothing to load, so that several rounds' loads are in
+        // flight)
+        const int k1 = lane & ((1 << lgr) - 1), kc = min(k1, p - 1) + 1, step = 64 >> lgr;
+        R *to = L.B + k1 * BRS;
+#pragma unroll 4
+        for (int s2 = lane >> lgr; s2 < ncol / 2; s2 += step) {
+            const int sc = g0 + min(s2, gn - 1);
+            const C2 b = mult[(int64_t)L.src[sc] * P1 + kc], f = Sf[L.off[sc] * 32 + kc];
+            const bool in = s2 < gn && k1 < p;
+            to[2 * s2] = in ? mul_re(b.x, b.y, f.x, f.y) : (R)0;
+            to[2 * s2 + 1] = in ? mul_im(b.x, b.y, f.x, f.y) : (R)0;
         }
         wave_sync();
         // Y = P B on the matrix cores, in place: a 16-column block of B is read
@@ -290,80 +416,102 @@ __global__ __launch_bounds__(64) void k_downward(int64_t lo, int lev, int p, dou
         }
         wave_sync();
         if (l >= 1 && l <= p)
+#pragma unroll 8
             for (int s2 = 0; s2 < gn; ++s2) {
                 const C2 t = Tf[L.off[g0 + s2] * 32 + l];
                 const R yr = L.B[(l - 1) * BRS + 2 * s2] - L.b0[g0 + s2].x * il;
                 const R yi = L.B[(l - 1) * BRS + 2 * s2 + 1] - L.b0[g0 + s2].y * il;
-                acc.x += t.x * yr - t.y * yi;
-                acc.y += t.x * yi + t.y * yr;
+                add_product(acc, t, Cx<R>::make(yr, yi));
             }
         wave_sync();   // the next group overwrites B
     }
     // P2L from the stars of interaction squares that are not nodes (parts of
     // coarser leaves): c_l += -m / (l zeta^l).  Lanes take the stars, the
-    // powers zeta^-l follow by one product per order, and each order's sum
-    // over the wavefront lands in lane l.
+    // powers zeta^-l follow by one product per order, and each order's sum over
+    // the wavefront (lanes 32 apart first, then 16, ...) lands in lane l.  Eight
+    // orders are summed together: of a pair of lanes each keeps half of them.
     double cx, cy, Lh, invL;
     node_geom(c, lev, L0, cx, cy, Lh, invL);
     C2 p2l = Cx<R>::make(0, 0);
-    {
-        const int cnt = (lane < NLIST && en.src == -1) ? en.shi - en.slo : 0;
-        int total;
-        const int excl = wave_excl_scan(cnt, lane, total);
-        for (int base = 0; base < total; base += 64) {
-            const int item = base + lane;
-            const int E = wave_find(excl, item);
-            const int s = __shfl(en.slo, E, 64) + item - __shfl(excl, E, 64);
-            C2 w = Cx<R>::make(0, 0);
-            R mq = 0;
-            if (item < total) {
-                w = cinv(Cx<R>::make((R)((sx[s] - cx) * invL), (R)((sy[s] - cy) * invL)));
-                mq = -(R)sm[s];
-            }
-            C2 t = cscale(w, mq);   // -m zeta^-1
-            for (int k = 1; k <= p; ++k) {
-                R vx = t.x, vy = t.y;
+    const int cnt = (lane < NLIST && en.src == -1) ? en.shi - en.slo : 0;
+    int total;
+    const int excl = wave_excl_scan(cnt, lane, total);
+    for (int base = 0; base < total; base += 64) {
+        const int item = base + lane;
+        const int E = wave_find(excl, item);
+        const int s = __shfl(en.slo, E, 64) + item - __shfl(excl, E, 64);
+        C2 w = Cx<R>::make(0, 0);
+        R mq = 0;
+        if (item < total) {
+            w = cinv(Cx<R>::make((R)((sx[s] - cx) * invL), (R)((sy[s] - cy) * invL)));
+            mq = -(R)sm[s];
+        }
+        C2 t = cscale(w, mq);   // -m zeta^-1
+        for (int o0 = 1; o0 <= p; o0 += 8) {
+            R vx[8], vy[8];
 #pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) {
-                    vx += __shfl_xor(vx, o, 64);
-                    vy += __shfl_xor(vy, o, 64);
+            for (int i = 0; i < 8; ++i) {
+                vx[i] = t.x;
+                vy[i] = t.y;
+                t = Cx<R>::make(mul_re(w.x, w.y, t.x, t.y), mul_im(w.x, w.y, t.x, t.y));
+            }
+#pragma unroll
+            for (int h = 4; h >= 1; h >>= 1) {
+                const bool up = lane & (8 * h);   // lane distances 32, 16, 8
+#pragma unroll
+                for (int i = 0; i < h; ++i) {
+                    const R gx = up ? vx[i] : vx[i + h], gy = up ? vy[i] : vy[i + h];
+                    vx[i] = (up ? vx[i + h] : vx[i]) + __shfl_xor(gx, 8 * h, 64);
+                    vy[i] = (up ? vy[i + h] : vy[i]) + __shfl_xor(gy, 8 * h, 64);
                 }
-                if (lane == k) {
-                    p2l.x += vx;
-                    p2l.y += vy;
-                }
-                t = cmul(t, w);
+            }
+#pragma unroll
+            for (int o = 4; o >= 1; o >>= 1) {
+                vx[0] += __shfl_xor(vx[0], o, 64);
+                vy[0] += __shfl_xor(vy[0], o, 64);
+            }
+            // order o0 + i is with the lanes whose bits 5, 4, 3 are i's
+            const int i = lane - o0, from = ((i & 4) << 3) | ((i & 2) << 3) | ((i & 1) << 3);
+            const R sxk = __shfl(vx[0], from, 64), syk = __shfl(vy[0], from, 64);
+            if (i >= 0 && i < 8) {
+                p2l.x += sxk;
+                p2l.y += syk;
             }
         }
     }
-    // coefficient l = lane
+    // coefficient l = lane (c_0 only shifts the potential)
     if (l > p) return;
     if (l == 0) {
-        local[q * P1] = Cx<R>::make(0, 0);   // c_0 only shifts the potential
-        return;
+        acc = p2l = Cx<R>::make(0, 0);
+    } else if (!p2l_out || lev == 2) {   // (level 2 has no parents' part)
+        acc = add_l2l<R>(acc, q, l, lev, p, code, parent, l2l, local);
+        acc.x += p2l.x * il;
+        acc.y += p2l.y * il;
     }
-    // L2L from the parent (levels 0 and 1 have no far field)
-    if (lev >= 3) {
-        const int quad = (int)((c & 1ull) | (((c >> 1) & 1ull) << 1));
-        const C2 *op = l2l + quad * P1 * P1 + l;
-        const C2 *cp = local + (int64_t)parent[q] * P1;
-#pragma unroll 4
-        for (int k = 1; k <= p; ++k) {   // (the table is 0 for k < l)
-            const C2 o = op[k * P1], v = cp[k];
-            acc.x += o.x * v.x - o.y * v.y;
-            acc.y += o.x * v.y + o.y * v.x;
-        }
-    }
-    acc.x += p2l.x * il;
-    acc.y += p2l.y * il;
     local[q * P1 + l] = acc;
+    if (p2l_out && lev > 2) p2l_out[(int64_t)k * P1 + l] = p2l;
 }
 
-template <class C2>
-__global__ void k_zero2(C2 *a, int64_t n)
+// The parents' part for n listed nodes of one level, after their own M2L, and
+// the P2L part after it: half a wavefront per node, lane l its coefficient l.
+template <class R>
+__global__ __launch_bounds__(BLK) void k_l2l(int64_t lo, int n, int lev, int p, const int32_t *__restrict__ act,
+                                             const uint64_t *__restrict__ code, const int32_t *__restrict__ parent,
+                                             const typename Cx<R>::c2 *__restrict__ l2l,
+                                             const typename Cx<R>::c2 *__restrict__ p2l,
+                                             typename Cx<R>::c2 *local)
 {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) a[t] = C2{0, 0};
+    using C2 = typename Cx<R>::c2;
+    const int P1 = p + 1;
+    const int k = (int)(((int64_t)blockIdx.x * BLK + threadIdx.x) >> 5), l = threadIdx.x & 31;
+    if (k >= n || l == 0 || l > p) return;
+    const int64_t q = act[lo + k];
+    C2 acc = add_l2l<R>(local[q * P1 + l], q, l, lev, p, code, parent, l2l, local);
+    const C2 d = p2l[(int64_t)k * P1 + l];
+    const R il = (R)1 / (R)l;
+    acc.x += d.x * il;
+    acc.y += d.y * il;
+    local[q * P1 + l] = acc;
 }
 
 // per-leaf data for the ray kernels, of the leaves that meet the rays'
@@ -458,7 +606,7 @@ void upload_ops(DevBuf &buf, const std::vector<double2> &h)
 }
 
 template <class R>
-void run_fmm_t(mlm_lens *lens, Tree &T, int p, hipStream_t st, typename Cx<R>::c2 *&mult,
+void run_fmm_t(mlm_lens *lens, Tree &T, int p, bool all, hipStream_t st, typename Cx<R>::c2 *&mult,
                typename Cx<R>::c2 *&local)
 {
     using C2 = typename Cx<R>::c2;
@@ -490,55 +638,81 @@ void run_fmm_t(mlm_lens *lens, Tree &T, int p, hipStream_t st, typename Cx<R>::c
     const R *Pm = reinterpret_cast<const R *>(Sf + 2 * 49 * 32);
     mult = static_cast<C2 *>(ws.mult.reserve((size_t)T.nnodes * P1 * sizeof(C2)));
     local = static_cast<C2 *>(ws.local.reserve((size_t)T.nnodes * P1 * sizeof(C2)));
-    // upward
-    for (int lev = T.nlevels - 1; lev >= 0; --lev) {
-        int64_t lo = T.level_lo[lev], hi = T.level_hi[lev];
-        hipLaunchKernelGGL(k_upward<R>, dim3(nblocks((hi - lo) * 32)), dim3(BLK), 0, st, lo, hi, lev, p, T.L0, T.code, T.leaf,
-                           T.slo, T.shi, T.child0, T.x, T.y, T.m, ws.ops_m2m.as<C2>(), mult);
+    LevelRange lo{}, listed{};
+    for (int lev = 0; lev < T.nlevels; ++lev) {
+        lo.first[lev] = (int32_t)T.level_lo[lev];
+        lo.first[lev + 1] = (int32_t)T.level_hi[lev];
+        listed.first[lev + 1] = listed.first[lev] + (lev >= 2 ? T.nactive[lev] : 0);
     }
-    // downward: levels 0, 1 have no far field
-    int64_t top = T.nlevels > 2 ? T.level_lo[2] : T.nnodes;
-    hipLaunchKernelGGL(k_zero2<C2>, dim3(nblocks(top * P1)), dim3(BLK), 0, st, local, top * P1);
-    for (int lev = 2; lev < T.nlevels; ++lev) {
-        if (T.nactive[lev] == 0) break;   // nor has any finer level
-        hipLaunchKernelGGL(k_downward<R>, dim3((unsigned)T.nactive[lev]), dim3(64), 0, st, T.level_lo[lev], lev, p,
-                           T.L0, T.active, T.code, T.parent, T.ilist, T.x, T.y, T.m, Sf, Tf, Pm, ws.ops_l2l.as<C2>(), mult, local);
+    // upward, to level 2, the coarsest that a list holds (all: to the root);
+    // levels 0, 1 have no far field
+    constexpr int per = BLK / 32;
+    constexpr size_t most = (4 * (MAX_ORDER + 1) * (MAX_ORDER + 1) + per * 4 * (MAX_ORDER + 1)) * sizeof(C2);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_upward<R>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+    MLM_HIP(attr);
+    const UpArgs u{p, T.L0, T.code, T.leaf, T.slo, T.shi, T.child0, T.x, T.y, T.m};
+    const int64_t none = T.nlevels > 2 ? T.level_lo[2] : T.nnodes;
+    const int top = all ? 0 : std::min(2, T.nlevels - 1);
+    for (int lev = T.nlevels - 1; lev >= top; --lev)
+        hipLaunchKernelGGL(k_upward<R>,
+                           dim3(std::min(nblocks(T.level_hi[lev] - T.level_lo[lev], per), (unsigned)UP_BLOCKS)),
+                           dim3(BLK), (4 * P1 + 4 * per) * P1 * sizeof(C2), st, u, T.level_lo[lev], T.level_hi[lev], lev,
+                           ws.ops_m2m.as<C2>(), mult, local, lev == top ? none : 0);
+    // downward
+    const int32_t n = listed.first[T.nlevels];
+    if (n == 0) return;
+    C2 *p2l = thread_arena() ? nullptr : static_cast<C2 *>(ws.p2l.reserve((size_t)n * P1 * sizeof(C2)));
+    const auto m2l = [&](int k0, int32_t cnt) {
+        hipLaunchKernelGGL(k_m2l<R>, dim3(nblocks(cnt, NXCD) * NXCD), dim3(64), 0, st, lo, listed, T.nlevels, k0, cnt, p, T.L0, T.active,
+                           T.code, T.ilist, T.x, T.y, T.m, Sf, Tf, Pm, T.parent, ws.ops_l2l.as<C2>(), mult, local, p2l);
+    };
+    if (p2l) m2l(0, n);
+    for (int lev = p2l ? 3 : 2; lev < T.nlevels && T.nactive[lev] > 0; ++lev) {   // (where a level has none, nor has any finer)
+        if (p2l)
+            hipLaunchKernelGGL(k_l2l<R>, dim3(nblocks((int64_t)T.nactive[lev] * 32)), dim3(BLK), 0, st, T.level_lo[lev],
+                               T.nactive[lev], lev, p, T.active, T.code, T.parent, ws.ops_l2l.as<C2>(),
+                               p2l + (size_t)listed.first[lev] * P1, local);
+        else
+            m2l(listed.first[lev], T.nactive[lev]);
     }
 }
 
 }  // namespace
 
-void run_fmm(mlm_lens *lens, Tree &T, int p, hipStream_t st)
+void run_fmm(mlm_lens *lens, Tree &T, int p, hipStream_t st, bool all)
 {
     if (p < 1 || p > MAX_ORDER) fail(MLM_EINVAL, "expansion order %d outside [1, %d]", p, MAX_ORDER);
     T.p = p;
     // FP64 in both modes: the low-order Taylor coefficients carry the field of
     // the whole star disc (about kappa_* |z|), far above what FP32 translation
     // chains could hold to a fraction of a pixel
-    run_fmm_t<double>(lens, T, p, st, T.mult, T.local);
+    run_fmm_t<double>(lens, T, p, all, st, T.mult, T.local);
 }
 
 void build_leaf_tables(mlm_lens *lens, Tree &T, hipStream_t st)
 {
     Workspace &ws = lens->ws;
     int64_t nl = T.nleaves;
-    int32_t *cnt = static_cast<int32_t *>(ws.flags.reserve(nl * 4));
-    int32_t *offs = static_cast<int32_t *>(ws.near_offs.reserve(nl * 4));
-    hipLaunchKernelGGL(k_leaf_block, dim3(nblocks(nl)), dim3(BLK), 0, st, nl, T.L0, ray_box(T), T.leaf_node,
-                       T.code, T.level, T.block, cnt);
-    T.near_total = scan_total_public(lens, cnt, offs, nl, st);
+    if (!T.near_numbered) {
+        int32_t *cnt = static_cast<int32_t *>(ws.flags.reserve(nl * 4));
+        T.near_offs = static_cast<int32_t *>(ws.near_offs.reserve(nl * 4));
+        hipLaunchKernelGGL(k_leaf_block, dim3(nblocks(nl)), dim3(BLK), 0, st, nl, T.L0, ray_box(T), T.leaf_node,
+                           T.code, T.level, T.block, cnt);
+        T.near_total = scan_total_public(lens, cnt, T.near_offs, nl, st);
+    }
     T.leaves = static_cast<LeafInfo *>(ws.leaves.reserve(nl * sizeof(LeafInfo)));
     const size_t nn = (size_t)(T.near_total > 0 ? T.near_total : 1);
     T.near = static_cast<double4 *>(ws.near.reserve(nn * sizeof(double4)));
     if (T.mixed) {
         T.deriv_f = static_cast<float2 *>(ws.deriv.reserve((size_t)nl * T.p * sizeof(float2)));
         hipLaunchKernelGGL(k_leaf_tables<float>, dim3(nblocks(nl * 64)), dim3(BLK), 0, st, nl, T.p, T.L0, ray_box(T),
-                           T.leaf_node, T.code, T.level, offs, T.coll, T.slo, T.shi, T.keys, T.x, T.y, T.m, T.local,
+                           T.leaf_node, T.code, T.level, T.near_offs, T.coll, T.slo, T.shi, T.keys, T.x, T.y, T.m, T.local,
                            T.leaves, T.deriv_f, T.near);
     } else {
         T.deriv = static_cast<double2 *>(ws.deriv.reserve((size_t)nl * T.p * sizeof(double2)));
         hipLaunchKernelGGL(k_leaf_tables<double>, dim3(nblocks(nl * 64)), dim3(BLK), 0, st, nl, T.p, T.L0, ray_box(T),
-                           T.leaf_node, T.code, T.level, offs, T.coll, T.slo, T.shi, T.keys, T.x, T.y, T.m, T.local,
+                           T.leaf_node, T.code, T.level, T.near_offs, T.coll, T.slo, T.shi, T.keys, T.x, T.y, T.m, T.local,
                            T.leaves, T.deriv, T.near);
     }
 }

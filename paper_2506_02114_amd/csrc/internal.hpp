@@ -250,6 +250,8 @@ struct Tree {
     int32_t *active = nullptr;           // nodes to evaluate, level by level from level_lo[level]
     int32_t nactive[MAX_LEVELS] = {};    // their number per level
     int64_t nactive_leaves = 0;          // leaves that meet the rectangle
+    int32_t *near_offs = nullptr;        // where each leaf's star table starts
+    bool near_numbered = false;          // near_offs and near_total are known with the tree
     bool mixed = false;                  // FP32 Taylor evaluation (deriv_f) and near field
     double2 *mult = nullptr, *local = nullptr;   // FP64 in both modes
     // leaf tables
@@ -263,7 +265,7 @@ struct Tree {
 struct Workspace {
     DevBuf keys_in, keys, idx_in, idx, sx, sy, sm, scan_tmp;
     DevBuf code, level, leaf, slo, shi, block, parent, child0, coll, node_leaf, leaf_node, flags, offs;
-    DevBuf ilist, active, mult, local, ops_m2m, ops_m2l, ops_l2l;
+    DevBuf ilist, active, mult, local, p2l, ops_m2m, ops_m2l, ops_l2l;
     DevBuf leaves, near, deriv, near_offs;
     DevBuf bigcount, biglist;
     DevBuf search;
@@ -345,7 +347,8 @@ void build_tree(mlm_lens *lens, const Region &R, const mlm_map_request &req, Tre
                 hipStream_t st);
 
 // fmm.hip
-void run_fmm(mlm_lens *lens, Tree &T, int p, hipStream_t st);
+// (all: the multipoles of levels 0 and 1 too, which no list holds)
+void run_fmm(mlm_lens *lens, Tree &T, int p, hipStream_t st, bool all = false);
 void build_leaf_tables(mlm_lens *lens, Tree &T, hipStream_t st);
 
 // shoot.hip
