@@ -324,7 +324,8 @@ __device__ inline int column_pieces(const P2 (&Td)[3], const double (&svd)[3], c
     const int ja = (int)fmin(fmax(floor((double)cvmin) + fv0, (double)j0), (double)j1 + 1.0);
     const int jb = (int)fmax(fmin(floor((double)cvmax) + fv0, (double)j1), (double)j0 - 1.0);
     R rj = (R)((double)ja - fv0);   // row line j local to fv0 (an integer: exact, also in FP32)
-    R h0 = col_cumulative(S, rj);
+    // (0 below all of the column's edges, as it is unless the map cuts them off)
+    R h0 = floor((double)cvmin) + fv0 < (double)j0 ? col_cumulative(S, rj) : R(0);
     for (int j = ja; j <= jb; ++j) {
         rj += R(1);
         const R h1 = col_cumulative(S, rj);
@@ -444,19 +445,22 @@ __device__ inline void write_big(const BigList &bl, const BigRange &r, int big, 
 // v00-v11 into T1 = (v00, v10, v11) and T2 = (v00, v11, v01)): single-pixel
 // triangles are deposited, those within 2 x 2 pixels apportioned in place, and
 // the pixel columns of the others (the medium ones) are spread evenly over the
-// wavefront's lanes.  Which of the two triangles are large (bit k) is returned,
+// wavefront's lanes.  (One triangle in six is a small one on the 1e5-star map:
+// gathered in sq, two bytes of LDS a lane, and apportioned by the first lanes, they
+// cost the wavefront their 300 instructions once instead of for both triangles of
+// a cell: FIGURES.)  Which of the two triangles are large (bit k) is returned,
 // and they are listed in `bl` (LIST; `cell`: the cell's number in the strip).
 // Called by whole wavefronts.
 template <bool MIXED, int N, bool LIST>
 __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11, P2 v01, const MapGeom &g,
                                               double *__restrict__ map, const Window<N> &w,
                                               unsigned long long *__restrict__ counters, const BigList &bl,
-                                              int64_t cell, CellWork &cw)
+                                              int64_t cell, uint8_t *sq, CellWork &cw)
 {
     const int lane = threadIdx.x & 63;
     int mcols[2] = {0, 0};      // pixel columns of each medium triangle of the cell (0: none)
     int mi0[2] = {0, 0};
-    int big = 0;
+    int big = 0, small = 0;
     if (have) {
         int pi, pj;
         if (cell_in_one_pixel(v00, v10, v11, v01, g, pi, pj)) {
@@ -475,9 +479,7 @@ __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11,
                     if (c.pi >= 0) deposit_w(w, map, g, c.pi, c.pj, g.tri_weight);
                 } else if (c.kind == 2) {
                     if (c.small) {
-                        const double fu0 = floor(fmin(A.u, fmin(B.u, C.u))), fv0 = floor(fmin(A.v, fmin(B.v, C.v)));
-                        small_triangle(A, B, C, fu0, fv0, g, map, w);
-                        ++cw.small;
+                        small |= 1 << k;
                     } else {
                         mcols[k] = c.cols;
                         mi0[k] = c.i0;
@@ -490,6 +492,30 @@ __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11,
     }
     BigRange range;
     if constexpr (LIST) range = reserve_big(bl, big);
+    // the small triangles, a lane each: the first ones of the cells, then the second
+    const uint64_t s0 = __ballot(small & 1), s1 = __ballot(small & 2), lt = (1ull << lane) - 1ull;
+    const int n0 = __popcll(s0), ns = n0 + __popcll(s1);
+    if (ns > 0) {
+        if (small & 1) sq[__popcll(s0 & lt)] = (uint8_t)lane;
+        if (small & 2) sq[n0 + __popcll(s1 & lt)] = (uint8_t)(64 | lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int base = 0; base < ns; base += 64) {
+            const int e = sq[min(base + lane, ns - 1)], L = e & 63;
+            const bool second = e >= 64;
+            const P2 A{__shfl(v00.u, L, 64), __shfl(v00.v, L, 64)}, D{__shfl(v11.u, L, 64), __shfl(v11.v, L, 64)};
+            const P2 E{__shfl(v10.u, L, 64), __shfl(v10.v, L, 64)}, F{__shfl(v01.u, L, 64), __shfl(v01.v, L, 64)};
+            if (base + lane < ns) {
+                const P2 B{second ? D.u : E.u, second ? D.v : E.v}, C{second ? F.u : D.u, second ? F.v : D.v};
+                const double fu0 = floor(fmin(A.u, fmin(B.u, C.u))), fv0 = floor(fmin(A.v, fmin(B.v, C.v)));
+                small_triangle(A, B, C, fu0, fv0, g, map, w);
+                ++cw.small;
+            }
+        }
+        // (read before the wavefront's next cells are written)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     // the medium triangles' pixel columns, spread evenly over the wavefront's
     // lanes: first triangle of every cell, then the second
 #pragma unroll
@@ -580,8 +606,9 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
     const Window<N> w = tile_window<N>(acc, verts[(cb0 + cb - vb0) * nr1 + ca]);
     for (int k = threadIdx.x; k < N * N; k += blockDim.x) acc[k] = 0.0;
     __syncthreads();
+    __shared__ uint8_t sq[256 * 2];
     CellWork cw;
-    const int big = apportion_cell<MIXED, N, LIST>(have, v00, v10, v11, v01, g, map, w, counters, bl, brow * ncol + a, cw);
+    const int big = apportion_cell<MIXED, N, LIST>(have, v00, v10, v11, v01, g, map, w, counters, bl, brow * ncol + a, sq + wave * 128, cw);
     if constexpr (!LIST) {   // the tile's count of large triangles (tile_big is zeroed beforehand)
         int s = (big & 1) + (big >> 1);
 #pragma unroll
@@ -645,6 +672,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     __shared__ double acc[N * N];
     __shared__ unsigned short queue[FC * FROWS];   // cells of the tile
     __shared__ int nq;
+    __shared__ uint8_t sq[256 * 2];
     const int64_t ncol = nr1 - 1;
     const int64_t tiles_a = (ncol + FC - 1) / FC;
     const int64_t ta = (int64_t)blockIdx.x % tiles_a, tb = (int64_t)blockIdx.x / tiles_a;
@@ -731,7 +759,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         P2 v00{0.0, 0.0}, v10{0.0, 0.0}, v11{0.0, 0.0}, v01{0.0, 0.0};
         if (have) load_cell_at(verts, nr1, cb0 + tb * FROWS + c / FC - vb0, ta * FC + c % FC, v00, v10, v11, v01);
         apportion_cell<MIXED, N, true>(have, v00, v10, v11, v01, g, map, w, counters, bl,
-                                              (tb * FROWS + c / FC) * ncol + ta * FC + c % FC, cw);
+                                              (tb * FROWS + c / FC) * ncol + ta * FC + c % FC,
+                                       sq + (threadIdx.x >> 6) * 128, cw);
     }
     if (work) add_work(work, blockIdx.x, cw);
     __syncthreads();
