@@ -276,6 +276,7 @@ constexpr int64_t IRS_STRIP_PATCH_RAYS = 1ll << 29;   // the same by patches (44
 constexpr int64_t BIG_HOLD = 4ll << 20;       // large triangles kept over strips before they are banded (0.5 GiB)
 constexpr int64_t BIG_CELLS_PER_SLOT = 4;     // cells per entry of the large-triangle lists
 constexpr double QUEUE_CELLS_PER_PIXEL = 64.0;   // cells per map pixel from which the cell pass queues (k_ipm_fine)
+constexpr double MID_CELLS_PER_PIXEL = 30.0;     // cells per map pixel from which k_ipm's window is the smaller one
 constexpr double FINE_CELLS_PER_PIXEL = 400.0;  // cells per map pixel from which the cell pass is k_ipm_fine
 
 __global__ void k_fill(double *p, int64_t n, double v)
@@ -1075,9 +1076,15 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         // k_ipm_fine with its 48-pixel window: at 14 cells a pixel 4.3 and 5.5 ms
         // (1e5-star map), at 55 (elongated cells) 0.43 and 0.46, at 60 4.9 and
         // 5.5, at 78 1.5 and 1.2, at 90 0.48 and 0.39; the 24-pixel window at 900
-        // and at 1300.
+        // and at 1300.  k_ipm with its 48-pixel window and with its 32-pixel one: at
+        // 14 cells a pixel 3.94 and 4.63 ms (1e5-star map), at 18 0.150 and 0.141 or
+        // (elongated cells) 0.177 and 0.179, at 34 0.257 and 0.243, at 37 4.84 and
+        // 4.66 (a map across a fold caustic), at 60 4.82 and 4.79.
         const double cells_px = (double)(R.nr1 - 1) * (double)(R.nr2 - 1) / ((double)g.n1 * (double)g.n2);
-        const int fine = cells_px >= FINE_CELLS_PER_PIXEL ? 2 : (cells_px >= QUEUE_CELLS_PER_PIXEL ? 1 : 0);
+        const int pass = cells_px >= FINE_CELLS_PER_PIXEL    ? 3
+                         : cells_px >= QUEUE_CELLS_PER_PIXEL ? 2
+                         : cells_px >= MID_CELLS_PER_PIXEL   ? 1
+                                                             : 0;
         // (cell refinement shoots its rays one by one, and its decisions compare
         // them with the grid's: those go the same way there)
         const bool single = q.w_out || q.refine != MLM_REFINE_NONE || thread_arena();
@@ -1115,7 +1122,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 bl.list = static_cast<int64_t *>(ws.biglist.reserve((size_t)(BIG_SHARDS * bl.cap) * sizeof(int64_t)));
             }
             const int e_cells0 = tm.mark();
-            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, q.precision == MLM_PREC_MIXED, fine,
+            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, q.precision == MLM_PREC_MIXED, pass,
                        q.timing >= 2 ? cnt + 8 : nullptr, st);
             const int e_cells = tm.mark();
             BigStarts at{};

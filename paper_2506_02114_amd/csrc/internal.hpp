@@ -397,7 +397,7 @@ constexpr int64_t BIN_TRIS = 2048;
 // cell tiles of the cell pass over cell rows [cb0, cb0 + nrows): one workgroup and one
 // large-triangle count each
 int64_t ipm_tile_count(int64_t nr1, int64_t nrows);
-// (fine: the pass for maps of many cells per pixel)
+// (pass: 0, 1 k_ipm with its large and small window, 2, 3 k_ipm_fine)
 // lists of the large triangles that the cell pass meets: BIG_SHARDS of cap
 // entries each, their counts BIG_STRIDE apart (a count above cap: the list is
 // incomplete)
@@ -412,7 +412,7 @@ struct BigStarts {
     int64_t lo[BIG_SHARDS + 1];   // the lists laid end to end: list i's first slot
 };
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int fine,
+                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int pass,
                 unsigned long long *work, hipStream_t st);
 void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,
                       const BigStarts &at, int bh, BigPrep *prep, uint32_t *bands, hipStream_t st);

@@ -125,10 +125,11 @@ __device__ inline void deposit(double *map, const MapGeom &g, int i, int j, doub
 // pixel window of a workgroup in LDS: deposits inside it are summed there and
 // added to the map once per pixel at the end; the rest go straight to the map.
 // Its side N is 48 pixels (wide enough for most tiles' images at a few cells
-// per pixel; 18 KiB), or 24 where a tile's cells cover far less than a pixel
-// each (a highly magnified map), so that clearing and flushing the window does
-// not cost more than the tile's deposits.
+// per pixel; 18 KiB), 32 from some tens of cells per pixel on, or 24 where a
+// tile's cells cover far less than a pixel each (a highly magnified map), so that
+// clearing and flushing the window does not cost more than the tile's deposits.
 constexpr int WIN = 48;        // window side in pixels (WIN x WIN doubles)
+constexpr int WIN_MID = 32;
 constexpr int WIN_FINE = 24;   // the side for maps of many cells per pixel
 
 template <int N> struct Window {
@@ -448,7 +449,7 @@ __device__ inline void write_big(const BigList &bl, const BigRange &r, int big, 
 // wavefront's lanes.  (One triangle in six is a small one on the 1e5-star map:
 // gathered in sq, two bytes of LDS a lane, and apportioned by the first lanes, they
 // cost the wavefront their 300 instructions once instead of for both triangles of
-// a cell: FIGURES.)  Which of the two triangles are large (bit k) is returned,
+// a cell: 2268 instructions a wavefront before, 2119 now, 4.2 and 4.0 ms.)  Which of the two triangles are large (bit k) is returned,
 // and they are listed in `bl` (LIST; `cell`: the cell's number in the strip).
 // Called by whole wavefronts.
 template <bool MIXED, int N, bool LIST>
@@ -623,14 +624,14 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
 // Registers capped at 128 per lane (four waves per SIMD, no spills): the
 // compiler's free choice (132) holds three, and the cell pass gains more from
 // the fourth wave hiding its LDS and cross-lane latency than it loses.
-template <bool MIXED>
+template <bool MIXED, int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
                                              int64_t nrows, int64_t vb0, MapGeom g, double *__restrict__ map,
                                              unsigned long long *__restrict__ counters, BigList bl,
                                              unsigned long long *__restrict__ work)
 {
-    __shared__ double acc[WIN * WIN];
-    ipm_tile<MIXED, WIN, true>(verts, nr1, cb0, nrows, vb0, g, map, counters, bl, nullptr, blockIdx.x, acc, work);
+    __shared__ double acc[N * N];
+    ipm_tile<MIXED, N, true>(verts, nr1, cb0, nrows, vb0, g, map, counters, bl, nullptr, blockIdx.x, acc, work);
 }
 
 // The cell pass where cells are far smaller than pixels (a highly magnified
@@ -1595,15 +1596,18 @@ __global__ __launch_bounds__(256) void k_count_rows(int64_t nbig, const BigPrep 
 static __global__ void k_zero_shards(unsigned long long *count) { count[(size_t)threadIdx.x * BIG_STRIDE] = 0ull; }
 
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int fine,
+                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int pass,
                 unsigned long long *work, hipStream_t st)
 {
+    const bool fine = pass >= 2;
     const int64_t nrows = cb1 - cb0, ncol = nr1 - 1;
     const int64_t tiles = fine ? ((ncol + FC - 1) / FC) * ((nrows + FROWS - 1) / FROWS) : ipm_tile_count(nr1, nrows);
     if (ncol <= 0 || nrows <= 0) return;
     hipLaunchKernelGGL(k_zero_shards, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count);
-    auto *k = fine == 2 ? (mixed ? k_ipm_fine<true, WIN_FINE> : k_ipm_fine<false, WIN_FINE>)
-              : fine ? (mixed ? k_ipm_fine<true, WIN> : k_ipm_fine<false, WIN>) : (mixed ? k_ipm<true> : k_ipm<false>);
+    auto *k = pass == 3   ? (mixed ? k_ipm_fine<true, WIN_FINE> : k_ipm_fine<false, WIN_FINE>)
+              : pass == 2 ? (mixed ? k_ipm_fine<true, WIN> : k_ipm_fine<false, WIN>)
+              : pass == 1 ? (mixed ? k_ipm<true, WIN_MID> : k_ipm<false, WIN_MID>)
+                          : (mixed ? k_ipm<true, WIN> : k_ipm<false, WIN>);
     hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, nrows, vb0, g, map, counters,
                        bl, work);
 }

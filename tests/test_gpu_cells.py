@@ -65,3 +65,12 @@ def test_plain_refinement_equals_the_oracle(orc, nr1, nr2, gamma, window):
     assert st["n_refined"] == int(labels.sum())
     want = ref.mu + dmu
     assert np.abs(mu - want).max() < 1e-9 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("n1,n2,nr1,nr2,gamma", [
+    (20, 20, 131, 117, 0.1),      # 38 cells a pixel: the ordinary pass with its 32-pixel window
+    (12, 50, 181, 161, -0.4),     # 48, images of many tiles wider than the window
+    (3, 40, 65, 64, 0.2),         # 34, a map narrower than a window
+])
+def test_smaller_window_equals_clipping(orc, n1, n2, nr1, nr2, gamma):
+    test_map_equals_clipping(orc, n1, n2, nr1, nr2, gamma, 0)
