@@ -272,7 +272,7 @@ namespace {
 
 constexpr int64_t STRIP_VERTS = 1ll << 26;   // vertices per strip buffer (1 GiB of double2)
 constexpr int64_t IRS_STRIP_RAYS = 1ll << 30;   // rays per inverse-ray-shooting launch (nothing stored per ray)
-constexpr int64_t IRS_STRIP_PATCH_RAYS = 1ll << 29;   // the same by patches (448 bytes of coefficients per 1024 rays)
+constexpr int64_t IRS_STRIP_PATCHES = 1ll << 19;   // the same by patches (448 bytes of coefficients each)
 constexpr int64_t BIG_HOLD = 4ll << 20;       // large triangles kept over strips before they are banded (0.5 GiB)
 constexpr int64_t BIG_CELLS_PER_SLOT = 4;     // cells per entry of the large-triangle lists
 constexpr double QUEUE_CELLS_PER_PIXEL = 64.0;   // cells per map pixel from which the cell pass queues (k_ipm_fine)
@@ -1029,7 +1029,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         // (inside a scratch arena, without room for the patches' coefficients,
         // rays are shot one by one)
         const int side = fmm && !thread_arena() ? patch_side(R, T, cb1 - cb0) : 0;
-        const int64_t rows = std::max<int64_t>(1, (side ? IRS_STRIP_PATCH_RAYS : IRS_STRIP_RAYS) / std::max<int64_t>(R.nr1 - 1, 1));
+        const int64_t rows = std::max<int64_t>(1, (side ? IRS_STRIP_PATCHES * side * side : IRS_STRIP_RAYS) / std::max<int64_t>(R.nr1 - 1, 1));
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             const int64_t r1 = std::min(cb1, r0 + rows);
             int64_t nt = 0;
@@ -1039,7 +1039,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                                    T.nleaves, T.leaves, cnt);
             }
             const int ea = tm.mark();
-            if (side) launch_irs_patches(lens, T, R, lc, g, nt, r0, irs_cnt, st);
+            if (side) launch_irs_patches(lens, T, R, lc, g, side, nt, r0, irs_cnt, st);
             else if (fmm) launch_shoot_irs(lens, T, R, lc, g, nt, r0, irs_cnt, st);
             else launch_shoot_irs_direct(lens, R, lc, g, r0, r1, irs_cnt, st);
             const int eb = tm.mark();
@@ -1101,7 +1101,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                                    T.leaves, cnt);
             }
             int ea = tm.mark();
-            if (side) launch_shoot_patches(lens, T, R, lc, g, nt, vb0, verts, st);
+            if (side) launch_shoot_patches(lens, T, R, lc, g, side, nt, vb0, verts, st);
             else if (fmm) launch_shoot(lens, T, R, lc, g, nt, vb0, verts, w_here, st);
             else launch_shoot_direct(lens, R, lc, g, vb0, vb1, verts, w_here, st);
             int eb = tm.mark();

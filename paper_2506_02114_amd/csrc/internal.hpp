@@ -374,12 +374,11 @@ void launch_shoot(mlm_lens *lens, const Tree &T, const Region &R, const LensCons
 // patch.hip: shooting by patches of rays that share one power series, for grids
 // far denser than the stars.  The patch's side (0: shoot ray by ray), for
 // `rows` rows of rays; patches are planned as tiles of that side.
-constexpr double PATCH_RAYS_PER_LEAF = 16384.0;
 int patch_side(const Region &R, const Tree &T, int64_t rows);
 void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
-                          int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st);
+                          int side, int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st);
 void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
-                        int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st);
+                        int side, int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st);
 void launch_shoot_direct(mlm_lens *lens, const Region &R, const LensConst &lc, const MapGeom &g,
                          int64_t vb0, int64_t vb1, double2 *verts, double *w_out,
                          hipStream_t st);

@@ -27,6 +27,9 @@ namespace mlm {
 
 namespace {
 
+// rays per leaf from which patches pay: few rays, many rays
+constexpr double PATCH_RAYS_PER_LEAF[2] = {32768.0, 10000.0}, PATCH_MANY_RAYS = 3.2e7;
+constexpr double SMALL_PATCH_RAYS_PER_LEAF[2] = {8192.0, 3000.0}, SMALL_PATCH_MANY_RAYS = 1.6e7;
 constexpr int PC_MAX = 24;    // most coefficients of a patch
 constexpr int PC_DIRECT = 8;  // most stars summed directly
 constexpr int PC_STARS = 64;  // most near stars of a leaf in this path
@@ -580,17 +583,31 @@ PatchArgs patch_args(const Region &R, const MapGeom &g, int P)
 
 }  // namespace
 
-// Rays per leaf (of the leaves the rays meet) from which the grid is shot by
-// patches, and the patch's side.
+// Where the grid is shot by patches, and their side, by the rays per leaf (of the
+// leaves the rays meet), which say how far the stars lie from a patch, and by how
+// many rays there are to hide the coefficients' latency.  Measured on the 1e5-star
+// map with more and fewer rays, ms ray by ray / 16 x 16 / 32 x 32 (in brackets:
+// inverse ray shooting):
+//   3300 rays a leaf, 2.9e7 rays   0.47 / 0.42 / 0.58   (0.95 / 0.61 / 1.20)
+//   6700, 5.8e7                    0.81 / 0.67 / 0.75   (1.59 / 0.86 / 1.15)
+//   10000, 8.7e7                   1.30 / 1.15 / 1.04   (2.23 / 1.29 / 1.38)
+//   13300, 1.2e8                   1.74 / 1.49 / 1.05   (2.74 / 1.64 / 1.43)
+//   101500, 2.4e8                  5.06 / 2.50 / 1.61   (4.19 / 2.30 / 1.37)
+// and with 330 leaves met, so that the rays are few:
+//   6000, 2.0e6                    0.045 / 0.047 / 0.098   (0.062 / 0.055 / 0.192)
+//   8000, 2.6e6                    0.058 / 0.048 / 0.108   (0.083 / 0.065 / 0.209)
+//   24000, 7.9e6                   0.142 / 0.085 / 0.092   (0.197 / 0.118 / 0.111)
+//   32000, 1.0e7                   0.180 / 0.111 / 0.084   (0.238 / 0.149 / 0.120)
 int patch_side(const Region &R, const Tree &T, int64_t rows)
 {
     if (T.mixed || T.p < 1) return 0;
-    const double rays = (double)R.nr1 * (double)rows;
-    return rays >= PATCH_RAYS_PER_LEAF * (double)std::max<int64_t>(T.nactive_leaves, 1) ? 32 : 0;
+    const double rays = (double)R.nr1 * (double)rows, per_leaf = rays / (double)std::max<int64_t>(T.nactive_leaves, 1);
+    if (per_leaf >= PATCH_RAYS_PER_LEAF[rays >= PATCH_MANY_RAYS ? 1 : 0]) return 32;
+    return per_leaf >= SMALL_PATCH_RAYS_PER_LEAF[rays >= SMALL_PATCH_MANY_RAYS ? 1 : 0] ? 16 : 0;
 }
 
 static void patch_coefs(mlm_lens *lens, const Tree &T, const LensConst &lc, const ShootArgs &sa, const PatchArgs &pa,
-                        int64_t npatch, hipStream_t st)
+                        int side, int64_t npatch, hipStream_t st)
 {
     Workspace &ws = lens->ws;
     if (!ws.binom.p) {
@@ -603,33 +620,34 @@ static void patch_coefs(mlm_lens *lens, const Tree &T, const LensConst &lc, cons
     }
     PatchInfo *info = static_cast<PatchInfo *>(ws.patch_info.reserve((size_t)npatch * sizeof(PatchInfo)));
     double2 *coef = static_cast<double2 *>(ws.patch_coef.reserve((size_t)npatch * PC_MAX * sizeof(double2)));
-    hipLaunchKernelGGL(k_patch_coef<32>, dim3((unsigned)((npatch + 3) / 4)), dim3(64), 0, st, sa, lc, pa, npatch,
+    hipLaunchKernelGGL(side == 32 ? k_patch_coef<32> : k_patch_coef<16>, dim3((unsigned)((npatch + 3) / 4)), dim3(64), 0, st, sa, lc, pa, npatch,
                        ws.tile_leaf.as<int32_t>(), ws.tile_off.as<int32_t>(), T.leaves, T.near, T.deriv,
                        ws.binom.as<double>(), info, coef);
 }
 
 void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
-                          int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st)
+                          int side, int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st)
 {
     if (npatch <= 0) return;
     const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1, vb0, T.p, 0, 0.0};
-    const PatchArgs pa = patch_args(R, g, 32);
-    patch_coefs(lens, T, lc, sa, pa, npatch, st);
-    hipLaunchKernelGGL(k_shoot_patch<32>, dim3((unsigned)npatch), dim3(64), 0, st, sa, lc, g, pa,
+    const PatchArgs pa = patch_args(R, g, side);
+    patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
+    hipLaunchKernelGGL(side == 32 ? k_shoot_patch<32> : k_shoot_patch<16>, dim3((unsigned)npatch), dim3(64), 0, st, sa, lc, g, pa,
                        lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves, T.near,
                        T.deriv, verts);
 }
 
 void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
-                        int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st)
+                        int side, int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st)
 {
     if (npatch <= 0) return;
     const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1 - 1, cb0, T.p, 0, 0.5};
-    const PatchArgs pa = patch_args(R, g, 32);
-    patch_coefs(lens, T, lc, sa, pa, npatch, st);
-    // the window: a patch's unlensed image is 32 d / pixel wide
-    const bool wide = 32.0 * std::max(R.d1 / R.pix1, R.d2 / R.pix2) > 4.0;
-    auto *k = wide ? k_irs_patch<32, 32> : k_irs_patch<32, 16>;
+    const PatchArgs pa = patch_args(R, g, side);
+    patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
+    // the window: a patch's unlensed image is side d / pixel wide
+    const bool wide = side * std::max(R.d1 / R.pix1, R.d2 / R.pix2) > 4.0;
+    auto *k = side == 32 ? (wide ? k_irs_patch<32, 32> : k_irs_patch<32, 16>)
+                         : (wide ? k_irs_patch<16, 32> : k_irs_patch<16, 16>);
     hipLaunchKernelGGL(k, dim3((unsigned)npatch), dim3(64), 0, st, sa,
                        lc, g, pa, lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves,
                        T.near, T.deriv, counts);
