@@ -1855,8 +1855,8 @@ mlm_status mlm_refiner_create(const float *params, uint64_t seed, mlm_refiner **
     r->M.reserve(nb);
     r->V.reserve(nb);
     r->G.reserve(nb);
-    r->W1b.reserve(16 * 64 * sizeof(uint16_t));
-    r->W2b.reserve(64 * 64 * sizeof(uint16_t));
+    r->W1b.reserve(2 * 16 * 64 * sizeof(uint16_t));   // (each with its transpose)
+    r->W2b.reserve(2 * 64 * 64 * sizeof(uint16_t));
     r->tstep.reserve(sizeof(int64_t));
     r->lacc.reserve(sizeof(double));
     mlp_step_reset(r->tstep.as<int64_t>(), r->lacc.as<double>(), true, nullptr);
@@ -1939,26 +1939,29 @@ mlm_status mlm_refiner_predict(mlm_refiner *r, const float *feats, int64_t n, fl
 // gradients (20 KB a wavefront of 32 rows) to 40 MB
 constexpr int64_t GRAD_CHUNK = 65536;
 
-// the staging and partial-gradient buffers of a batch of n rows (reserved
-// before a graph is captured, so that capturing allocates nothing)
+// the partial-gradient buffer of a batch of n rows (reserved before a graph is
+// captured, so that capturing allocates nothing)
 static void refiner_reserve(mlm_refiner *r, int64_t n)
 {
     const int64_t c = std::min(n, GRAD_CHUNK);
-    r->xbuf.reserve((size_t)((c + 127) / 128) * 128 * 12 * sizeof(float));
     r->gpart.reserve((size_t)mlp_part_rows(c) * (MLM_REFINER_PARAMS + 1) * sizeof(float));
 }
 
-// one forward/backward over rows idx[0, n) added to r->G (gradient + loss at
-// [NP]), in chunks of GRAD_CHUNK rows taken in order; the loss of each chunk
-// is divided by n
-static void refiner_batch(mlm_refiner *r, const float *df, const uint8_t *dy, const int64_t *didx, int64_t n,
-                          float pos_weight, hipStream_t st)
+// one forward/backward over rows idx[0, n) in chunks of GRAD_CHUNK rows taken in
+// order, each added to r->G (gradient + loss at [NP]; the loss of each chunk is
+// divided by n), the last excepted: its rows, whose number is returned, are left
+// in r->gpart for the caller to add
+static int64_t refiner_batch(mlm_refiner *r, const float *df, const uint8_t *dy, const int64_t *didx, int64_t n,
+                             float pos_weight, hipStream_t st)
 {
     refiner_reserve(r, n);
-    for (int64_t c0 = 0; c0 < n; c0 += GRAD_CHUNK) {
+    float *part = r->gpart.as<float>();
+    for (int64_t c0 = 0;; c0 += GRAD_CHUNK) {
         const int64_t c = std::min(GRAD_CHUNK, n - c0);
         mlp_train_batch(df, dy, didx + c0, c, r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), r->P.as<float>(),
-                        pos_weight, (float)n, r->G.as<float>(), r->gpart.as<float>(), r->xbuf.as<float>(), st);
+                        pos_weight, (float)n, part, st);
+        if (c0 + c >= n) return c;
+        mlp_grad_sum(part, c, r->G.as<float>(), st);
     }
 }
 
@@ -1980,7 +1983,8 @@ mlm_status mlm_refiner_grads(mlm_refiner *r, const float *feats, const uint8_t *
     int64_t *didx = static_cast<int64_t *>(r->idx.reserve((size_t)n * sizeof(int64_t)));
     hipLaunchKernelGGL(k_iota64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, didx, n);
     mlp_zero(r->G.as<float>(), MLM_REFINER_PARAMS + 1, st);
-    refiner_batch(r, df, dy, didx, n, pos_weight, st);
+    const int64_t last = refiner_batch(r, df, dy, didx, n, pos_weight, st);
+    mlp_grad_sum(r->gpart.as<float>(), last, r->G.as<float>(), st);
     std::vector<float> h(MLM_REFINER_PARAMS + 1);
     MLM_HIP(hipMemcpyAsync(h.data(), r->G.p, h.size() * sizeof(float), hipMemcpyDeviceToHost, st));
     mlp_zero(r->G.as<float>(), MLM_REFINER_PARAMS + 1, st);
@@ -2007,7 +2011,7 @@ mlm_status mlm_refiner_train(mlm_refiner *r, const mlm_train_opts *opts, const f
         dy = d;
     }
     int64_t *didx = static_cast<int64_t *>(r->idx.reserve((size_t)n * sizeof(int64_t)));
-    std::vector<int64_t> perm((size_t)n);
+    std::vector<int64_t> perm[2] = {std::vector<int64_t>((size_t)n), std::vector<int64_t>((size_t)n)};
     uint64_t x = o.seed ^ 0x5DEECE66Dull;
     auto next = [&x]() {
         uint64_t z = (x += 0x9E3779B97F4A7C15ull);
@@ -2035,11 +2039,11 @@ mlm_status mlm_refiner_train(mlm_refiner *r, const mlm_train_opts *opts, const f
     auto epoch_steps = [&]() {
         for (int64_t b0 = 0; b0 < n; b0 += o.batch) {
             const int64_t nb = std::min<int64_t>(o.batch, n - b0);
-            refiner_batch(r, df, dy, didx + b0, nb, o.pos_weight, ts);
-            mlp_adam(r->P.as<float>(), r->M.as<float>(), r->V.as<float>(), G, o.lr, tstep, ts);
-            mlp_step_end(G, tstep, lacc, (float)nb, ts);
-            mlp_pack(r->P.as<float>(), r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), ts);
+            const int64_t last = refiner_batch(r, df, dy, didx + b0, nb, o.pos_weight, ts);
+            mlp_grad_step(r->gpart.as<float>(), last, r->P.as<float>(), r->M.as<float>(), r->V.as<float>(), G, o.lr, tstep,
+                          (int)(b0 / o.batch), lacc, (float)nb, r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), ts);
         }
+        mlp_steps_taken(tstep, (n + o.batch - 1) / o.batch, ts);
     };
     hipGraphExec_t ge = nullptr;
     if (o.graph && o.epochs > 0) {
@@ -2057,18 +2061,25 @@ mlm_status mlm_refiner_train(mlm_refiner *r, const mlm_train_opts *opts, const f
         MLM_HIP(ie);
     }
     try {
+        // (an epoch's permutation is drawn while the device runs the one before; the
+        // loss is asked for after that, as its copy waits for the epoch)
+        auto epoch_done = [&](int32_t e) {
+            double hl = 0.0;
+            if (loss_per_epoch) MLM_HIP(hipMemcpyAsync(&hl, lacc, sizeof(double), hipMemcpyDeviceToHost, ts));
+            MLM_HIP(hipStreamSynchronize(ts));
+            if (loss_per_epoch) loss_per_epoch[e] = (float)(hl / (double)n);
+        };
         for (int32_t e = 0; e < o.epochs; ++e) {
-            for (int64_t k = 0; k < n; ++k) perm[k] = k;
-            for (int64_t k = n - 1; k > 0; --k) std::swap(perm[k], perm[next() % (uint64_t)(k + 1)]);
-            MLM_HIP(hipMemcpyAsync(didx, perm.data(), (size_t)n * sizeof(int64_t), hipMemcpyHostToDevice, ts));
+            std::vector<int64_t> &p = perm[e & 1];
+            for (int64_t k = 0; k < n; ++k) p[k] = k;
+            for (int64_t k = n - 1; k > 0; --k) std::swap(p[k], p[next() % (uint64_t)(k + 1)]);
+            if (e > 0) epoch_done(e - 1);
+            MLM_HIP(hipMemcpyAsync(didx, p.data(), (size_t)n * sizeof(int64_t), hipMemcpyHostToDevice, ts));
             mlp_step_reset(tstep, lacc, false, ts);
             if (ge) MLM_HIP(hipGraphLaunch(ge, ts));
             else epoch_steps();
-            double hl = 0.0;
-            if (loss_per_epoch) MLM_HIP(hipMemcpyAsync(&hl, lacc, sizeof(double), hipMemcpyDeviceToHost, ts));
-            MLM_HIP(hipStreamSynchronize(ts));   // perm (and hl) are reused by the next epoch
-            if (loss_per_epoch) loss_per_epoch[e] = (float)(hl / (double)n);
         }
+        if (o.epochs > 0) epoch_done(o.epochs - 1);
     } catch (...) {
         if (ge) (void)hipGraphExecDestroy(ge);
         throw;

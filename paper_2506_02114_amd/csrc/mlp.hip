@@ -11,10 +11,9 @@
 // W3 [64], b3; layer l computes h_l = relu(h_{l-1} W_l + b_l).
 // Loss: mean_i [ w+ y_i softplus(-z_i) + (1 - y_i) softplus(z_i) ].
 //
-// One wavefront takes 32 samples; a workgroup of four wavefronts takes 128.
-// Every product is a 32 x 32 block tile (one MFMA per 8 of the reduced
-// dimension) whose operands are read from LDS or global memory with the
-// strides that make the transposes of the backward pass free.
+// One wavefront takes 32 samples.  Every product is a 32 x 32 block tile (one
+// MFMA per 8 of the reduced dimension): lane l holds A(l % 32, 4 (l / 32) + t) and
+// B(4 (l / 32) + t, l % 32), t < 4, read as 8 bytes along the reduced dimension.
 #include <algorithm>
 
 #include "cellfeat.hpp"
@@ -29,103 +28,22 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int NP = 5057;
 constexpr int OW1 = 0, OB1 = 768, OW2 = 832, OB2 = 4928, OW3 = 4992, OB3 = 5056;
-constexpr int MB = 128;   // samples per workgroup (4 wavefronts x 32)
+constexpr int MB = 128;   // samples are padded to whole groups of so many
 
 // float -> bf16, round to nearest even (finite inputs): one hardware
 // conversion (v_cvt_pk_bf16_f32) in the default rounding mode
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// C (32 x 32 tile) += A (32 x K) B (K x 32); A(m, k) = a[m * sam + k * sak],
-// B(k, n) = b[k * sbk + n * sbn] (bf16); K a multiple of 8.  Operand layout
-// of the instruction: lane l holds A(l % 32, 4 (l / 32) + t) and
-// B(4 (l / 32) + t, l % 32), t < 4.
-__device__ inline f32x16 tile_mma(const uint16_t *a, int sam, int sak, const uint16_t *b, int sbk, int sbn, int K,
-                                  f32x16 acc, int lane)
-{
-    const int r = lane & 31, h = (lane >> 5) * 4;
-    for (int k0 = 0; k0 < K; k0 += 8) {
-        bf16x4 av, bv;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            av[t] = (short)a[r * sam + (k0 + h + t) * sak];
-            bv[t] = (short)b[(k0 + h + t) * sbk + r * sbn];
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
 // row and column of accumulator element j of lane `lane` in a 32 x 32 tile
 __device__ inline int acc_row(int j, int lane) { return 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3); }
 __device__ inline int acc_col(int lane) { return lane & 31; }
-
-struct WaveLds {
-    uint16_t x[32 * 16];     // inputs, 12 features + 4 zero columns
-    uint16_t h1[32 * 64];    // layer-1 activations, bf16 part
-    uint16_t h1lo[32 * 64];  // and the bf16 residual: h1 + h1lo carries 16 bits
-    float h2[32 * 64];       // layer-2 activations
-    uint16_t d2[32 * 64];    // gradient at layer-2 pre-activations
-    uint16_t d1[32 * 64];    // gradient at layer-1 pre-activations
-    float z[32], dz[32];
-};
-
-// forward pass of the wavefront's 32 samples [s0, s0 + 32) (rows past n
-// are zero); W1b is [16][64] (rows 12..15 zero), W2b [64][64], bf16
-__device__ inline void forward(const float *__restrict__ feats, int64_t s0, int64_t n, const uint16_t *__restrict__ W1b,
-                               const uint16_t *__restrict__ W2b, const float *__restrict__ P, WaveLds &L, int lane)
-{
-    for (int e = lane; e < 32 * 16; e += 64) {
-        const int m = e >> 4, k = e & 15;
-        const int64_t s = s0 + m;
-        L.x[e] = (k < 12 && s < n) ? f2bf(feats[s * 12 + k]) : (uint16_t)0;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int nh = 0; nh < 2; ++nh) {
-        f32x16 acc = {};
-        acc = tile_mma(L.x, 16, 1, W1b + nh * 32, 64, 1, 16, acc, lane);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int m = acc_row(j, lane), c = nh * 32 + acc_col(lane);
-            const float h = fmaxf(acc[j] + P[OB1 + c], 0.0f);
-            const uint16_t hi = f2bf(h);
-            L.h1[m * 64 + c] = hi;
-            L.h1lo[m * 64 + c] = f2bf(h - bf2f(hi));
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int nh = 0; nh < 2; ++nh) {
-        f32x16 acc = {};
-        acc = tile_mma(L.h1, 64, 1, W2b + nh * 32, 64, 1, 64, acc, lane);
-        acc = tile_mma(L.h1lo, 64, 1, W2b + nh * 32, 64, 1, 64, acc, lane);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int m = acc_row(j, lane), c = nh * 32 + acc_col(lane);
-            L.h2[m * 64 + c] = fmaxf(acc[j] + P[OB2 + c], 0.0f);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < 32) {
-        float z = P[OB3];
-        for (int c = 0; c < 64; ++c) z += L.h2[lane * 64 + c] * bf2f(f2bf(P[OW3 + c]));
-        L.z[lane] = z;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Inference only: the weights are staged once per workgroup in LDS, rows of
 // every operand are stored so that the four consecutive values of the
 // reduced dimension that a lane feeds one MFMA are one 8-byte LDS read, and
 // each wavefront loops over tiles of 32 samples (a grid sized to the device,
-// not to the samples).  Same arithmetic as `forward` (bf16 inputs, two-part
+// not to the samples).  Same arithmetic as the training's forward pass (bf16 inputs, two-part
 // bf16 hidden layer, FP32 accumulation); the final 64-term sum runs in
 // another order.
 constexpr int PS = 68;    // padded row stride (bf16) of the 64-wide operands: 136 B, so rows fall in other banks
@@ -301,41 +219,130 @@ __global__ __launch_bounds__(256) void k_mlp_flag_cells(int64_t nr1, int64_t cb0
 
 __device__ inline float softplus(float x) { return x > 0.0f ? x + log1pf(expf(-x)) : log1pf(expf(x)); }
 
-// forward and backward of samples idx[s] (s in [0, n)); each wavefront (32
-// samples) writes its whole gradient (FP32) and its part of the loss (at
-// [NP]; the loss is divided by `norm`, the batch size) to its own row
-// part[w * (NP + 1) ..], w = 4 blockIdx.x + wave, with no atomics: k_grad_sum
-// adds the rows in a fixed order, so a batch's gradient is the same bits on
-// every run
-__global__ __launch_bounds__(256) void k_mlp_train(const float *__restrict__ feats_all, const uint8_t *__restrict__ y_all,
-                                                   const int64_t *__restrict__ idx, int64_t n,
-                                                   const uint16_t *__restrict__ W1b,
-                                                   const uint16_t *__restrict__ W2b, const float *__restrict__ P,
-                                                   float pos_weight, float norm, float *__restrict__ part,
-                                                   float *__restrict__ xbuf)
+// A training wavefront's LDS.  Every product reads its operands as rows along
+// the reduced dimension, 8 bytes a lane and MFMA, so what enters products in
+// both directions is stored both ways.
+constexpr int TS = 36;    // row stride (bf16) of the operands reduced over the 32 samples: 72 B
+constexpr int ZS = 33;    // and of the FP32 layer-2 activations
+struct TrainLds {
+    uint16_t x[32 * XS], xt[16 * TS];          // inputs [sample][feature] and [feature][sample]
+    uint16_t h1[32 * PS], h1lo[32 * PS];       // layer-1 activations [sample][unit], two bf16 parts
+    uint16_t h1t[64 * TS], h1lot[64 * TS];     // [unit][sample]
+    uint16_t d2t[64 * TS];                     // gradient at layer-2 pre-activations [unit][sample]
+    float h2t[64 * ZS];                        // layer-2 activations [unit][sample]
+    float z[32], dz[32];
+    // (re-used once what they held is spent)
+    __device__ uint16_t *d2() { return h1; }                                      // [sample][unit]
+    __device__ uint16_t *d1t() { return reinterpret_cast<uint16_t *>(h2t); }      // layer 1's, [unit][sample]
+};
+
+__device__ inline bf16x4 row4(const uint16_t *p) { return *reinterpret_cast<const bf16x4 *>(p); }
+__device__ inline f32x16 mma32(bf16x4 a, bf16x4 b, f32x16 c)
 {
-    __shared__ WaveLds lds[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    WaveLds &L = lds[wave];
-    const int64_t s0 = (int64_t)blockIdx.x * MB + wave * 32;
-    float *g = part + ((int64_t)blockIdx.x * 4 + wave) * (NP + 1);
-    // gather this wavefront's samples into a contiguous staging area
-    float *xs = xbuf + ((int64_t)blockIdx.x * MB + wave * 32) * 12;
-    for (int e = lane; e < 32 * 12; e += 64) {
-        const int64_t s = s0 + e / 12;
-        xs[e] = s < n ? feats_all[idx[s] * 12 + e % 12] : 0.0f;
+    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
+}
+
+// forward and backward of samples idx[s] (s in [0, n)); each wavefront (32
+// samples, a workgroup of its own, so that a batch's few wavefronts spread over
+// the CUs) writes its whole gradient (FP32) and its part of the loss (at [NP]; the
+// loss is divided by `norm`, the batch size) to its own row part[w * (NP + 1) ..],
+// w = blockIdx.x, with no atomics: the rows are then added in a fixed order, so a
+// batch's gradient is the same bits on every run.  The pass is one chain of
+// latencies; the weights (W1t, W2t: transposed; W2b) are loaded to registers at
+// its start, beside the samples (4096 samples: 11.8 us; through strided two-byte
+// reads of LDS and memory, four wavefronts a workgroup, 26).
+__global__ __launch_bounds__(64) void k_mlp_train(const float *__restrict__ feats_all, const uint8_t *__restrict__ y_all,
+                                                  const int64_t *__restrict__ idx, int64_t n,
+                                                  const uint16_t *__restrict__ W1t, const uint16_t *__restrict__ W2t,
+                                                  const uint16_t *__restrict__ W2b, const float *__restrict__ P,
+                                                  float pos_weight, float norm, float *__restrict__ part)
+{
+    __shared__ TrainLds L;
+    const int lane = threadIdx.x, r = lane & 31, hh = lane >> 5, h4 = 4 * hh;
+    const int64_t s0 = (int64_t)blockIdx.x * 32;
+    float *g = part + (int64_t)blockIdx.x * (NP + 1);
+    // sample r of the wavefront, half hh of its features on this lane
+    const bool have = s0 + r < n;
+    const int64_t row = have ? idx[s0 + r] : 0;
+    bf16x4 w1[2][2], w2[2][8], w2n[2][8];
+    float b1v[2], b2v[2];
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+        const int c = nh * 32 + r;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) w1[nh][k] = row4(W1t + c * 16 + 8 * k + h4);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            w2[nh][k] = row4(W2t + c * 64 + 8 * k + h4);
+            w2n[nh][k] = row4(W2b + c * 64 + 8 * k + h4);
+        }
+        b1v[nh] = P[OB1 + c];
+        b2v[nh] = P[OB2 + c];
     }
-    __threadfence_block();
-    __syncthreads();
-    forward(xbuf + (int64_t)blockIdx.x * MB * 12, wave * 32, MB, W1b, W2b, P, L, lane);
-    // loss and dL/dz
+    const float w3 = bf2f(f2bf(P[OW3 + lane])), b3 = P[OB3];
+    float f[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) f[k] = have ? feats_all[row * 12 + 6 * hh + k] : 0.0f;
+    const float y = have ? (float)y_all[row] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const uint16_t v = f2bf(f[k]);
+        L.x[r * XS + 6 * hh + k] = v;
+        L.xt[(6 * hh + k) * TS + r] = v;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        L.x[r * XS + 12 + 2 * hh + k] = 0;
+        L.xt[(12 + 2 * hh + k) * TS + r] = 0;
+    }
+    wave_sync_lds();
+    // layer 1
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+        f32x16 acc = {};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) acc = mma32(row4(L.x + r * XS + 8 * k + h4), w1[nh][k], acc);
+        const int c = nh * 32 + r;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            bf16x4 hi4, lo4;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float h = fmaxf(acc[4 * q + t] + b1v[nh], 0.0f);
+                const uint16_t hi = f2bf(h), lo = f2bf(h - bf2f(hi));
+                L.h1[(8 * q + h4 + t) * PS + c] = hi;
+                L.h1lo[(8 * q + h4 + t) * PS + c] = lo;
+                hi4[t] = (short)hi;
+                lo4[t] = (short)lo;
+            }
+            *reinterpret_cast<bf16x4 *>(L.h1t + c * TS + 8 * q + h4) = hi4;
+            *reinterpret_cast<bf16x4 *>(L.h1lot + c * TS + 8 * q + h4) = lo4;
+        }
+    }
+    wave_sync_lds();
+    // layer 2
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+        f32x16 acc = {};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc = mma32(row4(L.h1 + r * PS + 8 * k + h4), w2[nh][k], acc);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc = mma32(row4(L.h1lo + r * PS + 8 * k + h4), w2[nh][k], acc);
+        const int c = nh * 32 + r;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) L.h2t[c * ZS + acc_row(j, lane)] = fmaxf(acc[j] + b2v[nh], 0.0f);
+    }
+    wave_sync_lds();
+    // layer 3, the loss and dL/dz (lanes of the first half: a sample each)
     {
+        float z = b3;
+#pragma unroll
+        for (int c = 0; c < 64; ++c)
+            z += L.h2t[c * ZS + r] * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w3), c));
         float l = 0.0f;
         if (lane < 32) {
-            const int64_t s = s0 + lane;
             float dz = 0.0f;
-            if (s < n) {
-                const float z = L.z[lane], y = (float)y_all[idx[s]];
+            if (have) {
                 const float sg = 1.0f / (1.0f + expf(-z));
                 l = pos_weight * y * softplus(-z) + (1.0f - y) * softplus(z);
                 dz = (pos_weight * y * (sg - 1.0f) + (1.0f - y) * sg) / norm;
@@ -346,78 +353,88 @@ __global__ __launch_bounds__(256) void k_mlp_train(const float *__restrict__ fea
         for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o, 64);
         if (lane == 0) g[NP] = l / norm;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // layer 3: dW3, db3; gradient at layer-2 pre-activations
+    wave_sync_lds();
+    // layer 3: dW3, db3; gradient at layer-2 pre-activations (lane: a unit)
     {
-        const int c = lane;   // unit 0..63
-        const float w3 = bf2f(f2bf(P[OW3 + c]));
         float gw = 0.0f, gb = 0.0f;
-        for (int m = 0; m < 32; ++m) {
-            const float h = L.h2[m * 64 + c], dz = L.dz[m];
-            gw += dz * h;
-            const float d = h > 0.0f ? dz * w3 : 0.0f;
-            gb += d;
-            L.d2[m * 64 + c] = f2bf(d);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            bf16x4 d4;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int m = 4 * q + t;
+                const float h = L.h2t[lane * ZS + m], dz = L.dz[m];
+                gw += dz * h;
+                const float d = h > 0.0f ? dz * w3 : 0.0f;
+                gb += d;
+                const uint16_t v = f2bf(d);
+                L.d2()[m * PS + lane] = v;
+                d4[t] = (short)v;
+            }
+            *reinterpret_cast<bf16x4 *>(L.d2t + lane * TS + 4 * q) = d4;
         }
-        g[OW3 + c] = gw;
-        g[OB2 + c] = gb;
+        g[OW3 + lane] = gw;
+        g[OB2 + lane] = gb;
         if (lane == 0) {
             float s = 0.0f;
             for (int m = 0; m < 32; ++m) s += L.dz[m];
             g[OB3] = s;
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // dW2 (64 x 64) = h1^T d2: A(i, m) = h1[m][i], B(m, j) = d2[m][j]
+    wave_sync_lds();
+    // dW2 (64 x 64) = h1^T d2
+#pragma unroll
     for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
         for (int jh = 0; jh < 2; ++jh) {
             f32x16 acc = {};
-            acc = tile_mma(L.h1 + ih * 32, 1, 64, L.d2 + jh * 32, 64, 1, 32, acc, lane);
-            acc = tile_mma(L.h1lo + ih * 32, 1, 64, L.d2 + jh * 32, 64, 1, 32, acc, lane);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) g[OW2 + (ih * 32 + acc_row(j, lane)) * 64 + jh * 32 + acc_col(lane)] = acc[j];
+            for (int k = 0; k < 4; ++k)
+                acc = mma32(row4(L.h1t + (ih * 32 + r) * TS + 8 * k + h4), row4(L.d2t + (jh * 32 + r) * TS + 8 * k + h4), acc);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                acc = mma32(row4(L.h1lot + (ih * 32 + r) * TS + 8 * k + h4), row4(L.d2t + (jh * 32 + r) * TS + 8 * k + h4), acc);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) g[OW2 + (ih * 32 + acc_row(j, lane)) * 64 + jh * 32 + r] = acc[j];
         }
-    // gradient at layer-1 pre-activations: (d2 W2^T) masked; A(m, j) = d2[m][j], B(j, i) = W2[i][j]
+    // gradient at layer-1 pre-activations: (d2 W2^T) masked
+#pragma unroll
     for (int ih = 0; ih < 2; ++ih) {
         f32x16 acc = {};
-        acc = tile_mma(L.d2, 64, 1, W2b + ih * 32 * 64, 1, 64, 64, acc, lane);
-        float b1 = 0.0f;   // db1 of unit ih * 32 + acc_col(lane): this lane's rows, then the other half's
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int m = acc_row(j, lane), c = ih * 32 + acc_col(lane);
-            const float d = L.h1[m * 64 + c] != 0 ? acc[j] : 0.0f;   // relu'(pre) = [h1 > 0]
-            L.d1[m * 64 + c] = f2bf(d);
-            b1 += d;
+        for (int k = 0; k < 8; ++k) acc = mma32(row4(L.d2() + r * PS + 8 * k + h4), w2n[ih][k], acc);
+        const int c = ih * 32 + r;
+        float b1 = 0.0f;   // db1 of unit c: this lane's rows, then the other half's
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bf16x4 h = row4(L.h1t + c * TS + 8 * q + h4);
+            bf16x4 d4;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float d = h[t] != 0 ? acc[4 * q + t] : 0.0f;   // relu'(pre) = [h1 > 0]
+                d4[t] = (short)f2bf(d);
+                b1 += d;
+            }
+            *reinterpret_cast<bf16x4 *>(L.d1t() + c * TS + 8 * q + h4) = d4;
         }
         b1 += __shfl_xor(b1, 32, 64);
-        if (lane < 32) g[OB1 + ih * 32 + lane] = b1;
+        if (lane < 32) g[OB1 + c] = b1;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // dW1 (16 x 64, rows 12.. zero) = x^T d1: A(k, m) = x[m][k] (rows >= 16 read as zero via x's padding)
+    wave_sync_lds();
+    // dW1 (16 x 64, rows 12.. zero) = x^T d1
+#pragma unroll
     for (int jh = 0; jh < 2; ++jh) {
         f32x16 acc = {};
-        {
-            const int r = lane & 31, h = (lane >> 5) * 4;
-            for (int k0 = 0; k0 < 32; k0 += 8) {
-                bf16x4 av, bv;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    av[t] = r < 16 ? (short)L.x[(k0 + h + t) * 16 + r] : (short)0;
-                    bv[t] = (short)L.d1[(k0 + h + t) * 64 + jh * 32 + r];
-                }
-                acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
-            }
+        for (int k = 0; k < 4; ++k) {
+            bf16x4 av = row4(L.xt + (r & 15) * TS + 8 * k + h4);
+            if (r >= 16) av = bf16x4{0, 0, 0, 0};
+            acc = mma32(av, row4(L.d1t() + (jh * 32 + r) * TS + 8 * k + h4), acc);
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int k = acc_row(j, lane);
-            if (k < 12) g[OW1 + k * 64 + jh * 32 + acc_col(lane)] = acc[j];
+            if (k < 12) g[OW1 + k * 64 + jh * 32 + r] = acc[j];
         }
     }
 }
@@ -427,60 +444,108 @@ __global__ __launch_bounds__(256) void k_mlp_train(const float *__restrict__ fea
 // the rows g, g + GS_GROUPS, ... of parameter p in order, and the GS_GROUPS
 // partial sums are then added in the order g = 0, 1, ...
 constexpr int GS_GROUPS = 8;
+
+__device__ inline float grad_rows(const float *__restrict__ part, int64_t nrows, int t, int g, int p,
+                                  float (&ps)[GS_GROUPS][32])
+{
+    float s = 0.0f;
+    if (t <= NP) {
+        int64_t w = g;
+        for (; w + 7 * GS_GROUPS < nrows; w += 8 * GS_GROUPS) {   // (eight loads in flight, added in order)
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = part[(w + k * GS_GROUPS) * (NP + 1) + t];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += v[k];
+        }
+        for (; w < nrows; w += GS_GROUPS) s += part[w * (NP + 1) + t];
+    }
+    ps[g][p] = s;
+    __syncthreads();
+    float a = 0.0f;
+    if (g == 0) {
+#pragma unroll
+        for (int k = 0; k < GS_GROUPS; ++k) a += ps[k][p];
+    }
+    return a;
+}
+
 __global__ __launch_bounds__(32 * GS_GROUPS) void k_grad_sum(const float *__restrict__ part, int64_t nrows,
                                                              float *__restrict__ grad)
 {
     __shared__ float ps[GS_GROUPS][32];
     const int p = threadIdx.x & 31, g = threadIdx.x >> 5;
     const int t = blockIdx.x * 32 + p;
-    float s = 0.0f;
-    if (t <= NP)
-        for (int64_t w = g; w < nrows; w += GS_GROUPS) s += part[w * (NP + 1) + t];
-    ps[g][p] = s;
-    __syncthreads();
-    if (g == 0 && t <= NP) {
-        float a = 0.0f;
-#pragma unroll
-        for (int k = 0; k < GS_GROUPS; ++k) a += ps[k][p];
-        grad[t] += a;
+    const float a = grad_rows(part, nrows, t, g, p, ps);
+    if (g == 0 && t <= NP) grad[t] += a;
+}
+
+// The bf16 copies of the weights in the layouts the kernels read, for parameter
+// t of value v: W1b [16][64] (rows 12 .. zero, set once) and behind it W1t
+// [64][16], W2b [64][64] and behind it W2t, its transpose.
+__device__ inline void pack_weight(int t, float v, uint16_t *W1b, uint16_t *W2b)
+{
+    if (t < OB1) {
+        const int k = t >> 6, c = t & 63;
+        W1b[t] = f2bf(v);
+        W1b[16 * 64 + c * 16 + k] = f2bf(v);
+    } else if (t >= OW2 && t < OB2) {
+        const int k = (t - OW2) >> 6, c = (t - OW2) & 63;
+        W2b[t - OW2] = f2bf(v);
+        W2b[64 * 64 + c * 64 + k] = f2bf(v);
     }
 }
 
-// bf16 copies of the weights in the layouts the kernels read
 __global__ void k_mlp_pack(const float *__restrict__ P, uint16_t *__restrict__ W1b, uint16_t *__restrict__ W2b)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < 16 * 64) W1b[t] = t < 12 * 64 ? f2bf(P[OW1 + t]) : (uint16_t)0;
-    if (t < 64 * 64) W2b[t] = f2bf(P[OW2 + t]);
+    if (t < NP) pack_weight(t, P[t], W1b, W2b);
+    if (t < 4 * 64) {   // the rows (columns) of features 12 .. 15
+        W1b[12 * 64 + t] = 0;
+        W1b[16 * 64 + (t >> 2) * 16 + 12 + (t & 3)] = 0;
+    }
 }
 
-// Adam step (bias-corrected) on the FP32 master weights; clears the gradient.
-// The step number is read from the device (steps taken + 1), so a captured
-// sequence of steps replays with the right corrections.
-__global__ void k_adam(float *__restrict__ P, float *__restrict__ M, float *__restrict__ V, float *__restrict__ grad,
-                       float lr, float b1, float b2, float eps, const int64_t *__restrict__ tstep)
+// The end of a step: the rows of the batch's (last) launch added to the gradient
+// as in k_grad_sum, the Adam step (bias-corrected) on the FP32 master weights with
+// their bf16 copies, the gradient cleared, and the batch's loss (the mean over its
+// nb rows, at [NP]) times nb added to the epoch's sum.  One launch where four took
+// 20 us a step.  The step number is read from the device (the steps taken before
+// the epoch, tstep, and this one's place k in it), so a captured epoch replays
+// with the right corrections.
+__global__ __launch_bounds__(32 * GS_GROUPS) void k_grad_step(const float *__restrict__ part, int64_t nrows,
+                                                              float *__restrict__ P, float *__restrict__ M,
+                                                              float *__restrict__ V, float *__restrict__ grad, float lr,
+                                                              float b1, float b2, float eps,
+                                                              const int64_t *__restrict__ tstep, int k,
+                                                              double *__restrict__ lacc, float nb,
+                                                              uint16_t *__restrict__ W1b, uint16_t *__restrict__ W2b)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= NP) return;
-    const float s = (float)(tstep[0] + 1);
+    __shared__ float ps[GS_GROUPS][32];
+    const int p = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const int t = blockIdx.x * 32 + p;
+    const float a = grad_rows(part, nrows, t, g, p, ps);
+    if (g != 0 || t > NP) return;
+    const float gv = grad[t] + a;
+    grad[t] = 0.0f;
+    if (t == NP) {
+        *lacc += (double)gv * (double)nb;
+        return;
+    }
+    const float s = (float)(tstep[0] + k + 1);
     const float c1 = 1.0f - powf(b1, s), c2 = 1.0f - powf(b2, s);
-    const float gv = grad[t];
     const float m = b1 * M[t] + (1.0f - b1) * gv, v = b2 * V[t] + (1.0f - b2) * gv * gv;
     M[t] = m;
     V[t] = v;
-    P[t] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
-    grad[t] = 0.0f;
+    const float w = P[t] - lr * (m / c1) / (sqrtf(v / c2) + eps);
+    P[t] = w;
+    pack_weight(t, w, W1b, W2b);
 }
 
-// after a step: counts it, adds the batch's loss (the mean over its nb rows,
-// in G[NP]) times nb to the epoch's sum, and clears it
-__global__ void k_step_end(float *__restrict__ G, int64_t *__restrict__ tstep, double *__restrict__ lacc, float nb)
+// after an epoch: its steps counted
+__global__ void k_steps_taken(int64_t *__restrict__ tstep, int64_t steps)
 {
-    if (threadIdx.x == 0) {
-        *lacc += (double)G[NP] * (double)nb;
-        G[NP] = 0.0f;
-        *tstep += 1;
-    }
+    if (threadIdx.x == 0) *tstep += steps;
 }
 
 __global__ void k_step_reset(int64_t *__restrict__ tstep, double *__restrict__ lacc, int steps)
@@ -502,7 +567,7 @@ __global__ void k_zero_f32(float *p, int64_t n)
 // host launchers (device pointers throughout)
 void mlp_pack(const float *P, uint16_t *W1b, uint16_t *W2b, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mlp_pack, dim3(16), dim3(256), 0, st, P, W1b, W2b);
+    hipLaunchKernelGGL(k_mlp_pack, dim3((NP + 255) / 256), dim3(256), 0, st, P, W1b, W2b);
 }
 
 // a grid the device holds at once (three workgroups per CU at this LDS
@@ -530,23 +595,29 @@ void mlp_predict(const float *feats, int64_t n, const uint16_t *W1b, const uint1
 int64_t mlp_part_rows(int64_t n) { return (n + MB - 1) / MB * 4; }
 
 void mlp_train_batch(const float *feats, const uint8_t *y, const int64_t *idx, int64_t n, const uint16_t *W1b,
-                     const uint16_t *W2b, const float *P, float pos_weight, float norm, float *grad, float *part,
-                     float *xbuf, hipStream_t st)
+                     const uint16_t *W2b, const float *P, float pos_weight, float norm, float *part, hipStream_t st)
 {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)((n + MB - 1) / MB)), dim3(256), 0, st, feats, y, idx, n, W1b, W2b,
-                       P, pos_weight, norm, part, xbuf);
-    hipLaunchKernelGGL(k_grad_sum, dim3((NP + 1 + 31) / 32), dim3(32 * GS_GROUPS), 0, st, part, mlp_part_rows(n), grad);
+    if (n > 0)
+        hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)mlp_part_rows(n)), dim3(64), 0, st, feats, y, idx, n, W1b + 16 * 64,
+                           W2b + 64 * 64, W2b, P, pos_weight, norm, part);
 }
 
-void mlp_adam(float *P, float *M, float *V, float *grad, float lr, const int64_t *tstep, hipStream_t st)
+void mlp_grad_sum(const float *part, int64_t n, float *grad, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_adam, dim3((NP + 255) / 256), dim3(256), 0, st, P, M, V, grad, lr, 0.9f, 0.999f, 1e-8f, tstep);
+    if (n > 0)
+        hipLaunchKernelGGL(k_grad_sum, dim3((NP + 1 + 31) / 32), dim3(32 * GS_GROUPS), 0, st, part, mlp_part_rows(n), grad);
 }
 
-void mlp_step_end(float *G, int64_t *tstep, double *lacc, float nb, hipStream_t st)
+void mlp_grad_step(const float *part, int64_t n, float *P, float *M, float *V, float *grad, float lr,
+                   const int64_t *tstep, int k, double *lacc, float nb, uint16_t *W1b, uint16_t *W2b, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, st, G, tstep, lacc, nb);
+    hipLaunchKernelGGL(k_grad_step, dim3((NP + 1 + 31) / 32), dim3(32 * GS_GROUPS), 0, st, part, mlp_part_rows(n), P, M, V,
+                       grad, lr, 0.9f, 0.999f, 1e-8f, tstep, k, lacc, nb, W1b, W2b);
+}
+
+void mlp_steps_taken(int64_t *tstep, int64_t steps, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_steps_taken, dim3(1), dim3(64), 0, st, tstep, steps);
 }
 
 void mlp_step_reset(int64_t *tstep, double *lacc, bool steps, hipStream_t st)
