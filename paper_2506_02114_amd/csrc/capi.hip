@@ -1174,7 +1174,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                     mlm_refiner *nn = q.refiner;
                     int32_t *flag = static_cast<int32_t *>(ws.rflag.reserve((size_t)ncells * sizeof(int32_t)));
                     int64_t *pos = static_cast<int64_t *>(ws.rpos.reserve((size_t)(ncells + 1) * sizeof(int64_t)));
-                    mlp_flag_cells(R.nr1, r0, ncells, vb0, verts, nn->W1b.as<uint16_t>(), nn->W2b.as<uint16_t>(),
+                    mlp_flag_cells(R.nr1, r0, ncells, vb0, verts, nn->W1t.as<uint16_t>(), nn->W2b.as<uint16_t>(),
                                    nn->P.as<float>(), (float)q.refine_threshold, flag, st);
                     ncand = scan_i32_to_i64(lens, flag, pos, ncells, st);
                     launch_compact(ncells, flag, pos, base, cand, st);
@@ -1840,7 +1840,7 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
 static void refiner_upload(mlm_refiner *r, const float *params, hipStream_t st)
 {
     MLM_HIP(hipMemcpyAsync(r->P.p, params, MLM_REFINER_PARAMS * sizeof(float), hipMemcpyHostToDevice, st));
-    mlp_pack(r->P.as<float>(), r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), st);
+    mlp_pack(r->P.as<float>(), r->W1t.as<uint16_t>(), r->W2b.as<uint16_t>(), st);
     MLM_HIP(hipStreamSynchronize(st));
 }
 
@@ -1855,8 +1855,8 @@ mlm_status mlm_refiner_create(const float *params, uint64_t seed, mlm_refiner **
     r->M.reserve(nb);
     r->V.reserve(nb);
     r->G.reserve(nb);
-    r->W1b.reserve(2 * 16 * 64 * sizeof(uint16_t));   // (each with its transpose)
-    r->W2b.reserve(2 * 64 * 64 * sizeof(uint16_t));
+    r->W1t.reserve(16 * 64 * sizeof(uint16_t));
+    r->W2b.reserve(2 * 64 * 64 * sizeof(uint16_t));   // (with its transpose)
     r->tstep.reserve(sizeof(int64_t));
     r->lacc.reserve(sizeof(double));
     mlp_step_reset(r->tstep.as<int64_t>(), r->lacc.as<double>(), true, nullptr);
@@ -1929,7 +1929,7 @@ mlm_status mlm_refiner_predict(mlm_refiner *r, const float *feats, int64_t n, fl
     if (n == 0) return MLM_OK;
     const float *df = stage_feats(r, feats, n, device_ptrs, st);
     float *dl = device_ptrs ? logits : static_cast<float *>(r->logits.reserve((size_t)n * sizeof(float)));
-    mlp_predict(df, n, r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), r->P.as<float>(), dl, st);
+    mlp_predict(df, n, r->W1t.as<uint16_t>(), r->W2b.as<uint16_t>(), r->P.as<float>(), dl, st);
     if (!device_ptrs) MLM_HIP(hipMemcpyAsync(logits, dl, (size_t)n * sizeof(float), hipMemcpyDeviceToHost, st));
     MLM_HIP(hipStreamSynchronize(st));
     API_END
@@ -1958,7 +1958,7 @@ static int64_t refiner_batch(mlm_refiner *r, const float *df, const uint8_t *dy,
     float *part = r->gpart.as<float>();
     for (int64_t c0 = 0;; c0 += GRAD_CHUNK) {
         const int64_t c = std::min(GRAD_CHUNK, n - c0);
-        mlp_train_batch(df, dy, didx + c0, c, r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), r->P.as<float>(),
+        mlp_train_batch(df, dy, didx + c0, c, r->W1t.as<uint16_t>(), r->W2b.as<uint16_t>(), r->P.as<float>(),
                         pos_weight, (float)n, part, st);
         if (c0 + c >= n) return c;
         mlp_grad_sum(part, c, r->G.as<float>(), st);
@@ -2041,7 +2041,7 @@ mlm_status mlm_refiner_train(mlm_refiner *r, const mlm_train_opts *opts, const f
             const int64_t nb = std::min<int64_t>(o.batch, n - b0);
             const int64_t last = refiner_batch(r, df, dy, didx + b0, nb, o.pos_weight, ts);
             mlp_grad_step(r->gpart.as<float>(), last, r->P.as<float>(), r->M.as<float>(), r->V.as<float>(), G, o.lr, tstep,
-                          (int)(b0 / o.batch), lacc, (float)nb, r->W1b.as<uint16_t>(), r->W2b.as<uint16_t>(), ts);
+                          (int)(b0 / o.batch), lacc, (float)nb, r->W1t.as<uint16_t>(), r->W2b.as<uint16_t>(), ts);
         }
         mlp_steps_taken(tstep, (n + o.batch - 1) / o.batch, ts);
     };

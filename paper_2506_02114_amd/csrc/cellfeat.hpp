@@ -53,6 +53,7 @@ __device__ inline float log1p_hw(float x)
 // inference, which rounds its inputs to bf16 (8 significant bits) anyway: the
 // offsets and the ear signs are still formed in FP64, and the logarithm is
 // within a few FP32 units of its last place, far inside the bf16 rounding.
+// (Finite corners; the zero of an offset may come out negative.)
 __device__ inline void cell_features_half_f32(const double *u4, const double *v4, int h, float *f)
 {
     const double cu = floor(0.25 * (u4[0] + u4[1] + u4[2] + u4[3]));
@@ -61,10 +62,11 @@ __device__ inline void cell_features_half_f32(const double *u4, const double *v4
     for (int j = 0; j < 2; ++j) {
         const int k = 2 * h + j;
         const double du = u4[k] - cu, dv = v4[k] - cv;
-        f[2 * j] = (float)sgn(du) * log1p_hw((float)fabs(du));
-        f[2 * j + 1] = (float)sgn(dv) * log1p_hw((float)fabs(dv));
+        f[2 * j] = copysignf(log1p_hw((float)fabs(du)), (float)du);
+        f[2 * j + 1] = copysignf(log1p_hw((float)fabs(dv)), (float)dv);
         const int p = (k + 3) & 3, q = (k + 1) & 3;
-        f[4 + j] = (float)sgn(area2(u4[k], v4[k], u4[q], v4[q], u4[p], v4[p]));
+        const double a = area2(u4[k], v4[k], u4[q], v4[q], u4[p], v4[p]);
+        f[4 + j] = a > 0.0 ? 1.0f : (a < 0.0 ? -1.0f : 0.0f);
     }
 }
 

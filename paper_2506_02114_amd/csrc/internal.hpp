@@ -300,7 +300,7 @@ struct mlm_lens {
 // refinement network: FP32 master weights, Adam moments, gradient (+ loss),
 // bf16 copies in the kernels' layouts, staging
 struct mlm_refiner {
-    mlm::DevBuf P, M, V, G, W1b, W2b, gpart, idx, feats, labels, logits;
+    mlm::DevBuf P, M, V, G, W1t, W2b, gpart, idx, feats, labels, logits;
     mlm::DevBuf tstep;     // Adam steps taken (int64, on the device: read by the step kernels)
     mlm::DevBuf lacc;      // loss summed over an epoch's rows (double)
     hipStream_t gst = nullptr;   // training stream (graph capture needs a stream of its own)
@@ -498,13 +498,13 @@ void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, c
 void launch_compact(int64_t n, const int32_t *flag, const int64_t *pos, int64_t base, int64_t *cand, hipStream_t st);
 
 // mlp.hip
-void mlp_pack(const float *P, uint16_t *W1b, uint16_t *W2b, hipStream_t st);
+void mlp_pack(const float *P, uint16_t *W1t, uint16_t *W2b, hipStream_t st);
 // flag[t] for the cells t of a strip (cells cb0 + t / (nr1 - 1) rows, vertex
 // rows from vb0): the network's logit of the cell's features above thr, or
 // the cell folded; the features are formed on the fly
-void mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0, const double2 *verts, const uint16_t *W1b,
+void mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0, const double2 *verts, const uint16_t *W1t,
                     const uint16_t *W2b, const float *P, float thr, int32_t *flag, hipStream_t st);
-void mlp_predict(const float *feats, int64_t n, const uint16_t *W1b, const uint16_t *W2b, const float *P,
+void mlp_predict(const float *feats, int64_t n, const uint16_t *W1t, const uint16_t *W2b, const float *P,
                  float *logits, hipStream_t st);
 // rows of per-wavefront partial gradients (MLM_REFINER_PARAMS + 1 floats
 // each) that a batch of n samples needs
@@ -513,11 +513,11 @@ int64_t mlp_part_rows(int64_t n);
 // term divided by norm, a row per 32 samples in part; and their sum in a fixed
 // order (the same bits on every run) added to grad, or, for the last of a step's
 // launches, the whole end of the step (the k-th of its epoch)
-void mlp_train_batch(const float *feats, const uint8_t *y, const int64_t *idx, int64_t n, const uint16_t *W1b,
+void mlp_train_batch(const float *feats, const uint8_t *y, const int64_t *idx, int64_t n, const uint16_t *W1t,
                      const uint16_t *W2b, const float *P, float pos_weight, float norm, float *part, hipStream_t st);
 void mlp_grad_sum(const float *part, int64_t n, float *grad, hipStream_t st);
 void mlp_grad_step(const float *part, int64_t n, float *P, float *M, float *V, float *grad, float lr,
-                   const int64_t *tstep, int k, double *lacc, float nb, uint16_t *W1b, uint16_t *W2b, hipStream_t st);
+                   const int64_t *tstep, int k, double *lacc, float nb, uint16_t *W1t, uint16_t *W2b, hipStream_t st);
 void mlp_steps_taken(int64_t *tstep, int64_t steps, hipStream_t st);
 void mlp_zero(float *p, int64_t n, hipStream_t st);
 void mlp_step_reset(int64_t *tstep, double *lacc, bool steps, hipStream_t st);

@@ -35,61 +35,12 @@ constexpr int MB = 128;   // samples are padded to whole groups of so many
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// row and column of accumulator element j of lane `lane` in a 32 x 32 tile
+// row of accumulator element j of lane `lane` in a 32 x 32 tile (its column is
+// lane % 32)
 __device__ inline int acc_row(int j, int lane) { return 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3); }
-__device__ inline int acc_col(int lane) { return lane & 31; }
 
-// Inference only: the weights are staged once per workgroup in LDS, rows of
-// every operand are stored so that the four consecutive values of the
-// reduced dimension that a lane feeds one MFMA are one 8-byte LDS read, and
-// each wavefront loops over tiles of 32 samples (a grid sized to the device,
-// not to the samples).  Same arithmetic as the training's forward pass (bf16 inputs, two-part
-// bf16 hidden layer, FP32 accumulation); the final 64-term sum runs in
-// another order.
 constexpr int PS = 68;    // padded row stride (bf16) of the 64-wide operands: 136 B, so rows fall in other banks
 constexpr int XS = 20;    // and of the 16-wide input rows: 40 B
-
-struct PredictLds {
-    uint16_t w1t[64 * XS];   // W1 transposed: w1t[n][k] = W1[k][n], k < 16
-    uint16_t w2t[64 * PS];   // W2 transposed: w2t[n][k] = W2[k][n]
-    float b1[64], b2[64], w3[64];
-    struct Wave {
-        uint16_t x[32 * XS];   // the tile's inputs, 12 features + 4 zero columns
-        uint16_t h1[32 * PS];  // layer-1 activations, bf16 part (then the layer-3 partial sums)
-        uint16_t h1lo[32 * PS];
-    } w[4];
-};
-
-// C (32 x 32) += A (32 x K) B (K x 32), A(m, k) = a[m * sa + k], B(k, n) =
-// bt[n * sb + k] (bf16 in LDS, rows 8-byte aligned): one 8-byte read per
-// operand and MFMA
-__device__ inline f32x16 tile_mma_rows(const uint16_t *a, int sa, const uint16_t *bt, int sb, int K, f32x16 acc,
-                                       int lane)
-{
-    const int r = lane & 31, h = (lane >> 5) * 4;
-    for (int k0 = 0; k0 < K; k0 += 8) {
-        const bf16x4 av = *reinterpret_cast<const bf16x4 *>(a + r * sa + k0 + h);
-        const bf16x4 bv = *reinterpret_cast<const bf16x4 *>(bt + r * sb + k0 + h);
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-// the weights of the inference into the workgroup's LDS
-__device__ inline void stage_weights(PredictLds &S, const uint16_t *__restrict__ W1b, const uint16_t *__restrict__ W2b,
-                                     const float *__restrict__ P)
-{
-    for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-        const int k = e >> 6, c = e & 63;   // W2b[k][c]
-        S.w2t[c * PS + k] = W2b[e];
-        if (k < 16) S.w1t[c * XS + k] = W1b[e];
-    }
-    if (threadIdx.x < 64) {
-        S.b1[threadIdx.x] = P[OB1 + threadIdx.x];
-        S.b2[threadIdx.x] = P[OB2 + threadIdx.x];
-        S.w3[threadIdx.x] = bf2f(f2bf(P[OW3 + threadIdx.x]));
-    }
-}
 
 __device__ inline void wave_sync_lds()
 {
@@ -98,122 +49,192 @@ __device__ inline void wave_sync_lds()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// the logit of sample `lane` (lanes < 32) of the tile whose inputs the wavefront
-// has staged in L.x
-__device__ __forceinline__ float tile_logit(const PredictLds &S, PredictLds::Wave &L, float b3, int lane)
+__device__ inline bf16x4 row4(const uint16_t *p) { return *reinterpret_cast<const bf16x4 *>(p); }
+__device__ inline f32x16 mma32(bf16x4 a, bf16x4 b, f32x16 c)
 {
-    for (int nh = 0; nh < 2; ++nh) {
-        f32x16 acc = {};
-        acc = tile_mma_rows(L.x, XS, S.w1t + nh * 32 * XS, XS, 16, acc, lane);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int m = acc_row(j, lane), c = nh * 32 + acc_col(lane);
-            const float h = fmaxf(acc[j] + S.b1[c], 0.0f);
-            const uint16_t hi = f2bf(h);
-            L.h1[m * PS + c] = hi;
-            L.h1lo[m * PS + c] = f2bf(h - bf2f(hi));
-        }
-    }
-    wave_sync_lds();
-    // layer 2 and each lane's share of layer 3: sum over its two columns
-    float part[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) part[j] = 0.0f;
-    for (int nh = 0; nh < 2; ++nh) {
-        f32x16 acc = {};
-        acc = tile_mma_rows(L.h1, PS, S.w2t + nh * 32 * PS, PS, 64, acc, lane);
-        acc = tile_mma_rows(L.h1lo, PS, S.w2t + nh * 32 * PS, PS, 64, acc, lane);
-        const int c = nh * 32 + acc_col(lane);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) part[j] += fmaxf(acc[j] + S.b2[c], 0.0f) * S.w3[c];
-    }
-    wave_sync_lds();
-    // the 32 partial sums of each sample, through LDS (h1 is free now)
-    float *zb = reinterpret_cast<float *>(L.h1);   // [32 samples][32 lanes]
-#pragma unroll
-    for (int j = 0; j < 16; ++j) zb[acc_row(j, lane) * 32 + acc_col(lane)] = part[j];
-    wave_sync_lds();
-    float z = b3;
-    if (lane < 32)
-        for (int q = 0; q < 32; ++q) z += zb[lane * 32 + ((q + lane) & 31)];
-    wave_sync_lds();   // the next tile overwrites the LDS
-    return z;
+    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
 }
 
-__global__ __launch_bounds__(256) void k_mlp_predict(const float *__restrict__ feats, int64_t n,
-                                                     const uint16_t *__restrict__ W1b, const uint16_t *__restrict__ W2b,
-                                                     const float *__restrict__ P, float *__restrict__ logits)
+// Inference only.  The products are formed transposed (units by samples): what a
+// lane then holds of a layer's result, units 8 q + 4 (lane / 32) + t of sample
+// lane % 32, is just what it feeds the next layer's product, so the activations
+// stay in registers, as the weights do (a lane's 224 bytes of them and 384 of
+// biases, loaded once; a wavefront loops over the samples).  Same arithmetic as the
+// training's forward pass (bf16 inputs, two-part bf16 hidden layer, FP32
+// accumulation); the final 64-term sum runs in another order, through LDS.  Bound
+// by vector issue (555 instructions per 32 cells beside the products): 4.7e8 cells
+// in 21.0 ms, with every operand through LDS 23.7; the products alone would take 7.
+struct PredictNet {
+    bf16x4 w1[2][2], w2[2][8];
+    float b1[2][16], b2[2][16], w3[2][16], b3;
+
+    __device__ void load(const uint16_t *__restrict__ W1t, const uint16_t *__restrict__ W2t, const float *__restrict__ P,
+                         int lane)
+    {
+        const int r = lane & 31, h4 = 4 * (lane >> 5);
+#pragma unroll
+        for (int nh = 0; nh < 2; ++nh) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) w1[nh][k] = row4(W1t + (nh * 32 + r) * 16 + 8 * k + h4);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w2[nh][k] = row4(W2t + (nh * 32 + r) * 64 + 8 * k + h4);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int c = nh * 32 + acc_row(j, lane);
+                b1[nh][j] = P[OB1 + c];
+                b2[nh][j] = P[OB2 + c];
+                w3[nh][j] = bf2f(f2bf(P[OW3 + c]));
+            }
+        }
+        b3 = P[OB3];
+    }
+
+    // the terms of 32 samples' logits, of units j and 32 + j together, to zb
+    // [sample][ZP], twice, so that they can be read from any of them on; x0, x1: this lane's inputs 4 (lane / 32) .. + 3 and 8 more on
+    // of sample lane % 32
+    static constexpr int ZP = 65;
+    __device__ __forceinline__ void terms(bf16x4 x0, bf16x4 x1, float *zb, int lane) const
+    {
+        bf16x4 hi[8], lo[8];
+#pragma unroll
+        for (int nh = 0; nh < 2; ++nh) {
+            f32x16 acc = {};
+            acc = mma32(w1[nh][0], x0, acc);
+            acc = mma32(w1[nh][1], x1, acc);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const float h = fmaxf(acc[j] + b1[nh][j], 0.0f);
+                const uint16_t v = f2bf(h);
+                hi[nh * 4 + (j >> 2)][j & 3] = (short)v;
+                lo[nh * 4 + (j >> 2)][j & 3] = (short)f2bf(h - bf2f(v));
+            }
+        }
+        float part[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) part[j] = 0.0f;
+#pragma unroll
+        for (int nh = 0; nh < 2; ++nh) {
+            f32x16 acc = {};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc = mma32(w2[nh][k], hi[k], acc);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc = mma32(w2[nh][k], lo[k], acc);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) part[j] += fmaxf(acc[j] + b2[nh][j], 0.0f) * w3[nh][j];
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            float *to = zb + (lane & 31) * ZP + acc_row(j, lane);
+            to[0] = part[j];
+            to[32] = part[j];
+        }
+    }
+
+    // the logit of sample `lane` of 64, from their terms, term lane % 32 first
+    __device__ float logit(const float *zb, int lane) const
+    {
+        const float *from = zb + lane * ZP + (lane & 31);
+        float z = b3;
+#pragma unroll
+        for (int q = 0; q < 32; ++q) z += from[q];
+        return z;
+    }
+};
+constexpr int PW = 4;   // wavefronts of an inference workgroup
+
+__global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_predict(const float *__restrict__ feats, int64_t n,
+                                                         const uint16_t *__restrict__ W1t,
+                                                         const uint16_t *__restrict__ W2t, const float *__restrict__ P,
+                                                         float *__restrict__ logits)
 {
-    __shared__ PredictLds S;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    stage_weights(S, W1b, W2b, P);
-    const float b3 = P[OB3];
-    __syncthreads();
-    PredictLds::Wave &L = S.w[wave];
-    const int64_t ntiles = (n + 31) / 32, nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += nwaves) {
-        const int64_t s0 = tile * 32;
-        for (int e = lane; e < 32 * 16; e += 64) {
-            const int m = e >> 4, k = e & 15;
-            const int64_t s = s0 + m;
-            L.x[m * XS + k] = (k < 12 && s < n) ? f2bf(feats[s * 12 + k]) : (uint16_t)0;
+    __shared__ float zs[PW][64 * PredictNet::ZP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, hh = lane >> 5;
+    PredictNet net;
+    net.load(W1t, W2t, P, lane);
+    float *zb = zs[wave];
+    const int64_t nblocks = (n + 63) / 64, nwaves = (int64_t)gridDim.x * PW;
+    for (int64_t blk = (int64_t)blockIdx.x * PW + wave; blk < nblocks; blk += nwaves) {
+        const int64_t s0 = blk * 64;
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            const int64_t s = s0 + 32 * half + r;
+            bf16x4 x0 = {}, x1 = {};
+            if (s < n) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    x0[k] = (short)f2bf(feats[s * 12 + 4 * hh + k]);
+                    if (hh == 0) x1[k] = (short)f2bf(feats[s * 12 + 8 + k]);
+                }
+            }
+            net.terms(x0, x1, zb + 32 * half * PredictNet::ZP, lane);
         }
         wave_sync_lds();
-        const float z = tile_logit(S, L, b3, lane);
-        if (lane < 32 && s0 + lane < n) logits[s0 + lane] = z;
+        const float z = net.logit(zb, lane);
+        if (s0 + lane < n) logits[s0 + lane] = z;
+        wave_sync_lds();   // (the next samples overwrite zb)
     }
 }
 
 // The cells of a strip (cells [cb0, cb0 + ncells / (nr1 - 1)) of the grid,
 // vertex rows from vb0 in `verts`) that the refinement tests: the network's
 // logit above thr, or folded.  Features are formed from the mapped corners
-// in the tile that uses them (zero for a cell with a non-finite corner, which
-// the test then leaves alone), so nothing per cell goes through memory but
+// by the two lanes that feed them in (zero for a cell with a non-finite corner,
+// which the test then leaves alone), so nothing per cell goes through memory but
 // the flag.
-__global__ __launch_bounds__(256) void k_mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0,
-                                                        const double2 *__restrict__ verts,
-                                                        const uint16_t *__restrict__ W1b,
-                                                        const uint16_t *__restrict__ W2b, const float *__restrict__ P,
-                                                        float thr, int32_t *__restrict__ flag)
+__global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0,
+                                                            const double2 *__restrict__ verts,
+                                                            const uint16_t *__restrict__ W1t,
+                                                            const uint16_t *__restrict__ W2t,
+                                                            const float *__restrict__ P, float thr,
+                                                            int32_t *__restrict__ flag)
 {
-    __shared__ PredictLds S;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    stage_weights(S, W1b, W2b, P);
-    const float b3 = P[OB3];
-    __syncthreads();
-    PredictLds::Wave &L = S.w[wave];
-    const int64_t ntiles = (ncells + 31) / 32, nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += nwaves) {
-        // cell m of the tile, half h of its features on this lane
-        const int m = lane & 31, h = lane >> 5;
-        const int64_t t = tile * 32 + m;
-        float f[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) f[k] = 0.0f;
-        if (t < ncells) {
-            const int64_t a = t % (nr1 - 1), b = cb0 + t / (nr1 - 1);
-            const double2 *r0 = verts + (b - vb0) * nr1, *r1 = r0 + nr1;
-            const double2 q[4] = {r0[a], r0[a + 1], r1[a + 1], r1[a]};
-            const double u4[4] = {q[0].x, q[1].x, q[2].x, q[3].x}, v4[4] = {q[0].y, q[1].y, q[2].y, q[3].y};
-            if (isfinite(u4[0]) && isfinite(u4[1]) && isfinite(u4[2]) && isfinite(u4[3]) && isfinite(v4[0]) &&
-                isfinite(v4[1]) && isfinite(v4[2]) && isfinite(v4[3]))
-                cell_features_half_f32(u4, v4, h, f);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) L.x[m * XS + 4 * h + k] = f2bf(f[k]);
-        L.x[m * XS + 8 + 2 * h] = f2bf(f[4]);
-        L.x[m * XS + 9 + 2 * h] = f2bf(f[5]);
-        L.x[m * XS + 12 + 2 * h] = 0;
-        L.x[m * XS + 13 + 2 * h] = 0;
-        wave_sync_lds();
-        // folded: the four ear signs (0 or +-1, exact in bf16) of the staged row
+    __shared__ float zs[PW][64 * PredictNet::ZP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, hh = lane >> 5;
+    PredictNet net;
+    net.load(W1t, W2t, P, lane);
+    float *zb = zs[wave];
+    const int64_t nblocks = (ncells + 63) / 64, nwaves = (int64_t)gridDim.x * PW;
+    // (a strip's cells number fewer than 2^32)
+    const uint32_t ncol = (uint32_t)(nr1 - 1);
+    for (int64_t blk = (int64_t)blockIdx.x * PW + wave; blk < nblocks; blk += nwaves) {
         bool fold = false;
-        if (lane < 32) {
-            const uint16_t *e = L.x + m * XS + 8;
-            fold = !(e[0] == e[1] && e[1] == e[2] && e[2] == e[3]);
+        // row and column of the block's first cell
+        const uint32_t t0 = __builtin_amdgcn_readfirstlane((uint32_t)(blk * 64)), row0 = t0 / ncol, a0 = t0 - row0 * ncol;
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            // cell r of the half, half hh of its features on this lane
+            const uint32_t t = t0 + 32 * half + r;
+            float f[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) f[k] = 0.0f;
+            if ((int64_t)t < ncells) {
+                uint32_t row = row0, a = a0 + 32 * half + r;
+                while (a >= ncol) {   // (once at most, unless the grid is narrower than a block)
+                    a -= ncol;
+                    ++row;
+                }
+                const double2 *r0 = verts + (cb0 + row - vb0) * nr1 + a, *r1 = r0 + nr1;
+                const double2 q[4] = {r0[0], r0[1], r1[1], r1[0]};
+                const double u4[4] = {q[0].x, q[1].x, q[2].x, q[3].x}, v4[4] = {q[0].y, q[1].y, q[2].y, q[3].y};
+                if (isfinite(u4[0]) && isfinite(u4[1]) && isfinite(u4[2]) && isfinite(u4[3]) && isfinite(v4[0]) &&
+                    isfinite(v4[1]) && isfinite(v4[2]) && isfinite(v4[3]))
+                    cell_features_half_f32(u4, v4, hh, f);
+            }
+            // the four ear signs (0 or +-1): this lane's two, and its partner's
+            const float g4 = __shfl_xor(f[4], 32, 64), g5 = __shfl_xor(f[5], 32, 64);
+            const bool flat = f[4] == f[5] && f[5] == g4 && g4 == g5;
+            if (half == hh) fold = !flat;
+            bf16x4 x0, x1 = {};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x0[k] = (short)f2bf(f[k]);
+            if (hh == 0) x1 = bf16x4{(short)f2bf(f[4]), (short)f2bf(f[5]), (short)f2bf(g4), (short)f2bf(g5)};
+            net.terms(x0, x1, zb + 32 * half * PredictNet::ZP, lane);
         }
-        const float z = tile_logit(S, L, b3, lane);
-        if (lane < 32 && t < ncells) flag[t] = (z > thr || fold) ? 1 : 0;
+        wave_sync_lds();
+        const float z = net.logit(zb, lane);
+        const int64_t t = blk * 64 + lane;
+        if (t < ncells) flag[t] = (z > thr || fold) ? 1 : 0;
+        wave_sync_lds();
     }
 }
 
@@ -235,12 +256,6 @@ struct TrainLds {
     __device__ uint16_t *d2() { return h1; }                                      // [sample][unit]
     __device__ uint16_t *d1t() { return reinterpret_cast<uint16_t *>(h2t); }      // layer 1's, [unit][sample]
 };
-
-__device__ inline bf16x4 row4(const uint16_t *p) { return *reinterpret_cast<const bf16x4 *>(p); }
-__device__ inline f32x16 mma32(bf16x4 a, bf16x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
-}
 
 // forward and backward of samples idx[s] (s in [0, n)); each wavefront (32
 // samples, a workgroup of its own, so that a batch's few wavefronts spread over
@@ -481,14 +496,13 @@ __global__ __launch_bounds__(32 * GS_GROUPS) void k_grad_sum(const float *__rest
 }
 
 // The bf16 copies of the weights in the layouts the kernels read, for parameter
-// t of value v: W1b [16][64] (rows 12 .. zero, set once) and behind it W1t
-// [64][16], W2b [64][64] and behind it W2t, its transpose.
-__device__ inline void pack_weight(int t, float v, uint16_t *W1b, uint16_t *W2b)
+// t of value v: W1t [64][16] (layer 1's transposed; columns 12 .. zero, set once),
+// W2b [64][64] and behind it W2t, its transpose.
+__device__ inline void pack_weight(int t, float v, uint16_t *W1t, uint16_t *W2b)
 {
     if (t < OB1) {
         const int k = t >> 6, c = t & 63;
-        W1b[t] = f2bf(v);
-        W1b[16 * 64 + c * 16 + k] = f2bf(v);
+        W1t[c * 16 + k] = f2bf(v);
     } else if (t >= OW2 && t < OB2) {
         const int k = (t - OW2) >> 6, c = (t - OW2) & 63;
         W2b[t - OW2] = f2bf(v);
@@ -496,14 +510,11 @@ __device__ inline void pack_weight(int t, float v, uint16_t *W1b, uint16_t *W2b)
     }
 }
 
-__global__ void k_mlp_pack(const float *__restrict__ P, uint16_t *__restrict__ W1b, uint16_t *__restrict__ W2b)
+__global__ void k_mlp_pack(const float *__restrict__ P, uint16_t *__restrict__ W1t, uint16_t *__restrict__ W2b)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < NP) pack_weight(t, P[t], W1b, W2b);
-    if (t < 4 * 64) {   // the rows (columns) of features 12 .. 15
-        W1b[12 * 64 + t] = 0;
-        W1b[16 * 64 + (t >> 2) * 16 + 12 + (t & 3)] = 0;
-    }
+    if (t < NP) pack_weight(t, P[t], W1t, W2b);
+    if (t < 4 * 64) W1t[(t >> 2) * 16 + 12 + (t & 3)] = 0;   // (no features 12 .. 15)
 }
 
 // The end of a step: the rows of the batch's (last) launch added to the gradient
@@ -519,7 +530,7 @@ __global__ __launch_bounds__(32 * GS_GROUPS) void k_grad_step(const float *__res
                                                               float b1, float b2, float eps,
                                                               const int64_t *__restrict__ tstep, int k,
                                                               double *__restrict__ lacc, float nb,
-                                                              uint16_t *__restrict__ W1b, uint16_t *__restrict__ W2b)
+                                                              uint16_t *__restrict__ W1t, uint16_t *__restrict__ W2b)
 {
     __shared__ float ps[GS_GROUPS][32];
     const int p = threadIdx.x & 31, g = threadIdx.x >> 5;
@@ -539,7 +550,7 @@ __global__ __launch_bounds__(32 * GS_GROUPS) void k_grad_step(const float *__res
     V[t] = v;
     const float w = P[t] - lr * (m / c1) / (sqrtf(v / c2) + eps);
     P[t] = w;
-    pack_weight(t, w, W1b, W2b);
+    pack_weight(t, w, W1t, W2b);
 }
 
 // after an epoch: its steps counted
@@ -565,40 +576,42 @@ __global__ void k_zero_f32(float *p, int64_t n)
 }  // namespace
 
 // host launchers (device pointers throughout)
-void mlp_pack(const float *P, uint16_t *W1b, uint16_t *W2b, hipStream_t st)
+void mlp_pack(const float *P, uint16_t *W1t, uint16_t *W2b, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mlp_pack, dim3((NP + 255) / 256), dim3(256), 0, st, P, W1b, W2b);
+    hipLaunchKernelGGL(k_mlp_pack, dim3((NP + 255) / 256), dim3(256), 0, st, P, W1t, W2b);
 }
 
-// a grid the device holds at once (three workgroups per CU at this LDS
-// size), each wavefront looping over tiles of 32 samples
+// a grid the device holds at once (two workgroups per CU at these registers), a
+// few times over, each wavefront looping over blocks of 64 samples
 static unsigned predict_grid(int64_t n)
 {
-    const int64_t tiles = (n + 31) / 32;
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((tiles + 3) / 4, 256 * 3 * 4));
+    const int64_t blocks = (n + 63) / 64;
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((blocks + PW - 1) / PW, 256 * 2 * 4));
 }
 
-void mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0, const double2 *verts, const uint16_t *W1b,
+void mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0, const double2 *verts, const uint16_t *W1t,
                     const uint16_t *W2b, const float *P, float thr, int32_t *flag, hipStream_t st)
 {
     if (ncells > 0)
-        hipLaunchKernelGGL(k_mlp_flag_cells, dim3(predict_grid(ncells)), dim3(256), 0, st, nr1, cb0, ncells, vb0, verts,
-                           W1b, W2b, P, thr, flag);
+        hipLaunchKernelGGL(k_mlp_flag_cells, dim3(predict_grid(ncells)), dim3(64 * PW), 0, st, nr1, cb0, ncells, vb0, verts,
+                           W1t, W2b + 64 * 64, P, thr, flag);
 }
 
-void mlp_predict(const float *feats, int64_t n, const uint16_t *W1b, const uint16_t *W2b, const float *P,
+void mlp_predict(const float *feats, int64_t n, const uint16_t *W1t, const uint16_t *W2b, const float *P,
                  float *logits, hipStream_t st)
 {
-    if (n > 0) hipLaunchKernelGGL(k_mlp_predict, dim3(predict_grid(n)), dim3(256), 0, st, feats, n, W1b, W2b, P, logits);
+    if (n > 0)
+        hipLaunchKernelGGL(k_mlp_predict, dim3(predict_grid(n)), dim3(64 * PW), 0, st, feats, n, W1t, W2b + 64 * 64, P,
+                           logits);
 }
 
 int64_t mlp_part_rows(int64_t n) { return (n + MB - 1) / MB * 4; }
 
-void mlp_train_batch(const float *feats, const uint8_t *y, const int64_t *idx, int64_t n, const uint16_t *W1b,
+void mlp_train_batch(const float *feats, const uint8_t *y, const int64_t *idx, int64_t n, const uint16_t *W1t,
                      const uint16_t *W2b, const float *P, float pos_weight, float norm, float *part, hipStream_t st)
 {
     if (n > 0)
-        hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)mlp_part_rows(n)), dim3(64), 0, st, feats, y, idx, n, W1b + 16 * 64,
+        hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)mlp_part_rows(n)), dim3(64), 0, st, feats, y, idx, n, W1t,
                            W2b + 64 * 64, W2b, P, pos_weight, norm, part);
 }
 
@@ -609,10 +622,10 @@ void mlp_grad_sum(const float *part, int64_t n, float *grad, hipStream_t st)
 }
 
 void mlp_grad_step(const float *part, int64_t n, float *P, float *M, float *V, float *grad, float lr,
-                   const int64_t *tstep, int k, double *lacc, float nb, uint16_t *W1b, uint16_t *W2b, hipStream_t st)
+                   const int64_t *tstep, int k, double *lacc, float nb, uint16_t *W1t, uint16_t *W2b, hipStream_t st)
 {
     hipLaunchKernelGGL(k_grad_step, dim3((NP + 1 + 31) / 32), dim3(32 * GS_GROUPS), 0, st, part, mlp_part_rows(n), P, M, V,
-                       grad, lr, 0.9f, 0.999f, 1e-8f, tstep, k, lacc, nb, W1b, W2b);
+                       grad, lr, 0.9f, 0.999f, 1e-8f, tstep, k, lacc, nb, W1t, W2b);
 }
 
 void mlp_steps_taken(int64_t *tstep, int64_t steps, hipStream_t st)
