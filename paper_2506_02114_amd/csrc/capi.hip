@@ -1168,18 +1168,27 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             if (q.refine != MLM_REFINE_NONE) {
                 // cell refinement of this strip's cells (a + (nr1 - 1) b, b in [r0, r1))
                 const int64_t base = (R.nr1 - 1) * r0;
-                int64_t *cand = static_cast<int64_t *>(ws.rcand.reserve((size_t)ncells * sizeof(int64_t)));
-                int64_t ncand = ncells;
+                const auto listed = [&](int64_t n, auto &&flag_them, DevBuf &to, int64_t from, int64_t &count) {
+                    const int64_t nm = (n + 63) / 64;
+                    uint64_t *mask = static_cast<uint64_t *>(ws.rmask.reserve((size_t)nm * sizeof(uint64_t)));
+                    int32_t *mcnt = static_cast<int32_t *>(ws.rcount.reserve((size_t)nm * sizeof(int32_t)));
+                    int64_t *pos = static_cast<int64_t *>(ws.rtpos.reserve((size_t)(nm + 1) * sizeof(int64_t)));
+                    flag_them(mask, mcnt);
+                    count = scan_i32_to_i64(lens, mcnt, pos, nm, st);
+                    int64_t *item = static_cast<int64_t *>(to.reserve((size_t)std::max<int64_t>(count, 1) * sizeof(int64_t)));
+                    if (count > 0) launch_list_flagged(n, mask, pos, from, item, st);
+                    return item;
+                };
+                int64_t *cand, ncand = ncells;
                 if (q.refine == MLM_REFINE_LEARNED) {
                     mlm_refiner *nn = q.refiner;
-                    int32_t *flag = static_cast<int32_t *>(ws.rflag.reserve((size_t)ncells * sizeof(int32_t)));
-                    int64_t *pos = static_cast<int64_t *>(ws.rpos.reserve((size_t)(ncells + 1) * sizeof(int64_t)));
-                    mlp_flag_cells(R.nr1, r0, ncells, vb0, verts, nn->W1t.as<uint16_t>(), nn->W2b.as<uint16_t>(),
-                                   nn->P.as<float>(), (float)q.refine_threshold, flag, st);
-                    ncand = scan_i32_to_i64(lens, flag, pos, ncells, st);
-                    launch_compact(ncells, flag, pos, base, cand, st);
+                    cand = listed(ncells, [&](uint64_t *mask, int32_t *mcnt) {
+                        mlp_flag_cells(R.nr1, r0, ncells, vb0, verts, nn->W1t.as<uint16_t>(), nn->W2b.as<uint16_t>(),
+                                       nn->P.as<float>(), (float)q.refine_threshold, mask, mcnt, st);
+                    }, ws.rcand, base, ncand);
                 } else {
-                    launch_compact(ncells, nullptr, nullptr, base, cand, st);
+                    cand = static_cast<int64_t *>(ws.rcand.reserve((size_t)ncells * sizeof(int64_t)));
+                    launch_list_flagged(ncells, nullptr, nullptr, base, cand, st);
                 }
                 unsigned long long *rst3 = static_cast<unsigned long long *>(ws.rstats.reserve(REFINE_SLOTS * REFINE_STRIDE * sizeof(unsigned long long)));
                 if (!refine_stats_zeroed) {
@@ -1194,17 +1203,18 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 const void *list = nullptr;   // level 0: the candidate cells themselves
                 DevBuf *next = &ws.rsub0;
                 for (int d = 0; d < q.refine_depth && nlev > 0; ++d) {
-                    int32_t *flag = static_cast<int32_t *>(ws.rtflag.reserve((size_t)nlev * sizeof(int32_t)));
-                    int64_t *pos = static_cast<int64_t *>(ws.rtpos.reserve((size_t)(nlev + 1) * sizeof(int64_t)));
+                    uint8_t *flag = static_cast<uint8_t *>(ws.rtflag.reserve((size_t)nlev));
                     launch_refine_test(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, cand, list,
                                        R.nr1, vb0, verts, flag, rst3, st);
-                    const int64_t nref = scan_i32_to_i64(lens, flag, pos, nlev, st);
+                    int64_t nref = 0;
+                    const int64_t *item = listed(nlev, [&](uint64_t *mask, int32_t *mcnt) {
+                        launch_flag_masks(nlev, flag, mask, mcnt, st);
+                    }, ws.ritem, 0, nref);
                     if (d == 0) n_refined += nref;
                     if (nref == 0) break;
                     void *out = next->reserve((size_t)(4 * nref) * sub);
-                    int64_t *item = static_cast<int64_t *>(ws.ritem.reserve((size_t)nref * sizeof(int64_t)));
                     launch_refine_expand(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, nref, cand,
-                                         list, R.nr1, vb0, verts, flag, pos, item, map, out, st);
+                                         list, R.nr1, vb0, verts, item, map, out, st);
                     list = out;
                     nlev = 4 * nref;
                     next = next == &ws.rsub0 ? &ws.rsub1 : &ws.rsub0;

@@ -271,7 +271,7 @@ struct Workspace {
     DevBuf search;
     DevBuf binom, patch_info, patch_coef;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
-        bandcur, bandlist, rfeat, rflag, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map;
+        bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
     int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
@@ -486,24 +486,26 @@ constexpr int REFINE_STRIDE = 16;
 size_t refine_subcell_bytes();
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, int32_t *flag, unsigned long long *stats, hipStream_t st);
+                        const double2 *verts, uint8_t *flag, unsigned long long *stats, hipStream_t st);
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                           int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
-                          int64_t vb0, const double2 *verts, const int32_t *flag, const int64_t *pos, int64_t *item,
-                          double *map, void *out, hipStream_t st);
+                          int64_t vb0, const double2 *verts, const int64_t *item, double *map, void *out, hipStream_t st);
 void launch_sample_features(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t n,
                             const int64_t *ab, float *feats, hipStream_t st);
 void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau,
                           int window, int64_t n, const int64_t *ab, uint8_t *label, hipStream_t st);
-void launch_compact(int64_t n, const int32_t *flag, const int64_t *pos, int64_t base, int64_t *cand, hipStream_t st);
+// flags as masks of 64 with their counts, and the flagged base + t in order (pos:
+// exclusive scan of the counts; no mask: all of them)
+void launch_flag_masks(int64_t n, const uint8_t *flag, uint64_t *mask, int32_t *cnt, hipStream_t st);
+void launch_list_flagged(int64_t n, const uint64_t *mask, const int64_t *pos, int64_t base, int64_t *item, hipStream_t st);
 
 // mlp.hip
 void mlp_pack(const float *P, uint16_t *W1t, uint16_t *W2b, hipStream_t st);
-// flag[t] for the cells t of a strip (cells cb0 + t / (nr1 - 1) rows, vertex
+// the flags (masks of 64 and their counts) of the cells t of a strip (cells cb0 + t / (nr1 - 1) rows, vertex
 // rows from vb0): the network's logit of the cell's features above thr, or
 // the cell folded; the features are formed on the fly
 void mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0, const double2 *verts, const uint16_t *W1t,
-                    const uint16_t *W2b, const float *P, float thr, int32_t *flag, hipStream_t st);
+                    const uint16_t *W2b, const float *P, float thr, uint64_t *mask, int32_t *cnt, hipStream_t st);
 void mlp_predict(const float *feats, int64_t n, const uint16_t *W1t, const uint16_t *W2b, const float *P,
                  float *logits, hipStream_t st);
 // rows of per-wavefront partial gradients (MLM_REFINER_PARAMS + 1 floats

@@ -180,13 +180,13 @@ __global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) vo
 // logit above thr, or folded.  Features are formed from the mapped corners
 // by the two lanes that feed them in (zero for a cell with a non-finite corner,
 // which the test then leaves alone), so nothing per cell goes through memory but
-// the flag.
+// its bit in the block's mask.
 __global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0,
                                                             const double2 *__restrict__ verts,
                                                             const uint16_t *__restrict__ W1t,
                                                             const uint16_t *__restrict__ W2t,
                                                             const float *__restrict__ P, float thr,
-                                                            int32_t *__restrict__ flag)
+                                                            uint64_t *__restrict__ mask, int32_t *__restrict__ cnt)
 {
     __shared__ float zs[PW][64 * PredictNet::ZP];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, hh = lane >> 5;
@@ -232,8 +232,11 @@ __global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
         wave_sync_lds();
         const float z = net.logit(zb, lane);
-        const int64_t t = blk * 64 + lane;
-        if (t < ncells) flag[t] = (z > thr || fold) ? 1 : 0;
+        const uint64_t flags = __ballot(blk * 64 + lane < ncells && (z > thr || fold));
+        if (lane == 0) {
+            mask[blk] = flags;
+            cnt[blk] = __popcll(flags);
+        }
         wave_sync_lds();
     }
 }
@@ -590,11 +593,11 @@ static unsigned predict_grid(int64_t n)
 }
 
 void mlp_flag_cells(int64_t nr1, int64_t cb0, int64_t ncells, int64_t vb0, const double2 *verts, const uint16_t *W1t,
-                    const uint16_t *W2b, const float *P, float thr, int32_t *flag, hipStream_t st)
+                    const uint16_t *W2b, const float *P, float thr, uint64_t *mask, int32_t *cnt, hipStream_t st)
 {
     if (ncells > 0)
         hipLaunchKernelGGL(k_mlp_flag_cells, dim3(predict_grid(ncells)), dim3(64 * PW), 0, st, nr1, cb0, ncells, vb0, verts,
-                           W1t, W2b + 64 * 64, P, thr, flag);
+                           W1t, W2b + 64 * 64, P, thr, mask, cnt);
 }
 
 void mlp_predict(const float *feats, int64_t n, const uint16_t *W1t, const uint16_t *W2b, const float *P,

@@ -497,7 +497,7 @@ __device__ inline void add_stats(unsigned long long *__restrict__ stats, int tes
 // 20,000 stars, with k_refine_rest's 19 where one kernel for all took 90.
 __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_test(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
                                                       const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                      const double2 *__restrict__ verts, int32_t *__restrict__ flag,
+                                                      const double2 *__restrict__ verts, uint8_t *__restrict__ flag,
                                                       unsigned long long *__restrict__ stats)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void 
     if (t < n) {
         const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
         v = refine_test<KEEP>(ra, c, large);
-        flag[t] = v;
+        flag[t] = (uint8_t)v;
     }
     add_stats(stats, t < n ? 1 : 0, v == REFINE ? 1 : 0, large);
 }
@@ -517,7 +517,7 @@ constexpr int REST = 1024;
 template <int kind>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_rest(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
                                                      const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                     const double2 *__restrict__ verts, int32_t *__restrict__ flag,
+                                                     const double2 *__restrict__ verts, uint8_t *__restrict__ flag,
                                                      unsigned long long *__restrict__ stats)
 {
     __shared__ unsigned short queue[REST];
@@ -537,18 +537,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
             int large = 0;
             refined = refine_test<kind>(ra, c, large) == REFINE ? 1 : 0;   // (not too large: that was decided)
-            flag[t] = refined;
+            flag[t] = (uint8_t)refined;
         }
         add_stats(stats, 0, refined, 0);
     }
 }
 
-// item[pos[t]] = t for the refined items (pos: exclusive scan of the flags)
-__global__ __launch_bounds__(256) void k_refined_list(int64_t n, const int32_t *__restrict__ flag,
-                                                      const int64_t *__restrict__ pos, int64_t *__restrict__ item)
+// 64 items' flags as one mask, and how many are set (a scan of these, and not of
+// the items' flags, numbers the flagged ones: with 4-byte flags and 8-byte places
+// of every item, numbering the cells and subcells of the learned refinement of a
+// 400 x 400 map moved 17 GB)
+__global__ __launch_bounds__(256) void k_flag_masks(int64_t n, const uint8_t *__restrict__ flag,
+                                                    uint64_t *__restrict__ mask, int32_t *__restrict__ cnt)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n && flag[t]) item[pos[t]] = t;
+    const uint64_t m = __ballot(t < n && flag[t] != 0);
+    if ((threadIdx.x & 63) == 0 && t < n) {
+        mask[t >> 6] = m;
+        cnt[t >> 6] = __popcll(m);
+    }
+}
+
+// item[..] = base + t for the flagged t in order (pos: exclusive scan of the
+// masks' counts); with mask == NULL for every t
+__global__ __launch_bounds__(256) void k_list_flagged(int64_t n, const uint64_t *__restrict__ mask,
+                                                      const int64_t *__restrict__ pos, int64_t base,
+                                                      int64_t *__restrict__ item)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    if (!mask) {
+        item[t] = base + t;
+        return;
+    }
+    const uint64_t m = mask[t >> 6], bit = 1ull << (t & 63);
+    if (m & bit) item[pos[t >> 6] + __popcll(m & (bit - 1ull))] = base + t;
 }
 
 // the k-th refined item, k < n: the map loses its deposits and gains its four
@@ -647,18 +670,6 @@ __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void 
     label[t] = r == REFINE ? 1 : 0;
 }
 
-// cand[pos[t]] = base + t for flagged t (pos: exclusive scan of the flags,
-// pos[t + 1] - pos[t] = flag[t]); with flag == NULL every t
-__global__ __launch_bounds__(256) void k_compact(int64_t n, const int32_t *__restrict__ flag,
-                                                 const int64_t *__restrict__ pos, int64_t base,
-                                                 int64_t *__restrict__ cand)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    if (!flag) cand[t] = base + t;
-    else if (flag[t]) cand[pos[t]] = base + t;
-}
-
 }  // namespace
 
 RefineArgs make_refine_args(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau,
@@ -691,7 +702,7 @@ size_t refine_subcell_bytes() { return sizeof(SubCell); }
 
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, int32_t *flag, unsigned long long *stats, hipStream_t st)
+                        const double2 *verts, uint8_t *flag, unsigned long long *stats, hipStream_t st)
 {
     if (n <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);
@@ -704,12 +715,11 @@ void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, con
 
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                           int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
-                          int64_t vb0, const double2 *verts, const int32_t *flag, const int64_t *pos, int64_t *item,
+                          int64_t vb0, const double2 *verts, const int64_t *item,
                           double *map, void *out, hipStream_t st)
 {
     if (nref <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);
-    hipLaunchKernelGGL(k_refined_list, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, flag, pos, item);
     hipLaunchKernelGGL(k_refine_expand, dim3((unsigned)((nref + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, nref, item,
                        cand, static_cast<const SubCell *>(list), nr1, vb0, verts, map, static_cast<SubCell *>(out));
 }
@@ -731,10 +741,15 @@ void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, c
     hipLaunchKernelGGL(k_sample_labels, dim3((unsigned)((n + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, n, ab, label);
 }
 
-void launch_compact(int64_t n, const int32_t *flag, const int64_t *pos, int64_t base, int64_t *cand, hipStream_t st)
+void launch_flag_masks(int64_t n, const uint8_t *flag, uint64_t *mask, int32_t *cnt, hipStream_t st)
+{
+    if (n > 0) hipLaunchKernelGGL(k_flag_masks, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, flag, mask, cnt);
+}
+
+void launch_list_flagged(int64_t n, const uint64_t *mask, const int64_t *pos, int64_t base, int64_t *item, hipStream_t st)
 {
     if (n > 0)
-        hipLaunchKernelGGL(k_compact, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, flag, pos, base, cand);
+        hipLaunchKernelGGL(k_list_flagged, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, mask, pos, base, item);
 }
 
 }  // namespace mlm
