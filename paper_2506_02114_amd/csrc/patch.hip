@@ -29,6 +29,7 @@ namespace {
 
 // rays per leaf from which patches pay: few rays, many rays
 constexpr double PATCH_RAYS_PER_LEAF[2] = {32768.0, 10000.0}, PATCH_MANY_RAYS = 3.2e7;
+constexpr double LARGE_PATCH_RAYS_PER_LEAF = 262144.0;   // (many rays alone)
 constexpr double SMALL_PATCH_RAYS_PER_LEAF[2] = {8192.0, 3000.0}, SMALL_PATCH_MANY_RAYS = 1.6e7;
 constexpr int PC_MAX = 24;    // most coefficients of a patch
 constexpr int PC_DIRECT = 8;  // most stars summed directly
@@ -598,10 +599,17 @@ PatchArgs patch_args(const Region &R, const MapGeom &g, int P)
 //   8000, 2.6e6                    0.058 / 0.048 / 0.108   (0.083 / 0.065 / 0.209)
 //   24000, 7.9e6                   0.142 / 0.085 / 0.092   (0.197 / 0.118 / 0.111)
 //   32000, 1.0e7                   0.180 / 0.111 / 0.084   (0.238 / 0.149 / 0.120)
+// and 32 x 32 / 64 x 64, whose coefficients cost a quarter and whose stars lie
+// nearer in their units:
+//   101500, 2.4e8                  1.62 / 1.76   (1.38 / 1.60)
+//   330000, 4.2e7                  0.220 / 0.193   (0.226 / 0.220)
+//   714000, 1.5e8                  0.803 / 0.701   (0.754 / 0.742)
+//   5074000, 1.2e10                68.4 / 54.8   (48.0 / 35.6)
 int patch_side(const Region &R, const Tree &T, int64_t rows)
 {
     if (T.mixed || T.p < 1) return 0;
     const double rays = (double)R.nr1 * (double)rows, per_leaf = rays / (double)std::max<int64_t>(T.nactive_leaves, 1);
+    if (per_leaf >= LARGE_PATCH_RAYS_PER_LEAF && rays >= PATCH_MANY_RAYS) return 64;
     if (per_leaf >= PATCH_RAYS_PER_LEAF[rays >= PATCH_MANY_RAYS ? 1 : 0]) return 32;
     return per_leaf >= SMALL_PATCH_RAYS_PER_LEAF[rays >= SMALL_PATCH_MANY_RAYS ? 1 : 0] ? 16 : 0;
 }
@@ -620,7 +628,7 @@ static void patch_coefs(mlm_lens *lens, const Tree &T, const LensConst &lc, cons
     }
     PatchInfo *info = static_cast<PatchInfo *>(ws.patch_info.reserve((size_t)npatch * sizeof(PatchInfo)));
     double2 *coef = static_cast<double2 *>(ws.patch_coef.reserve((size_t)npatch * PC_MAX * sizeof(double2)));
-    hipLaunchKernelGGL(side == 32 ? k_patch_coef<32> : k_patch_coef<16>, dim3((unsigned)((npatch + 3) / 4)), dim3(64), 0, st, sa, lc, pa, npatch,
+    hipLaunchKernelGGL(side == 64 ? k_patch_coef<64> : side == 32 ? k_patch_coef<32> : k_patch_coef<16>, dim3((unsigned)((npatch + 3) / 4)), dim3(64), 0, st, sa, lc, pa, npatch,
                        ws.tile_leaf.as<int32_t>(), ws.tile_off.as<int32_t>(), T.leaves, T.near, T.deriv,
                        ws.binom.as<double>(), info, coef);
 }
@@ -632,7 +640,7 @@ void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const 
     const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1, vb0, T.p, 0, 0.0};
     const PatchArgs pa = patch_args(R, g, side);
     patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
-    hipLaunchKernelGGL(side == 32 ? k_shoot_patch<32> : k_shoot_patch<16>, dim3((unsigned)npatch), dim3(64), 0, st, sa, lc, g, pa,
+    hipLaunchKernelGGL(side == 64 ? k_shoot_patch<64> : side == 32 ? k_shoot_patch<32> : k_shoot_patch<16>, dim3((unsigned)npatch), dim3(64), 0, st, sa, lc, g, pa,
                        lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves, T.near,
                        T.deriv, verts);
 }
@@ -646,8 +654,9 @@ void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const Le
     patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
     // the window: a patch's unlensed image is side d / pixel wide
     const bool wide = side * std::max(R.d1 / R.pix1, R.d2 / R.pix2) > 4.0;
-    auto *k = side == 32 ? (wide ? k_irs_patch<32, 32> : k_irs_patch<32, 16>)
-                         : (wide ? k_irs_patch<16, 32> : k_irs_patch<16, 16>);
+    auto *k = side == 64   ? (wide ? k_irs_patch<64, 32> : k_irs_patch<64, 16>)
+              : side == 32 ? (wide ? k_irs_patch<32, 32> : k_irs_patch<32, 16>)
+                           : (wide ? k_irs_patch<16, 32> : k_irs_patch<16, 16>);
     hipLaunchKernelGGL(k, dim3((unsigned)npatch), dim3(64), 0, st, sa,
                        lc, g, pa, lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves,
                        T.near, T.deriv, counts);

@@ -45,3 +45,30 @@ def test_equals_ray_by_ray(name):
     lens.map(out=out, **req)
     lens.map(out=exact, w_out=w, **req)
     assert float((out - exact).norm() / exact.norm()) < 1e-9
+
+
+LARGE = {
+    "disc": (dict(), 60, dict(hw1=1.0, hw2=1.0, n1=100, n2=90, nray1=6001, nray2=5503, dx1=4.0, dx2=4.0)),
+    "rectangle": (dict(sheet="rect", rect_aspect=1.7), 80, dict(hw1=1.0, hw2=1.0, n1=64, n2=64, nray1=5733, nray2=6000,
+                                                                dx1=3.0, dx2=3.0)),
+    "no_sheet": (dict(sheet="none"), 1, dict(hw1=1.0, hw2=1.5, n1=50, n2=75, nray1=5800, nray2=5815, dx1=3.0, dx2=3.0)),
+}
+
+
+@pytest.mark.parametrize("name", list(LARGE))
+def test_large_patches_equal_ray_by_ray(name):
+    """Patches of 64 x 64 rays, from some 260,000 rays a leaf on."""
+    import torch
+    CASES["large_" + name] = LARGE[name]
+    lens, req = _lens("large_" + name)
+    got, st = lens.map(mapping="irs", **req)
+    ref, sr = lens.map(mapping="irs", noalloc=True, **req)
+    assert sr["n_tiles"] / 66 < st["n_tiles"] < sr["n_tiles"] / 50      # 4096 rays against 64
+    assert np.array_equal(got, ref) and ref.sum() > 0
+    R = lens.region(**req)
+    out = torch.empty((req["n2"], req["n1"]), dtype=torch.float64, device="cuda")
+    exact = torch.empty_like(out)
+    w = torch.empty((R["nr2"], R["nr1"], 2), dtype=torch.float64, device="cuda")
+    lens.map(out=out, **req)
+    lens.map(out=exact, w_out=w, **req)
+    assert float((out - exact).norm() / exact.norm()) < 1e-9
