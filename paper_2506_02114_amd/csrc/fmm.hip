@@ -258,10 +258,11 @@ template <> struct V4T<double> {
 
 // The sources of a node go through the matrix cores in groups of GS: a
 // group's scaled coefficients fill a 32 x 2 GS block of LDS (row stride BRS,
-// one more than its columns so the rows of a column fall in other banks), so
-// a node's wavefront needs 9 KB of LDS, not the 17 KB that all 27 sources at
-// once would take, and more wavefronts fit a CU.
-constexpr int GS = 16;
+// one more than its columns so the rows of a column fall in other banks).  The
+// pass is a chain of latencies, so it is the wavefronts a CU holds that count:
+// five per SIMD at 5 KB and 96 registers each (groups of 16, 9 KB and 116
+// registers: 330 us for 78k nodes, here 300; all 27 at once, 17 KB: 370).
+constexpr int GS = 8;
 constexpr int BRS = 2 * GS + 1;
 template <class R> struct DownLds {
     R B[32 * BRS];         // a group's scaled source coefficients: row k - 1, columns (2 s, 2 s + 1) =
@@ -321,7 +322,7 @@ __device__ inline typename Cx<R>::c2 add_l2l(typename Cx<R>::c2 acc, int64_t q, 
 // coefficient's sum runs M2L, L2L, P2L.  Without p2l (inside a scratch arena) a
 // launch takes one level, and adds the parents' part itself.
 template <class R>
-__global__ __launch_bounds__(64) void k_m2l(LevelRange lo, LevelRange listed, int nlevels, int k0, int count, int p, double L0,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_m2l(LevelRange lo, LevelRange listed, int nlevels, int k0, int count, int p, double L0,
                                             const int32_t *__restrict__ act, const uint64_t *__restrict__ code,
                                             const IEntry *__restrict__ ilist, const double *__restrict__ sx,
                                             const double *__restrict__ sy, const double *__restrict__ sm,
