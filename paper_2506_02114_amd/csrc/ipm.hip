@@ -178,9 +178,8 @@ __device__ inline TriClass classify(P2 A, P2 B, P2 C, const MapGeom &g)
     TriClass c{0, 0, false, 0, -1, -1};
     if (!(isfinite(A.u) && isfinite(A.v) && isfinite(B.u) && isfinite(B.v) && isfinite(C.u) && isfinite(C.v)))
         return c;
-    const double umin = fmin(A.u, fmin(B.u, C.u)), umax = fmax(A.u, fmax(B.u, C.u));
-    const double vmin = fmin(A.v, fmin(B.v, C.v)), vmax = fmax(A.v, fmax(B.v, C.v));
-    const double fu0 = floor(umin), fu1 = floor(umax), fv0 = floor(vmin), fv1 = floor(vmax);
+    const double fu0 = floor(lesser(A.u, lesser(B.u, C.u))), fu1 = floor(greater(A.u, greater(B.u, C.u)));
+    const double fv0 = floor(lesser(A.v, lesser(B.v, C.v))), fv1 = floor(greater(A.v, greater(B.v, C.v)));
     if (fu1 < 0.0 || fv1 < 0.0 || fu0 > (double)(g.n1 - 1) || fv0 > (double)(g.n2 - 1)) return c;
     if (fu0 == fu1 && fv0 == fv1) {
         c.kind = 1;
@@ -353,10 +352,10 @@ struct ColSetup {
 __device__ inline ColSetup col_setup(P2 A, P2 B, P2 C, int i0, const MapGeom &g, bool mixed)
 {
     ColSetup c;
-    const double umin = fmin(A.u, fmin(B.u, C.u)), vmin = fmin(A.v, fmin(B.v, C.v));
-    const double umax = fmax(A.u, fmax(B.u, C.u)), vmax = fmax(A.v, fmax(B.v, C.v));
-    c.fu0 = floor(umin);
-    c.fv0 = floor(vmin);
+    const double u0 = lesser(A.u, lesser(B.u, C.u)), v0 = lesser(A.v, lesser(B.v, C.v));
+    const double u1 = greater(A.u, greater(B.u, C.u)), v1 = greater(A.v, greater(B.v, C.v));
+    c.fu0 = floor(u0);
+    c.fv0 = floor(v0);
     c.T[0] = P2{A.u - c.fu0, A.v - c.fv0};
     c.T[1] = P2{B.u - c.fu0, B.v - c.fv0};
     c.T[2] = P2{C.u - c.fu0, C.v - c.fv0};
@@ -365,8 +364,8 @@ __device__ inline ColSetup col_setup(P2 A, P2 B, P2 C, int i0, const MapGeom &g,
     c.scale = fdiv(g.tri_weight, S2);
     c.i0 = (int)i0;
     c.j0 = (int)fmax(c.fv0, 0.0);
-    c.j1 = (int)fmin(floor(vmax), (double)(g.n2 - 1));
-    const double eu = umax - umin, ev = vmax - vmin;
+    c.j1 = (int)fmin(floor(v1), (double)(g.n2 - 1));
+    const double eu = u1 - u0, ev = v1 - v0;
     c.fp32 = mixed && eu * eu + ev * ev <= MIXED_MAX_COND * fabs(S2);
     return c;
 }
@@ -508,7 +507,7 @@ __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11,
             const P2 E{__shfl(v10.u, L, 64), __shfl(v10.v, L, 64)}, F{__shfl(v01.u, L, 64), __shfl(v01.v, L, 64)};
             if (base + lane < ns) {
                 const P2 B{second ? D.u : E.u, second ? D.v : E.v}, C{second ? F.u : D.u, second ? F.v : D.v};
-                const double fu0 = floor(fmin(A.u, fmin(B.u, C.u))), fv0 = floor(fmin(A.v, fmin(B.v, C.v)));
+                const double fu0 = floor(lesser(A.u, lesser(B.u, C.u))), fv0 = floor(lesser(A.v, lesser(B.v, C.v)));
                 small_triangle(A, B, C, fu0, fv0, g, map, w);
                 ++cw.small;
             }
@@ -648,20 +647,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // of its area (coordinates relative to the box, exact: a double minus a nearby
 // integer).  The cells of a column move slowly over the pixels, so a thread
 // sums its deposits in registers while they fall into the same pixels.
+// (The kernel is bound by its FP64 instructions.  On the 2.1e10-ray map the
+// share formed without a test for a crossing line, areas from the vertices'
+// differences and minima of one instruction took the map from 409 to 386 ms.)
 constexpr int FC = 32;         // tile columns (cells)
 constexpr int FR = 4;          // cells of a thread, one below the other
 constexpr int FROWS = 256 / FC * FR;   // tile rows
 
-// share of a triangle's area where x < 1 (x: its vertices' coordinates)
-__device__ inline double left_share(double a, double b, double c, bool &crossed)
+// share of a triangle's area where x < 1 (x: its vertices' coordinates).  The
+// lone vertex's distance beyond the line is 0 where the line misses the triangle,
+// and the share then 0 or 1 (the added 1e-300, far below any product of extents a
+// line can cross, only keeps 0 / 0 away).
+__device__ inline double left_share(double a, double b, double c)
 {
-    const double lo = fmin(a, b), hi = fmax(a, b);
-    const double mn = fmin(lo, c), mx = fmax(hi, c), md = fmax(lo, fmin(hi, c));
+    const double lo = lesser(a, b), hi = greater(a, b);
+    const double mn = lesser(lo, c), mx = greater(hi, c), md = greater(lo, lesser(hi, c));
     const bool low = md < 1.0;               // the lone vertex lies right of the line
-    const double e = low ? mx - 1.0 : 1.0 - mn, h = low ? mx - md : md - mn;
-    const double q = fdiv(e * e, (mx - mn) * h);
-    crossed = mn < 1.0 && mx >= 1.0;
-    return !crossed ? (mx < 1.0 ? 1.0 : 0.0) : (low ? 1.0 - q : q);
+    const double e = low ? fmax(mx - 1.0, 0.0) : fmax(1.0 - mn, 0.0), h = fabs((low ? mx : mn) - md);
+    const double q = fdiv(e * e, fma(mx - mn, h, 1e-300));
+    return low ? 1.0 - q : q;
 }
 
 template <bool MIXED, int N>
@@ -712,13 +716,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         for (int s = 0; s < FR; ++s) {
             if (s >= rows) break;
             const P2 v00 = va[s], v10 = vb[s], v01 = va[s + 1], v11 = vb[s + 1];
-            const double fu = floor(fmin(fmin(v00.u, v10.u), fmin(v11.u, v01.u)));
-            const double fv = floor(fmin(fmin(v00.v, v10.v), fmin(v11.v, v01.v)));
-            const double du = fmax(fmax(v00.u, v10.u), fmax(v11.u, v01.u)) - fu;
-            const double dv = fmax(fmax(v00.v, v10.v), fmax(v11.v, v01.v)) - fv;
+            const double fu = floor(lesser(lesser(v00.u, v10.u), lesser(v11.u, v01.u)));
+            const double fv = floor(lesser(lesser(v00.v, v10.v), lesser(v11.v, v01.v)));
+            const double du = greater(greater(v00.u, v10.u), greater(v11.u, v01.u)) - fu;
+            const double dv = greater(greater(v00.v, v10.v), greater(v11.v, v01.v)) - fv;
             const bool along_u = du < 2.0 && dv < 1.0;
             bool queued = !(along_u || (du < 1.0 && dv < 2.0));   // (a NaN is caught below: no area)
-            const double s1 = twice_area(v00, v10, v11, fu, fv), s2 = twice_area(v00, v11, v01, fu, fv);
+            // (the areas of twice_area: within two pixels coordinates relative to a
+            // pixel are exact, and so are differences without it)
+            double s1, s2;
+            {
+#pragma clang fp contract(off)
+                const double eu = v11.u - v00.u, ev = v11.v - v00.v;
+                s1 = (v10.u - v00.u) * ev - eu * (v10.v - v00.v);
+                s2 = eu * (v01.v - v00.v) - (v01.u - v00.u) * ev;
+            }
             queued = queued || !(fabs(s1) > 0.0 && fabs(s2) > 0.0);
             if (queued) {
                 queue[atomicAdd(&nq, 1)] = (unsigned short)((tr + s) * FC + tc);
@@ -726,9 +738,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 const double o = along_u ? fu : fv;
                 const double x0 = (along_u ? v00.u : v00.v) - o, x1 = (along_u ? v10.u : v10.v) - o;
                 const double x2 = (along_u ? v11.u : v11.v) - o, x3 = (along_u ? v01.u : v01.v) - o;
-                bool c1, c2;
-                const double left = left_share(x0, x1, x2, c1) + left_share(x0, x2, x3, c2);
-                cw.small += (unsigned)c1 + (unsigned)c2;
+                const double left = left_share(x0, x1, x2) + left_share(x0, x2, x3);
+                if (work) {   // (statistics: the triangles that a line crosses)
+                    const double mx = fmax(x0, x2), mn = fmin(x0, x2);
+                    cw.small += (unsigned)(fmin(mn, x1) < 1.0 && fmax(mx, x1) >= 1.0) +
+                                (unsigned)(fmin(mn, x3) < 1.0 && fmax(mx, x3) >= 1.0);
+                }
                 const int i = (int)fu, j = (int)fv, i2 = i + (along_u ? 1 : 0), j2 = j + (along_u ? 0 : 1);
                 if (i != pi || j != pj) {
                     put(pi, pj, ps);
@@ -737,7 +752,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                     ps = 0.0;
                 }
                 ps += left;
-                if (c1 || c2 || left < 2.0) {
+                if (left < 2.0) {
                     if (i2 != qi || j2 != qj) {
                         put(qi, qj, qs);
                         qi = i2;
@@ -1274,7 +1289,7 @@ __global__ __launch_bounds__(256) void k_band_scatter(int64_t nbig, const uint32
 // P the clip's product is then an exact zero).
 __device__ inline bool row_clip(P2 P, P2 Q, double rl, double su, double &ua, double &ub, double &dv)
 {
-    const double ev = fmin(fmax(P.v, rl), rl + 1.0), xv = fmin(fmax(Q.v, rl), rl + 1.0);
+    const double rh = rl + 1.0, ev = lesser(greater(P.v, rl), rh), xv = lesser(greater(Q.v, rl), rh);
     ua = fma(ev - P.v, su, P.u);
     ub = xv == Q.v ? Q.u : P.u + (xv - P.v) * su;
     dv = xv - ev;
@@ -1319,8 +1334,9 @@ __device__ inline void band_rows(int64_t band, int64_t r0, int64_t r1, const int
             // column beyond the map on either side (which changes nothing
             // below) so they fit 32 bits
             const double lo = (double)cmin - 1.0, hi = (double)cmax + 1.0;
-            const int x0 = (int)fmin(fmax(floor(fmin(ua, ub)), lo), hi);
-            const int x1 = (int)fmin(fmax(floor(fmax(ua, ub)), lo), hi);
+            const double umin = lesser(ua, ub);
+            const int x0 = (int)lesser(greater(floor(umin), lo), hi);
+            const int x1 = (int)lesser(greater(floor(greater(ua, ub)), lo), hi);
             const double f = -2.0 * bp.scale * dv;   // deposit for a fully covered difference
             const int is = max(x0, cmin);
             if (is > x1) {   // the segment lies left of the map
@@ -1333,7 +1349,7 @@ __device__ inline void band_rows(int64_t band, int64_t r0, int64_t r1, const int
             // f (x - umin)^2 / (2 w) = kc (x - umin)^2 up to x1 (f / w is
             // fixed along the edge), the linear form at x1 + 1 (past the
             // edge), so the walk needs neither case tests nor a division
-            const double umin = fmin(ua, ub), kc = bp.kc[m];
+            const double kc = bp.kc[m];
             auto cross = [&](int x) {
                 const double t = (double)x - umin;
                 return kc * t * t;

@@ -338,8 +338,8 @@ __device__ inline void split_columns(const RefineArgs &ra, const SubCell &c, con
 // x0) (x2 - x0)) of the area
 __device__ inline double line_share(double a, double b, double c)
 {
-    const double lo = fmin(a, b), hi = fmax(a, b);
-    const double mn = fmin(lo, c), mx = fmax(hi, c), md = fmax(lo, fmin(hi, c));
+    const double lo = lesser(a, b), hi = greater(a, b);
+    const double mn = lesser(lo, c), mx = greater(hi, c), md = greater(lo, lesser(hi, c));
     const bool low = md < 1.0;
     const double e = low ? mx - 1.0 : 1.0 - mn, h = low ? mx - md : md - mn;
     const double q = fdiv(e * e, (mx - mn) * h);
