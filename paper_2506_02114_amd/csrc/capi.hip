@@ -1122,8 +1122,17 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 bl.list = static_cast<int64_t *>(ws.biglist.reserve((size_t)(BIG_SHARDS * bl.cap) * sizeof(int64_t)));
             }
             const int e_cells0 = tm.mark();
-            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, q.precision == MLM_PREC_MIXED, pass,
-                       q.timing >= 2 ? cnt + 8 : nullptr, st);
+            unsigned long long *const work = q.timing >= 2 ? cnt + 8 : nullptr;
+            ThinList thin;
+            if (side && pass < 2) {
+                thin.cell = static_cast<int64_t *>(ws.thin.reserve((THIN_CELLS + 1) * sizeof(int64_t)));
+                thin.count = reinterpret_cast<unsigned *>(thin.cell + THIN_CELLS);
+            }
+            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, thin, q.precision == MLM_PREC_MIXED, pass, work, st);
+            if (thin.count) {
+                launch_shoot_thin(T, R, lc, g, vb0, thin, verts, st);
+                launch_ipm_thin(verts, R.nr1, r0, vb0, g, map, cnt, bl, thin, work, st);
+            }
             const int e_cells = tm.mark();
             BigStarts at{};
             const bool listed = bl.cap > 0 && read_big_counts(lens, bl, at, st);

@@ -269,7 +269,7 @@ struct Workspace {
     DevBuf leaves, near, deriv, near_offs;
     DevBuf bigcount, biglist;
     DevBuf search;
-    DevBuf binom, patch_info, patch_coef;
+    DevBuf binom, patch_info, patch_coef, thin;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
         bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
@@ -377,6 +377,10 @@ void launch_shoot(mlm_lens *lens, const Tree &T, const Region &R, const LensCons
 int patch_side(const Region &R, const Tree &T, int64_t rows);
 void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
                           int side, int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st);
+// the vertices of the cells in `thin` (of a strip from vertex row vb0) ray by ray
+struct ThinList;
+void launch_shoot_thin(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t vb0,
+                       const ThinList &thin, double2 *verts, hipStream_t st);
 void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
                         int side, int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st);
 void launch_shoot_direct(mlm_lens *lens, const Region &R, const LensConst &lc, const MapGeom &g,
@@ -410,9 +414,30 @@ struct BigList {
 struct BigStarts {
     int64_t lo[BIG_SHARDS + 1];   // the lists laid end to end: list i's first slot
 };
+// Cells with a triangle thinner than THIN pixels where the vertices were shot by
+// patches: the cell pass lists them (by their numbers in the strip) instead of
+// apportioning them, and they go ray by ray (launch_shoot_thin, launch_ipm_thin).
+// A triangle's deposits are quotients by its area, which the rounding of its
+// vertices' positions (some 1e-13 pixels, in other digits by patches than ray by
+// ray) changes by 1e-13 / its thickness.  On maps of ~10 to 40 cells a pixel that
+// reached 1e-9 of a pixel in most maps and 1e-7 in a few; with THIN it is below
+// 1e-7 of any deposit, at most 6e-9 of a pixel over 64 star fields.  It costs
+// ~50 us a strip (8.63 to 8.70 ms on the 1e5-star map).  (k_ipm_fine forms most shares
+// without the area, and hundreds of cells a pixel average the others: 4e-11 on the
+// 2.1e10-ray map.)  Cells beyond THIN_CELLS are apportioned as they are.
+constexpr double THIN = 1.0 / 65536.0;
+constexpr unsigned THIN_CELLS = 65536, THIN_BLOCKS = 64;
+struct ThinList {
+    unsigned *count = nullptr;   // null: no cell is listed
+    int64_t *cell = nullptr;
+};
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int pass,
+                double *map, unsigned long long *counters, const BigList &bl, const ThinList &thin, bool mixed, int pass,
                 unsigned long long *work, hipStream_t st);
+// the listed cells, by their vertices as they are now
+void launch_ipm_thin(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, double *map,
+                     unsigned long long *counters, const BigList &bl, const ThinList &thin, unsigned long long *work,
+                     hipStream_t st);
 void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,
                       const BigStarts &at, int bh, BigPrep *prep, uint32_t *bands, hipStream_t st);
 // the counts of the lists (waits for them), laid end to end; false if one is incomplete

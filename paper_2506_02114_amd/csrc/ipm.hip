@@ -575,6 +575,23 @@ template <int N> __device__ inline void flush_window(const Window<N> &w, double 
     }
 }
 
+// whether the cell is thin, and then listed
+__device__ inline bool list_thin(const ThinList &thin, P2 v00, P2 v10, P2 v11, P2 v01, int64_t cell)
+{
+    const double du = v11.u - v00.u, dv = v11.v - v00.v;
+    const double eu = v10.u - v00.u, ev = v10.v - v00.v, fu = v01.u - v00.u, fv = v01.v - v00.v;
+    const double s1 = eu * dv - du * ev, s2 = du * fv - fu * dv;
+    const double q = THIN * THIN * (du * du + dv * dv + eu * eu + ev * ev + fu * fu + fv * fv);
+    if (!(lesser(s1 * s1, s2 * s2) < q)) return false;
+    // (a full list is not counted up further: where every cell is thin the
+    // atomics on one address would take seconds)
+    if (__hip_atomic_load(thin.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= THIN_CELLS) return false;
+    const unsigned k = atomicAdd(thin.count, 1u);
+    if (k >= THIN_CELLS) return false;
+    thin.cell[k] = cell;
+    return true;
+}
+
 // IPM of the ordinary triangles.  A workgroup takes a tile of 16 x 16 cells
 // (each wavefront 16 x 4), one cell a thread.  A tile of cells maps to a
 // compact patch of the source plane, so deposits are summed in an LDS window
@@ -587,7 +604,7 @@ constexpr int CT = 16;   // cells per tile side
 template <bool MIXED, int N, bool LIST>
 __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t nrows,
                                 int64_t vb0, const MapGeom &g, double *__restrict__ map,
-                                unsigned long long *__restrict__ counters, const BigList &bl,
+                                unsigned long long *__restrict__ counters, const BigList &bl, const ThinList &thin,
                                 int32_t *__restrict__ tile_big, int64_t tile,
                                 double *acc, unsigned long long *__restrict__ work)
 {
@@ -599,7 +616,7 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
     const int64_t brow = tb * CT + wave * 4 + (lane >> 4);   // cell row within the strip
     // (the cell's corners are asked for before the barrier, beside the window's
     // anchor: one wait for memory instead of two)
-    const bool have = a < ncol && brow < nrows;
+    bool have = a < ncol && brow < nrows;
     P2 v00, v10, v11, v01;
     load_cell_at(verts, nr1, cb0 + min(brow, nrows - 1) - vb0, min(a, ncol - 1), v00, v10, v11, v01);
     const int64_t ca = min(ta * CT + CT / 2, ncol), cb = min(tb * CT + CT / 2, nrows);
@@ -608,6 +625,7 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
     __syncthreads();
     __shared__ uint8_t sq[256 * 2];
     CellWork cw;
+    if (LIST && thin.count) have = have && !list_thin(thin, v00, v10, v11, v01, brow * ncol + a);
     const int big = apportion_cell<MIXED, N, LIST>(have, v00, v10, v11, v01, g, map, w, counters, bl, brow * ncol + a, sq + wave * 128, cw);
     if constexpr (!LIST) {   // the tile's count of large triangles (tile_big is zeroed beforehand)
         int s = (big & 1) + (big >> 1);
@@ -626,11 +644,32 @@ __device__ __forceinline__ void ipm_tile(const double2 *__restrict__ verts, int6
 template <bool MIXED, int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
                                              int64_t nrows, int64_t vb0, MapGeom g, double *__restrict__ map,
-                                             unsigned long long *__restrict__ counters, BigList bl,
+                                             unsigned long long *__restrict__ counters, BigList bl, ThinList thin,
                                              unsigned long long *__restrict__ work)
 {
     __shared__ double acc[N * N];
-    ipm_tile<MIXED, N, true>(verts, nr1, cb0, nrows, vb0, g, map, counters, bl, nullptr, blockIdx.x, acc, work);
+    ipm_tile<MIXED, N, true>(verts, nr1, cb0, nrows, vb0, g, map, counters, bl, thin, nullptr, blockIdx.x, acc, work);
+}
+
+// the cells of `thin`, one a thread, straight into the map
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_thin(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t vb0, MapGeom g,
+                                                 double *__restrict__ map, unsigned long long *__restrict__ counters,
+                                                 BigList bl, ThinList thin, unsigned long long *__restrict__ work)
+{
+    __shared__ double acc[1];
+    __shared__ uint8_t sq[128];
+    Window<1> w;   // (a window that no pixel lies in)
+    w.acc = acc;
+    w.i0 = w.j0 = -(1 << 30);
+    const int64_t n = min(*thin.count, THIN_CELLS);
+    CellWork cw;
+    for (int64_t base = (int64_t)blockIdx.x * 64; base < n; base += (int64_t)gridDim.x * 64) {
+        const int64_t cell = thin.cell[min(base + threadIdx.x, n - 1)], row = cell / (nr1 - 1);
+        P2 v00, v10, v11, v01;
+        load_cell_at(verts, nr1, cb0 + row - vb0, cell % (nr1 - 1), v00, v10, v11, v01);
+        apportion_cell<false, 1, true>(base + threadIdx.x < n, v00, v10, v11, v01, g, map, w, counters, bl, cell, sq, cw);
+    }
+    if (work) add_work(work, blockIdx.x, cw);
 }
 
 // The cell pass where cells are far smaller than pixels (a highly magnified
@@ -794,10 +833,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const int32_t m = batch_find(maps, nmaps, t, &BatchMap::ctile_lo);
         const BatchMap &d = maps[m];
         if (d.mixed)
-            ipm_tile<true, WIN, false>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, BigList{}, tile_big + d.ctile_lo,
+            ipm_tile<true, WIN, false>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, BigList{}, ThinList{}, tile_big + d.ctile_lo,
                                        t - d.ctile_lo, acc, nullptr);
         else
-            ipm_tile<false, WIN, false>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, BigList{}, tile_big + d.ctile_lo,
+            ipm_tile<false, WIN, false>(d.verts, d.nr1, 0, d.nrows, 0, d.g, d.map, d.counters, BigList{}, ThinList{}, tile_big + d.ctile_lo,
                                         t - d.ctile_lo, acc, nullptr);
     }
 }
@@ -1609,23 +1648,38 @@ __global__ __launch_bounds__(256) void k_count_rows(int64_t nbig, const BigPrep 
 
 }  // namespace
 
-static __global__ void k_zero_shards(unsigned long long *count) { count[(size_t)threadIdx.x * BIG_STRIDE] = 0ull; }
+static __global__ void k_zero_shards(unsigned long long *count, unsigned *nthin)
+{
+    count[(size_t)threadIdx.x * BIG_STRIDE] = 0ull;
+    if (nthin && threadIdx.x == 0) *nthin = 0;
+}
 
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                double *map, unsigned long long *counters, const BigList &bl, bool mixed, int pass,
+                double *map, unsigned long long *counters, const BigList &bl, const ThinList &thin, bool mixed, int pass,
                 unsigned long long *work, hipStream_t st)
 {
     const bool fine = pass >= 2;
     const int64_t nrows = cb1 - cb0, ncol = nr1 - 1;
     const int64_t tiles = fine ? ((ncol + FC - 1) / FC) * ((nrows + FROWS - 1) / FROWS) : ipm_tile_count(nr1, nrows);
     if (ncol <= 0 || nrows <= 0) return;
-    hipLaunchKernelGGL(k_zero_shards, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count);
-    auto *k = pass == 3   ? (mixed ? k_ipm_fine<true, WIN_FINE> : k_ipm_fine<false, WIN_FINE>)
-              : pass == 2 ? (mixed ? k_ipm_fine<true, WIN> : k_ipm_fine<false, WIN>)
-              : pass == 1 ? (mixed ? k_ipm<true, WIN_MID> : k_ipm<false, WIN_MID>)
-                          : (mixed ? k_ipm<true, WIN> : k_ipm<false, WIN>);
-    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, nrows, vb0, g, map, counters,
-                       bl, work);
+    hipLaunchKernelGGL(k_zero_shards, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count, thin.count);
+    if (fine) {
+        auto *k = pass == 3 ? (mixed ? k_ipm_fine<true, WIN_FINE> : k_ipm_fine<false, WIN_FINE>)
+                            : (mixed ? k_ipm_fine<true, WIN> : k_ipm_fine<false, WIN>);
+        hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, nrows, vb0, g, map, counters, bl, work);
+        return;
+    }
+    auto *k = pass == 1 ? (mixed ? k_ipm<true, WIN_MID> : k_ipm<false, WIN_MID>)
+                        : (mixed ? k_ipm<true, WIN> : k_ipm<false, WIN>);
+    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, nrows, vb0, g, map, counters, bl, thin,
+                       work);
+}
+
+void launch_ipm_thin(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, double *map,
+                     unsigned long long *counters, const BigList &bl, const ThinList &thin, unsigned long long *work,
+                     hipStream_t st)
+{
+    hipLaunchKernelGGL(k_ipm_thin, dim3(THIN_BLOCKS), dim3(64), 0, st, verts, nr1, cb0, vb0, g, map, counters, bl, thin, work);
 }
 
 void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,

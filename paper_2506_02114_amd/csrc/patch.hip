@@ -47,6 +47,13 @@ struct PatchInfo : PatchHead {
 };
 enum PatchLin { LIN_NONE = 0, LIN_DISC = 1, LIN_RECT = 2 };
 
+// the tree as find_leaf goes down it
+struct LeafFinder {
+    int nlevels, L0_exp;
+    double L0;
+    const int32_t *child0, *leaf, *node_leaf;
+};
+
 struct PatchArgs {
     double r, ir;          // a patch's half diagonal (the largest |t|) and its inverse
     double hx, hy;         // half sides
@@ -424,6 +431,29 @@ __device__ inline double2 exact_ray(const ShootArgs &sa, const LensConst &lc, co
     return uv;
 }
 
+// The vertices of the cells that the cell pass found too thin for patches
+// (ThinList), ray by ray; cells that share a vertex write the same value to it.
+// (A map lists tens of cells.)
+__global__ __launch_bounds__(64) void k_shoot_thin(ShootArgs sa, LensConst lc, MapGeom g, LeafFinder find,
+                                                   const LeafInfo *__restrict__ leaves,
+                                                   const double4 *__restrict__ near,
+                                                   const double2 *__restrict__ deriv, ThinList thin,
+                                                   double2 *__restrict__ verts)
+{
+    const int64_t n = 4 * (int64_t)min(*thin.count, THIN_CELLS);
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t c = thin.cell[t >> 2];
+        const int64_t a = c % (sa.nr1 - 1) + (t & 1), row = c / (sa.nr1 - 1) + ((t >> 1) & 1);
+        const double x = grid_pos(sa.x0, sa.d1, a), y = grid_pos(sa.y0, sa.d2, sa.vb0 + row);
+        const int64_t lf = find_leaf(x, y, find.nlevels, find.L0, find.L0_exp, find.child0, find.leaf, find.node_leaf);
+        if (lf < 0) continue;
+        const LeafInfo li = leaves[lf];
+        double ax, ay, w1, w2;
+        leaf_alpha<double>(x - li.cx, y - li.cy, li, near + li.near_off, deriv + lf * sa.p, sa.p, ax, ay);
+        finish_vertex(lc, g, x, y, ax, ay, w1, w2, verts[row * sa.nr1 + a]);
+    }
+}
+
 // patch column and row of ray s of a sweep
 template <int P> __device__ inline int ray_col(int col, int s) { return s & 1 ? P - 1 - col : col; }
 template <int P> __device__ inline int ray_row(int row0, int s)
@@ -650,6 +680,15 @@ void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const 
     hipLaunchKernelGGL(side == 64 ? k_shoot_patch<64> : side == 32 ? k_shoot_patch<32> : k_shoot_patch<16>, dim3((unsigned)npatch), dim3(64), 0, st, sa, lc, g, pa,
                        lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves, T.near,
                        T.deriv, verts);
+}
+
+void launch_shoot_thin(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t vb0,
+                       const ThinList &thin, double2 *verts, hipStream_t st)
+{
+    const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1, vb0, T.p, 0, 0.0};
+    const LeafFinder find{T.nlevels, T.L0_exp, T.L0, T.child0, T.leaf, T.node_leaf};
+    hipLaunchKernelGGL(k_shoot_thin, dim3(THIN_BLOCKS), dim3(64), 0, st, sa, lc, g, find, T.leaves, T.near, T.deriv, thin,
+                       verts);
 }
 
 void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
