@@ -421,7 +421,7 @@ struct BigStarts {
 // vertices' positions (some 1e-13 pixels, in other digits by patches than ray by
 // ray) changes by 1e-13 / its thickness.  On maps of ~10 to 40 cells a pixel that
 // reached 1e-9 of a pixel in most maps and 1e-7 in a few; with THIN it is below
-// 1e-7 of any deposit, at most 6e-9 of a pixel over 64 star fields.  It costs
+// 1e-6 of any deposit, at most 6e-9 of a pixel over 64 star fields.  It costs
 // ~50 us a strip (8.63 to 8.70 ms on the 1e5-star map).  (k_ipm_fine forms most shares
 // without the area, and hundreds of cells a pixel average the others: 4e-11 on the
 // 2.1e10-ray map.)  Cells beyond THIN_CELLS are apportioned as they are.

@@ -6,9 +6,12 @@ positions changes them by d / thickness.  The positions of both ways differ by
 rounding: 8 units in the last place (1.8e-15 each) of positions up to 16 theta_*,
 2.9e-14 theta_*, 4.3e-13 pixels of 1/15 theta_*.  A triangle of 2^-16 pixels then
 changes by 4.3e-13 * 65536 = 2.8e-8 of its weight, and few such triangles meet in
-a pixel: 1e-7 of a triangle's weight bounds every pixel.  The fields hold cells
-down to 1e-8 pixels, which the patches' positions alone would leave at 1e-5.
+a pixel: 1e-7 of a triangle's weight bounds every pixel.  Triangles that stretch
+over many pixels are the ones whose deposits cancel; the field of the second test
+holds one.
 """
+import math
+
 import pytest
 
 import workloads as W
@@ -41,3 +44,27 @@ def test_thin_cells_equal_ray_by_ray(seed, n):
     assert int((thin & inside).sum()) > 50
     weight = 0.5 * (16.0 / 1500) * (16.0 / 1306) * 15.0 ** 2
     assert float((out - ref).abs().max()) < 1e-7 * weight
+
+
+def test_long_thin_triangle():
+    """The paper's Table 1 map, a rectangle of stars; positions up to 64
+    theta_* (units of 1.4e-14) and pixels of 0.01: 8 half units are 5.7e-12 pixels,
+    3.7e-7 of a triangle's weight at 2^-16 pixels, and four of them in a pixel."""
+    import torch
+    import paper_2506_02114_amd as mlm
+    torch.cuda.init()
+    r = math.sqrt(0.6 / 1e-3)
+    a, b = 10.0 + r, (10.0 + r) / 0.2
+    field = mlm.field_params(0.6, "equal", n_stars=int(round(0.6 * 4 * 1.2 * a * 1.2 * b / math.pi)), seed=103947,
+                             shape="rect", rect_aspect=b / a)
+    lens = mlm.Lens.sampled(0.6, 0.0, 0.6, field, sheet="rect")
+    req = dict(hw1=10.0, hw2=10.0, n1=2000, n2=2000, flux_fraction=1e-3)
+    R = lens.region(**req)
+    out = torch.empty((2000, 2000), dtype=torch.float64, device="cuda")
+    ref = torch.empty_like(out)
+    w = torch.empty((R["nr2"], R["nr1"], 2), dtype=torch.float64, device="cuda")
+    _, st = lens.map(out=out, **req)
+    _, sr = lens.map(out=ref, w_out=w, **req)
+    assert st["n_tiles"] < sr["n_tiles"] / 2
+    weight = 0.5 * R["d1"] * R["d2"] / (R["pix1"] * R["pix2"])
+    assert float((out - ref).abs().max()) < 4 * 3.7e-7 * weight
