@@ -40,20 +40,20 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6          # MI355X FP64 vector, dense
 # taken with (ipm.hip and colarea.hpp), identified by the SHA-256 prefix of
 # the two files' bytes in that order.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
-IPM_TRAFFIC = {"ipm_sha256": "a530c3ebbb5bdec1",                     # (fetch KiB, write KiB)
-               "k_ipm": (719906.85, 2278836.5375), "k_band_queue1": (5470672.9125, 280193.3625)}
+IPM_TRAFFIC = {"ipm_sha256": "9e83018a96ecc49b",                     # (fetch KiB, write KiB)
+               "k_ipm": (710556.7750, 2359602.7687), "k_band_queue1": (3075502.7250, 274037.8063)}
 # Wavefront vector instructions per launch of the same kernels (SQ_INSTS_VALU,
 # same runs and source).  A wave64 vector instruction holds its SIMD four
 # cycles, so 1024 SIMDs at 2.4 GHz issue at most 6.144e11 of them per second:
 # the kernels' issue time, set against their launch time, says how close they
 # run to the vector-issue limit that bounds them.
-IPM_VALU = {"k_ipm": 2.057e+09, "k_band_queue1": 1.173e+09}
+IPM_VALU = {"k_ipm": 1.920e+09, "k_band_queue1": 1.136e+09}
 VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4
 # The IPM scatter per launch (same runs and source): FP64 deposits summed in
 # LDS (SQ_INSTS_LDS_ATOMIC_BANDWIDTH x 64 B / 8 B) and atomic requests to L2
 # (TCC_ATOMIC: window flushes, deposits outside the window, shared band rows)
-IPM_SCATTER = {"k_ipm": {"lds_atomic_lanes": 3.239e8, "l2_atomic_requests": 5.790e7},
-               "k_band_queue1": {"lds_atomic_lanes": 1.053e9, "l2_atomic_requests": 4.340e6}}
+IPM_SCATTER = {"k_ipm": {"lds_atomic_lanes": 3.270e+08, "l2_atomic_requests": 5.795e+07},
+               "k_band_queue1": {"lds_atomic_lanes": 1.052e+09, "l2_atomic_requests": 4.340e+06}}
 LDS_BYTES_PER_S = 256 * 2.4e9 * 128      # 128 bytes per clock per CU
 
 
@@ -517,12 +517,6 @@ def main():
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms = (t1 - t0) * 1e3 / args.steps
-    # the same map with every kernel on one stream (the large-triangle passes
-    # after the cell pass instead of beside it), for comparison
-    one = []
-    for _ in range(3):
-        _, s1 = lens.map(out=out, timing=1, one_stream=1, **spec)
-        one.append(s1)
     # one more map, untimed, for the IPM kernels' work counts (timing 2)
     _, counts = lens.map(out=out, timing=2, **spec)
     torch.cuda.synchronize()
@@ -535,7 +529,7 @@ def main():
     t_shoot, t_ipm, t_band = avg("t_shoot_ms"), avg("t_ipm_ms"), avg("t_band_ms")
     flops = shoot_flops(stats[0])
     shoot_roof = {"bound": "alu", "achieved": flops / (t_shoot * 1e-3) / 1e12, "peak": FP64_VECTOR_PEAK_TFLOPS,
-                  "unit": "TFLOP/s", "kernel": "k_shoot", "launch_ms": t_shoot}
+                  "unit": "TFLOP/s", "kernel": "k_shoot (by patches; flops counted ray by ray)", "launch_ms": t_shoot}
     shoot_roof["frac"] = shoot_roof["achieved"] / shoot_roof["peak"]
     # the two IPM kernels (one launch each per map on this workload); the
     # headline roofline is the one that takes longer
@@ -552,41 +546,32 @@ def main():
                   "cells": counts["n_cells"], "small_triangles": counts["n_small"],
                   "column_items": counts["n_col_items"], "pieces": counts["n_col_pieces"]}
     cells_roof["frac"] = cells_roof["achieved"] / cells_roof["peak"]
-    # in the timed maps the cell pass shares the device with the large-triangle
-    # chain; the one-stream maps time each IPM kernel alone
-    t_cells1 = sum(t["t_cells_ms"] for t in one) / len(one)
-    t_band1 = sum(t["t_band_ms"] for t in one) / len(one)
-    cells_roof["alone"] = {"launch_ms": t_cells1, "achieved": cells_flops(counts) / (t_cells1 * 1e-3) / 1e12}
-    cells_roof["alone"]["frac"] = cells_roof["alone"]["achieved"] / cells_roof["peak"]
-
-    def valu_issue(kernel, t_alone_ms):
+    def valu_issue(kernel, t_ms):
         if not fresh:
             return None
         issue_ms = IPM_VALU[kernel] / VALU_ISSUE_PER_S * 1e3
-        return {"instructions": IPM_VALU[kernel], "issue_ms": issue_ms, "frac_of_launch_alone": issue_ms / t_alone_ms}
+        return {"instructions": IPM_VALU[kernel], "issue_ms": issue_ms, "frac_of_launch": issue_ms / t_ms}
 
-    cells_roof["valu_issue"] = valu_issue("k_ipm", t_cells1)
+    cells_roof["valu_issue"] = valu_issue("k_ipm", t_cells)
 
-    def scatter(kernel, t_alone_ms):
+    def scatter(kernel, t_ms):
         if not fresh:
             return None
         c = IPM_SCATTER[kernel]
-        t = t_alone_ms * 1e-3
+        t = t_ms * 1e-3
         return {"lds_atomic_lanes": c["lds_atomic_lanes"], "lds_atomics_per_s": c["lds_atomic_lanes"] / t,
                 "lds_atomic_frac_of_lds_bytes": c["lds_atomic_lanes"] * 8 / t / LDS_BYTES_PER_S,
                 "l2_atomic_requests": c["l2_atomic_requests"], "l2_atomic_requests_per_s": c["l2_atomic_requests"] / t}
 
-    cells_roof["scatter"] = scatter("k_ipm", t_cells1)
+    cells_roof["scatter"] = scatter("k_ipm", t_cells)
     band_roof = {"bound": "alu", "achieved": band_flops(counts) / (t_band * 1e-3) / 1e12,
                  "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s", "traffic": traffic("k_band_queue1"),
                  "kernel": "k_band_queue1",
                  "launch_ms": t_band, "launches_per_step": stats[0]["n_ipm_launches"],
                  "row_items": counts["n_band_rows"], "pieces": counts["n_band_pieces"]}
     band_roof["frac"] = band_roof["achieved"] / band_roof["peak"]
-    band_roof["alone"] = {"launch_ms": t_band1, "achieved": band_flops(counts) / (t_band1 * 1e-3) / 1e12}
-    band_roof["alone"]["frac"] = band_roof["alone"]["achieved"] / band_roof["peak"]
-    band_roof["valu_issue"] = valu_issue("k_band_queue1", t_band1)
-    band_roof["scatter"] = scatter("k_band_queue1", t_band1)
+    band_roof["valu_issue"] = valu_issue("k_band_queue1", t_band)
+    band_roof["scatter"] = scatter("k_band_queue1", t_band)
     roof, other = (cells_roof, band_roof) if t_cells >= t_band else (band_roof, cells_roof)
     # the IPM stage priced per piece: 25 flops per (triangle, pixel) piece
     # and 30 per triangle, over the whole stage's time
@@ -613,10 +598,6 @@ def main():
                                "2000x2000 px, half-width 25, 1 ray/px, FMM order 20, leaf <= 32 block stars",
                    "rays_per_map": rays, "grid": [region["nr1"], region["nr2"]], "precision": "fp64"},
         "maps_per_hour": 3600.0 / (ms * 1e-3),
-        "one_stream": {"ms_per_map_device": sum(t["t_total_ms"] for t in one) / len(one),
-                       "ipm_ms": sum(t["t_ipm_ms"] for t in one) / len(one),
-                       "ipm_cells_ms": sum(t["t_cells_ms"] for t in one) / len(one),
-                       "ipm_band_ms": sum(t["t_band_ms"] for t in one) / len(one)},
         "stages_ms": {"tree": avg("t_tree_ms"), "fmm": avg("t_fmm_ms"), "shoot": t_shoot, "ipm": t_ipm,
                       "ipm_cells": avg("t_cells_ms"), "ipm_band": t_band, "total_device": avg("t_total_ms")},
         "roofline": roof,

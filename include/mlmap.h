@@ -366,8 +366,8 @@ typedef struct mlm_map_stats {
     int64_t n_skipped;       /* triangles skipped for a non-finite vertex */
     int64_t n_nodes, n_leaves;
     int32_t n_levels, order;
-    int64_t near_pairs;      /* ray-star pairs summed directly */
-    int64_t n_tiles;         /* ray tiles launched */
+    int64_t near_pairs;      /* pairs of a ray and a star near it (summed directly, or by a patch's series) */
+    int64_t n_tiles;         /* ray tiles launched (8 x 8 rays, or patches of 16, 32 or 64 squared) */
     double tri_area;         /* image-plane area of one triangle, d1 d2 / 2 */
     double t_tree_ms;        /* sort + tree + lists (device time, if timing) */
     double t_fmm_ms;         /* P2M, M2M, M2L/P2L/L2L, leaf tables */

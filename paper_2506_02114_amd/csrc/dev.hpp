@@ -47,18 +47,6 @@ __device__ inline uint32_t fine_cell(double t, double L0, double scale)
     return (uint32_t)u;
 }
 
-// first index in sorted a[0, n) with a[k] >= v
-__device__ inline int32_t lower_bound_u64(const uint64_t *a, int32_t n, uint64_t v)
-{
-    int32_t lo = 0, hi = n;
-    while (lo < hi) {
-        int32_t mid = (lo + hi) >> 1;
-        if (a[mid] < v) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
 // the indices in sorted a[lo, hi) of the first keys >= v and >= w (v <= w):
 // both searches in step, so that their loads are in flight together
 __device__ inline void two_bounds_u64(const uint64_t *a, int32_t lo, int32_t hi, uint64_t v, uint64_t w, int32_t &i,

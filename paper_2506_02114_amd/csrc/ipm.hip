@@ -448,9 +448,9 @@ __device__ inline void write_big(const BigList &bl, const BigRange &r, int big, 
 // wavefront's lanes.  (One triangle in six is a small one on the 1e5-star map:
 // gathered in sq, two bytes of LDS a lane, and apportioned by the first lanes, they
 // cost the wavefront their 300 instructions once instead of for both triangles of
-// a cell: 2268 instructions a wavefront before, 2119 now, 4.2 and 4.0 ms.)  Which of the two triangles are large (bit k) is returned,
-// and they are listed in `bl` (LIST; `cell`: the cell's number in the strip).
-// Called by whole wavefronts.
+// a cell: 2268 instructions a wavefront before, 2119 now, 4.2 and 4.0 ms.)  Which
+// of the two triangles are large (bit k) is returned, and they are listed in `bl`
+// (LIST; `cell`: the cell's number in the strip).  Called by whole wavefronts.
 template <bool MIXED, int N, bool LIST>
 __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11, P2 v01, const MapGeom &g,
                                               double *__restrict__ map, const Window<N> &w,

@@ -1,6 +1,7 @@
 // Shooting region, ray grid, tree root and expansion order of a map request.
-// Host arithmetic (but for the search of a lattice, the same on the device); built with -ffp-contract=off so every formula is
-// evaluated as written (plain IEEE double operations).
+// Host arithmetic (but for the search of a lattice, the same on the device);
+// built with -ffp-contract=off so every formula is evaluated as written (plain
+// IEEE double operations).
 #include <algorithm>
 #include <cmath>
 
