@@ -291,24 +291,6 @@ __global__ void k_zero_i32(int32_t *p, int64_t n)
     if (t < n) p[t] = 0;
 }
 
-// ray-star pairs and rays of a strip (for the statistics)
-__global__ void k_strip_work(int64_t nleaves, const LeafInfo *__restrict__ lv, unsigned long long *cnt)
-{
-    int64_t lf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long rays = 0, pairs = 0;
-    if (lf < nleaves) {
-        LeafInfo li = lv[lf];
-        if (li.na > 0 && li.nb > 0) {
-            rays = (unsigned long long)li.na * (unsigned long long)li.nb;
-            pairs = rays * (unsigned long long)li.near_cnt;
-        }
-    }
-    if (rays) {
-        atomicAdd(cnt + 1, pairs);
-        atomicAdd(cnt + 2, rays);
-    }
-}
-
 void fill(double *p, int64_t n, double v, hipStream_t st)
 {
     if (n > 0) hipLaunchKernelGGL(k_fill, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n, v);
@@ -1033,11 +1015,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             const int64_t r1 = std::min(cb1, r0 + rows);
             int64_t nt = 0;
-            if (fmm) {
-                nt = plan_tiles(lens, T, R, r0, r1, st, true, side ? side : TILE);
-                hipLaunchKernelGGL(k_strip_work, dim3((unsigned)((T.nleaves + 255) / 256)), dim3(256), 0, st,
-                                   T.nleaves, T.leaves, cnt);
-            }
+            if (fmm) nt = plan_tiles(lens, T, R, r0, r1, st, true, side ? side : TILE, cnt + 1);
             const int ea = tm.mark();
             if (side) launch_irs_patches(lens, T, R, lc, g, side, nt, r0, irs_cnt, st);
             else if (fmm) launch_shoot_irs(lens, T, R, lc, g, nt, r0, irs_cnt, st);
@@ -1095,11 +1073,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             double *w_here = nullptr;
             if (wdev) w_here = q.device_out ? wdev + 2 * (vb0 - cb0) * R.nr1 : wdev;
             int64_t nt = 0;
-            if (fmm) {
-                nt = plan_tiles(lens, T, R, vb0, vb1, st, false, side ? side : TILE);
-                hipLaunchKernelGGL(k_strip_work, dim3((unsigned)((T.nleaves + 255) / 256)), dim3(256), 0, st, T.nleaves,
-                                   T.leaves, cnt);
-            }
+            if (fmm) nt = plan_tiles(lens, T, R, vb0, vb1, st, false, side ? side : TILE, cnt + 1);
             int ea = tm.mark();
             if (side) launch_shoot_patches(lens, T, R, lc, g, side, nt, vb0, verts, st);
             else if (fmm) launch_shoot(lens, T, R, lc, g, nt, vb0, verts, w_here, st);

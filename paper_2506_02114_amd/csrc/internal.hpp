@@ -354,9 +354,10 @@ void build_leaf_tables(mlm_lens *lens, Tree &T, hipStream_t st);
 // shoot.hip
 LensConst lens_const(const mlm_lens *lens, const Region &R);
 // ray tiles of the grid vertices of rows [vb0, vb1), or (centres) of the
-// cell centres of cell rows [vb0, vb1)
+// cell centres of cell rows [vb0, vb1); their near field's pairs of a ray and a
+// star are added to *pairs (device memory; may be null)
 int64_t plan_tiles(mlm_lens *lens, Tree &T, const Region &R, int64_t vb0, int64_t vb1,
-                   hipStream_t st, bool centres = false, int tile = TILE);
+                   hipStream_t st, bool centres = false, int tile = TILE, unsigned long long *pairs = nullptr);
 // inverse ray shooting of the cell centres of cell rows [cb0, cb1): counts
 // per pixel (n2 x n1) are added to `counts`
 void launch_shoot_irs(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
