@@ -901,7 +901,7 @@ void apportion_bands(mlm_lens *lens, int64_t nb, int bh, const MapGeom &g, doubl
     const int64_t nlist = scan_i32_to_u64(lens, bcnt, boffs, nbands, st);
     int32_t *blist = static_cast<int32_t *>(ws.bandlist.reserve((size_t)(nlist > 0 ? nlist : 1) * sizeof(int32_t)));
     MLM_HIP(hipMemcpyAsync(bcur, boffs, (size_t)nbands * sizeof(unsigned long long), hipMemcpyDeviceToDevice, st));
-    launch_band_scatter(nb, bands, nbands, bcur, blist, st);
+    launch_band_scatter(nb, bands, nbands, nlist, bcur, blist, st);
     // the persistent band pass: every band with a list, cut into slices of at
     // most `cut` entries
     std::vector<unsigned long long> hoff((size_t)nbands + 1);

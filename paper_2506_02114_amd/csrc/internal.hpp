@@ -459,8 +459,9 @@ void launch_count_pieces(const double2 *verts, int64_t nr1, int64_t cb0, int64_t
                          unsigned long long *out, hipStream_t st);
 int band_height(int32_t n1, int32_t n2);
 void launch_band_count(int64_t nbig, const uint32_t *bands, int32_t nbands, int32_t *count, hipStream_t st);
-void launch_band_scatter(int64_t nbig, const uint32_t *bands, int32_t nbands, unsigned long long *cursor, int32_t *list,
-                         hipStream_t st);
+// (nlist: entries of all the lists)
+void launch_band_scatter(int64_t nbig, const uint32_t *bands, int32_t nbands, int64_t nlist, unsigned long long *cursor,
+                         int32_t *list, hipStream_t st);
 void launch_big_count(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
                       int32_t *tile_big, hipStream_t st);
 void launch_ipm_batch(const BatchMap *maps, int32_t nmaps, int64_t nctiles, int32_t *tile_big, hipStream_t st);

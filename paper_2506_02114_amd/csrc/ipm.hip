@@ -1291,6 +1291,112 @@ __device__ inline void bin_scatter(int64_t lo, int64_t hi, const uint32_t *__res
     }
 }
 
+// The same by way of LDS: the workgroup's entries of as many bands as fit are
+// sorted by band there and written band by band.  bin_scatter's writes, four
+// bytes each to another list, are as many requests of L2 as entries; a wavefront
+// here writes a band's part in one.  1e5-star map, 62 million entries: 363 to 255
+// us (12288 entries at a time and 512 threads; 24576: 337, 24576 and 1024: 281).
+// It pays for many entries (4e4 of them, of a 1000-star map, gain nothing, 1.4e7
+// 0.2 % of a map) of short triangles: where they cross 18 or 97 bands on average
+// (the 2.1e10-ray map, a strip of elongated cells) the passes over the triangles
+// cost what the writes save, and a workgroup that holds more than SORT_PASSES
+// passes' entries writes them directly (that strip's other triangles, 12 bands on
+// average: with it 306 us, a pass for every 12288 entries 427, bin_scatter 416).
+// Beyond some 2000 bands the LDS would leave a CU one workgroup.
+constexpr size_t SORT_LDS = (size_t)64 << 10;
+constexpr int64_t SORT_LISTS = (int64_t)1 << 24, SORT_BANDS = 16;
+constexpr int SORT_THREADS = 512;
+constexpr int SORT_PASSES = 3;
+constexpr int SORT_ENTRIES = 12288;    // entries sorted at a time (a band has at most BIN_TRIS)
+struct SortLds {
+    unsigned long long *base;   // [nb] where the workgroup's part of a band's list starts
+    int32_t *count;             // [nb + 1] then the waves' scan totals
+    int32_t *start, *pos;       // [nb + 1], [nb]
+    uint16_t *entry;            // [SORT_ENTRIES] triangles, by their numbers in the workgroup
+    static __host__ __device__ size_t bytes(int64_t nb)
+    {
+        return (size_t)nb * 8 + (size_t)(3 * nb + 2 + SORT_THREADS / 64) * 4 + SORT_ENTRIES * 2;
+    }
+    __device__ SortLds(unsigned long long *sh, int32_t nb)
+    {
+        base = sh;
+        count = reinterpret_cast<int32_t *>(base + nb);
+        start = count + nb + 1 + SORT_THREADS / 64;
+        pos = start + nb + 1;
+        entry = reinterpret_cast<uint16_t *>(pos + nb);
+    }
+};
+
+__device__ inline void bin_sort(int64_t lo, int64_t hi, const uint32_t *__restrict__ bands, int32_t nb,
+                                unsigned long long *sh, unsigned long long *__restrict__ cursor,
+                                int32_t *__restrict__ list)
+{
+    const SortLds S(sh, nb);
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+    int32_t *part = S.count + nb + 1;
+    for (int32_t b = t; b <= nb; b += SORT_THREADS) S.count[b] = 0;
+    __syncthreads();
+    for (int64_t k = lo + t; k < hi; k += SORT_THREADS) {
+        const uint32_t br = bands[k];
+        const int b0 = (int)(br & 0xffffu), b1 = (int)(br >> 16);
+        if (b0 > b1) continue;
+        atomicAdd(&S.count[b0], 1);
+        atomicAdd(&S.count[b1 + 1], -1);
+    }
+    band_diff_to_counts(S.count, nb, part);
+    const int chunk = (nb + SORT_THREADS - 1) / SORT_THREADS, c0 = min(t * chunk, (int)nb), c1 = min(c0 + chunk, (int)nb);
+    int sum = 0, total;
+    for (int b = c0; b < c1; ++b) {
+        const int n = S.count[b];
+        if (n) S.base[b] = atomicAdd(cursor + b, (unsigned long long)n);
+        sum += n;
+    }
+    int run = wave_excl_scan(sum, lane, total);
+    if (lane == 0) part[wave] = total;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) run += part[w];
+    for (int b = c0; b < c1; ++b) {
+        S.start[b] = run;
+        run += S.count[b];
+    }
+    if (t == SORT_THREADS - 1) S.start[nb] = run;
+    __syncthreads();
+    if (S.start[nb] > SORT_PASSES * SORT_ENTRIES) {   // (long triangles: directly)
+        for (int b = t; b < nb; b += SORT_THREADS) S.pos[b] = 0;
+        __syncthreads();
+        for (int64_t k = lo + t; k < hi; k += SORT_THREADS) {
+            const uint32_t br = bands[k];
+            const int b1 = (int)(br >> 16);
+            for (int b = (int)(br & 0xffffu); b <= b1; ++b) list[S.base[b] + atomicAdd(&S.pos[b], 1)] = (int32_t)k;
+        }
+        return;
+    }
+    for (int from = 0; from < nb;) {
+        // bands [from, to): as many as fit (one always does)
+        const int s0 = S.start[from];
+        int to = from + 1, above = nb + 1;
+        while (above - to > 1) {
+            const int mid = (to + above) >> 1;
+            if (S.start[mid] - s0 <= SORT_ENTRIES) to = mid;
+            else above = mid;
+        }
+        for (int b = from + t; b < to; b += SORT_THREADS) S.pos[b] = S.start[b] - s0;
+        __syncthreads();
+        for (int64_t k = lo + t; k < hi; k += SORT_THREADS) {
+            const uint32_t br = bands[k];
+            const int b1 = min((int)(br >> 16), to - 1);
+            for (int b = max((int)(br & 0xffffu), from); b <= b1; ++b) S.entry[atomicAdd(&S.pos[b], 1)] = (uint16_t)(k - lo);
+        }
+        __syncthreads();
+        for (int b = from + wave; b < to; b += SORT_THREADS / 64) {
+            const int e0 = S.start[b] - s0, n = S.start[b + 1] - s0 - e0;
+            for (int j = lane; j < n; j += 64) list[S.base[b] + j] = (int32_t)(lo + S.entry[e0 + j]);
+        }
+        __syncthreads();
+        from = to;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_band_count(int64_t nbig, const uint32_t *__restrict__ bands, int32_t nbands,
                                                     int32_t *__restrict__ count)
 {
@@ -1306,6 +1412,15 @@ __global__ __launch_bounds__(256) void k_band_scatter(int64_t nbig, const uint32
     extern __shared__ int32_t sh[];
     const int64_t lo = (int64_t)blockIdx.x * BIN_TRIS;
     bin_scatter(lo, min(lo + BIN_TRIS, nbig), bands, nbands, sh, cursor, list);
+}
+
+__global__ __launch_bounds__(SORT_THREADS) void k_band_sort(int64_t nbig, const uint32_t *__restrict__ bands,
+                                                            int32_t nbands, unsigned long long *__restrict__ cursor,
+                                                            int32_t *__restrict__ list)
+{
+    extern __shared__ unsigned long long sh8[];
+    const int64_t lo = (int64_t)blockIdx.x * BIN_TRIS;
+    bin_sort(lo, min(lo + BIN_TRIS, nbig), bands, nbands, sh8, cursor, list);
 }
 
 // A workgroup takes a band of bh pixel rows (or a slice of its list); a
@@ -1780,14 +1895,17 @@ void launch_band_count(int64_t nbig, const uint32_t *bands, int32_t nbands, int3
     MLM_HIP(hipGetLastError());   // a refused launch leaves the band lists unset: fail here
 }
 
-void launch_band_scatter(int64_t nbig, const uint32_t *bands, int32_t nbands, unsigned long long *cursor, int32_t *list,
-                         hipStream_t st)
+void launch_band_scatter(int64_t nbig, const uint32_t *bands, int32_t nbands, int64_t nlist, unsigned long long *cursor,
+                         int32_t *list, hipStream_t st)
 {
-    const size_t shmem = bin_lds_bytes(nbands);
+    const bool sorted = nlist >= SORT_LISTS && nlist <= SORT_BANDS * nbig && SortLds::bytes(nbands) <= SORT_LDS;
+    const size_t shmem = sorted ? SortLds::bytes(nbands) : bin_lds_bytes(nbands);
     (void)hipGetLastError();   // clear what earlier calls left, so the check below sees this launch
-    if (nbig > 0)
-        hipLaunchKernelGGL(k_band_scatter, dim3((unsigned)((nbig + BIN_TRIS - 1) / BIN_TRIS)), dim3(256), shmem, st, nbig, bands,
-                           nbands, cursor, list);
+    const dim3 grid((unsigned)((nbig + BIN_TRIS - 1) / BIN_TRIS));
+    if (nbig > 0 && sorted)
+        hipLaunchKernelGGL(k_band_sort, grid, dim3(SORT_THREADS), shmem, st, nbig, bands, nbands, cursor, list);
+    else if (nbig > 0)
+        hipLaunchKernelGGL(k_band_scatter, grid, dim3(256), shmem, st, nbig, bands, nbands, cursor, list);
     MLM_HIP(hipGetLastError());
 }
 
