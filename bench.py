@@ -40,20 +40,20 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6          # MI355X FP64 vector, dense
 # taken with (ipm.hip and colarea.hpp), identified by the SHA-256 prefix of
 # the two files' bytes in that order.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
-IPM_TRAFFIC = {"ipm_sha256": "9e83018a96ecc49b",                     # (fetch KiB, write KiB)
-               "k_ipm": (710556.7750, 2359602.7687), "k_band_queue1": (3075502.7250, 274037.8063)}
+IPM_TRAFFIC = {"ipm_sha256": "7819f726f7440616",                     # (fetch KiB, write KiB)
+               "k_ipm": (710484.2188, 2370746.9844), "k_band_queue1": (3064563.0312, 274081.1094)}
 # Wavefront vector instructions per launch of the same kernels (SQ_INSTS_VALU,
 # same runs and source).  A wave64 vector instruction holds its SIMD four
 # cycles, so 1024 SIMDs at 2.4 GHz issue at most 6.144e11 of them per second:
 # the kernels' issue time, set against their launch time, says how close they
 # run to the vector-issue limit that bounds them.
-IPM_VALU = {"k_ipm": 1.920e+09, "k_band_queue1": 1.136e+09}
+IPM_VALU = {"k_ipm": 1.937e+09, "k_band_queue1": 1.139e+09}
 VALU_ISSUE_PER_S = 1024 * 2.4e9 / 4
 # The IPM scatter per launch (same runs and source): FP64 deposits summed in
 # LDS (SQ_INSTS_LDS_ATOMIC_BANDWIDTH x 64 B / 8 B) and atomic requests to L2
 # (TCC_ATOMIC: window flushes, deposits outside the window, shared band rows)
-IPM_SCATTER = {"k_ipm": {"lds_atomic_lanes": 3.270e+08, "l2_atomic_requests": 5.795e+07},
-               "k_band_queue1": {"lds_atomic_lanes": 1.052e+09, "l2_atomic_requests": 4.340e+06}}
+IPM_SCATTER = {"k_ipm": {"lds_atomic_lanes": 3.270e+08, "l2_atomic_requests": 5.845e+07},
+               "k_band_queue1": {"lds_atomic_lanes": 1.052e+09, "l2_atomic_requests": 4.341e+06}}
 LDS_BYTES_PER_S = 256 * 2.4e9 * 128      # 128 bytes per clock per CU
 
 
