@@ -34,6 +34,16 @@ constexpr double SMALL_PATCH_RAYS_PER_LEAF[2] = {8192.0, 3000.0}, SMALL_PATCH_MA
 constexpr int PC_MAX = 24;    // most coefficients of a patch
 constexpr int PC_DIRECT = 8;  // most stars summed directly
 constexpr int PC_STARS = 64;  // most near stars of a leaf in this path
+// A patch begins at a leaf's first rays and may reach far beyond a leaf that is
+// smaller (next to a tight group of stars).  The leaf's series, good within the
+// leaf, is there a sum of huge terms that cancel, and so are the patch's
+// coefficients: over 16 x 16 rays a leaf 2 rays wide came out 2e-3 off, one of 1
+// ray worthless.  Their rounding grows with the sum of the terms' magnitudes at the
+// patch's far end; where that passes PC_REACH times the same sum at the leaf's
+// corner plus the size of the positions, the rays' own rounding, the patch goes ray
+// by ray.  (Over 1.2e7 patches among evenly spread stars the quotient was below 0.5
+// everywhere, so none of them does.)
+constexpr double PC_REACH = 2.0;
 // cost in vector instructions of one more coefficient and of a direct star,
 // per ray: what the number of coefficients is chosen by
 constexpr int COST_COEF = 2, COST_STAR = 18;
@@ -102,11 +112,18 @@ __global__ __launch_bounds__(64) void k_patch_coef(ShootArgs sa, LensConst lc, P
     // D_j = rho^j sum_{l >= j} C(l, j) d_l s^(l - j), Horner in s
     const int p = sa.p;
     double2 D0 = make_double2(0, 0), D1 = make_double2(0, 0);
+    bool general = li.near_cnt > PC_STARS;   // whether the patch goes ray by ray
     {
         const double sr = sx * li.invL, si = sy * li.invL, rho = r * li.invL;
         const double2 *dv = deriv + (int64_t)lf * p;
+        // the terms' magnitudes at the patch's far end and at the leaf's corner
+        const double reach = sqrt(sr * sr + si * si) + rho;
+        double far_end = 0.0, corner = 0.0;
         for (int l = p - 1; l >= 0; --l) {
             const double2 d = dv[l];
+            const double a = fabs(d.x) + fabs(d.y);
+            far_end = fma(far_end, reach, a);
+            corner = fma(corner, M_SQRT2, a);
             if (l >= j) {
                 const double c = binom[l * 32 + j];
                 const double nr = D0.x * sr - D0.y * si + c * d.x;
@@ -120,6 +137,7 @@ __global__ __launch_bounds__(64) void k_patch_coef(ShootArgs sa, LensConst lc, P
                 D1.x = nr;
             }
         }
+        general = general || !(far_end <= PC_REACH * (corner + fabs(px) + fabs(py) + pa.span));   // (true for NaN)
         double f = 1.0, b = rho;
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
@@ -137,7 +155,6 @@ __global__ __launch_bounds__(64) void k_patch_coef(ShootArgs sa, LensConst lc, P
     // corners' logarithms); outside the disc the field of its whole mass at
     // the origin; a patch its edge crosses goes ray by ray
     int lin = LIN_NONE;
-    bool general = li.near_cnt > PC_STARS;
     double xx = 0, xy = 0, xm = 0, xs = 0;   // this lane's extra pole: offset, mass (disc) or sign (corner)
     if (lc.sheet == 1) {
         const double d = sqrt(px * px + py * py), R = sqrt(lc.r_star2);
