@@ -1059,10 +1059,13 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         // (elongated cells) 0.177 and 0.179, at 34 0.257 and 0.243, at 37 4.84 and
         // 4.66 (a map across a fold caustic), at 60 4.82 and 4.79.
         const double cells_px = (double)(R.nr1 - 1) * (double)(R.nr2 - 1) / ((double)g.n1 * (double)g.n2);
-        const int pass = cells_px >= FINE_CELLS_PER_PIXEL    ? 3
-                         : cells_px >= QUEUE_CELLS_PER_PIXEL ? 2
-                         : cells_px >= MID_CELLS_PER_PIXEL   ? 1
-                                                             : 0;
+        // (k_ipm_fine apportions what lies within two pixels itself: not where a
+        // triangle of two is a large one)
+        const bool fine = g.big_px >= 2;
+        const int pass = fine && cells_px >= FINE_CELLS_PER_PIXEL    ? 3
+                         : fine && cells_px >= QUEUE_CELLS_PER_PIXEL ? 2
+                         : cells_px >= MID_CELLS_PER_PIXEL           ? 1
+                                                                     : 0;
         // (cell refinement shoots its rays one by one, and its decisions compare
         // them with the grid's: those go the same way there)
         const bool single = q.w_out || q.refine != MLM_REFINE_NONE || thread_arena();
