@@ -1102,12 +1102,13 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             unsigned long long *const work = q.timing >= 2 ? cnt + 8 : nullptr;
             ThinList thin;
             if (side && pass < 2) {
-                thin.cell = static_cast<int64_t *>(ws.thin.reserve((THIN_CELLS + 1) * sizeof(int64_t)));
+                thin.corner = static_cast<double2 *>(ws.thin.reserve(THIN_BYTES));
+                thin.cell = reinterpret_cast<int64_t *>(thin.corner + 4 * THIN_CELLS);
                 thin.count = reinterpret_cast<unsigned *>(thin.cell + THIN_CELLS);
             }
             launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, thin, q.precision == MLM_PREC_MIXED, pass, work, st);
             if (thin.count) {
-                launch_shoot_thin(T, R, lc, g, vb0, thin, verts, st);
+                launch_shoot_thin(T, R, lc, g, r0, vb0, thin, verts, st);
                 launch_ipm_thin(verts, R.nr1, r0, vb0, g, map, cnt, bl, thin, work, st);
             }
             const int e_cells = tm.mark();
@@ -1139,8 +1140,8 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 }
                 BigPrep *prep = ws.bigprep.as<BigPrep>() + held;
                 uint32_t *bands = ws.bigbands.as<uint32_t>() + held;
-                if (listed) launch_big_setup(verts, R.nr1, r0, vb0, g, bl, at, bh, prep, bands, st);
-                else launch_big_gather(verts, R.nr1, r0, r1, vb0, g, nb, toff, bh, prep, bands, st);
+                if (listed) launch_big_setup(verts, R.nr1, r0, vb0, g, bl, at, thin, bh, prep, bands, st);
+                else launch_big_gather(verts, R.nr1, r0, r1, vb0, g, nb, toff, thin, bh, prep, bands, st);
                 if (q.timing >= 2) launch_count_rows(nb, prep, cnt + 7, st);   // statistics only
                 held += nb;
                 n_big += nb;

@@ -378,10 +378,10 @@ void launch_shoot(mlm_lens *lens, const Tree &T, const Region &R, const LensCons
 int patch_side(const Region &R, const Tree &T, int64_t rows);
 void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
                           int side, int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st);
-// the vertices of the cells in `thin` (of a strip from vertex row vb0) ray by ray
+// the corners of the cells in `thin` (of a strip from vertex row vb0, cell row cb0) ray by ray
 struct ThinList;
-void launch_shoot_thin(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t vb0,
-                       const ThinList &thin, double2 *verts, hipStream_t st);
+void launch_shoot_thin(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t cb0,
+                       int64_t vb0, const ThinList &thin, const double2 *verts, hipStream_t st);
 void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
                         int side, int64_t npatch, int64_t cb0, unsigned long long *counts, hipStream_t st);
 void launch_shoot_direct(mlm_lens *lens, const Region &R, const LensConst &lc, const MapGeom &g,
@@ -428,19 +428,26 @@ struct BigStarts {
 // 2.1e10-ray map.)  Cells beyond THIN_CELLS are apportioned as they are.
 constexpr double THIN = 1.0 / 65536.0;
 constexpr unsigned THIN_CELLS = 65536, THIN_BLOCKS = 64;
+// Their vertices are shot to a place of their own: other cells share them, and every
+// pass has to see the vertices that the cell pass saw, or a triangle at the edge of
+// being large is apportioned twice or not at all.
 struct ThinList {
     unsigned *count = nullptr;   // null: no cell is listed
     int64_t *cell = nullptr;
+    double2 *corner = nullptr;   // ray by ray: a listed cell's (0, 0), (1, 0), (0, 1), (1, 1)
 };
+constexpr size_t THIN_BYTES = THIN_CELLS * (4 * sizeof(double2) + sizeof(int64_t)) + sizeof(unsigned);
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
                 double *map, unsigned long long *counters, const BigList &bl, const ThinList &thin, bool mixed, int pass,
                 unsigned long long *work, hipStream_t st);
-// the listed cells, by their vertices as they are now
+// the listed cells, by their own corners; a large triangle of listed cell k goes
+// to the lists as one of cell -1 - k
 void launch_ipm_thin(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, double *map,
                      unsigned long long *counters, const BigList &bl, const ThinList &thin, unsigned long long *work,
                      hipStream_t st);
 void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,
-                      const BigStarts &at, int bh, BigPrep *prep, uint32_t *bands, hipStream_t st);
+                      const BigStarts &at, const ThinList &thin, int bh, BigPrep *prep, uint32_t *bands,
+                      hipStream_t st);
 // the counts of the lists (waits for them), laid end to end; false if one is incomplete
 bool read_big_counts(mlm_lens *lens, const BigList &bl, BigStarts &at, hipStream_t st);
 // the large triangles of the tiles into prep and their bands of bh rows (bh 0: not
@@ -448,8 +455,8 @@ bool read_big_counts(mlm_lens *lens, const BigList &bl, BigStarts &at, hipStream
 // tile_off (nbig in all; with fewer than one a tile, a resident grid skips
 // the empty tiles)
 void launch_big_gather(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                       int64_t nbig, const int64_t *tile_off, int bh, BigPrep *prep, uint32_t *bands,
-                       hipStream_t st);
+                       int64_t nbig, const int64_t *tile_off, const ThinList &thin, int bh, BigPrep *prep,
+                       uint32_t *bands, hipStream_t st);
 void launch_big(int64_t nbig, const BigPrep *prep, const MapGeom &g, double *map, double *diff, hipStream_t st);
 // statistics: the pixel rows of nbig large triangles, added to *out
 void launch_count_rows(int64_t nbig, const BigPrep *prep, unsigned long long *out, hipStream_t st);

@@ -451,11 +451,12 @@ __device__ inline void write_big(const BigList &bl, const BigRange &r, int big, 
 // a cell: 2268 instructions a wavefront before, 2119 now, 4.2 and 4.0 ms.)  Which
 // of the two triangles are large (bit k) is returned, and they are listed in `bl`
 // (LIST; `cell`: the cell's number in the strip).  Called by whole wavefronts.
-template <bool MIXED, int N, bool LIST>
+// GIVEN: the large ones are those of `given`.
+template <bool MIXED, int N, bool LIST, bool GIVEN = false>
 __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11, P2 v01, const MapGeom &g,
                                               double *__restrict__ map, const Window<N> &w,
                                               unsigned long long *__restrict__ counters, const BigList &bl,
-                                              int64_t cell, uint8_t *sq, CellWork &cw)
+                                              int64_t cell, uint8_t *sq, CellWork &cw, int given = 0)
 {
     const int lane = threadIdx.x & 63;
     int mcols[2] = {0, 0};      // pixel columns of each medium triangle of the cell (0: none)
@@ -463,12 +464,16 @@ __device__ __forceinline__ int apportion_cell(bool have, P2 v00, P2 v10, P2 v11,
     int big = 0, small = 0;
     if (have) {
         int pi, pj;
-        if (cell_in_one_pixel(v00, v10, v11, v01, g, pi, pj)) {
+        if (!(GIVEN && given) && cell_in_one_pixel(v00, v10, v11, v01, g, pi, pj)) {
             if (pi >= 0) deposit_w(w, map, g, pi, pj, 2.0 * g.tri_weight);
         } else {
             const P2 tri[2][3] = {{v00, v10, v11}, {v00, v11, v01}};
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
+                if (GIVEN && (given >> k & 1)) {
+                    big |= 1 << k;
+                    continue;
+                }
                 const P2 A = tri[k][0], B = tri[k][1], C = tri[k][2];
                 const TriClass c = classify(A, B, C, g);
                 if (c.kind == 0) {
@@ -651,7 +656,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     ipm_tile<MIXED, N, true>(verts, nr1, cb0, nrows, vb0, g, map, counters, bl, thin, nullptr, blockIdx.x, acc, work);
 }
 
-// the cells of `thin`, one a thread, straight into the map
+// which of the cell's two triangles are large (bit k: triangle k), with the
+// cell pass's classification: none if the cell lies in one pixel
+__device__ inline int cell_big_mask(P2 v00, P2 v10, P2 v11, P2 v01, const MapGeom &g)
+{
+    int pi, pj;
+    if (cell_in_one_pixel(v00, v10, v11, v01, g, pi, pj)) return 0;
+    return (classify(v00, v10, v11, g).kind == 3 ? 1 : 0) | (classify(v00, v11, v01, g).kind == 3 ? 2 : 0);
+}
+
+// the corners of listed cell k
+__device__ inline void load_thin(const ThinList &thin, int64_t k, P2 &v00, P2 &v10, P2 &v11, P2 &v01)
+{
+    load_cell_at(thin.corner, 2, 2 * k, 0, v00, v10, v11, v01);   // (two rows of a grid two vertices wide)
+}
+
+// whether triangles `mask` of a cell have an area to apportion in the map
+__device__ inline bool cell_has_area(P2 v00, P2 v10, P2 v11, P2 v01, int mask, const MapGeom &g)
+{
+    return (!(mask & 1) || classify(v00, v10, v11, g).kind >= 2) && (!(mask & 2) || classify(v00, v11, v01, g).kind >= 2);
+}
+
+// The cells of `thin`, one a thread, straight into the map.  Which of their
+// triangles are large is decided by the strip's vertices, as the count by tiles
+// does; the others are apportioned whatever their size.  (A large one without area
+// by its own corners is set up by the strip's.)
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ipm_thin(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t vb0, MapGeom g,
                                                  double *__restrict__ map, unsigned long long *__restrict__ counters,
                                                  BigList bl, ThinList thin, unsigned long long *__restrict__ work)
@@ -663,11 +692,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     w.i0 = w.j0 = -(1 << 30);
     const int64_t n = min(*thin.count, THIN_CELLS);
     CellWork cw;
+    MapGeom all = g;
+    all.big_px = INT32_MAX;
     for (int64_t base = (int64_t)blockIdx.x * 64; base < n; base += (int64_t)gridDim.x * 64) {
-        const int64_t cell = thin.cell[min(base + threadIdx.x, n - 1)], row = cell / (nr1 - 1);
+        const int64_t k = min(base + threadIdx.x, n - 1), cell = thin.cell[k], row = cell / (nr1 - 1);
         P2 v00, v10, v11, v01;
         load_cell_at(verts, nr1, cb0 + row - vb0, cell % (nr1 - 1), v00, v10, v11, v01);
-        apportion_cell<false, 1, true>(base + threadIdx.x < n, v00, v10, v11, v01, g, map, w, counters, bl, cell, sq, cw);
+        const int large = cell_big_mask(v00, v10, v11, v01, g);
+        load_thin(thin, k, v00, v10, v11, v01);
+        apportion_cell<false, 1, true, true>(base + threadIdx.x < n, v00, v10, v11, v01, all, map, w, counters, bl,
+                                             cell_has_area(v00, v10, v11, v01, large, g) ? -1 - k : cell, sq, cw, large);
     }
     if (work) add_work(work, blockIdx.x, cw);
 }
@@ -841,15 +875,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
-// which of the cell's two triangles are large (bit k: triangle k), with the
-// cell pass's classification: none if the cell lies in one pixel
-__device__ inline int cell_big_mask(P2 v00, P2 v10, P2 v11, P2 v01, const MapGeom &g)
-{
-    int pi, pj;
-    if (cell_in_one_pixel(v00, v10, v11, v01, g, pi, pj)) return 0;
-    return (classify(v00, v10, v11, g).kind == 3 ? 1 : 0) | (classify(v00, v11, v01, g).kind == 3 ? 2 : 0);
-}
-
 // set-up of the cell's large triangles (`mask`), written to slots [slot,
 // end): integer local origin (inside or at the edge of the map, so nearby
 // pixel boundaries are exact), counter-clockwise local vertices, edge slopes,
@@ -904,8 +929,8 @@ __device__ inline void gather_cell(P2 v00, P2 v10, P2 v11, P2 v01, int mask, int
 // the same for the listed large triangles, slot k the k-th of the lists laid
 // end to end (list sh's entries are slots [at.lo[sh], at.lo[sh + 1]))
 __global__ __launch_bounds__(256) void k_big_setup(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
-                                                   int64_t vb0, MapGeom g, BigList bl, BigStarts at, int bh,
-                                                   BigPrep *__restrict__ prep, uint32_t *__restrict__ bands)
+                                                   int64_t vb0, MapGeom g, BigList bl, BigStarts at, ThinList thin,
+                                                   int bh, BigPrep *__restrict__ prep, uint32_t *__restrict__ bands)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= at.lo[BIG_SHARDS]) return;
@@ -915,7 +940,10 @@ __global__ __launch_bounds__(256) void k_big_setup(const double2 *__restrict__ v
         if (at.lo[sh + step] <= k) sh += step;
     const int64_t e = bl.list[sh * bl.cap + (k - at.lo[sh])], cell = e >> 1, ncol = nr1 - 1;
     P2 v00, v10, v11, v01;
-    load_cell_at(verts, nr1, cb0 + cell / ncol - vb0, cell % ncol, v00, v10, v11, v01);
+    // (a listed thin cell's corners are two rows of a grid two vertices wide)
+    const bool own = cell < 0;
+    load_cell_at(own ? thin.corner : verts, own ? 2 : nr1, own ? 2 * (-1 - cell) : cb0 + cell / ncol - vb0,
+                 own ? 0 : cell % ncol, v00, v10, v11, v01);
     gather_cell(v00, v10, v11, v01, 1 << (e & 1), k, k + 1, g, bh, prep, bands);
 }
 
@@ -923,10 +951,12 @@ __global__ __launch_bounds__(256) void k_big_setup(const double2 *__restrict__ v
 // cells over the threads as in the cell pass), written in thread order to
 // [lo, hi), the tile's range from the scan of the cell pass's per-tile counts.
 // Slots of that range this pass does not fill (none, as both passes classify
-// alike) are left as triangles without rows.
+// alike) are left as triangles without rows.  (thin: only the large triangles of
+// its listed cell `nth`, by that cell's own corners.)
 __device__ inline void gather_tile(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0, int64_t nrows,
                                    int64_t vb0, const MapGeom &g, int64_t tile, int64_t lo, int64_t hi, int bh,
-                                   BigPrep *__restrict__ prep, uint32_t *__restrict__ bands, int32_t *wsum)
+                                   BigPrep *__restrict__ prep, uint32_t *__restrict__ bands, int32_t *wsum,
+                                   const ThinList *thin = nullptr, int64_t nth = 0)
 {
     const int64_t ncol = nr1 - 1;
     const int64_t tiles_a = (ncol + CT - 1) / CT;
@@ -949,6 +979,14 @@ __device__ inline void gather_tile(const double2 *__restrict__ verts, int64_t nr
     for (int w = 0; w < 4; ++w) {
         if (w < wave) slot += wsum[w];
         found += wsum[w];
+    }
+    if (thin) {
+        if (mask && brow * ncol + a == thin->cell[nth]) {
+            load_thin(*thin, nth, v00, v10, v11, v01);
+            if (cell_has_area(v00, v10, v11, v01, mask, g))
+                gather_cell(v00, v10, v11, v01, mask, slot, min(slot + nb, hi), g, bh, prep, bands);
+        }
+        return;
     }
     if (mask) gather_cell(v00, v10, v11, v01, mask, slot, min(slot + nb, hi), g, bh, prep, bands);
     for (int64_t s = lo + found + threadIdx.x; s < hi; s += blockDim.x) {
@@ -1042,6 +1080,24 @@ __global__ __launch_bounds__(256) void k_big_gather_sparse(const double2 *__rest
     for_big_tiles(tiles, tile_off, [&](int64_t t) {
         gather_tile(verts, nr1, cb0, nrows, vb0, g, t, tile_off[t], tile_off[t + 1], bh, prep, bands, wsum);
     });
+}
+
+// after either: the large triangles of the thin cells, whose slots a workgroup finds
+// by counting its cell's tile again
+__global__ __launch_bounds__(256) void k_big_gather_thin(const double2 *__restrict__ verts, int64_t nr1, int64_t cb0,
+                                                         int64_t nrows, int64_t vb0, MapGeom g,
+                                                         const int64_t *__restrict__ tile_off, ThinList thin, int bh,
+                                                         BigPrep *__restrict__ prep, uint32_t *__restrict__ bands)
+{
+    __shared__ int32_t wsum[4];
+    const int64_t n = min(*thin.count, THIN_CELLS), ncol = nr1 - 1, tiles_a = (ncol + CT - 1) / CT;
+    for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
+        const int64_t cell = thin.cell[k], t = cell / ncol / CT * tiles_a + cell % ncol / CT;
+        const int64_t lo = tile_off[t], hi = tile_off[t + 1];
+        if (lo == hi) continue;   // (the whole workgroup)
+        gather_tile(verts, nr1, cb0, nrows, vb0, g, t, lo, hi, bh, prep, bands, wsum, &thin, k);
+        __syncthreads();          // (wsum is used again)
+    }
 }
 
 // the batch's cell tiles: tile_off is the scan over all maps' tiles
@@ -1798,12 +1854,13 @@ void launch_ipm_thin(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0
 }
 
 void launch_big_setup(const double2 *verts, int64_t nr1, int64_t cb0, int64_t vb0, const MapGeom &g, const BigList &bl,
-                      const BigStarts &at, int bh, BigPrep *prep, uint32_t *bands, hipStream_t st)
+                      const BigStarts &at, const ThinList &thin, int bh, BigPrep *prep, uint32_t *bands,
+                      hipStream_t st)
 {
     const int64_t n = at.lo[BIG_SHARDS];
     if (n > 0)
         hipLaunchKernelGGL(k_big_setup, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, verts, nr1, cb0, vb0, g,
-                           bl, at, bh, prep, bands);
+                           bl, at, thin, bh, prep, bands);
 }
 
 // grid of a persistent kernel: the workgroups of `threads` threads of `kernel`
@@ -1827,8 +1884,8 @@ int64_t ipm_tile_count(int64_t nr1, int64_t nrows)
 }
 
 void launch_big_gather(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
-                       int64_t nbig, const int64_t *tile_off, int bh, BigPrep *prep, uint32_t *bands,
-                       hipStream_t st)
+                       int64_t nbig, const int64_t *tile_off, const ThinList &thin, int bh, BigPrep *prep,
+                       uint32_t *bands, hipStream_t st)
 {
     const int64_t tiles = ipm_tile_count(nr1, cb1 - cb0);
     if (tiles <= 0) return;
@@ -1840,6 +1897,9 @@ void launch_big_gather(const double2 *verts, int64_t nr1, int64_t cb0, int64_t c
         hipLaunchKernelGGL(k_big_gather, dim3((unsigned)tiles), dim3(256), 0, st, verts, nr1, cb0, cb1 - cb0, vb0, g,
                            tile_off, bh, prep, bands);
     }
+    if (thin.count)
+        hipLaunchKernelGGL(k_big_gather_thin, dim3(4 * THIN_BLOCKS), dim3(256), 0, st, verts, nr1, cb0, cb1 - cb0, vb0,
+                           g, tile_off, thin, bh, prep, bands);
 }
 
 void launch_big_count(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,

@@ -42,7 +42,9 @@ constexpr int PC_STARS = 64;  // most near stars of a leaf in this path
 // patch's far end; where that passes PC_REACH times the same sum at the leaf's
 // corner plus the size of the positions, the rays' own rounding, the patch goes ray
 // by ray.  (Over 1.2e7 patches among evenly spread stars the quotient was below 0.5
-// everywhere, so none of them does.)
+// everywhere, so none of them does.  It is not formed for a patch within two
+// half-lengths: the stars of a leaf's series lie three away at least, so its terms
+// are at most a few times those at the corner there.)
 constexpr double PC_REACH = 2.0;
 // cost in vector instructions of one more coefficient and of a direct star,
 // per ray: what the number of coefficients is chosen by
@@ -116,14 +118,20 @@ __global__ __launch_bounds__(64) void k_patch_coef(ShootArgs sa, LensConst lc, P
     {
         const double sr = sx * li.invL, si = sy * li.invL, rho = r * li.invL;
         const double2 *dv = deriv + (int64_t)lf * p;
-        // the terms' magnitudes at the patch's far end and at the leaf's corner
         const double reach = sqrt(sr * sr + si * si) + rho;
-        double far_end = 0.0, corner = 0.0;
+        if (__any(reach > 2.0)) {
+            // the terms' magnitudes at the patch's far end and at the leaf's corner
+            double far_end = 0.0, corner = 0.0;
+            for (int l = p - 1; l >= 0; --l) {
+                const double2 d = dv[l];
+                const double a = fabs(d.x) + fabs(d.y);
+                far_end = fma(far_end, reach, a);
+                corner = fma(corner, M_SQRT2, a);
+            }
+            general = general || !(far_end <= PC_REACH * (corner + fabs(px) + fabs(py) + pa.span));   // (true for NaN)
+        }
         for (int l = p - 1; l >= 0; --l) {
             const double2 d = dv[l];
-            const double a = fabs(d.x) + fabs(d.y);
-            far_end = fma(far_end, reach, a);
-            corner = fma(corner, M_SQRT2, a);
             if (l >= j) {
                 const double c = binom[l * 32 + j];
                 const double nr = D0.x * sr - D0.y * si + c * d.x;
@@ -137,7 +145,6 @@ __global__ __launch_bounds__(64) void k_patch_coef(ShootArgs sa, LensConst lc, P
                 D1.x = nr;
             }
         }
-        general = general || !(far_end <= PC_REACH * (corner + fabs(px) + fabs(py) + pa.span));   // (true for NaN)
         double f = 1.0, b = rho;
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
@@ -448,26 +455,28 @@ __device__ inline double2 exact_ray(const ShootArgs &sa, const LensConst &lc, co
     return uv;
 }
 
-// The vertices of the cells that the cell pass found too thin for patches
-// (ThinList), ray by ray; cells that share a vertex write the same value to it.
-// (A map lists tens of cells.)
-__global__ __launch_bounds__(64) void k_shoot_thin(ShootArgs sa, LensConst lc, MapGeom g, LeafFinder find,
+// The corners of the cells that the cell pass found too thin for patches
+// (ThinList), ray by ray.  (A map lists tens of cells.)
+__global__ __launch_bounds__(64) void k_shoot_thin(ShootArgs sa, LensConst lc, MapGeom g, LeafFinder find, int64_t cb0,
                                                    const LeafInfo *__restrict__ leaves,
                                                    const double4 *__restrict__ near,
                                                    const double2 *__restrict__ deriv, ThinList thin,
-                                                   double2 *__restrict__ verts)
+                                                   const double2 *__restrict__ verts)
 {
     const int64_t n = 4 * (int64_t)min(*thin.count, THIN_CELLS);
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
         const int64_t c = thin.cell[t >> 2];
-        const int64_t a = c % (sa.nr1 - 1) + (t & 1), row = c / (sa.nr1 - 1) + ((t >> 1) & 1);
-        const double x = grid_pos(sa.x0, sa.d1, a), y = grid_pos(sa.y0, sa.d2, sa.vb0 + row);
+        const int64_t a = c % (sa.nr1 - 1) + (t & 1), b = cb0 + c / (sa.nr1 - 1) + ((t >> 1) & 1);
+        const double x = grid_pos(sa.x0, sa.d1, a), y = grid_pos(sa.y0, sa.d2, b);
         const int64_t lf = find_leaf(x, y, find.nlevels, find.L0, find.L0_exp, find.child0, find.leaf, find.node_leaf);
-        if (lf < 0) continue;
+        if (lf < 0) {
+            thin.corner[t] = verts[(b - sa.vb0) * sa.nr1 + a];
+            continue;
+        }
         const LeafInfo li = leaves[lf];
         double ax, ay, w1, w2;
         leaf_alpha<double>(x - li.cx, y - li.cy, li, near + li.near_off, deriv + lf * sa.p, sa.p, ax, ay);
-        finish_vertex(lc, g, x, y, ax, ay, w1, w2, verts[row * sa.nr1 + a]);
+        finish_vertex(lc, g, x, y, ax, ay, w1, w2, thin.corner[t]);
     }
 }
 
@@ -699,13 +708,13 @@ void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const 
                        T.deriv, verts);
 }
 
-void launch_shoot_thin(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t vb0,
-                       const ThinList &thin, double2 *verts, hipStream_t st)
+void launch_shoot_thin(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t cb0,
+                       int64_t vb0, const ThinList &thin, const double2 *verts, hipStream_t st)
 {
     const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1, vb0, T.p, 0, 0.0};
     const LeafFinder find{T.nlevels, T.L0_exp, T.L0, T.child0, T.leaf, T.node_leaf};
-    hipLaunchKernelGGL(k_shoot_thin, dim3(THIN_BLOCKS), dim3(64), 0, st, sa, lc, g, find, T.leaves, T.near, T.deriv, thin,
-                       verts);
+    hipLaunchKernelGGL(k_shoot_thin, dim3(THIN_BLOCKS), dim3(64), 0, st, sa, lc, g, find, cb0, T.leaves, T.near, T.deriv,
+                       thin, verts);
 }
 
 void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
