@@ -1010,7 +1010,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         hipLaunchKernelGGL(k_zero_u64n, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, irs_cnt, npix);
         // (inside a scratch arena, without room for the patches' coefficients,
         // rays are shot one by one)
-        const int side = fmm && !thread_arena() ? patch_side(R, T, cb1 - cb0) : 0;
+        const int side = fmm && !thread_arena() && irs_by_patches(R, lc, g) ? patch_side(R, T, cb1 - cb0) : 0;
         const int64_t rows = std::max<int64_t>(1, (side ? IRS_STRIP_PATCHES * side * side : IRS_STRIP_RAYS) / std::max<int64_t>(R.nr1 - 1, 1));
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             const int64_t r1 = std::min(cb1, r0 + rows);

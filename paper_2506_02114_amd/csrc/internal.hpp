@@ -376,6 +376,9 @@ void launch_shoot(mlm_lens *lens, const Tree &T, const Region &R, const LensCons
 // far denser than the stars.  The patch's side (0: shoot ray by ray), for
 // `rows` rows of rays; patches are planned as tiles of that side.
 int patch_side(const Region &R, const Tree &T, int64_t rows);
+// whether the pixels are large enough against the positions' rounding for ray
+// shooting by patches to count every ray where shooting ray by ray does
+bool irs_by_patches(const Region &R, const LensConst &lc, const MapGeom &g);
 void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g,
                           int side, int64_t npatch, int64_t vb0, double2 *verts, hipStream_t st);
 // the corners of the cells in `thin` (of a strip from vertex row vb0, cell row cb0) ray by ray

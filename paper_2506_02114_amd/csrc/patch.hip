@@ -70,6 +70,7 @@ struct PatchArgs {
     double r, ir;          // a patch's half diagonal (the largest |t|) and its inverse
     double hx, hy;         // half sides
     double span;           // extent of the source-plane map: the scale of the positions' rounding
+    double sure;           // inverse ray shooting: largest distance from a pixel's middle (pixels) at which a ray's pixel is certain
 };
 
 // coefficients needed for a star (m > 0) at distance |w0| = w from the centre
@@ -524,10 +525,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 }
 
-// Rays whose pixel coordinate lies this close to a pixel's edge are shot again
-// ray by ray, so that every ray counts in the pixel that k_shoot_irs counts it
-// in: the series' and the rounding's error is below 1e-9 pixels.
-constexpr double EDGE = 1e-6;
+// Rays whose pixel coordinate lies close to a pixel's edge are shot again ray by
+// ray, so that every ray counts in the pixel that k_shoot_irs counts it in: closer
+// than EDGE, or, where pixels are small against the positions, than EDGE_UNITS
+// units in the last place of what a position is the sum of (patch_edge), of which
+// the series' and the rounding's error is a few.
+constexpr double EDGE = 1e-6, EDGE_UNITS = 256.0;
+constexpr double EDGE_MOST = 1.0 / 64.0;   // (beyond this every sixteenth ray or more would be shot again)
 
 // inverse ray shooting of patch blockIdx.x: the patch's counts are summed in an
 // LDS window of W x W pixels about its centre's image (a lane adds a run of
@@ -600,7 +604,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const bool valid = ray_col<P>(col, s) < na && ray_row<P>(row0, s) < nb;
             const double fu = floor(u[s]), fv = floor(v[s]);
             // false for NaN
-            const bool sure = fabs((u[s] - fu) - 0.5) <= 0.5 - EDGE && fabs((v[s] - fv) - 0.5) <= 0.5 - EDGE;
+            const bool sure = fabs((u[s] - fu) - 0.5) <= pa.sure && fabs((v[s] - fv) - 0.5) <= pa.sure;
             if (valid && !sure) again |= 1u << s;
             const int iu = (int)fu, jv = (int)fv;   // (saturating: beyond the map stays beyond)
             const bool in = valid && sure && (unsigned)iu < (unsigned)g.n1 && (unsigned)jv < (unsigned)g.n2;
@@ -634,7 +638,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 }
 
-PatchArgs patch_args(const Region &R, const MapGeom &g, int P)
+// the edge's width in pixels: the rounding of a position in the map, the sum of the
+// lens's linear terms (the smooth sheet's among them), a deflection of about that
+// size and the map's corner
+double patch_edge(const Region &R, const LensConst &lc, const MapGeom &g)
+{
+    const double x = std::max(std::fabs(R.x0), std::fabs(R.x0 + (double)R.nr1 * R.d1));
+    const double y = std::max(std::fabs(R.y0), std::fabs(R.y0 + (double)R.nr2 * R.d2));
+    const double size = (1.0 + std::fabs(lc.lam1) + std::fabs(lc.lam2) + 2.0 * lc.kappa_star) * (x + y) +
+                        std::fabs(g.ylo1) + std::fabs(g.ylo2) + g.pix1 * g.n1 + g.pix2 * g.n2;
+    return std::max(EDGE, EDGE_UNITS * 0x1p-53 * size / std::min(g.pix1, g.pix2));
+}
+
+PatchArgs patch_args(const Region &R, const LensConst &lc, const MapGeom &g, int P)
 {
     PatchArgs pa;
     pa.hx = 0.5 * (P - 1) * R.d1;
@@ -642,6 +658,7 @@ PatchArgs patch_args(const Region &R, const MapGeom &g, int P)
     pa.r = std::sqrt(pa.hx * pa.hx + pa.hy * pa.hy);
     pa.ir = 1.0 / pa.r;
     pa.span = g.pix1 * g.n1 + g.pix2 * g.n2;
+    pa.sure = 0.5 - patch_edge(R, lc, g);
     return pa;
 }
 
@@ -677,6 +694,8 @@ int patch_side(const Region &R, const Tree &T, int64_t rows)
     return per_leaf >= SMALL_PATCH_RAYS_PER_LEAF[rays >= SMALL_PATCH_MANY_RAYS ? 1 : 0] ? 16 : 0;
 }
 
+bool irs_by_patches(const Region &R, const LensConst &lc, const MapGeom &g) { return patch_edge(R, lc, g) <= EDGE_MOST; }
+
 static void patch_coefs(mlm_lens *lens, const Tree &T, const LensConst &lc, const ShootArgs &sa, const PatchArgs &pa,
                         int side, int64_t npatch, hipStream_t st)
 {
@@ -701,7 +720,7 @@ void launch_shoot_patches(mlm_lens *lens, const Tree &T, const Region &R, const 
 {
     if (npatch <= 0) return;
     const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1, vb0, T.p, 0, 0.0};
-    const PatchArgs pa = patch_args(R, g, side);
+    const PatchArgs pa = patch_args(R, lc, g, side);
     patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
     hipLaunchKernelGGL(side == 64 ? k_shoot_patch<64> : side == 32 ? k_shoot_patch<32> : k_shoot_patch<16>, dim3((unsigned)npatch), dim3(64), 0, st, sa, lc, g, pa,
                        lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves, T.near,
@@ -722,7 +741,7 @@ void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const Le
 {
     if (npatch <= 0) return;
     const ShootArgs sa{R.x0, R.y0, R.d1, R.d2, R.nr1 - 1, cb0, T.p, 0, 0.5};
-    const PatchArgs pa = patch_args(R, g, side);
+    const PatchArgs pa = patch_args(R, lc, g, side);
     patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
     // the window: a patch's unlensed image is side d / pixel wide
     const bool wide = side * std::max(R.d1 / R.pix1, R.d2 / R.pix2) > 4.0;
