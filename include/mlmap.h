@@ -124,6 +124,13 @@ mlm_status mlm_lens_create(const mlm_lens_params *params, const double *x, const
 /* Release a lens (NULL is accepted). */
 void mlm_lens_destroy(mlm_lens *lens);
 
+/* Gives back the device and pinned memory that the library keeps for the next
+ * lens (idle blocks of destroyed lenses and grown buffers, at most 4 GiB a
+ * device; without this call a block idle for a minute, or while 64 lenses were
+ * destroyed, goes back when the library next allocates or frees one).  Returns
+ * the bytes of device memory given back.  Lenses in use keep theirs. */
+int64_t mlm_release_memory(void);
+
 /* Derived lens quantities (sec. 2.1, 3.1). */
 typedef struct mlm_lens_info {
     int64_t n_stars;

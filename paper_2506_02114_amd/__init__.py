@@ -34,7 +34,7 @@ EXPORTED = [
     "mlm_refiner_set_params", "mlm_refiner_predict", "mlm_refiner_grads", "mlm_train_opts_init",
     "mlm_refiner_train", "mlm_cell_samples", "mlm_map_noalloc", "mlm_lens_stars", "mlm_field_params_init",
     "mlm_field_moments", "mlm_field_count", "mlm_field_sample", "mlm_field_cover", "mlm_lens_create_sampled",
-    "mlm_philox4x32_10", "mlm_light_curve", "mlm_histogram",
+    "mlm_philox4x32_10", "mlm_light_curve", "mlm_histogram", "mlm_release_memory",
 ]
 
 
@@ -146,6 +146,8 @@ def _lib():
     L.mlm_lens_create.restype = C.c_int
     L.mlm_lens_destroy.argtypes = [vp]
     L.mlm_lens_destroy.restype = None
+    L.mlm_release_memory.argtypes = []
+    L.mlm_release_memory.restype = i64
     L.mlm_lens_get_info.argtypes = [vp, C.POINTER(LensInfo)]
     L.mlm_lens_get_info.restype = C.c_int
     L.mlm_map_request_init.argtypes = [C.POINTER(MapRequest)]
@@ -505,6 +507,12 @@ class Lens:
                                      ptr(ns), ptr(blk), ptr(mult), ptr(loc), n))
         return dict(info=_asdict(I), level=level, i=ix, j=iy, leaf=leaf, nstars=ns, block=blk,
                     mult=mult.view(np.complex128).reshape(n, P1), local=loc.view(np.complex128).reshape(n, P1))
+
+
+def release_memory() -> int:
+    """Give back the device memory kept for the next lens (mlm_release_memory);
+    returns the bytes.  For a program that needs the memory elsewhere."""
+    return _lib().mlm_release_memory()
 
 
 def map_batch(lenses, requests, outs, stream=None, autotune: bool = False, vertex_budget: int = 0):

@@ -34,14 +34,18 @@ std::mutex g_alloc_mu;
 // pool, and 70 ms where the driver had to clear the memory first).  A block is idle
 // when it comes here (its owner has synchronised its device), so any stream or
 // thread may have it next.  At most POOL_BYTES a device are kept; a block that
-// no lens took while POOL_AGE of them were destroyed is freed, and all are when
-// an allocation fails.
+// no lens took while POOL_AGE of them were destroyed, or for POOL_SECONDS, is freed
+// by the next call that gives a block back or allocates one; all are when an
+// allocation fails, and by mlm_release_memory.
 constexpr size_t POOL_BYTES = (size_t)4 << 30;
 constexpr uint64_t POOL_AGE = 64;
+constexpr std::chrono::seconds POOL_SECONDS{60};
+using PoolClock = std::chrono::steady_clock;
 struct Block {
     void *p;
     size_t cap;
     uint64_t epoch;
+    PoolClock::time_point since;   // idle since
 };
 struct Pool {
     std::map<int, std::vector<Block>> dev;         // (all under g_alloc_mu)
@@ -59,9 +63,10 @@ Pool &pool()
 void pool_trim(std::vector<Block> &v, uint64_t epoch, size_t most)
 {
     size_t total = 0;
+    const PoolClock::time_point now = PoolClock::now();
     for (size_t i = v.size(); i-- > 0;) {   // newest last
         total += v[i].cap;
-        if (total <= most && v[i].epoch + POOL_AGE >= epoch) continue;
+        if (total <= most && v[i].epoch + POOL_AGE >= epoch && now - v[i].since < POOL_SECONDS) continue;
         (void)hipFree(v[i].p);
         total -= v[i].cap;
         v.erase(v.begin() + (std::ptrdiff_t)i);
@@ -82,6 +87,7 @@ void *pool_take(size_t bytes, size_t &cap, int &dev)
         v.erase(v.begin() + (std::ptrdiff_t)best);
         return p;
     }
+    pool_trim(v, pool().epoch, POOL_BYTES);
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, bytes);
     if (e == hipErrorOutOfMemory && !v.empty()) {
@@ -98,7 +104,7 @@ void *pool_take(size_t bytes, size_t &cap, int &dev)
 void pool_give(void *p, size_t cap, int dev)
 {
     std::vector<Block> &v = pool().dev[dev];
-    v.push_back(Block{p, cap, pool().epoch});
+    v.push_back(Block{p, cap, pool().epoch, PoolClock::now()});
     pool_trim(v, pool().epoch, POOL_BYTES);
 }
 
@@ -123,7 +129,7 @@ void *host_take(std::map<int, std::vector<Block>> &kind, size_t bytes, unsigned 
 void host_give(std::map<int, std::vector<Block>> &kind, void *p, size_t cap, int dev)
 {
     std::vector<Block> &v = kind[dev];
-    if (v.size() < HOST_BLOCKS && cap <= 65536) v.push_back(Block{p, cap, 0});
+    if (v.size() < HOST_BLOCKS && cap <= 65536) v.push_back(Block{p, cap, 0, {}});
     else (void)hipHostFree(p);
 }
 }
@@ -820,6 +826,22 @@ void mlm_lens_destroy(mlm_lens *lens)
         ++pool().epoch;
     }
     delete lens;
+}
+
+int64_t mlm_release_memory(void)
+{
+    std::lock_guard<std::mutex> g(g_alloc_mu);
+    int64_t bytes = 0;
+    for (auto &d : pool().dev) {
+        for (const Block &b : d.second) bytes += (int64_t)b.cap;
+        pool_trim(d.second, pool().epoch, 0);
+    }
+    for (auto *kind : {&pool().spin, &pool().pinned})
+        for (auto &d : *kind) {
+            for (const Block &b : d.second) (void)hipHostFree(b.p);
+            d.second.clear();
+        }
+    return bytes;
 }
 
 mlm_status mlm_lens_get_info(const mlm_lens *lens, mlm_lens_info *out)
