@@ -189,7 +189,7 @@ void *DevBuf::reserve(size_t bytes)
     if (p && bytes <= cap) return p;
     std::lock_guard<std::mutex> g(g_alloc_mu);
     if (p) {
-        MLM_HIP(hipDeviceSynchronize());   // the old buffer may still be in use by queued work
+        MLM_HIP(wait_idle(dev));   // the old buffer may still be in use by queued work
         pool_give(p, cap, dev);
         p = nullptr;
         cap = 0;
@@ -242,6 +242,15 @@ void DevBuf::release()
     pool_give(p, cap, dev);
     p = nullptr;
     cap = 0;
+}
+
+hipError_t wait_idle(int device)
+{
+    int cur = 0;
+    const bool other = hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess;
+    const hipError_t e = hipDeviceSynchronize();
+    if (other) (void)hipSetDevice(cur);
+    return e;
 }
 
 Workspace::~Workspace()
@@ -816,11 +825,7 @@ mlm_status mlm_field_cover(const mlm_lens_params *params, const mlm_field_params
 void mlm_lens_destroy(mlm_lens *lens)
 {
     if (!lens) return;
-    // the lens's device idle: its buffers may go to another lens
-    int cur = 0;
-    const bool other = hipGetDevice(&cur) == hipSuccess && cur != lens->device && hipSetDevice(lens->device) == hipSuccess;
-    (void)hipDeviceSynchronize();
-    if (other) (void)hipSetDevice(cur);
+    (void)wait_idle(lens->device);   // its buffers may go to another lens
     {
         std::lock_guard<std::mutex> g(g_alloc_mu);
         ++pool().epoch;
@@ -1869,6 +1874,7 @@ mlm_status mlm_refiner_create(const float *params, uint64_t seed, mlm_refiner **
     if (!out) fail(MLM_EINVAL, "out must not be NULL");
     *out = nullptr;
     std::unique_ptr<mlm_refiner> r(new mlm_refiner);
+    MLM_HIP(hipGetDevice(&r->device));
     const size_t nb = (MLM_REFINER_PARAMS + 1) * sizeof(float);
     r->P.reserve(nb);
     r->M.reserve(nb);

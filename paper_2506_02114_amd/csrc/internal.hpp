@@ -283,6 +283,9 @@ struct Workspace {
     ~Workspace();
 };
 
+// waits for everything queued on the device, whichever is the current one
+hipError_t wait_idle(int device);
+
 }  // namespace mlm
 
 struct mlm_lens {
@@ -304,10 +307,11 @@ struct mlm_refiner {
     mlm::DevBuf tstep;     // Adam steps taken (int64, on the device: read by the step kernels)
     mlm::DevBuf lacc;      // loss summed over an epoch's rows (double)
     hipStream_t gst = nullptr;   // training stream (graph capture needs a stream of its own)
+    int device = 0;
     std::mutex mu;
     ~mlm_refiner()
     {
-        (void)hipDeviceSynchronize();   // the buffers go back to the pool idle
+        (void)mlm::wait_idle(device);   // the buffers go back to the pool idle
         if (gst) (void)hipStreamDestroy(gst);
     }
 };
