@@ -100,12 +100,16 @@ void *pool_take(size_t bytes, size_t &cap, int &dev)
     return p;
 }
 
-// an idle block back (g_alloc_mu held)
-void pool_give(void *p, size_t cap, int dev)
+// an idle block back (g_alloc_mu held); destructors call this, so it throws nothing
+void pool_give(void *p, size_t cap, int dev) noexcept
 {
-    std::vector<Block> &v = pool().dev[dev];
-    v.push_back(Block{p, cap, pool().epoch, PoolClock::now()});
-    pool_trim(v, pool().epoch, POOL_BYTES);
+    try {
+        std::vector<Block> &v = pool().dev[dev];
+        v.push_back(Block{p, cap, pool().epoch, PoolClock::now()});
+        pool_trim(v, pool().epoch, POOL_BYTES);
+    } catch (const std::bad_alloc &) {   // (no memory to list it)
+        (void)hipFree(p);
+    }
 }
 
 // the same for host blocks
@@ -126,11 +130,17 @@ void *host_take(std::map<int, std::vector<Block>> &kind, size_t bytes, unsigned 
     return p;
 }
 
-void host_give(std::map<int, std::vector<Block>> &kind, void *p, size_t cap, int dev)
+void host_give(std::map<int, std::vector<Block>> &kind, void *p, size_t cap, int dev) noexcept
 {
-    std::vector<Block> &v = kind[dev];
-    if (v.size() < HOST_BLOCKS && cap <= 65536) v.push_back(Block{p, cap, 0, {}});
-    else (void)hipHostFree(p);
+    try {
+        std::vector<Block> &v = kind[dev];
+        if (v.size() < HOST_BLOCKS && cap <= 65536) {
+            v.push_back(Block{p, cap, 0, {}});
+            return;
+        }
+    } catch (const std::bad_alloc &) {
+    }
+    (void)hipHostFree(p);
 }
 }
 
