@@ -254,6 +254,18 @@ void DevBuf::release()
     cap = 0;
 }
 
+void allow_lds(const void *kernel, size_t bytes)
+{
+    static std::mutex mu;
+    static std::set<std::pair<const void *, int>> done;
+    int dev = 0;
+    MLM_HIP(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> g(mu);
+    if (done.count({kernel, dev})) return;
+    MLM_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    done.insert({kernel, dev});
+}
+
 hipError_t wait_idle(int device)
 {
     int cur = 0;

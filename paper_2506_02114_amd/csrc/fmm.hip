@@ -649,9 +649,7 @@ void run_fmm_t(mlm_lens *lens, Tree &T, int p, bool all, hipStream_t st, typenam
     // levels 0, 1 have no far field
     constexpr int per = BLK / 32;
     constexpr size_t most = (4 * (MAX_ORDER + 1) * (MAX_ORDER + 1) + per * 4 * (MAX_ORDER + 1)) * sizeof(C2);
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_upward<R>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
-    MLM_HIP(attr);
+    allow_lds(reinterpret_cast<const void *>(&k_upward<R>), most);
     const UpArgs u{p, T.L0, T.code, T.leaf, T.slo, T.shi, T.child0, T.x, T.y, T.m};
     const int64_t none = T.nlevels > 2 ? T.level_lo[2] : T.nnodes;
     const int top = all ? 0 : std::min(2, T.nlevels - 1);

@@ -566,6 +566,8 @@ void mlp_zero(float *p, int64_t n, hipStream_t st);
 void mlp_step_reset(int64_t *tstep, double *lacc, bool steps, hipStream_t st);
 
 // helpers
+// allows a kernel `bytes` of dynamic LDS on the current device (once for each)
+void allow_lds(const void *kernel, size_t bytes);
 void *pinned(mlm_lens *lens, size_t bytes);
 // host memory the device writes coherently while it runs (zeroed)
 void *coherent_pinned(size_t bytes, size_t &cap, int &dev);

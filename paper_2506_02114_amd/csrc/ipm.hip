@@ -2010,10 +2010,7 @@ void launch_band_queue(const BatchMap *maps, int32_t nmaps, const BandItem *item
                        const ItemParts &parts, unsigned long long *queue, const int32_t *list, const BigPrep *prep,
                        int64_t lds_doubles, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_queue),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)(BAND_LDS_DOUBLES * sizeof(double)));
-    MLM_HIP(attr);
+    allow_lds(reinterpret_cast<const void *>(&k_band_queue), BAND_LDS_DOUBLES * sizeof(double));
     if (lds_doubles > BAND_LDS_DOUBLES) fail(MLM_EINVAL, "band of %lld doubles exceeds LDS", (long long)lds_doubles);
     if (nitems <= 0) return;
     if (parts.lo[0] != 0 || parts.lo[NXCD] != nitems) fail(MLM_EINVAL, "band item ranges do not cover the items");
@@ -2029,10 +2026,7 @@ void launch_band_queue1(const BandItem *items, int64_t nitems, const ItemParts &
                         const int32_t *list, const BigPrep *prep, int bh, const MapGeom &g, double *map,
                         unsigned long long *work, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_queue1),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)(BAND_LDS_DOUBLES * sizeof(double)));
-    MLM_HIP(attr);
+    allow_lds(reinterpret_cast<const void *>(&k_band_queue1), BAND_LDS_DOUBLES * sizeof(double));
     if (nitems <= 0) return;
     if (parts.lo[0] != 0 || parts.lo[NXCD] != nitems) fail(MLM_EINVAL, "band item ranges do not cover the items");
     const size_t shmem = (size_t)bh * (size_t)g.n1 * sizeof(double);
