@@ -1618,10 +1618,13 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
     std::vector<char> done((size_t)nmaps, 0);
     std::atomic<double> prep_ms{0.0};
     const auto t_prep0 = std::chrono::steady_clock::now();
+    int device = 0;
+    MLM_HIP(hipGetDevice(&device));
     auto prep_worker = [&](int t) {
         const hipStream_t ps = B.prep_st[t];
         Timer &pt = *ptm[t];
         try {
+            MLM_HIP(hipSetDevice(device));   // (a new thread's is the first one)
             MLM_HIP(hipStreamWaitEvent(ps, go, 0));
             for (int32_t i = next++; i < nmaps && !failed; i = next++) {
                 MapPlan &m = P[i];
