@@ -51,8 +51,10 @@ __device__ inline int hist_bin(double m, double lo, double inv_w, int nbins)
 
 // The same bin, mostly without the FP64 logarithm (some 90 instructions): from
 // log2 of the mantissa in FP32, good to 2^-22, so a position within eps bins of a
-// bin's edge is formed again in full.  eps: HIST_EPS bins' widths in log10.
-constexpr double HIST_EPS = 5e-7;
+// bin's edge is formed again in full.  eps: HIST_EPS in log10, and the rounding of
+// the differences from a far lower end (HIST_ROUND of the ends' size: half a unit of
+// the difference and of the product, in either form), in bins.
+constexpr double HIST_EPS = 5e-7, HIST_ROUND = 0x1p-50;
 __device__ inline int hist_bin_fast(double m, double lo, double inv_w, int nbins, double eps)
 {
     // (0.30103 = log10 2; the exponent of zeros, infinities and NaN is 0 here)
@@ -71,14 +73,13 @@ __device__ inline int hist_bin_fast(double m, double lo, double inv_w, int nbins
 // 32; its 32 MB take 7).  head: pixels before the first 16-byte boundary (0 or
 // 1), pairs: pairs of pixels behind it.
 __global__ __launch_bounds__(HIST_BLK) void k_histogram(const double *__restrict__ mu, int64_t npix, int head,
-                                                        int64_t pairs, double lo, double inv_w, int nbins,
+                                                        int64_t pairs, double lo, double inv_w, int nbins, double eps,
                                                         unsigned long long *__restrict__ counts)
 {
     extern __shared__ unsigned h[];   // (a workgroup's share is far below 2^32 pixels)
     const int nb = nbins + 2;
     for (int b = threadIdx.x; b < nb; b += blockDim.x) h[b] = 0;
     __syncthreads();
-    const double eps = HIST_EPS * inv_w;
     auto put = [&](double m) { atomicAdd(&h[hist_bin_fast(m, lo, inv_w, nbins, eps)], 1u); };
     const double2 *mp = reinterpret_cast<const double2 *>(mu + head);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x, k0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -139,12 +140,13 @@ void launch_histogram(const double *mu, int64_t npix, double lo, double hi, int 
     if (npix <= 0) return;
     const double inv_w = (double)nbins / (hi - lo);
     if (nb <= HIST_MAX_LDS_BINS) {
+        const double eps = (HIST_EPS + HIST_ROUND * (std::fabs(lo) + std::fabs(hi))) * inv_w;
         const int head = (reinterpret_cast<uintptr_t>(mu) & 15) ? 1 : 0;   // (mu is aligned to its doubles)
         const int64_t pairs = (npix - head) / 2;
         const int64_t want = (npix + HIST_BLK * 16 - 1) / (HIST_BLK * 16);
         const unsigned grid = (unsigned)std::min<int64_t>(std::max<int64_t>(want, 1), 512);
         hipLaunchKernelGGL(k_histogram, dim3(grid), dim3(HIST_BLK), (size_t)nb * sizeof(unsigned), st, mu, npix, head,
-                           pairs, lo, inv_w, nbins, counts);
+                           pairs, lo, inv_w, nbins, eps, counts);
     } else {
         hipLaunchKernelGGL(k_histogram_global, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, mu, npix, lo,
                            inv_w, nbins, counts);
