@@ -481,7 +481,7 @@ int order_for(const mlm_map_request &q, const Region &R, const Tree &T)
 }
 
 void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats,
-              const Region *region = nullptr);
+              const Region *region = nullptr, bool as_batch = false);
 
 // Autotuner of a class of maps (precision, order, log2 of rays per star):
 // 1. the leaf size (the split threshold of app. C.1) that minimises the time
@@ -542,7 +542,8 @@ Tuned tune_map(mlm_lens *lens, const mlm_map_request &q, const Region &R, hipStr
         }
     }
     if (q.mapping == MLM_MAP_IPM) {
-        // the sample strip mapped whole (device timing of the call) at each band threshold
+        // the sample strip mapped whole (device timing of the call) at each band
+        // threshold, by the passes that a batch has
         const int64_t npix = (int64_t)q.n1 * q.n2;
         double *mu = static_cast<double *>(lens->ws.tune_map.reserve((size_t)npix * sizeof(double)));
         double best_t = 1e300;
@@ -558,7 +559,7 @@ Tuned tune_map(mlm_lens *lens, const mlm_map_request &q, const Region &R, hipStr
             qc.refine = MLM_REFINE_NONE;
             qc.w_out = nullptr;
             mlm_map_stats S{};
-            map_impl(lens, &qc, mu, &S);
+            map_impl(lens, &qc, mu, &S, nullptr, true);
             const double t = S.t_total_ms - S.t_tree_ms - S.t_fmm_ms;
             if (t < best_t) {
                 best_t = t;
@@ -978,9 +979,10 @@ void apportion_bands(mlm_lens *lens, int64_t nb, int bh, const MapGeom &g, doubl
 }
 
 // one map (the body of mlm_map and of mlm_map_noalloc); the lens is locked
-// (region: its region, if the caller has it)
+// (region: its region, if the caller has it; as_batch: by the passes of a batch,
+// rays one by one and triangles by k_ipm_batch, whose threshold is being timed)
 void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_stats *stats,
-              const Region *region)
+              const Region *region, bool as_batch)
 {
     const mlm_map_request &q = *req;
     Region R{};
@@ -1117,7 +1119,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                                                                      : 0;
         // (cell refinement shoots its rays one by one, and its decisions compare
         // them with the grid's: those go the same way there)
-        const bool single = q.w_out || q.refine != MLM_REFINE_NONE || thread_arena();
+        const bool single = q.w_out || q.refine != MLM_REFINE_NONE || thread_arena() || as_batch;
         const int side = fmm && !single ? patch_side(R, T, cb1 - cb0 + 1) : 0;
         for (int64_t r0 = cb0; r0 < cb1; ++nstrips) {
             int64_t r1 = std::min(cb1, r0 + rows_per_strip - 1);   // cells [r0, r1), vertex rows [r0, r1]
@@ -1143,7 +1145,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             const int bh = band_height(g.n1, g.n2);
             BigList bl;
             bl.count = static_cast<unsigned long long *>(ws.bigcount.reserve(BIG_SHARDS * BIG_STRIDE * sizeof(unsigned long long)));
-            if (!thread_arena()) {
+            if (!thread_arena() && !as_batch) {
                 bl.cap = std::max<int64_t>(1024, (ncells / BIG_CELLS_PER_SLOT + BIG_SHARDS - 1) / BIG_SHARDS);
                 bl.list = static_cast<int64_t *>(ws.biglist.reserve((size_t)(BIG_SHARDS * bl.cap) * sizeof(int64_t)));
             }
@@ -1155,7 +1157,27 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 thin.cell = reinterpret_cast<int64_t *>(thin.corner + 4 * THIN_CELLS);
                 thin.count = reinterpret_cast<unsigned *>(thin.cell + THIN_CELLS);
             }
-            launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, thin, q.precision == MLM_PREC_MIXED, pass, work, st);
+            const auto tile_counts = [&] {
+                return static_cast<int32_t *>(ws.tbig.reserve((size_t)std::max<int64_t>(ntl, 1) * sizeof(int32_t)));
+            };
+            if (as_batch) {   // (the strip as the only map of a batch)
+                BatchMap d{};
+                d.nr1 = R.nr1;
+                d.nrows = r1 - r0;
+                d.g = g;
+                d.verts = verts;
+                d.map = map;
+                d.counters = cnt;
+                d.mixed = q.precision == MLM_PREC_MIXED;
+                BatchMap *dm = static_cast<BatchMap *>(ws.tune_desc.reserve(sizeof d));
+                MLM_HIP(hipMemcpyAsync(dm, &d, sizeof d, hipMemcpyHostToDevice, st));
+                MLM_HIP(hipStreamSynchronize(st));
+                int32_t *tbig = tile_counts();
+                hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((ntl + 255) / 256)), dim3(256), 0, st, tbig, ntl);
+                launch_ipm_batch(dm, 1, ntl, tbig, st);
+            } else {
+                launch_ipm(verts, R.nr1, r0, r1, vb0, g, map, cnt, bl, thin, q.precision == MLM_PREC_MIXED, pass, work, st);
+            }
             if (thin.count) {
                 launch_shoot_thin(T, R, lc, g, r0, vb0, thin, verts, st);
                 launch_ipm_thin(verts, R.nr1, r0, vb0, g, map, cnt, bl, thin, work, st);
@@ -1166,9 +1188,9 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
             int64_t nb = at.lo[BIG_SHARDS];
             int64_t *toff = nullptr;
             if (!listed) {
-                int32_t *tbig = static_cast<int32_t *>(ws.tbig.reserve((size_t)std::max<int64_t>(ntl, 1) * sizeof(int32_t)));
+                int32_t *tbig = tile_counts();
                 toff = static_cast<int64_t *>(ws.tbigoff.reserve((size_t)(ntl + 1) * sizeof(int64_t)));
-                launch_big_count(verts, R.nr1, r0, r1, vb0, g, tbig, st);
+                if (!as_batch) launch_big_count(verts, R.nr1, r0, r1, vb0, g, tbig, st);
                 nb = scan_i32_to_i64(lens, tbig, toff, ntl, st);
             }
             // set-ups are kept over the strips and banded together, as far as

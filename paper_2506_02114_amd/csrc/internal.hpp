@@ -271,7 +271,7 @@ struct Workspace {
     DevBuf search;
     DevBuf binom, patch_info, patch_coef, thin;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
-        bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map;
+        bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map, tune_desc;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
     int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
