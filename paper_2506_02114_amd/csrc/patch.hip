@@ -688,6 +688,13 @@ PatchArgs patch_args(const Region &R, const LensConst &lc, const MapGeom &g, int
 int patch_side(const Region &R, const Tree &T, int64_t rows)
 {
     if (T.mixed || T.p < 1) return 0;
+    // leaves that mostly hold more near stars than a patch takes would go ray by ray,
+    // and there more slowly than by k_shoot.  Shooting ray by ray / by patches, ms, by
+    // the mean number of a ray's near stars (8 rays a pixel; inverse ray shooting of
+    // 60): 46: 2.30 / 0.42 (16.4 / 1.9); 53: 2.49 / 1.30 (16.9 / 3.2); 63: 2.52 /
+    // 2.18 (17.7 / 11.1) and 4.09 / 3.89 (28.7 / 24.7); 76: 2.66 / 2.95 (18.8 / 19.0);
+    // 78: 2.03 / 2.31 (13.9 / 16.7).
+    if (T.near_total > PC_STARS * T.nactive_leaves) return 0;
     const double rays = (double)R.nr1 * (double)rows, per_leaf = rays / (double)std::max<int64_t>(T.nactive_leaves, 1);
     if (per_leaf >= LARGE_PATCH_RAYS_PER_LEAF && rays >= PATCH_MANY_RAYS) return 64;
     if (per_leaf >= PATCH_RAYS_PER_LEAF[rays >= PATCH_MANY_RAYS ? 1 : 0]) return 32;

@@ -63,3 +63,23 @@ def test_ipm_map_equals_ray_by_ray(name):
     _, sr = lens.map(out=ref, w_out=w, **req)
     assert st["n_tiles"] < sr["n_tiles"] / 2
     assert float((out - ref).norm() / ref.norm()) < 1e-9
+
+
+@pytest.mark.parametrize("mapping", ["ipm", "irs"])
+@pytest.mark.parametrize("leaf_max,patches", [(32, True), (64, True), (256, False), (1000, False)])
+def test_leaves_of_many_stars_are_shot_ray_by_ray(leaf_max, patches, mapping):
+    """A patch takes at most 64 near stars of its leaf: where leaves mostly hold
+    more, patches would be the slower way."""
+    import torch
+    import paper_2506_02114_amd as mlm
+    torch.cuda.init()
+    sf = W.star_field(5000, 0.4, "salpeter", seed=3)
+    lens = mlm.Lens(0.4, 0.1, 0.2, sf.x, sf.y, sf.m, sheet="none")
+    req = dict(hw1=6.0, hw2=6.0, n1=100, n2=100, rays_per_pixel=400.0, leaf_max=leaf_max, mapping=mapping)
+    got, st = lens.map(**req)
+    ref, sr = lens.map(noalloc=True, **req)
+    assert (st["n_tiles"] < sr["n_tiles"] / 2) == patches
+    if mapping == "irs":
+        assert np.array_equal(got, ref)
+    else:
+        assert np.linalg.norm(got - ref) < 1e-9 * np.linalg.norm(ref)
