@@ -314,7 +314,7 @@ constexpr int64_t BIG_HOLD = 4ll << 20;       // large triangles kept over strip
 constexpr int64_t BIG_CELLS_PER_SLOT = 4;     // cells per entry of the large-triangle lists
 constexpr double QUEUE_CELLS_PER_PIXEL = 64.0;   // cells per map pixel from which the cell pass queues (k_ipm_fine)
 constexpr double MID_CELLS_PER_PIXEL = 30.0;     // cells per map pixel from which k_ipm's window is the smaller one
-constexpr double FINE_CELLS_PER_PIXEL = 400.0;  // cells per map pixel from which the cell pass is k_ipm_fine
+constexpr double FINE_CELLS_PER_PIXEL = 900.0;   // cells per map pixel from which k_ipm_fine's window is the smaller one
 
 __global__ void k_fill(double *p, int64_t n, double v)
 {
@@ -1104,8 +1104,13 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         // the cells divide a pixel on average).  Measured, k_ipm against
         // k_ipm_fine with its 48-pixel window: at 14 cells a pixel 4.3 and 5.5 ms
         // (1e5-star map), at 55 (elongated cells) 0.43 and 0.46, at 60 4.9 and
-        // 5.5, at 78 1.5 and 1.2, at 90 0.48 and 0.39; the 24-pixel window at 900
-        // and at 1300.  k_ipm with its 48-pixel window and with its 32-pixel one: at
+        // 5.5, at 78 1.5 and 1.2, at 90 0.48 and 0.39.  k_ipm_fine with its 48-pixel
+        // window and with its 24-pixel one, on 600^2-pixel maps of magnification 1000
+        // and (in brackets) of ordinary and of elongated cells: at 100 1.52 and 2.19
+        // (0.88 and 1.18, 0.79 and 1.15), at 400 2.12 and 2.16 (2.28 and 2.55, 1.92 and
+        // 2.17), at 600 2.56 and 2.51 (3.11 and 3.28, 2.92 and 3.01), at 900 3.45 and
+        // 3.34 (4.32 and 4.34, 3.56 and 3.67), at 1300 on 300^2 pixels 1.22 and 1.17
+        // (1.56 and 1.52, 1.25 and 1.23).  k_ipm with its 48-pixel window and with its 32-pixel one: at
         // 14 cells a pixel 3.94 and 4.63 ms (1e5-star map), at 18 0.150 and 0.141 or
         // (elongated cells) 0.177 and 0.179, at 34 0.257 and 0.243, at 37 4.84 and
         // 4.66 (a map across a fold caustic), at 60 4.82 and 4.79.

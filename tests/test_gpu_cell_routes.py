@@ -6,10 +6,10 @@ which the other way counts as large, or the reverse, loses it or counts it twice
 
 Tolerances: 1e-9 relative as in test_gpu_cells.py, whose cells are at least 1e-4
 pixels thick.  The elongated cells of the overflowing lists fold to triangles
-1.7e-8, 1.0e-8 and 3.9e-9 pixels thick (from the positions in 64 bits); the rounding
-of a position below 64 pixels, 1.4e-14, is 3.6e-6 of the thinnest one, and a
-triangle's deposits are quotients by its area, so each pixel may be off by that much
-of a triangle's weight besides.
+1.7e-8, 1.0e-8 and 2.5e-9 pixels thick (from the positions in 64 bits); the rounding
+of a position below 64, 64 and 16 pixels, 1.4e-14 and 3.6e-15, is up to 1.4e-6 of
+that, and a triangle's deposits are quotients by its area, so each pixel may be off
+by a few times that, 3.6e-6, of a triangle's weight besides.
 """
 import numpy as np
 import pytest
@@ -23,13 +23,13 @@ GRIDS = {
     "window_48": ((40, 40), (65, 66)),            # 2.6 cells a pixel
     "window_32": ((20, 20), (131, 117)),          # 38
     "fine_48": ((16, 16), (131, 165)),            # 84
-    "fine_24": ((8, 8), (201, 185)),              # 575
+    "fine_24": ((6, 6), (201, 185)),              # 1022
 }
 OVERFLOW = {   # all rays inside the map, the cells of the last three several pixels long
     "window_48": ((300, 300), (401, 397)),        # 1.8 cells a pixel
     "window_32": ((64, 64), (11, 16001)),         # 39
     "fine_48": ((64, 64), (11, 30001)),           # 73
-    "fine_24": ((24, 24), (11, 30001)),           # 521
+    "fine_24": ((16, 16), (5, 60001)),            # 938
 }
 
 
