@@ -163,7 +163,8 @@ Arena *&thread_arena()
 void *Arena::take(size_t bytes)
 {
     const size_t b = (bytes + 255) & ~(size_t)255;
-    if (b > cap - used)
+    exhausted = b > cap - used;
+    if (exhausted)
         fail(MLM_ERANGE, "the scratch array of %zu MiB is exhausted (%zu bytes more needed); mlm_map takes this map",
              cap >> 20, b - (cap - used));
     void *q = base + used;
@@ -1085,10 +1086,11 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
     } else {
         int64_t rows_per_strip = STRIP_VERTS / R.nr1;
         if (Arena *a = thread_arena()) {
-            // inside a scratch arena the vertex strip takes at most a quarter of
-            // what is left; the rest serves the IPM's per-strip buffers
-            const int64_t fit = (int64_t)((a->cap - a->used) / 4 / (sizeof(double2) * (size_t)R.nr1));
+            // inside a scratch arena the vertex strip takes a quarter of what is
+            // left, or less; the rest serves the IPM's per-strip buffers
+            const int64_t fit = (int64_t)((a->cap - a->used) / a->strip_share / (sizeof(double2) * (size_t)R.nr1));
             rows_per_strip = std::min(rows_per_strip, fit);
+            a->strips = fit > 2;   // (smaller strips are possible)
         }
         if (rows_per_strip < 2) rows_per_strip = 2;
         int64_t nbuf = rows_per_strip * R.nr1;
@@ -1444,11 +1446,22 @@ mlm_status mlm_map_noalloc(mlm_lens *lens, const mlm_map_request *req, double *m
              need / 1048576.0, SCRATCH_BYTES >> 20);
     std::lock_guard<std::mutex> sguard(g_scratch_mu[dev]);
     std::lock_guard<std::mutex> guard(lens->mu);
-    Arena a;
-    a.base = scratch_on(dev);
-    a.cap = SCRATCH_BYTES;
-    ArenaScope scope(a, lens->ws, stream_of(req));
-    map_impl(lens, req, mu, stats, &R);
+    // what the large triangles of a strip need is known only when they are met:
+    // where it does not fit beside a quarter's strip, the map is made again by
+    // strips of an eighth
+    for (int64_t share = 4;; share = 8) {
+        Arena a;
+        a.base = scratch_on(dev);
+        a.cap = SCRATCH_BYTES;
+        a.strip_share = share;
+        try {
+            ArenaScope scope(a, lens->ws, stream_of(req));
+            map_impl(lens, req, mu, stats, &R);
+            break;
+        } catch (const Error &) {
+            if (!a.strips || !a.exhausted || share == 8) throw;
+        }
+    }
     API_END
 }
 

@@ -54,6 +54,8 @@ struct Arena {
     static constexpr int MAX_BUFS = 128;
     char *base = nullptr;
     size_t cap = 0, used = 0;
+    int64_t strip_share = 4;    // the vertex strip takes at most this part of what is left
+    bool strips = false, exhausted = false;   // whether the strips have begun; a slice was refused
     struct Saved {
         DevBuf *buf;
         void *p;
