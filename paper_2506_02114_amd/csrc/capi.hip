@@ -315,6 +315,7 @@ constexpr int64_t BIG_HOLD = 4ll << 20;       // large triangles kept over strip
 constexpr int64_t BIG_CELLS_PER_SLOT = 4;     // cells per entry of the large-triangle lists
 constexpr double QUEUE_CELLS_PER_PIXEL = 64.0;   // cells per map pixel from which the cell pass queues (k_ipm_fine)
 constexpr double MID_CELLS_PER_PIXEL = 30.0;     // cells per map pixel from which k_ipm's window is the smaller one
+constexpr int64_t QUEUE_CELLS = 4000000;         // cells of a strip from which it does
 constexpr double FINE_CELLS_PER_PIXEL = 900.0;   // cells per map pixel from which k_ipm_fine's window is the smaller one
 
 __global__ void k_fill(double *p, int64_t n, double v)
@@ -1118,8 +1119,14 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
         // 4.66 (a map across a fold caustic), at 60 4.82 and 4.79.
         const double cells_px = (double)(R.nr1 - 1) * (double)(R.nr2 - 1) / ((double)g.n1 * (double)g.n2);
         // (k_ipm_fine apportions what lies within two pixels itself: not where a
-        // triangle of two is a large one)
-        const bool fine = g.big_px >= 2;
+        // triangle of two is a large one.  And not in strips of few cells, as inside a
+        // scratch arena: its workgroups take 1024 cells where k_ipm's take 256, too
+        // few to fill the chip.  k_ipm with its 32-pixel window and k_ipm_fine, at 150
+        // cells a pixel: of 0.25e6 cells 0.028 and 0.051 ms, 1e6 0.052 and 0.078, 4e6
+        // 0.114 and 0.138, 8e6 0.194 and 0.207; at 600: 0.025 and 0.036, 0.043 and
+        // 0.054, 0.101 and 0.113, 0.170 and 0.163; at 1000: 4e6 0.096 and 0.095.)
+        const int64_t strip_cells = (R.nr1 - 1) * std::min(rows_per_strip - 1, cb1 - cb0);
+        const bool fine = g.big_px >= 2 && strip_cells >= QUEUE_CELLS;
         const int pass = fine && cells_px >= FINE_CELLS_PER_PIXEL    ? 3
                          : fine && cells_px >= QUEUE_CELLS_PER_PIXEL ? 2
                          : cells_px >= MID_CELLS_PER_PIXEL           ? 1

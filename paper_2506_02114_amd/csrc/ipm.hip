@@ -436,7 +436,7 @@ __device__ inline void write_big(const BigList &bl, const BigRange &r, int big, 
     int64_t k = (int64_t)__shfl(r.base, 0, 64) + r.at;
     for (int m = 0; m < 2; ++m)
         if (big >> m & 1) {
-            if (k < bl.cap) bl.list[sh * bl.cap + k] = 2 * cell + m;
+            if ((unsigned long long)k < (unsigned long long)bl.cap) bl.list[sh * bl.cap + k] = 2 * cell + m;
             ++k;
         }
 }
@@ -1833,7 +1833,10 @@ void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int
     const int64_t nrows = cb1 - cb0, ncol = nr1 - 1;
     const int64_t tiles = fine ? ((ncol + FC - 1) / FC) * ((nrows + FROWS - 1) / FROWS) : ipm_tile_count(nr1, nrows);
     if (ncol <= 0 || nrows <= 0) return;
-    hipLaunchKernelGGL(k_zero_shards, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count, thin.count);
+    // (where no lists are kept, inside a scratch arena, their counts are not read and
+    // need not start at zero: with this launch too a strip there took 12 us longer, a
+    // map of 300 strips 27.4 instead of 23.4 ms)
+    if (bl.cap > 0) hipLaunchKernelGGL(k_zero_shards, dim3(1), dim3(BIG_SHARDS), 0, st, bl.count, thin.count);
     if (fine) {
         auto *k = pass == 3 ? (mixed ? k_ipm_fine<true, WIN_FINE> : k_ipm_fine<false, WIN_FINE>)
                             : (mixed ? k_ipm_fine<true, WIN> : k_ipm_fine<false, WIN>);

@@ -3,6 +3,8 @@ keeps (mlm_map) and counted and gathered by cell tiles (mlm_map_noalloc, and
 mlm_map where a list overflows), for every cell pass and threshold of "large",
 against the oracle's clipping of every triangle.  A pass that deposits a triangle
 which the other way counts as large, or the reverse, loses it or counts it twice.
+(The densities named fine_* take k_ipm_fine only in strips of 4e6 cells and more:
+test_gpu_fine_pass.py.)
 
 Tolerances: 1e-9 relative as in test_gpu_cells.py, whose cells are at least 1e-4
 pixels thick.  The elongated cells of the overflowing lists fold to triangles
