@@ -1244,9 +1244,9 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                     const int64_t nm = (n + 63) / 64;
                     uint64_t *mask = static_cast<uint64_t *>(ws.rmask.reserve((size_t)nm * sizeof(uint64_t)));
                     int32_t *mcnt = static_cast<int32_t *>(ws.rcount.reserve((size_t)nm * sizeof(int32_t)));
-                    int64_t *pos = static_cast<int64_t *>(ws.rtpos.reserve((size_t)(nm + 1) * sizeof(int64_t)));
+                    int64_t *pos = static_cast<int64_t *>(ws.rtpos.reserve((size_t)nm * sizeof(int64_t)));
                     flag_them(mask, mcnt);
-                    count = scan_i32_to_i64(lens, mcnt, pos, nm, st);
+                    count = scan_excl(lens, mcnt, pos, nm, st);
                     int64_t *item = static_cast<int64_t *>(to.reserve((size_t)std::max<int64_t>(count, 1) * sizeof(int64_t)));
                     if (count > 0) launch_list_flagged(n, mask, pos, from, item, st);
                     return item;
@@ -1276,11 +1276,10 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 DevBuf *next = &ws.rsub0;
                 for (int d = 0; d < q.refine_depth && nlev > 0; ++d) {
                     uint8_t *flag = static_cast<uint8_t *>(ws.rtflag.reserve((size_t)nlev));
-                    launch_refine_test(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, cand, list,
-                                       R.nr1, vb0, verts, flag, rst3, st);
                     int64_t nref = 0;
                     const int64_t *item = listed(nlev, [&](uint64_t *mask, int32_t *mcnt) {
-                        launch_flag_masks(nlev, flag, mask, mcnt, st);
+                        launch_refine_test(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, cand, list,
+                                           R.nr1, vb0, verts, flag, mask, mcnt, rst3, st);
                     }, ws.ritem, 0, nref);
                     if (d == 0) n_refined += nref;
                     if (nref == 0) break;

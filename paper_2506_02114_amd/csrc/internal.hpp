@@ -494,6 +494,8 @@ void launch_band_queue(const BatchMap *maps, int32_t nmaps, const BandItem *item
 void launch_band_queue1(const BandItem *items, int64_t nitems, const ItemParts &parts, unsigned long long *queue,
                         const int32_t *list, const BigPrep *prep, int bh, const MapGeom &g, double *map,
                         unsigned long long *work, hipStream_t st);
+// exclusive prefix sums of n counts (the total is returned, not stored)
+int64_t scan_excl(mlm_lens *lens, const int32_t *in, int64_t *out, int64_t n, hipStream_t st);
 int64_t scan_i32_to_u64(mlm_lens *lens, const int32_t *in, unsigned long long *out, int64_t n, hipStream_t st);
 
 // scan.hip: device-wide prefix sums (tmp: scan_tmp_bytes(n)); the total is
@@ -527,9 +529,11 @@ void launch_histogram(const double *mu, int64_t npix, double lo, double hi, int 
 constexpr int REFINE_SLOTS = 256;
 constexpr int REFINE_STRIDE = 16;
 size_t refine_subcell_bytes();
+// (flag: a byte per item of scratch; the refined items as masks of 64 with their counts)
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, uint8_t *flag, unsigned long long *stats, hipStream_t st);
+                        const double2 *verts, uint8_t *flag, uint64_t *mask, int32_t *cnt, unsigned long long *stats,
+                        hipStream_t st);
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                           int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
                           int64_t vb0, const double2 *verts, const int64_t *item, double *map, void *out, hipStream_t st);
@@ -537,9 +541,8 @@ void launch_sample_features(const Tree &T, const Region &R, const LensConst &lc,
                             const int64_t *ab, float *feats, hipStream_t st);
 void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau,
                           int window, int64_t n, const int64_t *ab, uint8_t *label, hipStream_t st);
-// flags as masks of 64 with their counts, and the flagged base + t in order (pos:
-// exclusive scan of the counts; no mask: all of them)
-void launch_flag_masks(int64_t n, const uint8_t *flag, uint64_t *mask, int32_t *cnt, hipStream_t st);
+// the flagged base + t in order (pos: exclusive scan of the masks' counts; no mask:
+// all of them)
 void launch_list_flagged(int64_t n, const uint64_t *mask, const int64_t *pos, int64_t base, int64_t *item, hipStream_t st);
 
 // mlp.hip

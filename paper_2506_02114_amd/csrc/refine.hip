@@ -511,50 +511,54 @@ __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void 
     add_stats(stats, t < n ? 1 : 0, v == REFINE ? 1 : 0, large);
 }
 
-// The items of a level that need the test `kind`: a workgroup reads REST flags,
-// gathers those items in LDS and tests them with full lanes.
+// The items of a level that need one of the other tests: a workgroup reads REST
+// verdicts, gathers those items in LDS by their test and tests them with full lanes,
+// a wavefront one kind at a time.  Then 64 items' verdicts each make one mask, with
+// its number of refined items (a scan of these, and not of the items' flags, numbers
+// the refined ones: with 4-byte flags and 8-byte places of every item, numbering the
+// cells and subcells of the learned refinement of a 400 x 400 map moved 17 GB).
+// (One launch: by a launch for each test and one for the masks a small map's
+// refinement, three levels of launches, took 30 us longer.)
 constexpr int REST = 1024;
-template <int kind>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_rest(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
                                                      const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                     const double2 *__restrict__ verts, uint8_t *__restrict__ flag,
+                                                     const double2 *__restrict__ verts, const uint8_t *__restrict__ flag,
+                                                     uint64_t *__restrict__ mask, int32_t *__restrict__ cnt,
                                                      unsigned long long *__restrict__ stats)
 {
-    __shared__ unsigned short queue[REST];
-    __shared__ int nq;
-    if (threadIdx.x == 0) nq = 0;
+    __shared__ unsigned short queue[2][REST];
+    __shared__ uint8_t refined[REST];
+    __shared__ int nq[2];
+    if (threadIdx.x < 2) nq[threadIdx.x] = 0;
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * REST;
-    for (int k = threadIdx.x; k < REST; k += blockDim.x)
-        if (lo + k < n && flag[lo + k] == kind) queue[atomicAdd(&nq, 1)] = (unsigned short)k;
-    __syncthreads();
-    const int m = nq;
-    for (int k0 = threadIdx.x & ~63; k0 < m; k0 += 256) {   // the same for a whole wavefront
-        const int k = k0 + (threadIdx.x & 63);
-        int refined = 0;
-        if (k < m) {
-            const int64_t t = lo + queue[k];
-            const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
-            int large = 0;
-            refined = refine_test<kind>(ra, c, large) == REFINE ? 1 : 0;   // (not too large: that was decided)
-            flag[t] = (uint8_t)refined;
-        }
-        add_stats(stats, 0, refined, 0);
+    for (int k = threadIdx.x; k < REST; k += blockDim.x) {
+        const int v = lo + k < n ? flag[lo + k] : KEEP;
+        refined[k] = v == REFINE;
+        if (v >= NEEDS_BOX) queue[v - NEEDS_BOX][atomicAdd(&nq[v - NEEDS_BOX], 1)] = (unsigned short)k;
     }
-}
-
-// 64 items' flags as one mask, and how many are set (a scan of these, and not of
-// the items' flags, numbers the flagged ones: with 4-byte flags and 8-byte places
-// of every item, numbering the cells and subcells of the learned refinement of a
-// 400 x 400 map moved 17 GB)
-__global__ __launch_bounds__(256) void k_flag_masks(int64_t n, const uint8_t *__restrict__ flag,
-                                                    uint64_t *__restrict__ mask, int32_t *__restrict__ cnt)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t m = __ballot(t < n && flag[t] != 0);
-    if ((threadIdx.x & 63) == 0 && t < n) {
-        mask[t >> 6] = m;
-        cnt[t >> 6] = __popcll(m);
+    __syncthreads();
+    const int nbox = nq[0], ncol = nq[1], cbox = (nbox + 63) / 64, chunks = cbox + (ncol + 63) / 64;
+    for (int c = threadIdx.x >> 6; c < chunks; c += 4) {   // the same for a whole wavefront
+        const bool box = c < cbox;
+        const int k = (box ? c : c - cbox) * 64 + (threadIdx.x & 63);
+        int yes = 0;
+        if (k < (box ? nbox : ncol)) {
+            const int q = queue[box ? 0 : 1][k];
+            const SubCell cell = level_item(lo + q, cand, list, nr1, vb0, verts);
+            int large = 0;   // (not too large: that was decided)
+            yes = (box ? refine_test<NEEDS_BOX>(ra, cell, large) : refine_test<NEEDS_COLUMNS>(ra, cell, large)) == REFINE;
+            refined[q] = (uint8_t)yes;
+        }
+        add_stats(stats, 0, yes, 0);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < REST; k += blockDim.x) {
+        const uint64_t m = __ballot(refined[k] != 0);
+        if ((k & 63) == 0 && lo + k < n) {
+            mask[(lo + k) >> 6] = m;
+            cnt[(lo + k) >> 6] = __popcll(m);
+        }
     }
 }
 
@@ -702,15 +706,15 @@ size_t refine_subcell_bytes() { return sizeof(SubCell); }
 
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, uint8_t *flag, unsigned long long *stats, hipStream_t st)
+                        const double2 *verts, uint8_t *flag, uint64_t *mask, int32_t *cnt, unsigned long long *stats,
+                        hipStream_t st)
 {
     if (n <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);
     hipLaunchKernelGGL(k_refine_test, dim3((unsigned)((n + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, n, cand,
                        static_cast<const SubCell *>(list), nr1, vb0, verts, flag, stats);
-    for (auto *rest : {k_refine_rest<NEEDS_BOX>, k_refine_rest<NEEDS_COLUMNS>})
-        hipLaunchKernelGGL(rest, dim3((unsigned)((n + REST - 1) / REST)), dim3(256), 0, st, ra, n, cand,
-                           static_cast<const SubCell *>(list), nr1, vb0, verts, flag, stats);
+    hipLaunchKernelGGL(k_refine_rest, dim3((unsigned)((n + REST - 1) / REST)), dim3(256), 0, st, ra, n, cand,
+                       static_cast<const SubCell *>(list), nr1, vb0, verts, flag, mask, cnt, stats);
 }
 
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
@@ -739,11 +743,6 @@ void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, c
     if (n <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, 1, window);
     hipLaunchKernelGGL(k_sample_labels, dim3((unsigned)((n + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, n, ab, label);
-}
-
-void launch_flag_masks(int64_t n, const uint8_t *flag, uint64_t *mask, int32_t *cnt, hipStream_t st)
-{
-    if (n > 0) hipLaunchKernelGGL(k_flag_masks, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, flag, mask, cnt);
 }
 
 void launch_list_flagged(int64_t n, const uint64_t *mask, const int64_t *pos, int64_t base, int64_t *item, hipStream_t st)

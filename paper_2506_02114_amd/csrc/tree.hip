@@ -682,6 +682,14 @@ int64_t scan_i32_to_i64(mlm_lens *lens, const int32_t *in, int64_t *out, int64_t
     return read_total(t, st);
 }
 
+int64_t scan_excl(mlm_lens *lens, const int32_t *in, int64_t *out, int64_t n, hipStream_t st)
+{
+    if (n == 0) return 0;
+    const TotalSlot t = total_slot(lens);
+    dev_scan_i32_i64(in, out, n, false, scan_tmp(lens->ws, scan_tmp_bytes(n)), t.dev, t.host, t.seq, st);
+    return read_total(t, st);
+}
+
 // exclusive prefix sum of n int32 counts into n + 1 uint64 offsets; returns the total
 int64_t scan_i32_to_u64(mlm_lens *lens, const int32_t *in, unsigned long long *out, int64_t n, hipStream_t st)
 {
