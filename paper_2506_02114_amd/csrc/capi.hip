@@ -1275,11 +1275,10 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                 const void *list = nullptr;   // level 0: the candidate cells themselves
                 DevBuf *next = &ws.rsub0;
                 for (int d = 0; d < q.refine_depth && nlev > 0; ++d) {
-                    uint8_t *flag = static_cast<uint8_t *>(ws.rtflag.reserve((size_t)nlev));
                     int64_t nref = 0;
                     const int64_t *item = listed(nlev, [&](uint64_t *mask, int32_t *mcnt) {
                         launch_refine_test(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, cand, list,
-                                           R.nr1, vb0, verts, flag, mask, mcnt, rst3, st);
+                                           R.nr1, vb0, verts, mask, mcnt, rst3, st);
                     }, ws.ritem, 0, nref);
                     if (d == 0) n_refined += nref;
                     if (nref == 0) break;

@@ -273,7 +273,7 @@ struct Workspace {
     DevBuf search;
     DevBuf binom, patch_info, patch_coef, thin;
     DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
-        bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rtflag, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map, tune_desc;
+        bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map, tune_desc;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
     int64_t *spin = nullptr;              // coherent pinned slot of scan totals: {total, sequence}, then
@@ -529,11 +529,10 @@ void launch_histogram(const double *mu, int64_t npix, double lo, double hi, int 
 constexpr int REFINE_SLOTS = 256;
 constexpr int REFINE_STRIDE = 16;
 size_t refine_subcell_bytes();
-// (flag: a byte per item of scratch; the refined items as masks of 64 with their counts)
+// the refined items as masks of 64 with their counts
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, uint8_t *flag, uint64_t *mask, int32_t *cnt, unsigned long long *stats,
-                        hipStream_t st);
+                        const double2 *verts, uint64_t *mask, int32_t *cnt, unsigned long long *stats, hipStream_t st);
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                           int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
                           int64_t vb0, const double2 *verts, const int64_t *item, double *map, void *out, hipStream_t st);

@@ -269,8 +269,8 @@ __device__ inline void test_triangle(int t, const SubCell &c, const double (&gu)
     }
 }
 
-// What a test says: refined or not, or that another kind of test has to decide,
-// for a grid within 2 x 2 pixels or for a wider one
+// What the test by one line says: refined or not, or that another test has to
+// decide, for a grid within 2 x 2 pixels or for a wider one
 enum Verdict { KEEP = 0, REFINE = 1, NEEDS_BOX = 2, NEEDS_COLUMNS = 3 };
 
 // the box of the 3 x 3 grid: whether it is finite and within the window
@@ -412,37 +412,50 @@ __device__ inline void split_box(const SubCell &c, const double (&gu)[3][3], con
     }
 }
 
-// The test of one subcell, of the kind `kind` (KEEP: the first, by one line,
-// which sends the others on): its 3 x 3 grid of source points (corners from the
-// subcell, five new rays) and whether it is refined.
-template <int kind>
-__device__ inline Verdict refine_test(const RefineArgs &ra, const SubCell &c, int &too_large)
+// the test by the 2 x 2 pixels of the box
+__device__ inline bool test_box(const RefineArgs &ra, const SubCell &c, const double (&gu)[3][3],
+                                   const double (&gv)[3][3], double umin, double vmin)
+{
+    const double fu = floor(umin), fv = floor(vmin), n1 = ra.g.n1, n2 = ra.g.n2;
+    double d[4], l1 = 0.0;
+    split_box(c, gu, gv, fu, fv, d);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double i = fu + (k & 1), j = fv + (k >> 1);
+        if (i >= 0.0 && j >= 0.0 && i < n1 && j < n2) l1 += fabs(d[k]);
+    }
+    return l1 > ra.tau * 2.0;
+}
+
+// the test of a grid of any width
+__device__ inline bool test_columns(const RefineArgs &ra, const SubCell &c, const double (&gu)[3][3],
+                                       const double (&gv)[3][3], double umin, double umax, double vmin, double vmax)
+{
+    double l1 = 0.0;
+    split_columns(ra, c, gu, gv, umin, umax, vmin, vmax, [&](int64_t, int64_t, double d) { l1 += fabs(d); });
+    return l1 > ra.tau * 2.0 * (ra.g.tri_weight * c.h * c.h);
+}
+
+// The test of one subcell by its 3 x 3 grid of source points (corners from the
+// subcell, five new rays): whether it is refined.  (The tests of grids in a 2 x 2 box
+// and of wider ones in launches of their own, on gathered items whose rays had to be
+// shot again, were the faster way only while a lane loaded its own stars: one-level
+// refinement of 200 x 200 pixels at 8, 256 and 4096 cells a pixel takes 1.26, 6.1 and
+// 39 ms so and 0.80, 5.2 and 33 here, the learned refinement of a 400 x 400 map 89
+// and 83.)
+__device__ inline bool refine_test(const RefineArgs &ra, const SubCell &c, int &too_large)
 {
     double gu[3][3], gv[3][3], umin, umax, vmin, vmax;
     fill_grid(ra, c, gu, gv);
-    const bool small = grid_box(ra, gu, gv, umin, umax, vmin, vmax);
-    if constexpr (kind == KEEP) {
-        if (!small) {
-            too_large = 1;
-            return KEEP;
-        }
-        if (cell_folded(c)) return REFINE;
-        return test_line(ra, c, gu, gv, umin, umax, vmin, vmax);
-    } else if constexpr (kind == NEEDS_BOX) {
-        const double fu = floor(umin), fv = floor(vmin), n1 = ra.g.n1, n2 = ra.g.n2;
-        double d[4], l1 = 0.0;
-        split_box(c, gu, gv, fu, fv, d);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double i = fu + (k & 1), j = fv + (k >> 1);
-            if (i >= 0.0 && j >= 0.0 && i < n1 && j < n2) l1 += fabs(d[k]);
-        }
-        return l1 > ra.tau * 2.0 ? REFINE : KEEP;
-    } else {
-        double l1 = 0.0;
-        split_columns(ra, c, gu, gv, umin, umax, vmin, vmax, [&](int64_t, int64_t, double d) { l1 += fabs(d); });
-        return l1 > ra.tau * 2.0 * (ra.g.tri_weight * c.h * c.h) ? REFINE : KEEP;
+    if (!grid_box(ra, gu, gv, umin, umax, vmin, vmax)) {
+        too_large = 1;
+        return false;
     }
+    if (cell_folded(c)) return true;
+    const Verdict v = test_line(ra, c, gu, gv, umin, umax, vmin, vmax);
+    if (v == NEEDS_BOX) return test_box(ra, c, gu, gv, umin, vmin);
+    if (v == NEEDS_COLUMNS) return test_columns(ra, c, gu, gv, umin, umax, vmin, vmax);
+    return v == REFINE;
 }
 
 // Refinement level by level (breadth first): every (sub)cell of a level is
@@ -490,76 +503,26 @@ __device__ inline void add_stats(unsigned long long *__restrict__ stats, int tes
     }
 }
 
-// flag[t] = the verdict on item t, from the test that a grid within two pixels
-// needs; the others are left to k_refine_rest, so that the few lanes that need
-// more do not hold up the rest of their wavefronts.  Bound by instruction
-// issue: 26 ms over the levels of the learned refinement of a 400 x 400 map of
-// 20,000 stars, with k_refine_rest's 19 where one kernel for all took 90.
+// The refined items of a level, 64 items a mask (a workgroup's), with their number
+// (a scan of these, and not of a flag per item, numbers them: with 4-byte flags and
+// 8-byte places of every item, numbering the cells and subcells of the learned
+// refinement of a 400 x 400 map moved 17 GB).  Bound by instruction issue.
+static_assert(RBLK == 64, "a workgroup is a mask");
 __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_test(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
                                                       const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                      const double2 *__restrict__ verts, uint8_t *__restrict__ flag,
-                                                      unsigned long long *__restrict__ stats)
+                                                      const double2 *__restrict__ verts, uint64_t *__restrict__ mask,
+                                                      int32_t *__restrict__ cnt, unsigned long long *__restrict__ stats)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int large = 0;
-    Verdict v = KEEP;
-    if (t < n) {
-        const SubCell c = level_item(t, cand, list, nr1, vb0, verts);
-        v = refine_test<KEEP>(ra, c, large);
-        flag[t] = (uint8_t)v;
+    bool yes = false;
+    if (t < n) yes = refine_test(ra, level_item(t, cand, list, nr1, vb0, verts), large);
+    const uint64_t m = __ballot(yes);
+    if (threadIdx.x == 0) {
+        mask[blockIdx.x] = m;
+        cnt[blockIdx.x] = __popcll(m);
     }
-    add_stats(stats, t < n ? 1 : 0, v == REFINE ? 1 : 0, large);
-}
-
-// The items of a level that need one of the other tests: a workgroup reads REST
-// verdicts, gathers those items in LDS by their test and tests them with full lanes,
-// a wavefront one kind at a time.  Then 64 items' verdicts each make one mask, with
-// its number of refined items (a scan of these, and not of the items' flags, numbers
-// the refined ones: with 4-byte flags and 8-byte places of every item, numbering the
-// cells and subcells of the learned refinement of a 400 x 400 map moved 17 GB).
-// (One launch: by a launch for each test and one for the masks a small map's
-// refinement, three levels of launches, took 30 us longer.)
-constexpr int REST = 1024;
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_rest(RefineArgs ra, int64_t n, const int64_t *__restrict__ cand,
-                                                     const SubCell *__restrict__ list, int64_t nr1, int64_t vb0,
-                                                     const double2 *__restrict__ verts, const uint8_t *__restrict__ flag,
-                                                     uint64_t *__restrict__ mask, int32_t *__restrict__ cnt,
-                                                     unsigned long long *__restrict__ stats)
-{
-    __shared__ unsigned short queue[2][REST];
-    __shared__ uint8_t refined[REST];
-    __shared__ int nq[2];
-    if (threadIdx.x < 2) nq[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t lo = (int64_t)blockIdx.x * REST;
-    for (int k = threadIdx.x; k < REST; k += blockDim.x) {
-        const int v = lo + k < n ? flag[lo + k] : KEEP;
-        refined[k] = v == REFINE;
-        if (v >= NEEDS_BOX) queue[v - NEEDS_BOX][atomicAdd(&nq[v - NEEDS_BOX], 1)] = (unsigned short)k;
-    }
-    __syncthreads();
-    const int nbox = nq[0], ncol = nq[1], cbox = (nbox + 63) / 64, chunks = cbox + (ncol + 63) / 64;
-    for (int c = threadIdx.x >> 6; c < chunks; c += 4) {   // the same for a whole wavefront
-        const bool box = c < cbox;
-        const int k = (box ? c : c - cbox) * 64 + (threadIdx.x & 63);
-        int yes = 0;
-        if (k < (box ? nbox : ncol)) {
-            const int q = queue[box ? 0 : 1][k];
-            const SubCell cell = level_item(lo + q, cand, list, nr1, vb0, verts);
-            int large = 0;   // (not too large: that was decided)
-            yes = (box ? refine_test<NEEDS_BOX>(ra, cell, large) : refine_test<NEEDS_COLUMNS>(ra, cell, large)) == REFINE;
-            refined[q] = (uint8_t)yes;
-        }
-        add_stats(stats, 0, yes, 0);
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < REST; k += blockDim.x) {
-        const uint64_t m = __ballot(refined[k] != 0);
-        if ((k & 63) == 0 && lo + k < n) {
-            mask[(lo + k) >> 6] = m;
-            cnt[(lo + k) >> 6] = __popcll(m);
-        }
-    }
+    add_stats(stats, t < n ? 1 : 0, yes ? 1 : 0, large);
 }
 
 // item[..] = base + t for the flagged t in order (pos: exclusive scan of the
@@ -668,10 +631,7 @@ __global__ __launch_bounds__(RBLK) __attribute__((amdgpu_waves_per_eu(3))) void 
     shoot_uv(ra, c.A0 + 1.0, c.B0 + 1.0, c.u[2], c.v[2]);
     shoot_uv(ra, c.A0, c.B0 + 1.0, c.u[3], c.v[3]);
     int large = 0;
-    Verdict r = refine_test<KEEP>(ra, c, large);
-    if (r == NEEDS_BOX) r = refine_test<NEEDS_BOX>(ra, c, large);
-    else if (r == NEEDS_COLUMNS) r = refine_test<NEEDS_COLUMNS>(ra, c, large);
-    label[t] = r == REFINE ? 1 : 0;
+    label[t] = refine_test(ra, c, large) ? 1 : 0;
 }
 
 }  // namespace
@@ -706,15 +666,12 @@ size_t refine_subcell_bytes() { return sizeof(SubCell); }
 
 void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
-                        const double2 *verts, uint8_t *flag, uint64_t *mask, int32_t *cnt, unsigned long long *stats,
-                        hipStream_t st)
+                        const double2 *verts, uint64_t *mask, int32_t *cnt, unsigned long long *stats, hipStream_t st)
 {
     if (n <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);
     hipLaunchKernelGGL(k_refine_test, dim3((unsigned)((n + RBLK - 1) / RBLK)), dim3(RBLK), 0, st, ra, n, cand,
-                       static_cast<const SubCell *>(list), nr1, vb0, verts, flag, stats);
-    hipLaunchKernelGGL(k_refine_rest, dim3((unsigned)((n + REST - 1) / REST)), dim3(256), 0, st, ra, n, cand,
-                       static_cast<const SubCell *>(list), nr1, vb0, verts, flag, mask, cnt, stats);
+                       static_cast<const SubCell *>(list), nr1, vb0, verts, mask, cnt, stats);
 }
 
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
