@@ -1283,7 +1283,7 @@ void map_impl(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_map_st
                     if (d == 0) n_refined += nref;
                     if (nref == 0) break;
                     void *out = next->reserve((size_t)(4 * nref) * sub);
-                    launch_refine_expand(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nlev, nref, cand,
+                    launch_refine_expand(T, R, lc, g, q.refine_tau, q.refine_depth, q.refine_window, nref, cand,
                                          list, R.nr1, vb0, verts, item, map, out, st);
                     list = out;
                     nlev = 4 * nref;
@@ -1608,7 +1608,8 @@ mlm_status mlm_map_batch(mlm_lens *const *lenses, const mlm_map_request *reqs, i
             setup_region(lenses[i], &qi, &Ri, &lenses[i]->ws, st);
             (void)tune_map(lenses[i], qi, Ri, st);
         }
-    // Regions, sizes and the chunks first (host arithmetic only): chunks of
+    // Regions (of a lens with third-order terms searched for on the device, and
+    // waited for), sizes and the chunks first: chunks of
     // consecutive maps that fit the vertex budget, one fused launch per stage
     // for all maps of a chunk.
     int64_t max_verts = 0;

@@ -111,17 +111,6 @@ __device__ inline double2 cinv(double2 a)
     double r = 1.0 / (a.x * a.x + a.y * a.y);
     return make_double2(a.x * r, -a.y * r);
 }
-// z^n for n >= 0 by binary powering
-__device__ inline double2 cpowi(double2 z, int n)
-{
-    double2 r = make_double2(1.0, 0.0);
-    while (n) {
-        if (n & 1) r = cmul(r, z);
-        z = cmul(z, z);
-        n >>= 1;
-    }
-    return r;
-}
 
 // the same on float2, and the complex type of a real type
 __device__ __host__ inline float2 cmul(float2 a, float2 b)
@@ -133,16 +122,6 @@ __device__ inline float2 cinv(float2 a)
 {
     float r = __builtin_amdgcn_rcpf(a.x * a.x + a.y * a.y);
     return make_float2(a.x * r, -a.y * r);
-}
-__device__ inline float2 cpowi(float2 z, int n)
-{
-    float2 r = make_float2(1.0f, 0.0f);
-    while (n) {
-        if (n & 1) r = cmul(r, z);
-        z = cmul(z, z);
-        n >>= 1;
-    }
-    return r;
 }
 
 // wavefront-level load balancing: a wavefront owns 64 segments (cells, large

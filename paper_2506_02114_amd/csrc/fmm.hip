@@ -148,8 +148,7 @@ struct UpArgs {
     const double *sx, *sy, *sm;
 };
 
-// z^k for k < 32 by binary powering, without branches (a lane per k); the
-// roundings are cpowi's
+// z^k for k < 32 by binary powering, without branches (a lane per k)
 __device__ inline double2 cpow32(double2 z, int k)
 {
     double2 r = make_double2(1.0, 0.0);

@@ -272,7 +272,7 @@ struct Workspace {
     DevBuf bigcount, biglist;
     DevBuf search;
     DevBuf binom, patch_info, patch_coef, thin;
-    DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, items, itemoff, tbig, tbigoff, bigprep, bigbands, nbnd, nbndoff, diff, bandcnt, bandoff,
+    DevBuf tile_off, tile_leaf, verts, map, wbuf, pts, counters, tbig, tbigoff, bigprep, bigbands, diff, bandcnt, bandoff,
         bandcur, bandlist, rfeat, rpos, rcand, rlabel, rstats, irs_counts, rmask, rcount, rtpos, ritem, rsub0, rsub1, bitems, bqueue, tune_map, tune_desc;
     void *pinned = nullptr;               // small pinned host buffer for read-backs
     size_t pinned_cap = 0;
@@ -410,7 +410,6 @@ constexpr int64_t BIN_TRIS = 2048;
 // cell tiles of the cell pass over cell rows [cb0, cb0 + nrows): one workgroup and one
 // large-triangle count each
 int64_t ipm_tile_count(int64_t nr1, int64_t nrows);
-// (pass: 0, 1 k_ipm with its large and small window, 2, 3 k_ipm_fine)
 // lists of the large triangles that the cell pass meets: BIG_SHARDS of cap
 // entries each, their counts BIG_STRIDE apart (a count above cap: the list is
 // incomplete)
@@ -446,6 +445,7 @@ struct ThinList {
     double2 *corner = nullptr;   // ray by ray: a listed cell's (0, 0), (1, 0), (0, 1), (1, 1)
 };
 constexpr size_t THIN_BYTES = THIN_CELLS * (4 * sizeof(double2) + sizeof(int64_t)) + sizeof(unsigned);
+// the cell pass (0, 1: k_ipm with its large and small window; 2, 3: k_ipm_fine with its)
 void launch_ipm(const double2 *verts, int64_t nr1, int64_t cb0, int64_t cb1, int64_t vb0, const MapGeom &g,
                 double *map, unsigned long long *counters, const BigList &bl, const ThinList &thin, bool mixed, int pass,
                 unsigned long long *work, hipStream_t st);
@@ -507,14 +507,11 @@ void dev_scan_i32(const int32_t *in, int32_t *out, int64_t n, bool inclusive, vo
                   int64_t *total_host, int64_t seq, hipStream_t st);
 void dev_scan_i32_i64(const int32_t *in, int64_t *out, int64_t n, bool inclusive, void *tmp, int64_t *total_dev,
                       int64_t *total_host, int64_t seq, hipStream_t st);
-void dev_scan_i64(const int64_t *in, int64_t *out, int64_t n, bool inclusive, void *tmp, int64_t *total_dev,
-                  int64_t *total_host, int64_t seq, hipStream_t st);
 // stable radix sort of (key, value) pairs by key bits [0, bits); the result
 // ends in kout/vout, kin/vin are overwritten (tmp: radix_sort_tmp_bytes(n))
 size_t radix_sort_tmp_bytes(int64_t n);
 void radix_sort_pairs(uint64_t *kin, int32_t *vin, uint64_t *kout, int32_t *vout, int64_t n, int bits, void *tmp,
                       hipStream_t st);
-int64_t scan_total_i64(mlm_lens *lens, const int64_t *in, int64_t *out, int64_t n, hipStream_t st);
 int64_t scan_i32_to_i64(mlm_lens *lens, const int32_t *in, int64_t *out, int64_t n, hipStream_t st);
 
 // products.hip
@@ -534,8 +531,8 @@ void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, con
                         int window, int64_t n, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
                         const double2 *verts, uint64_t *mask, int32_t *cnt, unsigned long long *stats, hipStream_t st);
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
-                          int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
-                          int64_t vb0, const double2 *verts, const int64_t *item, double *map, void *out, hipStream_t st);
+                          int window, int64_t nref, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
+                          const double2 *verts, const int64_t *item, double *map, void *out, hipStream_t st);
 void launch_sample_features(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, int64_t n,
                             const int64_t *ab, float *feats, hipStream_t st);
 void launch_sample_labels(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau,

@@ -675,9 +675,8 @@ void launch_refine_test(const Tree &T, const Region &R, const LensConst &lc, con
 }
 
 void launch_refine_expand(const Tree &T, const Region &R, const LensConst &lc, const MapGeom &g, double tau, int depth,
-                          int window, int64_t n, int64_t nref, const int64_t *cand, const void *list, int64_t nr1,
-                          int64_t vb0, const double2 *verts, const int64_t *item,
-                          double *map, void *out, hipStream_t st)
+                          int window, int64_t nref, const int64_t *cand, const void *list, int64_t nr1, int64_t vb0,
+                          const double2 *verts, const int64_t *item, double *map, void *out, hipStream_t st)
 {
     if (nref <= 0) return;
     const RefineArgs ra = make_refine_args(T, R, lc, g, tau, depth, window);

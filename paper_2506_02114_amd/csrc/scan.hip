@@ -235,12 +235,6 @@ void dev_scan_i32_i64(const int32_t *in, int64_t *out, int64_t n, bool inclusive
         scan_launch<int32_t, int64_t>(in, out, n, inclusive, static_cast<int64_t *>(tmp), total_dev, total_host, seq, st);
 }
 
-void dev_scan_i64(const int64_t *in, int64_t *out, int64_t n, bool inclusive, void *tmp, int64_t *total_dev,
-                  int64_t *total_host, int64_t seq, hipStream_t st)
-{
-    if (n > 0)
-        scan_launch<int64_t, int64_t>(in, out, n, inclusive, static_cast<int64_t *>(tmp), total_dev, total_host, seq, st);
-}
 
 size_t radix_sort_tmp_bytes(int64_t n)
 {

@@ -696,15 +696,6 @@ int64_t scan_i32_to_u64(mlm_lens *lens, const int32_t *in, unsigned long long *o
     return scan_i32_to_i64(lens, in, reinterpret_cast<int64_t *>(out), n, st);
 }
 
-// exclusive prefix sum of n int64 values; returns the total
-int64_t scan_total_i64(mlm_lens *lens, const int64_t *in, int64_t *out, int64_t n, hipStream_t st)
-{
-    if (n == 0) return 0;
-    const TotalSlot t = total_slot(lens);
-    dev_scan_i64(in, out, n, false, scan_tmp(lens->ws, scan_tmp_bytes(n)), t.dev, t.host, t.seq, st);
-    return read_total(t, st);
-}
-
 bool read_big_counts(mlm_lens *lens, const BigList &bl, BigStarts &at, hipStream_t st)
 {
     const TotalSlot t = total_slot(lens);   // (pinned: lists are not kept inside a scratch arena)
