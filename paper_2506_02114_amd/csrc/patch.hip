@@ -119,8 +119,9 @@ __global__ __launch_bounds__(64) void k_patch_coef(ShootArgs sa, LensConst lc, P
     {
         const double sr = sx * li.invL, si = sy * li.invL, rho = r * li.invL;
         const double2 *dv = deriv + (int64_t)lf * p;
-        const double reach = sqrt(sr * sr + si * si) + rho;
-        if (__any(reach > 2.0)) {
+        const double s2 = sr * sr + si * si, room = 2.0 - rho;
+        if (__any(room < 0.0 || s2 > room * room)) {
+            const double reach = sqrt(s2) + rho;
             // the terms' magnitudes at the patch's far end and at the leaf's corner
             double far_end = 0.0, corner = 0.0;
             for (int l = p - 1; l >= 0; --l) {
@@ -535,8 +536,10 @@ constexpr double EDGE_MOST = 1.0 / 64.0;   // (beyond this every sixteenth ray o
 
 // inverse ray shooting of patch blockIdx.x: the patch's counts are summed in an
 // LDS window of W x W pixels about its centre's image (a lane adds a run of
-// rays in one pixel at once), the rest go to the map's counts
-template <int P, int W>
+// rays in one pixel at once), the rest go to the map's counts.  (WIDE: the edges are
+// wider than EDGE; as an argument for every map the width costs scalar registers that
+// the loop is short of: 0.4 % of the 2.4e10-ray map.)
+template <int P, int W, bool WIDE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_irs_patch(ShootArgs sa, LensConst lc, MapGeom g, PatchArgs pa,
                                                   const PatchInfo *__restrict__ info,
                                                   const double2 *__restrict__ coef,
@@ -587,7 +590,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         else
             atomicAdd(counts + (int64_t)j * g.n1 + i, (unsigned long long)k);
     };
-    const double n1 = g.n1, n2 = g.n2;
+    const double n1 = g.n1, n2 = g.n2, most = WIDE ? pa.sure : 0.5 - EDGE;
     // (the rays to shoot again, four bits a sweep: shot inside the loop below, their
     // constants had a quarter of its instructions move spilled scalars, and the
     // 2.4e10-ray map took 69 ms instead of 58)
@@ -604,7 +607,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const bool valid = ray_col<P>(col, s) < na && ray_row<P>(row0, s) < nb;
             const double fu = floor(u[s]), fv = floor(v[s]);
             // false for NaN
-            const bool sure = fabs((u[s] - fu) - 0.5) <= pa.sure && fabs((v[s] - fv) - 0.5) <= pa.sure;
+            const bool sure = fabs((u[s] - fu) - 0.5) <= most && fabs((v[s] - fv) - 0.5) <= most;
             if (valid && !sure) again |= 1u << s;
             const int iu = (int)fu, jv = (int)fv;   // (saturating: beyond the map stays beyond)
             const bool in = valid && sure && (unsigned)iu < (unsigned)g.n1 && (unsigned)jv < (unsigned)g.n2;
@@ -752,9 +755,11 @@ void launch_irs_patches(mlm_lens *lens, const Tree &T, const Region &R, const Le
     patch_coefs(lens, T, lc, sa, pa, side, npatch, st);
     // the window: a patch's unlensed image is side d / pixel wide
     const bool wide = side * std::max(R.d1 / R.pix1, R.d2 / R.pix2) > 4.0;
-    auto *k = side == 64   ? (wide ? k_irs_patch<64, 32> : k_irs_patch<64, 16>)
-              : side == 32 ? (wide ? k_irs_patch<32, 32> : k_irs_patch<32, 16>)
-                           : (wide ? k_irs_patch<16, 32> : k_irs_patch<16, 16>);
+    auto *k = side == 64   ? (wide ? k_irs_patch<64, 32, false> : k_irs_patch<64, 16, false>)
+              : side == 32 ? (wide ? k_irs_patch<32, 32, false> : k_irs_patch<32, 16, false>)
+                           : (wide ? k_irs_patch<16, 32, false> : k_irs_patch<16, 16, false>);
+    if (pa.sure < 0.5 - EDGE)   // (a rare map: one window for all)
+        k = side == 64 ? k_irs_patch<64, 32, true> : side == 32 ? k_irs_patch<32, 32, true> : k_irs_patch<16, 32, true>;
     hipLaunchKernelGGL(k, dim3((unsigned)npatch), dim3(64), 0, st, sa,
                        lc, g, pa, lens->ws.patch_info.as<PatchInfo>(), lens->ws.patch_coef.as<double2>(), T.leaves,
                        T.near, T.deriv, counts);

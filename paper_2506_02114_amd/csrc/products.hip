@@ -143,13 +143,13 @@ void launch_histogram(const double *mu, int64_t npix, double lo, double hi, int 
         const double eps = (HIST_EPS + HIST_ROUND * (std::fabs(lo) + std::fabs(hi))) * inv_w;
         const int head = (reinterpret_cast<uintptr_t>(mu) & 15) ? 1 : 0;   // (mu is aligned to its doubles)
         const int64_t pairs = (npix - head) / 2;
-        // 16 pixels a thread, 4 where that leaves fewer than 256 workgroups: pixels at
+        // 16 pixels a thread, 4 where that leaves fewer than 192 workgroups: pixels at
         // a bin's edge (a map of magnification 1 in bins that begin there) take the
         // logarithm in FP64 as well, and few workgroups then wait for it (1000 x 1000
         // of them, the whole call: 40 us by 62 workgroups, 32 by 245; spread over the
         // bins 29 and 28)
-        const int64_t want = std::max((npix + HIST_BLK * 16 - 1) / (HIST_BLK * 16),
-                                      std::min<int64_t>((npix + HIST_BLK * 4 - 1) / (HIST_BLK * 4), 256));
+        int64_t want = (npix + HIST_BLK * 16 - 1) / (HIST_BLK * 16);
+        if (want < 192) want = std::min<int64_t>((npix + HIST_BLK * 4 - 1) / (HIST_BLK * 4), 256);
         const unsigned grid = (unsigned)std::min<int64_t>(std::max<int64_t>(want, 1), 512);
         hipLaunchKernelGGL(k_histogram, dim3(grid), dim3(HIST_BLK), (size_t)nb * sizeof(unsigned), st, mu, npix, head,
                            pairs, lo, inv_w, nbins, eps, counts);
