@@ -40,8 +40,8 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6          # MI355X FP64 vector, dense
 # taken with (ipm.hip and colarea.hpp), identified by the SHA-256 prefix of
 # the two files' bytes in that order.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
-IPM_TRAFFIC = {"ipm_sha256": "7819f726f7440616",                     # (fetch KiB, write KiB)
-               "k_ipm": (710484.2188, 2370746.9844), "k_band_queue1": (3064563.0312, 274081.1094)}
+IPM_TRAFFIC = {"ipm_sha256": "651d0a647025ba0e",                     # (fetch KiB, write KiB)
+               "k_ipm": (710500.9688, 2372944.3125), "k_band_queue1": (3060958.0938, 274090.5156)}
 # Wavefront vector instructions per launch of the same kernels (SQ_INSTS_VALU,
 # same runs and source).  A wave64 vector instruction holds its SIMD four
 # cycles, so 1024 SIMDs at 2.4 GHz issue at most 6.144e11 of them per second:

@@ -429,7 +429,8 @@ mlm_status mlm_map(mlm_lens *lens, const mlm_map_request *req, double *mu, mlm_m
  *     the library's (a call returns after its work has completed); processes
  *     each have their own array.
  *   - The vertex strip is sized to what the array holds, so large grids run
- *     in more strips than under mlm_map.
+ *     in more strips than under mlm_map (of an eighth of that size where
+ *     large triangles exhaust what is left beside them).
  *   - MLM_ERANGE when the map cannot fit: at entry, if the sorted stars (48
  *     bytes each), two vertex rows and the host-bound map copy already
  *     exceed the array; later, if data-dependent lists (large triangles,

@@ -688,6 +688,11 @@ PatchArgs patch_args(const Region &R, const LensConst &lc, const MapGeom &g, int
 //   330000, 4.2e7                  0.220 / 0.193   (0.226 / 0.220)
 //   714000, 1.5e8                  0.803 / 0.701   (0.754 / 0.742)
 //   5074000, 1.2e10                68.4 / 54.8   (48.0 / 35.6)
+// Uneven fields are no worse off, though many leaves of a group hold less than a
+// patch each: m leaves have at most rays / P^2 + 2 sqrt(m rays) / P + m patches, and
+// in a group each of those replaces rays with full lists of near stars.  40 rays a
+// pixel, ray by ray / by patches: a tight cluster 3.26 / 1.50, a fold caustic's
+// field 4.79 / 1.66.
 int patch_side(const Region &R, const Tree &T, int64_t rows)
 {
     if (T.mixed || T.p < 1) return 0;

@@ -414,7 +414,7 @@ __device__ inline void split_box(const SubCell &c, const double (&gu)[3][3], con
 
 // the test by the 2 x 2 pixels of the box
 __device__ inline bool test_box(const RefineArgs &ra, const SubCell &c, const double (&gu)[3][3],
-                                   const double (&gv)[3][3], double umin, double vmin)
+                                const double (&gv)[3][3], double umin, double vmin)
 {
     const double fu = floor(umin), fv = floor(vmin), n1 = ra.g.n1, n2 = ra.g.n2;
     double d[4], l1 = 0.0;
@@ -429,7 +429,7 @@ __device__ inline bool test_box(const RefineArgs &ra, const SubCell &c, const do
 
 // the test of a grid of any width
 __device__ inline bool test_columns(const RefineArgs &ra, const SubCell &c, const double (&gu)[3][3],
-                                       const double (&gv)[3][3], double umin, double umax, double vmin, double vmax)
+                                    const double (&gv)[3][3], double umin, double umax, double vmin, double vmax)
 {
     double l1 = 0.0;
     split_columns(ra, c, gu, gv, umin, umax, vmin, vmax, [&](int64_t, int64_t, double d) { l1 += fabs(d); });
